@@ -65,8 +65,11 @@ __device__ __forceinline__ bool starts_run(const PairOrder& o, int allow_chain, 
     return pos % o.run_limit == 0 || !(allow_chain && pair_linked(dA, ga, dB, gb, p - 1, q + 1));
 }
 
-template <int MODE, bool PINT>
-__global__ void __launch_bounds__(256) accumulate_kernel(const AccArgs a) {
+// R elements per thread: 4 (one workgroup per 32 x 32 position) or 1 (four workgroups per position, each eight of its
+// columns).  DEPTH product loads are kept in flight per thread.
+template <int MODE, bool PINT, int R, int DEPTH>
+__device__ __forceinline__ void accumulate_body(const AccArgs& a) {
+    static_assert(R == 4 || R == 1, "a thread reads 16 bytes or one word of a stored product");
     constexpr bool HW = MODE == ACC_HW, EMU = MODE == ACC_EMU, EXACT = MODE == ACC_EXACT;
     typedef typename std::conditional<PINT, int64_t, int>::type run_t;      // exact sum of a run
     __shared__ int relA[MAX_SLICES][32];
@@ -76,14 +79,18 @@ __global__ void __launch_bounds__(256) accumulate_kernel(const AccArgs a) {
     __shared__ int n_entries;
 
     const int tid = threadIdx.x;
-    const int lane = tid & 63, g4 = tid >> 6;
-    const int pos = blockIdx.x & 63;                  // wave*16 + sub
-    const int tile = blockIdx.x >> 6;
+    const int lane = tid & 63;
+    const unsigned place = R == 4 ? blockIdx.x : blockIdx.x >> 2;
+    const int g4 = R == 4 ? tid >> 6 : (int)(blockIdx.x & 3);         // the eight columns of the position the thread works on
+    const int r0 = R == 4 ? 0 : tid >> 6;             // first of its R consecutive columns there
+    const int pos = place & 63;                       // wave*16 + sub
+    const int tile = place >> 6;
     const int tn = tile / a.tiles_m, tm = tile - tn * a.tiles_m;
     const int wave = pos >> 4, sub = pos & 15;
     const int wn = wave >> 1, wm = wave & 1, ti = sub >> 2, tj = sub & 3;
     const int64_t m0 = (int64_t)tm * TILE + wm * 128 + tj * 32;       // first row of C of this 32 x 32 position
     const int64_t n0 = (int64_t)tn * TILE + wn * 128 + ti * 32;       // first column
+    if (m0 >= a.m || n0 >= a.n) return;               // padding only
 
     // exponents of the 32 rows and 32 columns: slot 0 keeps the first-slice exponent, slots p >= 1 the difference to it
     for (int idx = tid; idx < a.order.s * 32; idx += 256) {
@@ -99,16 +106,16 @@ __global__ void __launch_bounds__(256) accumulate_kernel(const AccArgs a) {
     __syncthreads();
 
     const int ml = lane & 31;
-    const int nl = g4 * 8 + (lane >> 5) * 4;
-    const size_t tile_off = (size_t)tile * TILE_ELEMS + (size_t)pos * 1024 + (size_t)tid * 4;
+    const int nl = g4 * 8 + (lane >> 5) * 4 + r0;
+    const size_t tile_off = (size_t)tile * TILE_ELEMS + (size_t)pos * 1024 + (size_t)(g4 * 64 + lane) * 4 + r0;
     const size_t pair_stride = (size_t)a.tiles_m * a.tiles_n * TILE_ELEMS;
 
-    // the block sum of this thread's four elements, in the representation of the mode
-    double Sd[4];                                     // HW
-    RoundedSum E[4];                                  // EMU: x * 2^ex with an integer significand of at most 53 bits
-    Fixed192 X[4];                                    // EXACT
+    // the block sum of this thread's elements, in the representation of the mode
+    double Sd[R];                                     // HW
+    RoundedSum E[R];                                  // EMU: x * 2^ex with an integer significand of at most 53 bits
+    Fixed192 X[R];                                    // EXACT
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
+    for (int r = 0; r < R; ++r) {
         if constexpr (HW) Sd[r] = a.read_S ? __longlong_as_double((long long)a.S[tile_off + r]) : 0.0;
         if constexpr (EMU) {
             if (a.read_S) E[r].start_at(a.S[tile_off + r]);
@@ -159,18 +166,18 @@ __global__ void __launch_bounds__(256) accumulate_kernel(const AccArgs a) {
     // Per element, consecutive stored runs of one anti-diagonal with the same scale are merged further (integer,
     // units of 2^-p_frac) before the FP64 addition: together with the tile-wide runs formed by the GEMM
     // kernel this is the element-wise rule "consecutive pairs of an anti-diagonal with equal scale are summed exactly".
-    run_t run_sum[4] = {0, 0, 0, 0};
-    int run_e[4] = {0, 0, 0, 0};
-    auto process = [&](uint32_t entry, const uint4& v) {
+    run_t run_sum[R] = {};
+    int run_e[R] = {};
+    struct Words { uint32_t w[R]; };
+    auto process = [&](uint32_t entry, const Words& v) {
         const int p = (entry >> 12) & 63, q = (entry >> 18) & 63;
         const bool first = (entry >> 24) & 1;
         const int eA = p == 0 ? 0 : relA[p][ml];
-        const uint32_t vv[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
+        for (int r = 0; r < R; ++r) {
             const int e = eA + (q == 0 ? 0 : relB[q][nl + r]);
             // the product as an integer in units of 2^-p_frac: exact in FP32 (|integer| <= 2^24), no FP64 involved
-            const int iv = PINT ? (int)vv[r] : (int)ldexpf(__uint_as_float(vv[r]), a.p_frac);
+            const int iv = PINT ? (int)v.w[r] : (int)ldexpf(__uint_as_float(v.w[r]), a.p_frac);
             if (a.merge && !first && e == run_e[r]) {
                 run_sum[r] += iv;
             } else {
@@ -180,38 +187,40 @@ __global__ void __launch_bounds__(256) accumulate_kernel(const AccArgs a) {
             }
         }
     };
-    auto load_run = [&](int i) -> uint4 {
+    auto load_run = [&](int i) -> Words {
         const uint32_t entry = entries[i < n_runs ? i : n_runs - 1];
-        return *reinterpret_cast<const uint4*>(a.P + (size_t)(entry & 0xFFFu) * pair_stride + tile_off);
-    };
-    // four loads in flight per thread; the loop is unrolled by four so that each load keeps its registers
-    if (n_runs > 0) {
-        uint4 v0 = load_run(0), v1 = load_run(1), v2 = load_run(2), v3 = load_run(3);
-        int i = 0;
-        for (; i + 4 <= n_runs; i += 4) {
-            const uint4 w0 = v0;
-            v0 = load_run(i + 4);
-            process(entries[i], w0);
-            const uint4 w1 = v1;
-            v1 = load_run(i + 5);
-            process(entries[i + 1], w1);
-            const uint4 w2 = v2;
-            v2 = load_run(i + 6);
-            process(entries[i + 2], w2);
-            const uint4 w3 = v3;
-            v3 = load_run(i + 7);
-            process(entries[i + 3], w3);
+        const float* src = a.P + (size_t)(entry & 0xFFFu) * pair_stride + tile_off;
+        if constexpr (R == 4) {
+            const uint4 v = *reinterpret_cast<const uint4*>(src);
+            return Words{{v.x, v.y, v.z, v.w}};
+        } else {
+            return Words{{*reinterpret_cast<const uint32_t*>(src)}};
         }
-        if (i < n_runs) process(entries[i], v0);
-        if (i + 1 < n_runs) process(entries[i + 1], v1);
-        if (i + 2 < n_runs) process(entries[i + 2], v2);
+    };
+    // DEPTH loads in flight per thread; the loop is unrolled by DEPTH so that each load keeps its registers
+    if (n_runs > 0) {
+        Words v[DEPTH];
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) v[d] = load_run(d);
+        int i = 0;
+        for (; i + DEPTH <= n_runs; i += DEPTH) {
+#pragma unroll
+            for (int d = 0; d < DEPTH; ++d) {
+                const Words w = v[d];
+                v[d] = load_run(i + DEPTH + d);
+                process(entries[i + d], w);
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < DEPTH - 1; ++d)
+            if (i + d < n_runs) process(entries[i + d], v[d]);
     }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) add_run(r, run_sum[r], run_e[r]);
+    for (int r = 0; r < R; ++r) add_run(r, run_sum[r], run_e[r]);
 
     if (a.write_S) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
+        for (int r = 0; r < R; ++r) {
             if constexpr (HW) a.S[tile_off + r] = (uint64_t)__double_as_longlong(Sd[r]);
             if constexpr (EMU) a.S[tile_off + r] = E[r].value();
             if constexpr (EXACT) {
@@ -226,7 +235,7 @@ __global__ void __launch_bounds__(256) accumulate_kernel(const AccArgs a) {
     if (mi >= a.m) return;
     const int baseA = relA[0][ml];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
+    for (int r = 0; r < R; ++r) {
         const int64_t nj = n0 + nl + r;
         if (nj >= a.n) continue;
         const int base = baseA + relB[0][nl + r];
@@ -245,6 +254,13 @@ __global__ void __launch_bounds__(256) accumulate_kernel(const AccArgs a) {
         }
     }
 }
+
+template <int MODE, bool PINT>
+__global__ void __launch_bounds__(256) accumulate_kernel(const AccArgs a) { accumulate_body<MODE, PINT, 4, 4>(a); }
+
+// Few elements: a quarter of the work per thread
+template <int MODE, bool PINT>
+__global__ void __launch_bounds__(256) accumulate_fine_kernel(const AccArgs a) { accumulate_body<MODE, PINT, 1, 8>(a); }
 
 // Verification export: one thread per stored word; grid.y = pair slot of the pass.  Writes the plain column-major
 // matrices and, if asked, the number of pairs each slot sums for the element (see launch_export_products).
@@ -359,15 +375,23 @@ hipError_t launch_accumulate(const Plan& pl, const Operand& A, const Operand& B,
     a.add_to_C = t > 0;
     const int64_t blocks = pl.tiles_m * pl.tiles_n * 64;
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)blocks), block(256);
+    // With few positions a thread's serial chain (four elements per stored run, a round trip to memory per four runs) is the
+    // kernel's length: 361 positions, 21 runs, emulated 28 -> 22 us; 64 positions 18.8 -> 12.7; at 800 the two are equal, and
+    // beyond that four times the entry lists and word-wide loads lose (1024 positions 26 -> 37 us).
+    const bool fine = ((pl.m + 31) / 32) * ((pl.n + 31) / 32) <= 512;
+    const dim3 grid((unsigned)(fine ? 4 * blocks : blocks)), block(256);
+    auto launch = [&](auto coarse_kernel, auto fine_kernel) {
+        if (fine) hipLaunchKernelGGL(fine_kernel, grid, block, 0, st, a);
+        else hipLaunchKernelGGL(coarse_kernel, grid, block, 0, st, a);
+    };
     if (pl.p_is_int) {
-        if (accum_mode == ACC_EXACT) hipLaunchKernelGGL((accumulate_kernel<ACC_EXACT, true>), grid, block, 0, st, a);
-        else if (accum_mode == ACC_EMU) hipLaunchKernelGGL((accumulate_kernel<ACC_EMU, true>), grid, block, 0, st, a);
-        else hipLaunchKernelGGL((accumulate_kernel<ACC_HW, true>), grid, block, 0, st, a);
+        if (accum_mode == ACC_EXACT) launch(accumulate_kernel<ACC_EXACT, true>, accumulate_fine_kernel<ACC_EXACT, true>);
+        else if (accum_mode == ACC_EMU) launch(accumulate_kernel<ACC_EMU, true>, accumulate_fine_kernel<ACC_EMU, true>);
+        else launch(accumulate_kernel<ACC_HW, true>, accumulate_fine_kernel<ACC_HW, true>);
     } else {
-        if (accum_mode == ACC_EXACT) hipLaunchKernelGGL((accumulate_kernel<ACC_EXACT, false>), grid, block, 0, st, a);
-        else if (accum_mode == ACC_EMU) hipLaunchKernelGGL((accumulate_kernel<ACC_EMU, false>), grid, block, 0, st, a);
-        else hipLaunchKernelGGL((accumulate_kernel<ACC_HW, false>), grid, block, 0, st, a);
+        if (accum_mode == ACC_EXACT) launch(accumulate_kernel<ACC_EXACT, false>, accumulate_fine_kernel<ACC_EXACT, false>);
+        else if (accum_mode == ACC_EMU) launch(accumulate_kernel<ACC_EMU, false>, accumulate_fine_kernel<ACC_EMU, false>);
+        else launch(accumulate_kernel<ACC_HW, false>, accumulate_fine_kernel<ACC_HW, false>);
     }
     return hipGetLastError();
 }
