@@ -69,6 +69,53 @@ int slice_bits(int64_t kb, int fmt) {
 
 bool format_ok(int fmt) { return fmt >= OZAKI_SLICE_FP8_E4M3 && fmt <= OZAKI_SLICE_INT8; }
 
+// Groups of at most `len` pairs in a pass of `pairs` products (pl.npairs: all of them).
+int64_t groups_in_pass(const Plan& pl, int pairs, int len) {
+    const int64_t q = pl.s / len, r = pl.s % len, triangle = len * q * (q + 1) / 2 + r * (q + 1);   // sum of ceil(L / len), L = 1 ... s
+    const int64_t all = pl.full ? 2 * triangle - (pl.s + len - 1) / len : triangle;
+    return pairs >= pl.npairs ? all : (all * pairs + pl.npairs - 1) / pl.npairs;
+}
+
+// How the GEMMs of a pass of `pairs` products run: 256 x 256 or 128 x 128 blocks, and the length of the groups.  Any choice
+// gives the same bits (the accumulation kernel merges equal-scale products of an anti-diagonal element by element whatever
+// the grouping).  Long groups store fewer products, shorter ones and smaller blocks give a problem of few tiles enough
+// workgroups to keep 256 compute units busy.  The estimate below, in microseconds, was fitted to measurements from
+// 256^3 to 256 x 2048 x 8192 (FP8): a 64-byte stage takes 0.62 in a 256 x 256 block, 0.25 in a 128 x 128 block alone on its
+// compute unit and 0.42 where two share one; a workgroup costs 5 resp. 3 on top (filling the load ring, storing), a
+// stored product its bytes twice through memory, an entry of the accumulation lists 0.2; with more workgroups than slots the
+// last ones add half a group's time, little where whole anti-diagonals run from long to short.  Sums measured before and with
+// this rule (GEMM + accumulation): 256^3 49 -> 25, 600 x 600 x 1000 161 -> 58, 1000 x 777 x 1301 215 -> 125 us.  From 256 tiles on
+// long groups of the large blocks win by far (1500^3: 235 against 295 us).
+void choose_gemm(Plan& pl, int pairs) {
+    const int most = pl.run_limit < pl.s ? pl.run_limit : pl.s;
+    pl.small_tiles = 0;
+    pl.group_len = most;
+    const int64_t tiles = pl.tiles_m * pl.tiles_n;
+    if (tiles == 0 || tiles >= 256) return;
+    const int64_t quads = ((pl.m + QUAD - 1) / QUAD) * ((pl.n + QUAD - 1) / QUAD);
+    const int longest_diag = pairs < pl.s ? pairs : pl.s, shortest = most > 1 ? 2 : 1;
+    double best = 1e300;
+    for (int small = 0; small < 2; ++small) {
+        const int64_t blocks = small ? quads : tiles, slots = small ? 512 : 256;
+        for (int len = most; len >= shortest; len = len > 8 ? (len + 1) / 2 : len - 1) {
+            const int64_t ngroups = groups_in_pass(pl, pairs, len), wgs = ngroups * blocks;
+            const double stage = small ? (wgs <= 256 ? 0.25 : 0.42) : 0.62, fixed = small ? 3.0 : 5.0;
+            const double longest = (len < longest_diag ? len : longest_diag) * (double)pl.chunks * stage;
+            double t = longest + fixed;
+            if (wgs > slots) {
+                const double even = ((double)pairs * blocks * pl.chunks * stage + wgs * fixed) / slots + (len == pl.s ? 0.1 : 0.5) * longest;
+                if (even > t) t = even;
+            }
+            t += ngroups * (0.2 + blocks * (small ? 0.0146 : 0.0583) * 2.0);      // 64 resp. 256 KiB at 4.5 TB/s
+            if (t < best) {
+                best = t;
+                pl.small_tiles = small;
+                pl.group_len = len;
+            }
+        }
+    }
+}
+
 // Builds the plan; returns 0 or a status / negative argument index in the numbering of ozaki_dgemm.
 int make_plan(int64_t m, int64_t n, int64_t k, int fmt, int s, int64_t k_block, bool full, Plan& pl) {
     if (m < 0) return -1;
@@ -101,14 +148,7 @@ int make_plan(int64_t m, int64_t n, int64_t k, int fmt, int s, int64_t k_block, 
     pl.tiles_n = (n + TILE - 1) / TILE;
     pl.m_pad = pl.tiles_m * TILE;
     pl.n_pad = pl.tiles_n * TILE;
-    // Length of the GEMM kernel's groups.  Any length up to run_limit gives the same bits (the accumulation kernel
-    // merges equal-scale products of an anti-diagonal element by element whatever the grouping).  Long groups store
-    // fewer products; shorter ones give a problem of few tiles enough workgroups to keep 256 compute units evenly
-    // busy, which pays once a pair streams at least 64 stages, so that one more product store per group is small
-    // against it (measured at 16 tiles, 128 stages: 17 ... 28 % less GEMM time at 560 instead of 288 workgroups).
-    pl.group_len = pl.run_limit;
-    if (pl.chunks >= 64)
-        while (pl.group_len > 2 && pl.tiles_m * pl.tiles_n * order_num_groups(PairOrder{pl.s, pl.full, pl.group_len}) < 512) --pl.group_len;
+    choose_gemm(pl, pl.npairs);
     return 0;
 }
 
@@ -294,15 +334,17 @@ int check_dgemm_args(int64_t m, int64_t n, int64_t k, const double* A, int64_t l
 // One Ozaki product on (a panel of) the operands: C = alpha * (A B) + beta * C.  (alpha, beta) = (1, 0): the product
 // goes straight to C.  Otherwise it goes to the work memory's product buffer and one more kernel combines it with C.
 // The arguments have been checked and the plan made (check_dgemm_args).
-int dgemm_core(const Plan& pl, double alpha, const double* A, int64_t lda, const double* B, int64_t ldb, double beta, double* C,
+int dgemm_core(const Plan& plan, double alpha, const double* A, int64_t lda, const double* B, int64_t ldb, double beta, double* C,
                int64_t ldc, const Options& o, WorkMem wm) {
-    const int64_t m = pl.m, n = pl.n, k = pl.k;
+    const int64_t m = plan.m, n = plan.n, k = plan.k;
     if (m == 0 || n == 0) return 0;
     hipStream_t st = ctx().stream;
     const bool scaled = !(alpha == 1.0 && beta == 0.0);
     Carve c;
     c.W = nullptr;
-    if ((k > 0 || scaled) && !carve(pl, c, scaled, wm)) return OZAKI_STATUS_WORKSPACE;
+    if ((k > 0 || scaled) && !carve(plan, c, scaled, wm)) return OZAKI_STATUS_WORKSPACE;
+    Plan pl = plan;
+    if (k > 0 && c.chunk_pairs < pl.npairs) choose_gemm(pl, c.chunk_pairs);      // several passes: each is a launch of its own
     double* const out = scaled ? c.W : C;
     const int64_t ldo = scaled ? (m > 1 ? m : 1) : ldc;
     if (k == 0) {
@@ -643,6 +685,7 @@ int ozaki_pair_products(int64_t m, int64_t n, int64_t k, const double* A, int64_
     if (!P_out) return -13;
     Carve c;
     if (!carve(pl, c, false, context_workspace())) return OZAKI_STATUS_WORKSPACE;
+    if (c.chunk_pairs < pl.npairs) choose_gemm(pl, c.chunk_pairs);
     hipStream_t stream = ctx().stream;
     const PairOrder order = order_of(pl);
     int rc = run_split(pl, c, A, lda, B, ldb, true, true);

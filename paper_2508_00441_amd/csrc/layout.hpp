@@ -15,6 +15,7 @@ constexpr int TILE = 256;
 constexpr int CHUNK_BYTES = 64;           // bytes of the inner dimension per row staged per pipeline step (FP8, FP16)
 constexpr int CHUNK_BYTES_FP6 = 48;       // the same 64 inner indices as 6-bit codes
 constexpr int TILE_ELEMS = TILE * TILE;
+constexpr int QUAD = 128;                 // edge of a workgroup's block in the small-problem GEMM kernel
 
 // slice formats (values of ozaki_slice_format)
 constexpr int FMT_FP8 = 0, FMT_FP16 = 1, FMT_FP6 = 2, FMT_FP6_E3M2 = 3, FMT_INT8 = 4;     // FMT_FP6 is E2M3
@@ -75,6 +76,7 @@ struct Plan {
     int group_len;        // pairs per group of the GEMM kernel, <= run_limit (PairOrder::run_limit of the launches)
     int64_t tiles_m, tiles_n;
     int64_t m_pad, n_pad;
+    int small_tiles;      // 1: the GEMMs run in 128 x 128 blocks (launch_pair_gemm_small)
     int p_is_int;         // 1: the stored products are INT32 words (INT8 slices), 0: FP32
 };
 
@@ -111,27 +113,77 @@ struct Pass {
     int npairs, ngroups;
 };
 
-// The gi-th group of a pass: slices (p0 + j, q0 - j), j < len (1-based), first product slot `slot`.
+// Products of the anti-diagonals 2 .. g.
+__host__ __device__ inline int pairs_up_to_diag(const PairOrder& o, int g) {
+    return g <= o.s + 1 ? g * (g - 1) / 2 : o.s * o.s - (2 * o.s - g) * (2 * o.s + 1 - g) / 2;
+}
+
+// The gi-th group of a pass: slices (p0 + j, q0 - j), j < len (1-based), first product slot `slot`.  Groups are numbered
+// from the longest anti-diagonal of the pass outwards (g = s+1, s, s+2, s-1, ...), so that the workgroups with the most
+// work start first; the product slots keep the accumulation order.
 struct Group {
     int p0, q0, len, slot;
 };
 __host__ __device__ inline Group pass_group(const PairOrder& o, const Pass& ps, int gi) {
-    int slot = 0;
-    for (int g = ps.g_hi; g >= ps.g_lo; --g) {
-        const int len = diag_len(o, g), ng = (len + o.run_limit - 1) / o.run_limit;
-        if (gi < ng) {
-            const int pos = gi * o.run_limit;
-            Group r;
-            r.p0 = diag_first_p(o, g) + pos;
-            r.q0 = g - r.p0;
-            r.len = len - pos < o.run_limit ? len - pos : o.run_limit;
-            r.slot = slot + pos;
-            return r;
+    for (int d = 0; d < o.s; ++d)
+        for (int side = 0; side < 2; ++side) {
+            const int g = side == 0 ? o.s + 1 - d : o.s + 1 + d;
+            if (g < ps.g_lo || g > ps.g_hi || (side == 1 && d == 0)) continue;
+            const int len = diag_len(o, g), ng = (len + o.run_limit - 1) / o.run_limit;
+            if (gi < ng) {
+                const int pos = gi * o.run_limit;
+                Group r;
+                r.p0 = diag_first_p(o, g) + pos;
+                r.q0 = g - r.p0;
+                r.len = len - pos < o.run_limit ? len - pos : o.run_limit;
+                r.slot = pairs_up_to_diag(o, ps.g_hi) - pairs_up_to_diag(o, g) + pos;
+                return r;
+            }
+            gi -= ng;
         }
-        gi -= ng;
-        slot += len;
-    }
     return Group{1, 1, 0, 0};
+}
+
+// Which work item (group gi, block (bm, bn) of blocks_m x blocks_n) workgroup b of `total` takes.  Workgroups are handed to
+// the eight XCDs, each with an L2 of its own, round-robin by their index.  unit == 0: plain order, block rows fastest.
+// Otherwise the `unit` workgroups an XCD runs at the same time get consecutive items, and consecutive items of a group walk
+// strips of `height` block rows column by column, so that they form a compact patch that shares its slice panels.
+// Groups come longest first, so every second round deals the units in reverse order to keep the XCDs even.
+struct WorkOrder {
+    int unit, height;
+};
+struct WorkItem {
+    unsigned gi, bm, bn;
+};
+__host__ __device__ inline WorkItem work_item(unsigned b, unsigned total, const WorkOrder& o, unsigned blocks_m, unsigned blocks_n) {
+    unsigned w = b, strip_rows = blocks_m;
+    if (o.unit != 0) {
+        const unsigned unit = o.unit, round = 8 * unit, full = total / round * round, xcd = b & 7;
+        strip_rows = o.height;
+        if (b < full) {
+            const unsigned r = b / round;
+            w = r * round + ((r & 1) ? 7 - xcd : xcd) * unit + ((b - r * round) >> 3);
+        } else {                                   // the last, incomplete round: one contiguous piece per XCD
+            const unsigned rest = total - full, each = rest >> 3, more = rest & 7;
+            w = full + xcd * each + (xcd < more ? xcd : more) + ((b - full) >> 3);
+        }
+    }
+    WorkItem it;
+    it.gi = w / (blocks_m * blocks_n);
+    const unsigned r = w - it.gi * (blocks_m * blocks_n), strip = r / (strip_rows * blocks_n), in = r - strip * strip_rows * blocks_n;
+    const unsigned left = blocks_m - strip_rows * strip, height = left < strip_rows ? left : strip_rows;
+    it.bn = in / height;
+    it.bm = strip_rows * strip + (in - it.bn * height);
+    return it;
+}
+// The order for a launch of `total` workgroups of which `per_xcd` run at a time on an XCD.  Measured against the plain order:
+// 4096^3 FP8 4.08 -> 4.01 ms, 2048^3 FP16 in blocks of 1024 0.83 -> 0.78 ms, 600 x 600 x 1000 (128 x 128 blocks) 43 -> 35 us.
+// The plain order stays where it already gives every XCD a compact patch (32 block rows: four of them per XCD; strips
+// lose 2.5 % at 16384^2 FP16 there) and where a launch has few rounds of groups of unequal length (1024^3, all pairs:
+// 112 us plain, 138 us in strips, because a unit's XCD waits for its longest group).
+__host__ __device__ inline WorkOrder work_order(int64_t total, int per_xcd, int64_t blocks_m, int group_len) {
+    if (blocks_m % 32 == 0 || (group_len > 4 && total < 64 * (int64_t)per_xcd)) return WorkOrder{0, 0};
+    return WorkOrder{per_xcd, blocks_m > 8 ? 4 : 8};
 }
 
 // True if, for every element of a 32 x 32 tile, pair (p+1, q-1) carries the same scale factor 2^(cA + cB) as pair
@@ -186,6 +238,9 @@ hipError_t launch_deltas(const Plan& pl, const Operand* op0, const Operand* op1,
 // stored in the slot of the run's first pair; the slots of the other pairs of the run are left untouched.
 hipError_t launch_pair_gemm(const Plan& pl, const Operand& A, const Operand& B, const PairOrder& order, const Pass& ps,
                             bool allow_chain, int64_t t, float* P, hipStream_t st);
+// The same in 128 x 128 blocks (Plan::small_tiles; called by launch_pair_gemm).  Blocks without real elements are left out.
+hipError_t launch_pair_gemm_small(const Plan& pl, const Operand& A, const Operand& B, const PairOrder& order, const Pass& ps,
+                                  bool allow_chain, int64_t t, float* P, hipStream_t st);
 
 // Accumulate the pairs of pass `ps` of block t.  S_io: running block sum in accumulator order (read unless the
 // pass is the block's first, written unless it is the last): one 64-bit word per element (FP64 bits), three in the

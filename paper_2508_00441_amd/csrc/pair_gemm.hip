@@ -60,6 +60,7 @@ struct GemmArgs {
     int64_t chunks;
     int tiles_m, tiles_n;
     int allow_chain;
+    WorkOrder work;
     const int32_t* da;       // A deltas of the block: [s][rows_pad_a / 32]
     const int32_t* db;       // B deltas of the block: [s][rows_pad_b / 32]
     PairOrder order;
@@ -105,11 +106,9 @@ __global__ void __launch_bounds__(256) pair_gemm_kernel(const GemmArgs a) {
     const int wn = wave >> 1, wm = wave & 1;
 
     // one workgroup = one tile of one group of pairs (p0 + j, q0 - j), j < glen
-    const int tiles = a.tiles_m * a.tiles_n;
-    const int gi = blockIdx.x / tiles;
-    const int tile = blockIdx.x - gi * tiles;
-    const int tn = tile / a.tiles_m, tm = tile - tn * a.tiles_m;
-    const Group grp = pass_group(a.order, a.pass, gi);
+    const WorkItem item = work_item(blockIdx.x, gridDim.x, a.work, a.tiles_m, a.tiles_n);
+    const int tn = item.bn, tm = item.bm;
+    const Group grp = pass_group(a.order, a.pass, item.gi);
     const int glen = grp.len, p0 = grp.p0 - 1, q0 = grp.q0 - 1;       // 0-based slice indices from here on
     const int chunks = (int)a.chunks;
     // Whether pair jp+1 of the group keeps accumulating on top of pair jp is decided per MFMA tile (i, j) of the wave,
@@ -380,6 +379,7 @@ __global__ void __launch_bounds__(256) pair_gemm_kernel(const GemmArgs a) {
 hipError_t launch_pair_gemm(const Plan& pl, const Operand& A, const Operand& B, const PairOrder& order, const Pass& ps,
                             bool allow_chain, int64_t t, float* P, hipStream_t st) {
     if (ps.ngroups <= 0 || pl.tiles_m == 0 || pl.tiles_n == 0 || pl.chunks == 0) return hipSuccess;
+    if (pl.small_tiles) return launch_pair_gemm_small(pl, A, B, order, ps, allow_chain, t, P, st);
     GemmArgs a;
     const size_t slice_a = (size_t)pl.chunks * A.rows_pad * pl.row_bytes, slice_b = (size_t)pl.chunks * B.rows_pad * pl.row_bytes;
     a.sa = A.slices + (size_t)t * pl.s * slice_a;
@@ -393,6 +393,7 @@ hipError_t launch_pair_gemm(const Plan& pl, const Operand& A, const Operand& B, 
     a.order = order; a.pass = ps;
     const int64_t blocks = (int64_t)ps.ngroups * pl.tiles_m * pl.tiles_n;
     if (blocks > 0x7FFFFFFF || pl.chunks > 0x7FFFFFFF) return hipErrorInvalidValue;
+    a.work = work_order(blocks, 32, a.tiles_m, order.run_limit);
     if (pl.fmt == FMT_FP16) hipLaunchKernelGGL((pair_gemm_kernel<FMT_FP16>), dim3((unsigned)blocks), dim3(256), 0, st, a);
     else if (pl.fmt == FMT_FP6) hipLaunchKernelGGL((pair_gemm_kernel<FMT_FP6>), dim3((unsigned)blocks), dim3(256), 0, st, a);
     else if (pl.fmt == FMT_FP6_E3M2) hipLaunchKernelGGL((pair_gemm_kernel<FMT_FP6_E3M2>), dim3((unsigned)blocks), dim3(256), 0, st, a);
