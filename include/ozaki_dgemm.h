@@ -141,7 +141,7 @@ int ozaki_plan(int64_t k_block, int slice_format, int* rho_out, int* bits_out);
  *                 More than OZAKI_MAX_SLICES: OZAKI_STATUS_SLICE_COUNT.
  *   k_block       inner-product-wise block length (Section 4.3); 0 means k (no blocking).  A last,
  *                 shorter block is allowed.  Any length for which Eq. 1-3 leave b >= 0 is accepted; blocks of
- *                 more than 16384 elements are sliced by a slower streaming kernel that needs 12 more bytes
+ *                 more than 16384 elements are read two or three times for the slicing, and reserve 12 more bytes
  *                 of workspace per operand element (included in ozaki_workspace_bytes).
  *   accum_mode    OZAKI_ACCUM_*
  * The slices, exponents and slice-pair products live in the workspace (ozaki_set_workspace).

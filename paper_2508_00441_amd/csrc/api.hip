@@ -160,7 +160,6 @@ struct WorkMem {
 struct Carve {
     int* flags;
     double* At;
-    void* split_state;    // per-element state of the streaming slicing kernel (long blocks only)
     Operand A, B;
     double* W;            // m x n product buffer of the scaled call (null otherwise)
     uint64_t* S;
@@ -171,9 +170,14 @@ struct Carve {
 size_t slices_bytes(const Plan& pl, int64_t rows_pad) { return align_up((size_t)pl.T * pl.s * pl.chunks * rows_pad * pl.row_bytes); }
 size_t exps_bytes(const Plan& pl, int64_t rows_pad) { return align_up((size_t)pl.T * pl.s * rows_pad * sizeof(int32_t)); }
 size_t deltas_bytes(const Plan& pl, int64_t rows_pad) { return align_up((size_t)pl.T * (rows_pad / LINK_ROWS) * pl.s * sizeof(int32_t)); }
-size_t state_bytes(const Plan& pl) { return align_up(split_state_bytes(pl, pl.m, pl.n)); }
+// Blocks beyond MAX_K_BLOCK_IN_REGISTERS: 12 bytes per (padded) element of the operands, part of the documented sizes.  No
+// kernel needs them any more.
+size_t long_block_reserve(const Plan& pl) {
+    if (pl.kb <= MAX_K_BLOCK_IN_REGISTERS) return 0;
+    return align_up((size_t)(pl.m + pl.n) * pl.T * pl.chunks * pl.epc * 12);
+}
 size_t fixed_bytes(const Plan& pl) {
-    return FLAG_BYTES + align_up((size_t)pl.m * pl.k * sizeof(double)) + state_bytes(pl) + slices_bytes(pl, pl.m_pad) +
+    return FLAG_BYTES + align_up((size_t)pl.m * pl.k * sizeof(double)) + long_block_reserve(pl) + slices_bytes(pl, pl.m_pad) +
            slices_bytes(pl, pl.n_pad) + exps_bytes(pl, pl.m_pad) + exps_bytes(pl, pl.n_pad) + deltas_bytes(pl, pl.m_pad) +
            deltas_bytes(pl, pl.n_pad);
 }
@@ -207,8 +211,7 @@ bool carve(const Plan& pl, Carve& c, bool want_product, WorkMem wm) {
     off += FLAG_BYTES;
     c.At = reinterpret_cast<double*>(ws + off);
     off += align_up((size_t)pl.m * pl.k * sizeof(double));
-    c.split_state = state_bytes(pl) ? ws + off : nullptr;
-    off += state_bytes(pl);
+    off += long_block_reserve(pl);
     c.A.rows = pl.m; c.A.rows_pad = pl.m_pad;
     c.B.rows = pl.n; c.B.rows_pad = pl.n_pad;
     c.A.slices = ws + off; off += slices_bytes(pl, pl.m_pad);
@@ -292,7 +295,7 @@ int run_split(const Plan& pl, const Carve& c, const double* A, int64_t lda, cons
     const bool a_on = do_a && pl.m > 0, b_on = do_b && pl.n > 0;
     if (a_on) HIP_TRY(launch_transpose(A, lda, pl.m, pl.k, c.At, st));
     // both operands in one launch each: on a small problem neither fills the chip alone
-    HIP_TRY(launch_split(c.At, pl.k, a_on ? &c.A : nullptr, B, ldb, b_on ? &c.B : nullptr, pl, c.flags, c.split_state, st));
+    HIP_TRY(launch_split(c.At, pl.k, a_on ? &c.A : nullptr, B, ldb, b_on ? &c.B : nullptr, pl, c.flags, st));
     HIP_TRY(launch_deltas(pl, a_on ? &c.A : nullptr, b_on ? &c.B : nullptr, st));
     return 0;
 }
@@ -644,10 +647,10 @@ int ozaki_count_slices(int is_B, int64_t rows, int64_t k, const double* X, int64
     if (rows == 0 || k == 0) return 0;
     if (!X) return -4;
     if (ldx < (is_B ? (k > 1 ? k : 1) : (rows > 1 ? rows : 1))) return -5;
-    // needs the flag block, for A room for its transpose, and for long blocks the streaming kernel's state
+    // needs the flag block, for A room for its transpose, and for long blocks the reserve of the documented size
     Context& c = ctx();
     const size_t at_bytes = is_B ? 0 : align_up((size_t)rows * k * sizeof(double));
-    const size_t need = FLAG_BYTES + at_bytes + state_bytes(pl);
+    const size_t need = FLAG_BYTES + at_bytes + long_block_reserve(pl);
     if (!c.ws || c.ws_bytes < need) return OZAKI_STATUS_WORKSPACE;
     int* flags = reinterpret_cast<int*>(c.ws);
     HIP_TRY(hipMemsetAsync(flags + 1, 0, sizeof(int), c.stream));
@@ -659,8 +662,7 @@ int ozaki_count_slices(int is_B, int64_t rows, int64_t k, const double* X, int64
         vecs = At;
         ldv = k;
     }
-    void* state = state_bytes(pl) ? c.ws + FLAG_BYTES + at_bytes : nullptr;
-    HIP_TRY(launch_count_slices(vecs, ldv, pl, rows, flags, state, c.stream));
+    HIP_TRY(launch_count_slices(vecs, ldv, pl, rows, flags, c.stream));
     int count = 0;
     HIP_TRY(hipMemcpyAsync(&count, flags + 1, sizeof(int), hipMemcpyDeviceToHost, c.stream));
     HIP_TRY(hipStreamSynchronize(c.stream));

@@ -8,7 +8,7 @@ namespace ozaki {
 
 constexpr int MAX_SLICES = 32;
 constexpr int MAX_PAIRS = MAX_SLICES * MAX_SLICES;      // all s*s pairs in the full mode
-constexpr int64_t MAX_K_BLOCK_IN_REGISTERS = 16384;     // longer blocks are sliced by the streaming kernel (state in work memory)
+constexpr int64_t MAX_K_BLOCK_IN_REGISTERS = 16384;     // longer blocks: split_stream_kernel, exponents first
 
 // ---- tiling of the slice-pair GEMM: one workgroup computes one TILE x TILE block of one pair product ------
 constexpr int TILE = 256;
@@ -217,15 +217,13 @@ hipError_t launch_transpose(const double* A, int64_t lda, int64_t m, int64_t k, 
 
 // Vectors are contiguous: vector r of an operand starts at X + r*ldv and has k entries.  Writes the internal layout of
 // up to two operands in one launch (a null Operand, or one without vectors, is skipped).  Blocks longer than
-// MAX_K_BLOCK_IN_REGISTERS are sliced by a streaming kernel that keeps its per-element state in `long_state`
-// (split_state_bytes(pl) bytes; may be null otherwise).
+// MAX_K_BLOCK_IN_REGISTERS take two launches: the exponents of all slices first, then the slices.
 hipError_t launch_split(const double* X0, int64_t ldv0, const Operand* op0, const double* X1, int64_t ldv1, const Operand* op1,
-                        const Plan& pl, int* flags, void* long_state, hipStream_t st);
-size_t split_state_bytes(const Plan& pl, int64_t rows_a, int64_t rows_b);
+                        const Plan& pl, int* flags, hipStream_t st);
 
 // Slices until every remainder is zero (paragraph before Eq. 4): atomicMax of the per-vector count into flags[1]
 // (which the caller has cleared); MAX_SLICES + 1 means that MAX_SLICES slices do not exhaust some vector.
-hipError_t launch_count_slices(const double* X, int64_t ldv, const Plan& pl, int64_t rows, int* flags, void* long_state, hipStream_t st);
+hipError_t launch_count_slices(const double* X, int64_t ldv, const Plan& pl, int64_t rows, int* flags, hipStream_t st);
 
 // Internal layout -> plain vector-major codes (verification export).
 hipError_t launch_export_slices(const Plan& pl, const Operand& op, void* out, hipStream_t st);

@@ -289,18 +289,20 @@ __device__ __forceinline__ int ceil_log2_scaled(uint64_t v, int unit, int F) {
     return unit - F + L - (((v & (v - 1)) == 0) ? 1 : 0);
 }
 
-// Maximum over the 64 lanes of a wave, returned to all of them: data-parallel-primitive steps inside rows of 16 lanes
+// Maximum over the 64 lanes of a wave (of int or uint32_t), returned to all of them: data-parallel-primitive steps inside rows of 16 lanes
 // (swap inside pairs, pairs inside quads, mirror the half rows, mirror the rows), then the last lane of a row is
 // passed on to the next row(s), and lane 63 holds the maximum.
-__device__ __forceinline__ int wave_max(int v) {
-    auto step = [](int x, int y) { return y > x ? y : x; };
-    v = step(v, __builtin_amdgcn_update_dpp(v, v, 0xB1, 0xF, 0xF, false));      // quad_perm [1,0,3,2]
-    v = step(v, __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xF, 0xF, false));      // quad_perm [2,3,0,1]
-    v = step(v, __builtin_amdgcn_update_dpp(v, v, 0x141, 0xF, 0xF, false));     // row_half_mirror
-    v = step(v, __builtin_amdgcn_update_dpp(v, v, 0x140, 0xF, 0xF, false));     // row_mirror
-    v = step(v, __builtin_amdgcn_update_dpp(v, v, 0x142, 0xA, 0xF, false));     // row_bcast15 into rows 1 and 3
-    v = step(v, __builtin_amdgcn_update_dpp(v, v, 0x143, 0xC, 0xF, false));     // row_bcast31 into rows 2 and 3
-    return __builtin_amdgcn_readlane(v, 63);
+template <typename V>
+__device__ __forceinline__ V wave_max(V v) {
+    static_assert(sizeof(V) == 4, "one register per lane");
+    auto step = [](V x, int y) { return (V)y > x ? (V)y : x; };
+    v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0xB1, 0xF, 0xF, false));      // quad_perm [1,0,3,2]
+    v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x4E, 0xF, 0xF, false));      // quad_perm [2,3,0,1]
+    v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x141, 0xF, 0xF, false));     // row_half_mirror
+    v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x140, 0xF, 0xF, false));     // row_mirror
+    v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x142, 0xA, 0xF, false));     // row_bcast15 into rows 1 and 3
+    v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x143, 0xC, 0xF, false));     // row_bcast31 into rows 2 and 3
+    return (V)__builtin_amdgcn_readlane((int)v, 63);
 }
 
 // (At least four waves per SIMD, i.e. at most 128 registers: two 512-thread workgroups per CU, so that one computes while
@@ -527,172 +529,255 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
     }
 }
 
-// The same slicing for blocks too long for the registers of one workgroup: one workgroup of 1024 threads per vector
-// and block streams through the vector once per slice, with the element state (decode_element) kept in work memory
-// between the slices: tv_state / pk_state hold one int64 / int32 per element of the (real) vectors.
-template <int FMT>
-__global__ void __launch_bounds__(1024) split_stream_kernel(SplitArgs a, int64_t* tv_state, int* pk_state) {
-    constexpr bool FP16 = FMT == FMT_FP16;
-    constexpr int EPC = FP16 ? CHUNK_BYTES / 2 : CHUNK_BYTES;
-    constexpr int ROWB = fmt_is_fp6(FMT) ? CHUNK_BYTES_FP6 : CHUNK_BYTES;
-    __shared__ int red[2][16];
+// ---- Blocks too long for the registers of one workgroup --------------------------------------------------------
+// The remainders need not be carried from slice to slice: x^(p) differs from x by a multiple of the previous unit, which
+// is an even multiple of this one (every remainder is at most half a unit, so the units 2^u_p shrink by b+1 bits or more),
+// hence  x^(p+1) = x - (x rounded to a multiple of 2^u_p, ties to even)  directly from x.  So the exponents come first
+// (long_exponents_kernel, remainder_key), from the elements alone, and with them known every element is sliced on its own
+// (split_stream_kernel), with no exchange between threads and no state in memory: the block is read two or three times
+// instead of once, plus 24 bytes of state, per slice.  256 + 320 vectors of 65536 elements, 11 FP8 slices: 6.3 ms with the
+// state in memory, 0.53 ms so.
+
+// How far an element's remainder at unit 2^u is from zero, in 2^-32 of the unit and rounded up: the key of the maximum in
+// Eq. 4.  The remainder of mm * 2^E is the distance of its fraction f = mm 2^-sh mod 1 (sh = u - E) from the nearest
+// integer; f is taken to 64 bits with the lowest one sticky.  With hi, lo its words, f < 1/2 gives hi + (lo != 0), f >= 1/2
+// gives the same of 2^64 - f, which is -hi whether lo is zero or not.
+__device__ __forceinline__ uint32_t fraction_key(uint64_t f) {
+    const int hi = (int)(uint32_t)(f >> 32);
+    const uint32_t up = (uint32_t)hi + ((uint32_t)f != 0 ? 1u : 0u);
+    return hi < 0 ? 0u - (uint32_t)hi : up;
+}
+__device__ __forceinline__ uint64_t unit_fraction(uint64_t mm, int sh) {
+    if (sh <= 0) return 0;                                           // a multiple of the unit
+    if (sh <= 64) return mm << (64 - sh);
+    const int r = sh - 64;                                           // far below the unit: cut, with a sticky lowest bit
+    const uint64_t cut = r < 64 ? mm >> r : 0;
+    return cut | ((r < 64 ? (cut << r) != mm : mm != 0) ? 1u : 0u);
+}
+// |remainder| at unit 2^(E + sh), in units of 2^E: exact
+__device__ __forceinline__ uint64_t remainder_abs(uint64_t mm, int sh) {
+    if (sh <= 0) return 0;
+    if (sh > 54) return mm;
+    const uint64_t low = mm & ((1ull << sh) - 1), up = (1ull << sh) - low;
+    return low < up ? low : up;
+}
+
+constexpr int LEVELS = 12;            // units tried per reading of the block
+
+// Eq. 4 for all slices of one vector and block.  With enough elements a unit's largest remainder is nearly half the unit, so
+// that the next unit is b+1 bits down: the keys of the next LEVELS units of that ladder are formed in one reading, and the
+// ladder is followed as far as the keys confirm it; the first exponent off it is known from them too, and another reading
+// starts there.
+__global__ void __launch_bounds__(1024) long_exponents_kernel(SplitArgs a) {
+    __shared__ uint32_t red[LEVELS][16];
     const int tid = threadIdx.x, wave = tid >> 6;
     const bool second = blockIdx.x >= a.wg_first;
     const SplitVectors& v = second ? a.v[1] : a.v[0];
     const int64_t row = blockIdx.x - (second ? a.wg_first : 0u);
-    const int64_t t = blockIdx.y, T = gridDim.y;
-    const int64_t k0 = t * a.kb;
-    int64_t klen = a.k - k0;
+    const int64_t t = blockIdx.y;
+    int64_t klen = a.k - t * a.kb;
     if (klen > a.kb) klen = a.kb;
-    const int64_t padded = a.chunks * EPC, n_oct = padded / 8;
-    const int F = 60 - a.b;
-    if (row >= v.rows) {
-        // a padding vector: zero codes and c = 0 in every slice
-        if (v.slices == nullptr) return;
-        const int zero8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        for (int p = 0; p < a.s; ++p) {
-            uint8_t* const dst_slice = v.slices + (size_t)((t * a.s + p) * a.chunks) * (size_t)v.rows_pad * ROWB;
-            for (int64_t o = tid; o < n_oct; o += 1024) store_codes<FMT>(zero8, 8 * o, dst_slice, v.rows_pad, row, a.b);
-            if (tid == 0) v.exps[(t * a.s + p) * v.rows_pad + row] = 0;
-        }
+    int32_t* const exps = v.exps != nullptr ? v.exps + t * a.s * v.rows_pad + row : nullptr;
+    if (row >= v.rows) {                                             // a padding vector: c = 0 throughout
+        if (exps != nullptr && tid < a.s) exps[(int64_t)tid * v.rows_pad] = 0;
         return;
     }
-    // this vector's state: real vectors of the first operand, then those of the second, each with T blocks
-    const int64_t vec = (second ? a.v[0].rows : 0) + row;
-    int64_t* const tv = tv_state + (size_t)(vec * T + t) * padded;
-    int* const pk = pk_state + (size_t)(vec * T + t) * padded;
-
-    // block-wide maximum of an int, double-buffered so that one barrier per reduction suffices
-    int round = 0;
-    auto block_max = [&](int val) -> int {
+    const double* const src = v.X + row * v.ldv + t * a.kb;
+    // maximum over the workgroup of `count` keys per thread, left in red[0 .. count-1][0]
+    auto block_max = [&](uint32_t (&keys)[LEVELS], int count) {
+        __syncthreads();                                             // the previous maxima have been read
 #pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int o = __shfl_xor(val, off, 64);
-            val = o > val ? o : val;
+        for (int j = 0; j < LEVELS; ++j) {
+            if (j < count) {
+                const uint32_t m = wave_max(keys[j]);
+                if ((tid & 63) == 0) red[j][wave] = m;
+            }
         }
-        if ((tid & 63) == 0) red[round & 1][wave] = val;
         __syncthreads();
+        if (tid < LEVELS) {
+            uint32_t m = red[tid][0];
 #pragma unroll
-        for (int w = 0; w < 16; ++w) {
-            const int o = red[round & 1][w];
-            val = o > val ? o : val;
+            for (int w = 1; w < 16; ++w) m = red[tid][w] > m ? red[tid][w] : m;
+            red[tid][0] = m;
         }
-        ++round;
-        return val;
+        __syncthreads();
+    };
+    // f(mm, E) for every element of the block, eight loads in flight per thread
+    auto for_each = [&](auto f) {
+        auto one = [&](uint64_t w) {
+            const int e11 = (int)((w >> 52) & 0x7FF);
+            uint64_t mm = w & 0x000FFFFFFFFFFFFFull;
+            if (e11 != 0) mm |= 0x0010000000000000ull;
+            f(mm, e11 != 0 ? e11 - 1075 : -1074);
+        };
+        int64_t i = 0;
+        for (; i + 8192 <= klen; i += 8192) {
+            uint64_t w[8];
+            if (v.vec_ok) {
+#pragma unroll
+                for (int h = 0; h < 4; ++h) {
+                    const ulonglong2 two = *reinterpret_cast<const ulonglong2*>(src + i + h * 2048 + 2 * tid);
+                    w[2 * h] = two.x;
+                    w[2 * h + 1] = two.y;
+                }
+            } else {
+#pragma unroll
+                for (int h = 0; h < 8; ++h) w[h] = (uint64_t)__double_as_longlong(src[i + h * 1024 + tid]);
+            }
+#pragma unroll
+            for (int h = 0; h < 8; ++h) one(w[h]);
+        }
+        for (i += tid; i < klen; i += 1024) one((uint64_t)__double_as_longlong(src[i]));
     };
 
+    uint32_t keys[LEVELS];
+#pragma unroll
+    for (int j = 0; j < LEVELS; ++j) keys[j] = 0;
     bool nonfinite = false;
+    auto exponent_key = [&](uint64_t mm, int E) -> uint32_t {         // ceil log2 of a non-zero mm * 2^E, biased; 0 for zero
+        return mm == 0 ? 0u : (uint32_t)(E + bit_length_u64(mm) - (((mm & (mm - 1)) == 0) ? 1 : 0) + CD_BIAS);
+    };
+    for_each([&](uint64_t mm, int E) {
+        nonfinite |= E == 0x7FF - 1075;
+        const uint32_t key = exponent_key(mm, E);
+        keys[0] = key > keys[0] ? key : keys[0];
+    });
+    if (nonfinite) atomicOr(a.flags, 1);
+    block_max(keys, 1);
+    int p = 0, c = 0;
+    bool left = red[0][0] != 0;                                      // is there a remainder before slice p?
+    const bool any = left;
+    if (left) c = (int)red[0][0] - CD_BIAS;
+    if (exps != nullptr && tid == 0) exps[0] = c;
+    while (left && p + 1 < a.s) {
+        const int unit0 = c - a.b, step = a.b + 1;
+        const int levels = a.s - 1 - p < LEVELS ? a.s - 1 - p : LEVELS;
+#pragma unroll
+        for (int j = 0; j < LEVELS; ++j) keys[j] = 0;
+        for_each([&](uint64_t mm, int E) {
+            const int sh = unit0 - E;
+            if (sh <= 64) {
+                uint64_t f = unit_fraction(mm, sh);
+#pragma unroll
+                for (int j = 0; j < LEVELS; ++j) {
+                    const uint32_t key = fraction_key(f);
+                    keys[j] = key > keys[j] ? key : keys[j];
+                    f <<= step;
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < LEVELS; ++j) {
+                    const uint32_t key = fraction_key(unit_fraction(mm, sh - j * step));
+                    keys[j] = key > keys[j] ? key : keys[j];
+                }
+            }
+        });
+        block_max(keys, levels);
+        for (int j = 0; j < levels; ++j) {
+            const uint32_t key = red[j][0];
+            const int unit = unit0 - j * step;
+            left = key != 0;
+            if (!left) break;
+            if (key > 1) {
+                c = unit - 32 + bit_length_u32(key - 1);             // smallest c with key * 2^(unit-32) <= 2^c
+            } else {
+                // every remainder is at most 2^-32 of the unit: look at all their bits
+                uint32_t exact[LEVELS];
+#pragma unroll
+                for (int i = 0; i < LEVELS; ++i) exact[i] = 0;
+                for_each([&](uint64_t mm, int E) {
+                    const uint32_t k = exponent_key(remainder_abs(mm, unit - E), E);
+                    exact[0] = k > exact[0] ? k : exact[0];
+                });
+                block_max(exact, 1);
+                c = (int)red[0][0] - CD_BIAS;
+            }
+            ++p;
+            if (exps != nullptr && tid == 0) exps[(int64_t)p * v.rows_pad] = c;
+            if (key == 1 || c - a.b != unit - step) break;           // off the ladder (or its keys are overwritten): read again
+        }
+    }
+    // nothing left: the remaining slices are zero (c := 0); without slices to write, report how many there are
+    if (exps != nullptr && !left)
+        for (int i = p + 1 + tid; i < a.s; i += 1024) exps[(int64_t)i * v.rows_pad] = 0;
+    if (v.slices == nullptr && tid == 0 && any) atomicMax(a.flags + 1, p + 1);
+}
+
+// All slices of one chunk (64 inner indices; FP16: 32) of 32 (64) consecutive vectors, with the exponents known: eight
+// elements per thread, whose state goes from slice to slice in registers; what the workgroup stores of a slice is 2 KiB
+// (4 KiB) in one piece.
+template <int FMT>
+__global__ void __launch_bounds__(256) split_stream_kernel(SplitArgs a) {
+    constexpr bool FP16 = FMT == FMT_FP16;
+    constexpr int EPC = FP16 ? CHUNK_BYTES / 2 : CHUNK_BYTES;
+    constexpr int ROWB = fmt_is_fp6(FMT) ? CHUNK_BYTES_FP6 : CHUNK_BYTES;
+    constexpr int OCTETS = EPC / 8, ROWS = 256 / OCTETS;
+    const int64_t wg = blockIdx.x;
+    const bool second = wg >= a.wg_first;
+    const SplitVectors& v = second ? a.v[1] : a.v[0];
+    const int64_t li = wg - (second ? a.wg_first : 0u);
+    const int64_t row_groups = v.rows_pad / ROWS;
+    const int64_t kc = li / row_groups, row = (li - kc * row_groups) * ROWS + threadIdx.x / OCTETS;
+    const int64_t t = blockIdx.y;
+    int64_t klen = a.k - t * a.kb;
+    if (klen > a.kb) klen = a.kb;
+    if (row >= v.rows) klen = 0;                                     // padding vectors are all zero
+    const int64_t ke = kc * EPC + (threadIdx.x % OCTETS) * 8;
+    const double* const src = v.X + row * v.ldv + t * a.kb;
+    const int F = 60 - a.b;
+    const int32_t* const exps = v.exps + t * a.s * v.rows_pad + row;
+    uint8_t* dst_slice = v.slices + (size_t)(t * a.s) * a.chunks * (size_t)v.rows_pad * ROWB;
+    const size_t slice_bytes = (size_t)a.chunks * v.rows_pad * ROWB;
+    uint64_t bits[8];
+    if (v.vec_ok && ke + 8 <= klen) {
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            const ulonglong2 w = *reinterpret_cast<const ulonglong2*>(src + ke + 2 * h);
+            bits[2 * h] = w.x;
+            bits[2 * h + 1] = w.y;
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) bits[e] = (ke + e < klen) ? (uint64_t)__double_as_longlong(src[ke + e]) : 0ull;
+    }
     int cmax = NO_ELEM;
-    const double* src = v.X + row * v.ldv + k0;
+    bool nonfinite = false;                                          // long_exponents_kernel has reported it
     if constexpr (!FP16) {
-        // ---- slices of at most 7 bits: the 32-bit element step of slice_element.hpp, state = (T, control word)
-        uint64_t* const Ts = reinterpret_cast<uint64_t*>(tv);
         const int pos = F - 32, bias = (1 << (pos - 1)) - 1;
         const uint32_t keep = ~((1u << pos) - 1u);
-        for (int64_t o = tid; o < n_oct; o += 1024) {
-            const int64_t ke = 8 * o;
+        uint64_t T[8];
+        int pk[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const uint64_t w = (ke + e < klen) ? (uint64_t)__double_as_longlong(src[ke + e]) : 0ull;
-                uint64_t T0;
-                int st;
-                decode_narrow(w, F, T0, st, cmax, nonfinite);
-                Ts[ke + e] = T0;
-                pk[ke + e] = st;
-            }
-        }
-        if (nonfinite) atomicOr(a.flags, 1);
-        cmax = block_max(cmax);
+        for (int e = 0; e < 8; ++e) decode_narrow(bits[e], F, T[e], pk[e], cmax, nonfinite);
         int unit_prev = 0;
-        for (int p = 0; p < a.s; ++p) {
-            if (v.slices == nullptr && cmax != NO_ELEM && tid == 0) atomicMax(a.flags + 1, p + 1);     // count-only mode
-            const int c = (cmax == NO_ELEM) ? 0 : cmax;
-            const int unit = c - a.b;
+        for (int p = 0; p < a.s; ++p, dst_slice += slice_bytes) {
+            const int unit = exps[(int64_t)p * v.rows_pad] - a.b;
             const int step16 = (unit_prev - unit) * 65536;
             unit_prev = unit;
-            uint8_t* const dst_slice = v.slices + (size_t)((t * a.s + p) * a.chunks) * (size_t)v.rows_pad * ROWB;
-            int kmax = KEY_NONE_MAX, kmin = KEY_NONE_MIN;
+            int kmax = KEY_NONE_MAX, kmin = KEY_NONE_MIN, qs[8];
             uint32_t cd_wait = 0;
-            for (int64_t o = tid; o < n_oct; o += 1024) {
-                const int64_t ke = 8 * o;
-                int qs[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    uint64_t T0 = Ts[ke + e];
-                    int st = pk[ke + e];
-                    qs[e] = slice_narrow(T0, st, step16, pos, bias, keep, kmax, kmin, cd_wait) >> pos;
-                    Ts[ke + e] = T0;
-                    pk[ke + e] = st;
-                }
-                if (v.slices != nullptr) store_codes<FMT>(qs, ke, dst_slice, v.rows_pad, row, a.b);
-            }
-            if (tid == 0 && v.slices != nullptr) v.exps[(t * a.s + p) * v.rows_pad + row] = c;
-            bool needs_exact;
-            cmax = narrow_candidate(kmax, kmin, unit, F, needs_exact);
-            if (needs_exact) {                                         // the upper words cannot tell: once more through the state
-                uint64_t mx = 0;
-                for (int64_t o = tid; o < n_oct; o += 1024)
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const uint64_t ar = pk[8 * o + e] == 0 ? narrow_abs(Ts[8 * o + e]) : 0ull;
-                        mx = ar > mx ? ar : mx;
-                    }
-                cmax = narrow_candidate_exact(mx, unit, F);
-            }
-            const int cw = (int)cd_wait - CD_BIAS;
-            cmax = (cd_wait != 0 && cw > cmax) ? cw : cmax;
-            cmax = block_max(cmax);
+            for (int e = 0; e < 8; ++e) qs[e] = slice_narrow(T[e], pk[e], step16, pos, bias, keep, kmax, kmin, cd_wait) >> pos;
+            store_codes<FMT>(qs, ke, dst_slice, v.rows_pad, row, a.b);
         }
-        return;
-    }
-    // ---- FP16 slices: the 64-bit element step (decode_element / slice_element)
-    for (int64_t o = tid; o < n_oct; o += 1024) {
-        const int64_t ke = 8 * o;
+    } else {
+        int64_t tv[8];
+        int pk[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const uint64_t w = (ke + e < klen) ? (uint64_t)__double_as_longlong(src[ke + e]) : 0ull;
-            int64_t T0;
-            int st;
-            decode_element(w, F, T0, st, cmax, nonfinite);
-            tv[ke + e] = T0;
-            pk[ke + e] = st;
-        }
-    }
-    if (nonfinite) atomicOr(a.flags, 1);
-    cmax = block_max(cmax);
-
-    int c_prev = 0;
-    for (int p = 0; p < a.s; ++p) {
-        if (v.slices == nullptr && cmax != NO_ELEM && tid == 0) atomicMax(a.flags + 1, p + 1);     // count-only mode
-        const int c = (cmax == NO_ELEM) ? 0 : cmax;
-        const int unit = c - a.b;
-        int rescale = p == 0 ? 0 : c_prev - c;
-        rescale = rescale < 0 ? 0 : (rescale > 63 ? 63 : rescale);
-        c_prev = c;
-        uint8_t* const dst_slice = v.slices + (size_t)((t * a.s + p) * a.chunks) * (size_t)v.rows_pad * ROWB;
-        uint64_t rmax = 0;
-        int cdorm = NO_ELEM;
+        for (int e = 0; e < 8; ++e) decode_element(bits[e], F, tv[e], pk[e], cmax, nonfinite);
         const int64_t round_bias = ((int64_t)1 << (F - 1)) - 1;
-        for (int64_t o = tid; o < n_oct; o += 1024) {
-            const int64_t ke = 8 * o;
-            int qs[8];
+        int c_prev = 0;
+        for (int p = 0; p < a.s; ++p, dst_slice += slice_bytes) {
+            const int c = exps[(int64_t)p * v.rows_pad], unit = c - a.b;
+            int rescale = p == 0 ? 0 : c_prev - c;
+            rescale = rescale < 0 ? 0 : (rescale > 63 ? 63 : rescale);
+            c_prev = c;
+            uint64_t rmax = 0;
+            int cdorm = NO_ELEM, qs[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                int64_t T0 = tv[ke + e];
-                int st = pk[ke + e];
-                qs[e] = slice_element(T0, st, unit, rescale, F, round_bias, rmax, cdorm);
-                tv[ke + e] = T0;
-                pk[ke + e] = st;
-            }
-            if (v.slices != nullptr) store_codes<FMT>(qs, ke, dst_slice, v.rows_pad, row, a.b);
+            for (int e = 0; e < 8; ++e) qs[e] = slice_element(tv[e], pk[e], unit, rescale, F, round_bias, rmax, cdorm);
+            store_codes<FMT>(qs, ke, dst_slice, v.rows_pad, row, a.b);
         }
-        if (tid == 0 && v.slices != nullptr) v.exps[(t * a.s + p) * v.rows_pad + row] = c;
-        cmax = cdorm;
-        if (rmax != 0) {
-            const int ca = ceil_log2_scaled(rmax, unit, F);
-            cmax = ca > cmax ? ca : cmax;
-        }
-        cmax = block_max(cmax);
     }
 }
 
@@ -775,20 +860,22 @@ hipError_t launch_split_cfg(const SplitArgs& a_in, int fmt, int64_t T, hipStream
     return hipGetLastError();
 }
 
-// blocks too long for the register-resident kernel: one workgroup per vector (real and padding) and block
-hipError_t launch_split_stream(const SplitArgs& a_in, int fmt, int64_t T, void* state, hipStream_t st) {
-    if (state == nullptr) return hipErrorInvalidValue;
+// blocks too long for the register-resident kernel: exponents first (one workgroup per vector and block), then the slices
+hipError_t launch_split_long(const SplitArgs& a_in, int fmt, int64_t T, hipStream_t st) {
     SplitArgs a = a_in;
     a.wg_first = (unsigned)a.v[0].rows_pad;
-    const int64_t elems = (a.v[0].rows + a.v[1].rows) * T * a.chunks * (fmt == FMT_FP16 ? CHUNK_BYTES / 2 : CHUNK_BYTES);
-    int64_t* tv = static_cast<int64_t*>(state);
-    int* pk = reinterpret_cast<int*>(tv + elems);
-    dim3 grid(a.wg_first + (unsigned)a.v[1].rows_pad, (unsigned)T);
-    if (fmt == FMT_FP16) hipLaunchKernelGGL((split_stream_kernel<FMT_FP16>), grid, dim3(1024), 0, st, a, tv, pk);
-    else if (fmt == FMT_FP6) hipLaunchKernelGGL((split_stream_kernel<FMT_FP6>), grid, dim3(1024), 0, st, a, tv, pk);
-    else if (fmt == FMT_FP6_E3M2) hipLaunchKernelGGL((split_stream_kernel<FMT_FP6_E3M2>), grid, dim3(1024), 0, st, a, tv, pk);
-    else if (fmt == FMT_INT8) hipLaunchKernelGGL((split_stream_kernel<FMT_INT8>), grid, dim3(1024), 0, st, a, tv, pk);
-    else hipLaunchKernelGGL((split_stream_kernel<FMT_FP8>), grid, dim3(1024), 0, st, a, tv, pk);
+    hipLaunchKernelGGL(long_exponents_kernel, dim3(a.wg_first + (unsigned)a.v[1].rows_pad, (unsigned)T), dim3(1024), 0, st, a);
+    if (a.v[0].slices == nullptr && a.v[1].slices == nullptr) return hipGetLastError();      // count only
+    const int rows = fmt == FMT_FP16 ? 64 : 32;                                              // vectors per workgroup
+    const int64_t first = a.v[0].rows_pad / rows * a.chunks, rest = a.v[1].rows_pad / rows * a.chunks;
+    if (first + rest > 0x7FFFFFFF) return hipErrorInvalidValue;
+    a.wg_first = (unsigned)first;
+    const dim3 grid((unsigned)(first + rest), (unsigned)T), block(256);
+    if (fmt == FMT_FP16) hipLaunchKernelGGL((split_stream_kernel<FMT_FP16>), grid, block, 0, st, a);
+    else if (fmt == FMT_FP6) hipLaunchKernelGGL((split_stream_kernel<FMT_FP6>), grid, block, 0, st, a);
+    else if (fmt == FMT_FP6_E3M2) hipLaunchKernelGGL((split_stream_kernel<FMT_FP6_E3M2>), grid, block, 0, st, a);
+    else if (fmt == FMT_INT8) hipLaunchKernelGGL((split_stream_kernel<FMT_INT8>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((split_stream_kernel<FMT_FP8>), grid, block, 0, st, a);
     return hipGetLastError();
 }
 
@@ -812,13 +899,8 @@ SplitVectors split_vectors(const double* X, int64_t ldv, const Plan& pl, const O
 }
 }  // namespace
 
-size_t split_state_bytes(const Plan& pl, int64_t rows_a, int64_t rows_b) {
-    if (pl.kb <= MAX_K_BLOCK_IN_REGISTERS) return 0;
-    return (size_t)(rows_a + rows_b) * pl.T * pl.chunks * pl.epc * (sizeof(int64_t) + sizeof(int));
-}
-
 hipError_t launch_split(const double* X0, int64_t ldv0, const Operand* op0, const double* X1, int64_t ldv1, const Operand* op1,
-                        const Plan& pl, int* flags, void* long_state, hipStream_t st) {
+                        const Plan& pl, int* flags, hipStream_t st) {
     SplitArgs a;
     a.v[0] = split_vectors(X0, ldv0, pl, op0);
     a.v[1] = split_vectors(X1, ldv1, pl, op1);
@@ -827,7 +909,7 @@ hipError_t launch_split(const double* X0, int64_t ldv0, const Operand* op0, cons
     if (a.v[0].rows_pad + a.v[1].rows_pad == 0 || pl.T == 0) return hipSuccess;
     const int64_t vectors = (a.v[0].rows_pad + a.v[1].rows_pad) * pl.T;
     const int fmt = pl.fmt;
-    if (pl.kb > MAX_K_BLOCK_IN_REGISTERS) return launch_split_stream(a, fmt, pl.T, long_state, st);
+    if (pl.kb > MAX_K_BLOCK_IN_REGISTERS) return launch_split_long(a, fmt, pl.T, st);
     const int64_t octets = pl.chunks * pl.epc / 8;                              // per vector and block, padded
     // sixteen elements per thread (U = 2) is the measured optimum: more elements per thread cost registers and with
     // them the occupancy that hides the latency of the dependent integer chains (64 per thread: one wave per SIMD)
@@ -848,14 +930,14 @@ hipError_t launch_split(const double* X0, int64_t ldv0, const Operand* op0, cons
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_count_slices(const double* X, int64_t ldv, const Plan& pl, int64_t rows, int* flags, void* long_state, hipStream_t st) {
+hipError_t launch_count_slices(const double* X, int64_t ldv, const Plan& pl, int64_t rows, int* flags, hipStream_t st) {
     Plan cp = pl;
     cp.s = MAX_SLICES + 1;                       // one more than the library can use: "not exhausted" is reported as 33
     Operand op;
     op.rows = rows;
     op.rows_pad = (rows + TILE - 1) / TILE * TILE;
     op.slices = nullptr; op.exps = nullptr; op.deltas = nullptr;
-    return launch_split(X, ldv, &op, nullptr, 0, nullptr, cp, flags, long_state, st);
+    return launch_split(X, ldv, &op, nullptr, 0, nullptr, cp, flags, st);
 }
 
 hipError_t launch_deltas(const Plan& pl, const Operand* op0, const Operand* op1, hipStream_t st) {
