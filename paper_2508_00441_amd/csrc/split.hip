@@ -45,12 +45,16 @@ __global__ void __launch_bounds__(256) transpose_kernel(const double* __restrict
     }
 }
 
+// Two consecutive FP64 bit patterns, loaded with one 16-byte access.  Vectors with an odd leading dimension, or a base address
+// that is only a multiple of 8, put them 8 bytes off a 16-byte boundary: global loads of the GPU need 4-byte alignment only,
+// and the type says 8 to the compiler.  (Eight 8-byte loads per thread, 64 bytes apart from lane to lane, took twice the time.)
+typedef uint64_t two_doubles __attribute__((ext_vector_type(2), aligned(8)));
+
 // One operand of a split launch.
 struct SplitVectors {
     const double* X;       // vector r starts at X + r*ldv
     int64_t ldv;
     int64_t rows, rows_pad;
-    int vec_ok;            // 16-byte aligned loads allowed
     uint8_t* slices;       // null: count only, nothing is stored
     int32_t* exps;
 };
@@ -283,6 +287,21 @@ __device__ __forceinline__ void store_fp6_codes_at_pos(const int (&qs)[8], int p
     *reinterpret_cast<uint16_t*>(dst_slice + slot.at16) = (uint16_t)(slot.low32 ? hi16 : lo32);
 }
 
+// INT8 codes of the eight slice integers given as q * 2^pos: the byte at bit pos of each
+__device__ __forceinline__ void store_int8_codes_at_pos(const int (&qs)[8], int pos, int64_t ke, uint8_t* dst_slice, int64_t v_rows_pad, int64_t row) {
+    uint32_t w[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        w[h] = __builtin_amdgcn_ubfe((uint32_t)qs[4 * h], pos, 8);
+#pragma unroll
+        for (int e = 1; e < 4; ++e) w[h] |= __builtin_amdgcn_ubfe((uint32_t)qs[4 * h + e], pos, 8) << (8 * e);
+    }
+    uint2 v;
+    v.x = w[0];
+    v.y = w[1];
+    *reinterpret_cast<uint2*>(dst_slice + ((size_t)(ke / CHUNK_BYTES) * v_rows_pad + row) * CHUNK_BYTES + ke % CHUNK_BYTES) = v;
+}
+
 // smallest c with v * 2^(unit - F) <= 2^c, for v != 0
 __device__ __forceinline__ int ceil_log2_scaled(uint64_t v, int unit, int F) {
     const int L = 64 - __clzll((long long)v);
@@ -307,6 +326,10 @@ __device__ __forceinline__ V wave_max(V v) {
 
 // (At least four waves per SIMD, i.e. at most 128 registers: two 512-thread workgroups per CU, so that one computes while
 // the other waits at its barrier.)
+// A vector rarely fills its threads: a wave without elements in its second octet leaves that half of the work out, and with
+// one octet per thread (U = 1, TPR = 256) the launch has only the waves that hold elements (4096 + 4096 vectors of 4097
+// elements, nine FP8 slices: 0.40 ms with every octet worked on, 0.35 ms so; 0.36 ms with fewer waves per workgroup there too,
+// whose number should stay a multiple of the four SIMDs).
 template <int U, int TPR, int FMT>
 __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu_waves_per_eu(4))) split_kernel(SplitArgs a) {
     constexpr bool FP16 = FMT == FMT_FP16;
@@ -315,10 +338,12 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
     constexpr int RPB = BLOCK / TPR;                  // vectors per workgroup
     constexpr int EPC = FP16 ? CHUNK_BYTES / 2 : CHUNK_BYTES;   // elements per chunk
     constexpr int ROWB = FP6 ? CHUNK_BYTES_FP6 : CHUNK_BYTES;   // bytes per vector and chunk
-    constexpr int WAVES_PER_ROW = TPR / 64;
+    constexpr bool WHOLE = RPB == 1;                  // the workgroup is one vector, of blockDim.x <= TPR threads
+    constexpr int MAX_WAVES = TPR / 64;
     __shared__ int red[2][BLOCK / 64];
 
-    const int tr = threadIdx.x % TPR;
+    const int tr = WHOLE ? threadIdx.x : threadIdx.x % TPR;
+    const int threads = WHOLE ? blockDim.x : TPR;     // per vector
     // Workgroups are handed to the eight XCDs (each with an L2 of its own) round-robin by their index.  Neighbouring
     // vectors share the cache lines of the slice layout (a line holds the 16-byte pieces of eight vectors in the
     // FP6 planes, the 64-byte chunks of two vectors otherwise), so consecutive vectors go to workgroups of the SAME
@@ -327,7 +352,6 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
     const double* const vX = second ? a.v[1].X : a.v[0].X;
     const int64_t v_ldv = second ? a.v[1].ldv : a.v[0].ldv;
     const int64_t v_rows = second ? a.v[1].rows : a.v[0].rows, v_rows_pad = second ? a.v[1].rows_pad : a.v[0].rows_pad;
-    const int v_vec_ok = second ? a.v[1].vec_ok : a.v[0].vec_ok;
     uint8_t* const v_slices = second ? a.v[1].slices : a.v[0].slices;
     int32_t* const v_exps = second ? a.v[1].exps : a.v[0].exps;
     const unsigned li = blockIdx.x - (second ? a.wg_first : 0u);     // index and count inside the operand's part of the
@@ -340,6 +364,24 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
     if (klen > a.kb) klen = a.kb;
     if (row >= v_rows) klen = 0;                      // padding vectors are all zero
     const int64_t padded = a.chunks * EPC;
+    if (wg * RPB >= v_rows) {                         // padding vectors only: zero codes and c = 0 in every slice
+        if (v_slices == nullptr) return;
+        const int zero8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        for (int p = 0; p < a.s; ++p) {
+            uint8_t* const dst = v_slices + (size_t)((t * a.s + p) * a.chunks) * (size_t)v_rows_pad * ROWB;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t ke = 8 * ((int64_t)tr + (int64_t)threads * u);
+                if (ke < padded) store_codes<FMT>(zero8, ke, dst, v_rows_pad, row, a.b);
+            }
+            if (tr == 0) v_exps[(t * a.s + p) * v_rows_pad + row] = 0;
+        }
+        return;
+    }
+    if (WHOLE && MAX_WAVES > 1) {
+        if (threadIdx.x < 2 * MAX_WAVES) red[threadIdx.x / MAX_WAVES][threadIdx.x % MAX_WAVES] = NO_ELEM;
+        __syncthreads();
+    }
     // Fixed-point scale of the working representation: an active element holds T = x^(p) / 2^(c_p - b) * 2^F as a
     // signed 64-bit integer.  |x^(p)| <= 2^(c_p) bounds |T| by 2^(b+F) = 2^60.
     const int F = 60 - a.b;
@@ -349,12 +391,11 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
     const double* src = vX + row * v_ldv + k0;
     // the eight FP64 bit patterns of octet u of this thread (zeros beyond the block)
     auto load_octet = [&](int u, uint64_t (&bits)[8]) {
-        const int64_t ke = 8 * ((int64_t)tr + (int64_t)TPR * u);
-        if (v_vec_ok && ke + 8 <= klen) {
-            const ulonglong2* v = reinterpret_cast<const ulonglong2*>(src + ke);
+        const int64_t ke = 8 * ((int64_t)tr + (int64_t)threads * u);
+        if (ke + 8 <= klen) {
 #pragma unroll
             for (int h = 0; h < 4; ++h) {
-                ulonglong2 w = v[h];
+                const two_doubles w = *reinterpret_cast<const two_doubles*>(src + ke + 2 * h);
                 bits[2 * h] = w.x;
                 bits[2 * h + 1] = w.y;
             }
@@ -363,18 +404,22 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
             for (int e = 0; e < 8; ++e) bits[e] = (ke + e < klen) ? __double_as_longlong(src[ke + e]) : 0ull;
         }
     };
+    // does this wave hold elements of the block in octet u?  (wave-uniform)
+    auto wave_has = [&](int u) -> bool {
+        return 8 * ((int64_t)__builtin_amdgcn_readfirstlane(tr & ~63) + (int64_t)threads * u) < padded;
+    };
     // Eq. 4: c = max over the vector of ceil(log2 |x_i|); each thread contributes the maximum over its elements
     // (from the decoded inputs for the first slice, from the remainders afterwards)
     auto vector_max = [&](int val, int p) -> int {
         static_assert(TPR >= 64, "a wave never holds parts of two vectors");
         val = wave_max(val);
-        if (WAVES_PER_ROW > 1) {
+        if (MAX_WAVES > 1) {
             const int wave = threadIdx.x >> 6;
             if ((threadIdx.x & 63) == 0) red[p & 1][wave] = val;
             __syncthreads();
-            const int w0 = (wave / WAVES_PER_ROW) * WAVES_PER_ROW;
+            const int w0 = (wave / MAX_WAVES) * MAX_WAVES;
 #pragma unroll
-            for (int w = 0; w < WAVES_PER_ROW; ++w) {
+            for (int w = 0; w < MAX_WAVES; ++w) {                    // entries of waves that are not there never change
                 const int o = red[p & 1][w0 + w];
                 val = o > val ? o : val;
             }
@@ -390,7 +435,7 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
         Fp6Slot slots[FP6 ? U : 1];                                    // FP6 only: where each octet's codes go inside a slice matrix
         if constexpr (FP6) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) slots[u] = fp6_slot(8 * ((int64_t)tr + (int64_t)TPR * u), v_rows_pad, row);
+            for (int u = 0; u < U; ++u) slots[u] = fp6_slot(8 * ((int64_t)tr + (int64_t)threads * u), v_rows_pad, row);
         }
         uint64_t T[8 * U];                                             // element state, see slice_element.hpp
         int pk[8 * U];
@@ -422,15 +467,13 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
             cd_wait = 0;
         };
         auto store_octet = [&](int u, int (&qs)[8]) {                   // qs: q * 2^pos
-            const int64_t ke = 8 * ((int64_t)tr + (int64_t)TPR * u);
+            const int64_t ke = 8 * ((int64_t)tr + (int64_t)threads * u);
             if constexpr (FMT == FMT_FP8) {
                 if (ke < padded && v_slices != nullptr) store_fp8_codes_scaled(qs, code_scale, ke, dst_slice, v_rows_pad, row);
             } else if constexpr (FP6) {
                 if (ke < padded && v_slices != nullptr) store_fp6_codes_at_pos<FMT>(qs, pos, a.b, slots[u], dst_slice);
             } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) qs[e] >>= pos;
-                if (ke < padded && v_slices != nullptr) store_codes<FMT>(qs, ke, dst_slice, v_rows_pad, row, a.b);
+                if (ke < padded && v_slices != nullptr) store_int8_codes_at_pos(qs, pos, ke, dst_slice, v_rows_pad, row);
             }
         };
         // tail of slice p: the exponent goes out, the thread forms its candidate for the next one
@@ -457,6 +500,7 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
             const int step16 = step * 65536;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
+                if (u > 0 && !wave_has(u)) break;
                 int qs[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) qs[e] = slice_narrow(T[8 * u + e], pk[8 * u + e], step16, pos, bias, keep, kmax, kmin, cd_wait);
@@ -470,6 +514,7 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
             begin_slice(p);
 #pragma unroll
             for (int u = 0; u < U; ++u) {
+                if (u > 0 && !wave_has(u)) break;
                 int qs[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) qs[e] = slice_narrow_active(T[8 * u + e], step, pos, bias, keep, kmax, kmin);
@@ -513,10 +558,11 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
         const int64_t round_bias = ((int64_t)1 << (F - 1)) - 1;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+            if (u > 0 && !wave_has(u)) break;
             int qs[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) qs[e] = slice_element(tv[8 * u + e], pk[8 * u + e], unit, rescale, F, round_bias, rmax, cdorm);
-            const int64_t ke = 8 * ((int64_t)tr + (int64_t)TPR * u);
+            const int64_t ke = 8 * ((int64_t)tr + (int64_t)threads * u);
             if (ke < padded && v_slices != nullptr) store_codes<FMT>(qs, ke, dst_slice, v_rows_pad, row, a.b);
         }
         if (tr == 0 && v_slices != nullptr) v_exps[(t * a.s + p) * v_rows_pad + row] = c;
@@ -602,7 +648,7 @@ __global__ void __launch_bounds__(1024) long_exponents_kernel(SplitArgs a) {
         }
         __syncthreads();
     };
-    // f(mm, E) for every element of the block, eight loads in flight per thread
+    // f(mm, E) for every element of the block, four 16-byte loads in flight per thread
     auto for_each = [&](auto f) {
         auto one = [&](uint64_t w) {
             const int e11 = (int)((w >> 52) & 0x7FF);
@@ -612,20 +658,14 @@ __global__ void __launch_bounds__(1024) long_exponents_kernel(SplitArgs a) {
         };
         int64_t i = 0;
         for (; i + 8192 <= klen; i += 8192) {
-            uint64_t w[8];
-            if (v.vec_ok) {
+            two_doubles w[4];
 #pragma unroll
-                for (int h = 0; h < 4; ++h) {
-                    const ulonglong2 two = *reinterpret_cast<const ulonglong2*>(src + i + h * 2048 + 2 * tid);
-                    w[2 * h] = two.x;
-                    w[2 * h + 1] = two.y;
-                }
-            } else {
+            for (int h = 0; h < 4; ++h) w[h] = *reinterpret_cast<const two_doubles*>(src + i + h * 2048 + 2 * tid);
 #pragma unroll
-                for (int h = 0; h < 8; ++h) w[h] = (uint64_t)__double_as_longlong(src[i + h * 1024 + tid]);
+            for (int h = 0; h < 4; ++h) {
+                one(w[h].x);
+                one(w[h].y);
             }
-#pragma unroll
-            for (int h = 0; h < 8; ++h) one(w[h]);
         }
         for (i += tid; i < klen; i += 1024) one((uint64_t)__double_as_longlong(src[i]));
     };
@@ -729,10 +769,10 @@ __global__ void __launch_bounds__(256) split_stream_kernel(SplitArgs a) {
     uint8_t* dst_slice = v.slices + (size_t)(t * a.s) * a.chunks * (size_t)v.rows_pad * ROWB;
     const size_t slice_bytes = (size_t)a.chunks * v.rows_pad * ROWB;
     uint64_t bits[8];
-    if (v.vec_ok && ke + 8 <= klen) {
+    if (ke + 8 <= klen) {
 #pragma unroll
         for (int h = 0; h < 4; ++h) {
-            const ulonglong2 w = *reinterpret_cast<const ulonglong2*>(src + ke + 2 * h);
+            const two_doubles w = *reinterpret_cast<const two_doubles*>(src + ke + 2 * h);
             bits[2 * h] = w.x;
             bits[2 * h + 1] = w.y;
         }
@@ -852,11 +892,13 @@ hipError_t launch_split_cfg(const SplitArgs& a_in, int fmt, int64_t T, hipStream
     SplitArgs a = a_in;
     a.wg_first = (unsigned)(a.v[0].rows_pad / RPB);                     // rows_pad is a multiple of 256, RPB <= 4
     dim3 grid(a.wg_first + (unsigned)(a.v[1].rows_pad / RPB), (unsigned)T);
-    if (fmt == FMT_FP16) hipLaunchKernelGGL((split_kernel<U, TPR, FMT_FP16>), grid, dim3(BLOCK), 0, st, a);
-    else if (fmt == FMT_FP6) hipLaunchKernelGGL((split_kernel<U, TPR, FMT_FP6>), grid, dim3(BLOCK), 0, st, a);
-    else if (fmt == FMT_FP6_E3M2) hipLaunchKernelGGL((split_kernel<U, TPR, FMT_FP6_E3M2>), grid, dim3(BLOCK), 0, st, a);
-    else if (fmt == FMT_INT8) hipLaunchKernelGGL((split_kernel<U, TPR, FMT_INT8>), grid, dim3(BLOCK), 0, st, a);
-    else hipLaunchKernelGGL((split_kernel<U, TPR, FMT_FP8>), grid, dim3(BLOCK), 0, st, a);
+    const int64_t octets = a.chunks * (fmt == FMT_FP16 ? CHUNK_BYTES / 2 : CHUNK_BYTES) / 8;
+    const unsigned threads = RPB == 1 && U == 1 ? (unsigned)((octets + 64 * U - 1) / (64 * U)) * 64u : BLOCK;
+    if (fmt == FMT_FP16) hipLaunchKernelGGL((split_kernel<U, TPR, FMT_FP16>), grid, dim3(threads), 0, st, a);
+    else if (fmt == FMT_FP6) hipLaunchKernelGGL((split_kernel<U, TPR, FMT_FP6>), grid, dim3(threads), 0, st, a);
+    else if (fmt == FMT_FP6_E3M2) hipLaunchKernelGGL((split_kernel<U, TPR, FMT_FP6_E3M2>), grid, dim3(threads), 0, st, a);
+    else if (fmt == FMT_INT8) hipLaunchKernelGGL((split_kernel<U, TPR, FMT_INT8>), grid, dim3(threads), 0, st, a);
+    else hipLaunchKernelGGL((split_kernel<U, TPR, FMT_FP8>), grid, dim3(threads), 0, st, a);
     return hipGetLastError();
 }
 
@@ -889,12 +931,11 @@ hipError_t launch_transpose(const double* A, int64_t lda, int64_t m, int64_t k, 
 }
 
 namespace {
-SplitVectors split_vectors(const double* X, int64_t ldv, const Plan& pl, const Operand* op) {
+SplitVectors split_vectors(const double* X, int64_t ldv, const Operand* op) {
     SplitVectors v;
     memset(&v, 0, sizeof(v));
     if (op == nullptr || op->rows == 0) return v;                                 // no vectors: no workgroups
     v.X = X; v.ldv = ldv; v.rows = op->rows; v.rows_pad = op->rows_pad; v.slices = op->slices; v.exps = op->exps;
-    v.vec_ok = ((reinterpret_cast<uintptr_t>(X) & 15) == 0) && (ldv % 2 == 0) && (pl.kb % 2 == 0 || pl.T == 1);
     return v;
 }
 }  // namespace
@@ -902,8 +943,8 @@ SplitVectors split_vectors(const double* X, int64_t ldv, const Plan& pl, const O
 hipError_t launch_split(const double* X0, int64_t ldv0, const Operand* op0, const double* X1, int64_t ldv1, const Operand* op1,
                         const Plan& pl, int* flags, hipStream_t st) {
     SplitArgs a;
-    a.v[0] = split_vectors(X0, ldv0, pl, op0);
-    a.v[1] = split_vectors(X1, ldv1, pl, op1);
+    a.v[0] = split_vectors(X0, ldv0, op0);
+    a.v[1] = split_vectors(X1, ldv1, op1);
     a.wg_first = 0;
     a.k = pl.k; a.kb = pl.kb; a.chunks = pl.chunks; a.s = pl.s; a.b = pl.b; a.flags = flags;
     if (a.v[0].rows_pad + a.v[1].rows_pad == 0 || pl.T == 0) return hipSuccess;
