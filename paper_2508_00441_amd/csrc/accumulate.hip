@@ -50,6 +50,7 @@ struct AccArgs {
     int p_frac;              // the stored products are integer multiples of 2^-p_frac (2b; 2b - 2 for FP6 codes; 0 for INT32)
     int read_S, write_S, add_to_C;
     int allow_chain;         // the GEMM kernel summed tile-wide runs
+    const uint8_t* starts;   // measured runs (RunCheck), or null
     int merge;               // rule "runs": merge equal-scale products of an anti-diagonal element by element
     const int32_t* da;       // deltas of the block: [s][rows_pad_a / 32]
     const int32_t* db;       // [s][rows_pad_b / 32]
@@ -57,7 +58,8 @@ struct AccArgs {
     Pass pass;
 };
 
-// Is pair `pos` of anti-diagonal g (0-based position) stored on its own, i.e. does it start a run of the GEMM kernel?
+// Verification export: is pair `pos` of anti-diagonal g (0-based position) stored on its own, i.e. does it start a run of
+// the GEMM kernel?
 // dA / dB: the block's deltas advanced to the group of the 32 rows / 32 columns concerned, ga / gb: groups per slice;
 // p, q 0-based slice indices of the pair.
 __device__ __forceinline__ bool starts_run(const PairOrder& o, int allow_chain, const int32_t* dA, int64_t ga, const int32_t* dB,
@@ -76,6 +78,7 @@ __device__ __forceinline__ void accumulate_body(const AccArgs& a) {
     __shared__ int relB[MAX_SLICES][32];
     __shared__ uint32_t entries[MAX_PAIRS];           // stored runs of this tile: slot | p << 12 | q << 18 | first-of-diagonal << 24
     __shared__ int32_t linkA[MAX_SLICES], linkB[MAX_SLICES];      // deltas of the 32 rows / 32 columns, per slice
+    __shared__ uint8_t starts[MAX_PAIRS];
     __shared__ int n_entries;
 
     const int tid = threadIdx.x;
@@ -100,6 +103,8 @@ __device__ __forceinline__ void accumulate_body(const AccArgs& a) {
         relA[p][r] = p == 0 ? ca1 : ca - ca1;
         relB[p][r] = p == 0 ? cb1 : cb - cb1;
     }
+    if (a.starts != nullptr)
+        for (int z = tid; z < a.pass.npairs; z += 256) starts[z] = a.starts[((size_t)z * a.tiles_m * a.tiles_n + tile) * 64 + pos];
     // the deltas that decide where the GEMM kernel ended its runs at this position: fetched once, all at the same time
     if (tid < a.order.s) linkA[tid] = a.da[(int64_t)tid * (a.rows_pad_a / LINK_ROWS) + m0 / LINK_ROWS];
     else if (tid >= 64 && tid - 64 < a.order.s) linkB[tid - 64] = a.db[(int64_t)(tid - 64) * (a.rows_pad_b / LINK_ROWS) + n0 / LINK_ROWS];
@@ -133,10 +138,11 @@ __device__ __forceinline__ void accumulate_body(const AccArgs& a) {
     }
 
     // The stored runs of this 32 x 32 position, in accumulation order: a pair starts a run unless it is linked (for
-    // the whole position) to the pair before it inside its group.  Built by the first wave, one anti-diagonal at a time
+    // the whole position) to the pair before it inside its group; for measured runs the GEMM kernel wrote it down.  Built by the first wave, one anti-diagonal at a time
     // (an anti-diagonal has at most 32 pairs).
     if (tid < 64) {
         int count = 0, slot0 = 0;
+        const bool group_start = tid % a.order.run_limit == 0;
         for (int g = a.pass.g_hi; g >= a.pass.g_lo; --g) {
             const int len = diag_len(a.order, g);
             bool start = false;
@@ -144,7 +150,8 @@ __device__ __forceinline__ void accumulate_body(const AccArgs& a) {
             if (tid < len) {
                 const int p = diag_first_p(a.order, g) + tid - 1, q = g - p - 2;     // 0-based slice indices
                 const bool first = tid == 0;                                        // first pair of the anti-diagonal: ends every run
-                start = starts_run(a.order, a.allow_chain, linkA, 1, linkB, 1, tid, p, q);      // stored on its own
+                start = a.starts != nullptr ? starts[slot0 + tid] != 0                          // stored on its own
+                                            : group_start || !(a.allow_chain && pair_linked(linkA, 1, linkB, 1, p - 1, q + 1));
                 entry = (uint32_t)(slot0 + tid) | ((uint32_t)p << 12) | ((uint32_t)q << 18) | ((uint32_t)first << 24);
             }
             const unsigned long long mask = __ballot(start);
@@ -355,7 +362,7 @@ unsigned grid_for(int64_t work_items) {
 
 hipError_t launch_accumulate(const Plan& pl, const Operand& A, const Operand& B, const PairOrder& order, const Pass& ps,
                              bool first_pass, bool last_pass, int64_t t, const float* P, uint64_t* S_io,
-                             double* C, int64_t ldc, int accum_mode, int sum_rule, bool chained, hipStream_t st) {
+                             double* C, int64_t ldc, int accum_mode, int sum_rule, bool chained, const uint8_t* starts, hipStream_t st) {
     if (pl.tiles_m == 0 || pl.tiles_n == 0) return hipSuccess;
     AccArgs a;
     a.P = P; a.S = S_io; a.C = C; a.ldc = ldc;
@@ -366,6 +373,7 @@ hipError_t launch_accumulate(const Plan& pl, const Operand& A, const Operand& B,
     a.two_b = 2 * pl.b;
     a.p_frac = pl.p_frac;
     a.allow_chain = chained ? 1 : 0;
+    a.starts = starts;
     a.merge = (sum_rule == SUM_RUNS || accum_mode == ACC_EXACT) ? 1 : 0;
     a.da = A.deltas + (size_t)t * (A.rows_pad / LINK_ROWS) * pl.s;
     a.db = B.deltas + (size_t)t * (B.rows_pad / LINK_ROWS) * pl.s;

@@ -79,15 +79,16 @@ int64_t groups_in_pass(const Plan& pl, int pairs, int len) {
 // How the GEMMs of a pass of `pairs` products run: 256 x 256 or 128 x 128 blocks, and the length of the groups.  Any choice
 // gives the same bits (the accumulation kernel merges equal-scale products of an anti-diagonal element by element whatever
 // the grouping).  Long groups store fewer products, shorter ones and smaller blocks give a problem of few tiles enough
-// workgroups to keep 256 compute units busy.  The estimate below, in microseconds, was fitted to measurements from
-// 256^3 to 256 x 2048 x 8192 (FP8): a 64-byte stage takes 0.62 in a 256 x 256 block, 0.25 in a 128 x 128 block alone on its
-// compute unit and 0.42 where two share one; a workgroup costs 5 resp. 3 on top (filling the load ring, storing), a
-// stored product its bytes twice through memory, an entry of the accumulation lists 0.2; with more workgroups than slots the
-// last ones add half a group's time, little where whole anti-diagonals run from long to short.  Sums measured before and with
-// this rule (GEMM + accumulation): 256^3 49 -> 25, 600 x 600 x 1000 161 -> 58, 1000 x 777 x 1301 215 -> 125 us.  From 256 tiles on
-// long groups of the large blocks win by far (1500^3: 235 against 295 us).
-void choose_gemm(Plan& pl, int pairs) {
-    const int most = pl.run_limit < pl.s ? pl.run_limit : pl.s;
+// workgroups to keep 256 compute units busy.  The estimate below, in microseconds, was fitted to measurements from 256^3 to
+// 256 x 2048 x 8192 (FP8): a 64-byte stage takes 0.62 in a 256 x 256 block (0.58 where they do not fill the chip), 0.25 in a
+// 128 x 128 block alone on its compute unit and 0.42 where two share one; a workgroup costs 5 resp. 3 on top (filling the load
+// ring, storing), a stored product its bytes twice through memory, an entry of the accumulation lists 0.2; with more
+// workgroups than slots the last ones add part of a group's time, less where whole anti-diagonals run from long to short.
+// GEMM + accumulation before this rule and the smaller blocks, and with them: 256^3 49 -> 26, 512^3 emulated 91 -> 42,
+// 600 x 600 x 1000 161 -> 59, 1000 x 777 x 1301 214 -> 135, 400 x 3000 x 2000 348 -> 256 us.  From 256 tiles on long groups of the
+// large blocks are always the choice.
+void choose_gemm(Plan& pl, int pairs, bool measured_runs) {
+    const int most = measured_runs || pl.run_limit > pl.s ? pl.s : pl.run_limit;
     pl.small_tiles = 0;
     pl.group_len = most;
     const int64_t tiles = pl.tiles_m * pl.tiles_n;
@@ -100,10 +101,10 @@ void choose_gemm(Plan& pl, int pairs) {
         for (int len = most; len >= shortest; len = len > 8 ? (len + 1) / 2 : len - 1) {
             const int64_t ngroups = groups_in_pass(pl, pairs, len), wgs = ngroups * blocks;
             const double stage = small ? (wgs <= 256 ? 0.25 : 0.42) : 0.62, fixed = small ? 3.0 : 5.0;
-            const double longest = (len < longest_diag ? len : longest_diag) * (double)pl.chunks * stage;
+            const double longest = (len < longest_diag ? len : longest_diag) * (double)pl.chunks * (small ? stage : 0.58);
             double t = longest + fixed;
             if (wgs > slots) {
-                const double even = ((double)pairs * blocks * pl.chunks * stage + wgs * fixed) / slots + (len == pl.s ? 0.1 : 0.5) * longest;
+                const double even = ((double)pairs * blocks * pl.chunks * stage + wgs * fixed) / slots + (len == pl.s ? 0.2 : small ? 0.5 : 0.4) * longest;
                 if (even > t) t = even;
             }
             t += ngroups * (0.2 + blocks * (small ? 0.0146 : 0.0583) * 2.0);      // 64 resp. 256 KiB at 4.5 TB/s
@@ -143,12 +144,13 @@ int make_plan(int64_t m, int64_t n, int64_t k, int fmt, int s, int64_t k_block, 
     pl.full = full ? 1 : 0;
     pl.npairs = full ? pl.s * pl.s : pl.s * (pl.s + 1) / 2;
     const int64_t rl = exact_window(fmt) / (pl.kb << (2 * pl.b));
+    pl.pair_bound = (int)(pl.kb << (2 * pl.b));
     pl.run_limit = rl < 1 ? 1 : rl > MAX_SLICES ? MAX_SLICES : (int)rl;
     pl.tiles_m = (m + TILE - 1) / TILE;
     pl.tiles_n = (n + TILE - 1) / TILE;
     pl.m_pad = pl.tiles_m * TILE;
     pl.n_pad = pl.tiles_n * TILE;
-    choose_gemm(pl, pl.npairs);
+    choose_gemm(pl, pl.npairs, false);
     return 0;
 }
 
@@ -220,6 +222,7 @@ bool carve(const Plan& pl, Carve& c, bool want_product, WorkMem wm) {
     c.B.exps = reinterpret_cast<int32_t*>(ws + off); off += exps_bytes(pl, pl.n_pad);
     c.A.deltas = reinterpret_cast<int32_t*>(ws + off); off += deltas_bytes(pl, pl.m_pad);
     c.B.deltas = reinterpret_cast<int32_t*>(ws + off); off += deltas_bytes(pl, pl.n_pad);
+    c.A.l1 = c.B.l1 = c.A.bounds = c.B.bounds = nullptr;
     c.W = nullptr;
     if (want_product) { c.W = reinterpret_cast<double*>(ws + off); off += product_bytes(pl); }
     if (off > ws_bytes) return false;
@@ -238,6 +241,32 @@ bool carve(const Plan& pl, Carve& c, bool want_product, WorkMem wm) {
     size_t fit = (ws_bytes - off) / pb;
     c.chunk_pairs = fit > (size_t)pl.npairs ? pl.npairs : (int)fit;
     return c.chunk_pairs >= pl.s;
+}
+
+// Measured runs (RunCheck) where run_limit cuts anti-diagonals, and the buffers they need.  These live in memory whose own
+// contents are not needed at the time: the transposed A is dead once the operands are sliced (bounds, starts), the products
+// are not there yet while they are (l1).  Without room the runs keep to run_limit.  Anti-diagonals cut in two at most are
+// left so: looking at the accumulators then costs as much as the fewer products give (8192^3, 16 FP8 slices, run_limit 8:
+// GEMMs 46.6 -> 47.0 ms, accumulation 1.97 -> 1.78 ms).  Where every pair was stored on its own: 8192^3 FP16 in blocks of 1024
+// 57.8 -> 36.6 ms, in blocks of 4096 43.5 -> 37.9 ms, 2048^3 in blocks of 1024 1.36 -> 0.88 ms.
+RunCheck place_run_check(const Plan& pl, Carve& c) {
+    RunCheck none{nullptr, nullptr, nullptr};
+    if (pl.p_is_int || 2 * pl.run_limit >= pl.s) return none;
+    const bool from_slices = pl.run_limit == 1;            // a pair may fill the window: bounds from the slicing kernel
+    if (from_slices && (pl.fmt != OZAKI_SLICE_FP16 || pl.kb > MAX_K_BLOCK_IN_REGISTERS)) return none;
+    uint8_t* const at = reinterpret_cast<uint8_t*>(c.At);
+    const size_t room = align_up((size_t)pl.m * pl.k * sizeof(double));
+    const size_t ba = deltas_bytes(pl, pl.m_pad), bb = deltas_bytes(pl, pl.n_pad);
+    const size_t starts = (size_t)c.chunk_pairs * pl.tiles_m * pl.tiles_n * 64;
+    if ((from_slices ? ba + bb : 0) + starts > room) return none;
+    if (!from_slices) return RunCheck{at, nullptr, nullptr};
+    const size_t la = exps_bytes(pl, pl.m_pad), lb = exps_bytes(pl, pl.n_pad);
+    if (la + lb > (size_t)c.chunk_pairs * pair_bytes(pl)) return none;
+    c.A.l1 = reinterpret_cast<int32_t*>(c.P);
+    c.B.l1 = reinterpret_cast<int32_t*>(reinterpret_cast<uint8_t*>(c.P) + la);
+    c.A.bounds = reinterpret_cast<int32_t*>(at);
+    c.B.bounds = reinterpret_cast<int32_t*>(at + ba);
+    return RunCheck{at + ba + bb, c.A.bounds, c.B.bounds};
 }
 
 PairOrder order_of(const Plan& pl) { return PairOrder{pl.s, pl.full, pl.group_len}; }
@@ -347,15 +376,20 @@ int dgemm_core(const Plan& plan, double alpha, const double* A, int64_t lda, con
     c.W = nullptr;
     if ((k > 0 || scaled) && !carve(plan, c, scaled, wm)) return OZAKI_STATUS_WORKSPACE;
     Plan pl = plan;
-    if (k > 0 && c.chunk_pairs < pl.npairs) choose_gemm(pl, c.chunk_pairs);      // several passes: each is a launch of its own
+    // the plain rule adds every product on its own, so the matrix unit must not sum across pairs
+    const bool chained = o.sum_rule == OZAKI_SUM_RUNS || o.accum_mode == OZAKI_ACCUM_EXACT_FIXED;
+    RunCheck check{nullptr, nullptr, nullptr};
+    if (k > 0) {
+        if (chained) check = place_run_check(pl, c);
+        // several passes: each is a launch of its own
+        if (check.starts != nullptr || c.chunk_pairs < pl.npairs) choose_gemm(pl, c.chunk_pairs, check.starts != nullptr);
+    }
     double* const out = scaled ? c.W : C;
     const int64_t ldo = scaled ? (m > 1 ? m : 1) : ldc;
     if (k == 0) {
         HIP_TRY(launch_fill_zero_f64(out, ldo, m, n, st));
     } else {
         const PairOrder order = order_of(pl);
-        // the plain rule adds every product on its own, so the matrix unit must not sum across pairs
-        const bool chained = o.sum_rule == OZAKI_SUM_RUNS || o.accum_mode == OZAKI_ACCUM_EXACT_FIXED;
         int rc = run_split(pl, c, A, lda, B, ldb, true, true);
         if (rc) return rc;
         for (int64_t t = 0; t < pl.T; ++t) {
@@ -363,12 +397,12 @@ int dgemm_core(const Plan& plan, double alpha, const double* A, int64_t lda, con
                 const Pass ps = next_pass(order, g_hi, c.chunk_pairs);
                 {
                     Phase ph(1);
-                    HIP_TRY(launch_pair_gemm(pl, c.A, c.B, order, ps, chained, t, c.P, st));
+                    HIP_TRY(launch_pair_gemm(pl, c.A, c.B, order, ps, chained, check, t, c.P, st));
                 }
                 {
                     Phase ph(2);
                     HIP_TRY(launch_accumulate(pl, c.A, c.B, order, ps, g_hi == order_top_diag(order), ps.g_lo == 2, t, c.P, c.S, out,
-                                              ldo, o.accum_mode, o.sum_rule, chained, st));
+                                              ldo, o.accum_mode, o.sum_rule, chained, check.starts, st));
                 }
                 g_hi = ps.g_lo - 1;
             }
@@ -687,7 +721,7 @@ int ozaki_pair_products(int64_t m, int64_t n, int64_t k, const double* A, int64_
     if (!P_out) return -13;
     Carve c;
     if (!carve(pl, c, false, context_workspace())) return OZAKI_STATUS_WORKSPACE;
-    if (c.chunk_pairs < pl.npairs) choose_gemm(pl, c.chunk_pairs);
+    if (c.chunk_pairs < pl.npairs) choose_gemm(pl, c.chunk_pairs, false);
     hipStream_t stream = ctx().stream;
     const PairOrder order = order_of(pl);
     int rc = run_split(pl, c, A, lda, B, ldb, true, true);
@@ -697,7 +731,7 @@ int ozaki_pair_products(int64_t m, int64_t n, int64_t k, const double* A, int64_
         for (int g_hi = order_top_diag(order); g_hi >= 2;) {
             const Pass ps = next_pass(order, g_hi, c.chunk_pairs);
             const size_t at = ((size_t)t * pl.npairs + z0) * (size_t)m * n;
-            HIP_TRY(launch_pair_gemm(pl, c.A, c.B, order, ps, chained != 0, t, c.P, stream));
+            HIP_TRY(launch_pair_gemm(pl, c.A, c.B, order, ps, chained != 0, RunCheck{nullptr, nullptr, nullptr}, t, c.P, stream));
             HIP_TRY(launch_export_products(pl, c.A, c.B, order, ps, chained != 0, t, c.P, static_cast<float*>(P_out) + at,
                                            run_len_out ? run_len_out + at : nullptr, stream));
             z0 += ps.npairs;

@@ -47,6 +47,8 @@ struct Operand {
     int64_t rows_pad;     // multiple of TILE
     uint8_t* slices;      // [T][s][chunks][rows_pad][row_bytes]
     int32_t* exps;        // [T][s][rows_pad]   exponent c of Eq. 4 (0 for padding vectors)
+    int32_t* l1;          // [T][s][rows_pad]   sum |q| of the slice (null: not wanted)
+    int32_t* bounds;      // [T][s][rows_pad/LINK_ROWS]  2^b times the largest l1 of the group (see RunCheck)
     int32_t* deltas;      // [T][s][rows_pad/LINK_ROWS]  per slice p and group of 32 vectors (one matrix-unit tile edge):
                           //                        c_p - c_(p+1) if that difference is the same for all real vectors of
                           //                        the group, else DELTA_IRREGULAR (always for the last slice)
@@ -73,7 +75,8 @@ struct Plan {
     int npairs;           // s(s+1)/2 or s*s
     int run_limit;        // floor(window / (kb * 4^b)): equal-scale pair products that may be summed exactly in the
                           // matrix unit's accumulators (window 2^24 for FP32, 2^31 - 1 for INT32)
-    int group_len;        // pairs per group of the GEMM kernel, <= run_limit (PairOrder::run_limit of the launches)
+    int pair_bound;       // kb * 4^b: no partial sum of a pair product is larger (FP32 formats: at most 2^24)
+    int group_len;        // pairs per group of the GEMM kernel, <= run_limit, or s with measured runs (PairOrder::run_limit of the launches)
     int64_t tiles_m, tiles_n;
     int64_t m_pad, n_pad;
     int small_tiles;      // 1: the GEMMs run in 128 x 128 blocks (launch_pair_gemm_small)
@@ -99,6 +102,10 @@ __host__ __device__ inline int diag_len(const PairOrder& o, int g) {
     return hi - diag_first_p(o, g) + 1;
 }
 __host__ __device__ inline int diag_groups(const PairOrder& o, int g) { return (diag_len(o, g) + o.run_limit - 1) / o.run_limit; }
+// First position of group i of an anti-diagonal of `len` pairs: whole groups, then the rest.  (Cuts of equal length would even
+// out the workgroups, but groups of neighbouring anti-diagonals that start at the same slice read the same panels side by
+// side: 1024 x 1024 x 8192 takes 0.51 ms with these cuts, 0.56 ms with equal ones.)
+__host__ __device__ inline int group_first(const PairOrder& o, int len, int i) { return i * o.run_limit < len ? i * o.run_limit : len; }
 __host__ __device__ inline int order_num_groups(const PairOrder& o) {
     int n = 0;
     for (int g = order_top_diag(o); g >= 2; --g) n += diag_groups(o, g);
@@ -113,35 +120,60 @@ struct Pass {
     int npairs, ngroups;
 };
 
-// Products of the anti-diagonals 2 .. g.
-__host__ __device__ inline int pairs_up_to_diag(const PairOrder& o, int g) {
-    return g <= o.s + 1 ? g * (g - 1) / 2 : o.s * o.s - (2 * o.s - g) * (2 * o.s + 1 - g) / 2;
-}
-
-// The gi-th group of a pass: slices (p0 + j, q0 - j), j < len (1-based), first product slot `slot`.  Groups are numbered
-// from the longest anti-diagonal of the pass outwards (g = s+1, s, s+2, s-1, ...), so that the workgroups with the most
-// work start first; the product slots keep the accumulation order.
+// The gi-th group of a pass, in accumulation order: slices (p0 + j, q0 - j), j < len (1-based), first product slot `slot`.
 struct Group {
     int p0, q0, len, slot;
 };
 __host__ __device__ inline Group pass_group(const PairOrder& o, const Pass& ps, int gi) {
-    for (int d = 0; d < o.s; ++d)
-        for (int side = 0; side < 2; ++side) {
-            const int g = side == 0 ? o.s + 1 - d : o.s + 1 + d;
-            if (g < ps.g_lo || g > ps.g_hi || (side == 1 && d == 0)) continue;
-            const int len = diag_len(o, g), ng = (len + o.run_limit - 1) / o.run_limit;
-            if (gi < ng) {
-                const int pos = gi * o.run_limit;
-                Group r;
-                r.p0 = diag_first_p(o, g) + pos;
-                r.q0 = g - r.p0;
-                r.len = len - pos < o.run_limit ? len - pos : o.run_limit;
-                r.slot = pairs_up_to_diag(o, ps.g_hi) - pairs_up_to_diag(o, g) + pos;
-                return r;
-            }
-            gi -= ng;
+    int slot = 0;
+    for (int g = ps.g_hi; g >= ps.g_lo; --g) {
+        const int len = diag_len(o, g), ng = diag_groups(o, g);
+        if (gi < ng) {
+            const int pos = group_first(o, len, gi);
+            Group r;
+            r.p0 = diag_first_p(o, g) + pos;
+            r.q0 = g - r.p0;
+            r.len = group_first(o, len, gi + 1) - pos;
+            r.slot = slot + pos;
+            return r;
         }
+        gi -= ng;
+        slot += len;
+    }
     return Group{1, 1, 0, 0};
+}
+
+// The groups of a pass in the order in which workgroups take them, longest first (a long group that starts last would be
+// the launch's tail), packed for the kernel arguments: p0 | q0 << 6 | len << 12 | slot << 18.  A pass of more groups than fit
+// goes in accumulation order.
+constexpr int MAX_LISTED_GROUPS = 512;
+struct GroupList {
+    int listed;
+    uint32_t entry[MAX_LISTED_GROUPS];
+};
+inline void list_groups(const PairOrder& o, const Pass& ps, GroupList& list) {
+    list.listed = ps.ngroups <= MAX_LISTED_GROUPS ? ps.ngroups : 0;
+    if (list.listed == 0) return;
+    int place[MAX_SLICES + 2] = {};                             // place[len]: groups longer than len, then their next place
+    for (int pass = 0; pass < 2; ++pass) {
+        int slot = 0;
+        for (int g = ps.g_hi; g >= ps.g_lo; --g) {
+            const int len = diag_len(o, g), ng = diag_groups(o, g);
+            for (int i = 0; i < ng; ++i) {
+                const int pos = group_first(o, len, i), glen = group_first(o, len, i + 1) - pos, p0 = diag_first_p(o, g) + pos;
+                if (pass == 0) ++place[glen - 1];
+                else list.entry[place[glen]++] = (uint32_t)p0 | (uint32_t)(g - p0) << 6 | (uint32_t)glen << 12 | (uint32_t)(slot + pos) << 18;
+            }
+            slot += len;
+        }
+        if (pass == 0)
+            for (int len = MAX_SLICES; len >= 0; --len) place[len] += place[len + 1];
+    }
+}
+__host__ __device__ inline Group listed_group(const GroupList& list, const PairOrder& o, const Pass& ps, int gi) {
+    if (list.listed == 0) return pass_group(o, ps, gi);
+    const uint32_t e = list.entry[gi];
+    return Group{(int)(e & 63), (int)((e >> 6) & 63), (int)((e >> 12) & 63), (int)(e >> 18)};
 }
 
 // Which work item (group gi, block (bm, bn) of blocks_m x blocks_n) workgroup b of `total` takes.  Workgroups are handed to
@@ -180,11 +212,27 @@ __host__ __device__ inline WorkItem work_item(unsigned b, unsigned total, const 
 // 4096^3 FP8 4.08 -> 4.01 ms, 2048^3 FP16 in blocks of 1024 0.83 -> 0.78 ms, 600 x 600 x 1000 (128 x 128 blocks) 43 -> 35 us.
 // The plain order stays where it already gives every XCD a compact patch (32 block rows: four of them per XCD; strips
 // lose 2.5 % at 16384^2 FP16 there) and where a launch has few rounds of groups of unequal length (1024^3, all pairs:
-// 112 us plain, 138 us in strips, because a unit's XCD waits for its longest group).
-__host__ __device__ inline WorkOrder work_order(int64_t total, int per_xcd, int64_t blocks_m, int group_len) {
-    if (blocks_m % 32 == 0 || (group_len > 4 && total < 64 * (int64_t)per_xcd)) return WorkOrder{0, 0};
+// 112 us plain, 138 us in strips, because a unit's XCD waits for its longest group), also when a group of 256 x 256 blocks has
+// fewer of them than an XCD runs at a time (1024 x 1024 x 8192: 0.49 ms plain, 0.55 to 0.62 in strips).
+__host__ __device__ inline WorkOrder work_order(int64_t total, int per_xcd, int64_t blocks_m, int64_t blocks_n, int group_len) {
+    if (blocks_m % 32 == 0 || (group_len > (per_xcd == 32 ? 4 : 6) && total < 64 * (int64_t)per_xcd)) return WorkOrder{0, 0};
+    if (per_xcd == 32 && blocks_m * blocks_n < 32) return WorkOrder{0, 0};
     return WorkOrder{per_xcd, blocks_m > 8 ? 4 : 8};
 }
+
+// Runs longer than run_limit pairs ("measured" runs).  run_limit assumes that every product of slice entries is as large as it
+// can be; real slices stay far below that.  With measured runs a group may hold a whole anti-diagonal, and when a pair is
+// complete the GEMM kernel looks at the accumulators of each 32 x 32 tile: the next pair may be added on top if their largest
+// magnitude plus a bound on every partial sum of the next pair stays inside the exact window, so all sums are exact as
+// before.  The bound is kb 4^b where run_limit >= 2; where a single pair may fill the window (FP16 with the widest slices) it
+// is 2^b sum |q| over a vector, from the slicing, the smaller of the two operands' maxima over the tile's 32 vectors.  Which
+// pairs start a run is then data; the GEMM kernel writes it down for the accumulation, a byte per product slot and tile:
+// starts[slot][tile_n][tile_m][position in the order of the product storage], 1 if the slot holds a run's sum.
+struct RunCheck {
+    uint8_t* starts;          // null: runs of at most run_limit pairs, decided from the deltas alone
+    const int32_t* bound_a;   // [T][s][rows_pad_a / LINK_ROWS] bounds of the slices' pair products, or null: pair_bound for all
+    const int32_t* bound_b;
+};
 
 // True if, for every element of a 32 x 32 tile, pair (p+1, q-1) carries the same scale factor 2^(cA + cB) as pair
 // (p, q) (0-based slice indices): then the two products can be summed in the accumulator of the matrix unit
@@ -235,19 +283,20 @@ hipError_t launch_deltas(const Plan& pl, const Operand* op0, const Operand* op1,
 // allow_chain, consecutive pairs of a group that are linked for a tile (pair_linked) form a run whose exact sum is
 // stored in the slot of the run's first pair; the slots of the other pairs of the run are left untouched.
 hipError_t launch_pair_gemm(const Plan& pl, const Operand& A, const Operand& B, const PairOrder& order, const Pass& ps,
-                            bool allow_chain, int64_t t, float* P, hipStream_t st);
+                            bool allow_chain, const RunCheck& check, int64_t t, float* P, hipStream_t st);
 // The same in 128 x 128 blocks (Plan::small_tiles; called by launch_pair_gemm).  Blocks without real elements are left out.
 hipError_t launch_pair_gemm_small(const Plan& pl, const Operand& A, const Operand& B, const PairOrder& order, const Pass& ps,
-                                  bool allow_chain, int64_t t, float* P, hipStream_t st);
+                                  bool allow_chain, const RunCheck& check, int64_t t, float* P, hipStream_t st);
 
 // Accumulate the pairs of pass `ps` of block t.  S_io: running block sum in accumulator order (read unless the
 // pass is the block's first, written unless it is the last): one 64-bit word per element (FP64 bits), three in the
 // exact mode, word w of element e at S_io[w * tiles * TILE_ELEMS + e].  On the last pass the block sum is rescaled by
 // the first-slice exponents and stored to C (t == 0) or added to C (t > 0).  `chained`: the products were written
-// with allow_chain.  sum_rule SUM_PLAIN: every product is added on its own.
+// with allow_chain; starts: RunCheck::starts of that launch.  sum_rule SUM_PLAIN: every product is added on its own.
 hipError_t launch_accumulate(const Plan& pl, const Operand& A, const Operand& B, const PairOrder& order, const Pass& ps,
                              bool first_pass, bool last_pass, int64_t t, const float* P, uint64_t* S_io,
-                             double* C, int64_t ldc, int accum_mode, int sum_rule, bool chained, hipStream_t st);
+                             double* C, int64_t ldc, int accum_mode, int sum_rule, bool chained, const uint8_t* starts,
+                             hipStream_t st);
 
 // P in accumulator order -> [nz][n][m] column-major matrices (verification export): FP32 values of Eq. 10-11, or INT32
 // integers for INT8 slices.  run_len_out (may be null): for every element and pair slot of the pass, how many pairs'

@@ -8,6 +8,8 @@
 //
 // The pipeline is the one of pair_gemm.hip: direct-to-LDS loads through a ring of NSTAGE stages, fragments read one
 // k-step ahead.  Two waves load the B slices (the matrix unit's "row" operand), two the A slices.
+#include <math.h>
+
 #include <type_traits>
 
 #include "layout.hpp"
@@ -38,6 +40,13 @@ struct SmallGemmArgs {
     const int32_t* db;       // B deltas of the block: [s][rows_pad_b / 32]
     PairOrder order;
     Pass pass;
+    GroupList groups;
+    uint8_t* starts;         // measured runs (RunCheck): where runs start, or null
+    const int32_t* ba;       // bounds of the block, as the deltas; null: pair_bound for every pair
+    const int32_t* bb;
+    int pair_bound;
+    int sure;                // pairs of a group whose sum is inside the window whatever the data
+    float unit;              // 2^-p_frac, the unit of the stored sums
 };
 
 #define OZAKI_GPTR(p) ((const __attribute__((address_space(1))) void*)(p))
@@ -77,7 +86,7 @@ __global__ void __launch_bounds__(256, 2) pair_gemm_small_kernel(const SmallGemm
 
     const WorkItem item = work_item(blockIdx.x, gridDim.x, a.work, a.quads_m, a.quads_n);
     const int qn = item.bn, qm = item.bm;
-    const Group grp = pass_group(a.order, a.pass, item.gi);
+    const Group grp = listed_group(a.groups, a.order, a.pass, item.gi);
     const int glen = grp.len, p0 = grp.p0 - 1, q0 = grp.q0 - 1;       // 0-based slice indices from here on
     const int chunks = a.chunks;
 
@@ -99,6 +108,28 @@ __global__ void __launch_bounds__(256, 2) pair_gemm_small_kernel(const SmallGemm
             for (int j = 0; j < 2; ++j)
                 cont |= deltas_link(__builtin_amdgcn_readfirstlane(dav[j]), __builtin_amdgcn_readfirstlane(dbv[i])) ? (1u << (i * 2 + j)) : 0u;
         return cont;
+    };
+
+    // Measured runs, as in pair_gemm.hip
+    auto drop_full_tiles = [&](unsigned cont, const v2s& bav, const v2s& bbv, const auto& acc) -> unsigned {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                if ((cont >> (i * 2 + j)) & 1u) {
+                    const int next = bav[j] < bbv[i] ? bav[j] : bbv[i];
+                    const float room = (float)((1 << 24) - next) * a.unit;
+                    float most = 0.0f;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) most = fmaxf(most, fabsf((float)acc[i][j][r]));
+                    if (__ballot(!(most <= room)) != 0ull) cont &= ~(1u << (i * 2 + j));
+                }
+        return cont;
+    };
+    auto write_starts = [&](int jp, unsigned first) {
+        if (lane < 4)
+            a.starts[((size_t)((grp.slot + jp) * a.tiles_n + (qn >> 1)) * a.tiles_m + (qm >> 1)) * 64 + ((qn & 1) * 2 + (qm & 1)) * 16 +
+                     (wn * 2 + (lane >> 1)) * 4 + wm * 2 + (lane & 1)] = (uint8_t)((first >> lane) & 1u);
     };
 
     // Loader: waves 0 and 1 fetch the X (B slice) half of a stage, waves 2 and 3 the Y (A slice) half, LPW kilobytes each.
@@ -251,10 +282,20 @@ __global__ void __launch_bounds__(256, 2) pair_gemm_small_kernel(const SmallGemm
     };
     const std::integral_constant<int, 0> c0;
     const std::integral_constant<int, 1> c1;
+    if constexpr (!INT8) {
+        if (a.starts != nullptr) write_starts(0, 0xFu);
+    }
     unsigned run_start = 0;                             // byte i*2+j: first pair of the run tile (i, j) is accumulating
     for (int jp = 0; jp < glen; ++jp) {
         const bool last_pair = jp + 1 == glen;
-        const unsigned cont = last_pair ? 0u : continue_mask(jp);
+        unsigned cont = last_pair ? 0u : continue_mask(jp);
+        v2s bav = {a.pair_bound, a.pair_bound}, bbv = bav;
+        if constexpr (!INT8) {
+            if (a.ba != nullptr && !last_pair) {
+                bav = *(delta2_ptr)(a.ba + (qm * 4 + wm * 2) + (size_t)(p0 + jp + 1) * groups_a);
+                bbv = *(delta2_ptr)(a.bb + (qn * 4 + wn * 2) + (size_t)(q0 - jp - 1) * groups_b);
+            }
+        }
         if constexpr (KS == 1) {
             int c = 0;
             for (; c + 1 < chunks; c += 2) {
@@ -274,6 +315,12 @@ __global__ void __launch_bounds__(256, 2) pair_gemm_small_kernel(const SmallGemm
             for (int c = 0; c < chunks; ++c) {
                 kstep(c0, c0);
                 kstep(c1, c1);
+            }
+        }
+        if constexpr (!INT8) {
+            if (a.starts != nullptr && !last_pair) {
+                if (jp + 2 > a.sure && cont != 0u) cont = drop_full_tiles(cont, bav, bbv, acc);
+                write_starts(jp + 1, ~cont);
             }
         }
         if (cont != 0xFu) {
@@ -297,7 +344,7 @@ __global__ void __launch_bounds__(256, 2) pair_gemm_small_kernel(const SmallGemm
 }  // namespace
 
 hipError_t launch_pair_gemm_small(const Plan& pl, const Operand& A, const Operand& B, const PairOrder& order, const Pass& ps,
-                                  bool allow_chain, int64_t t, float* P, hipStream_t st) {
+                                  bool allow_chain, const RunCheck& check, int64_t t, float* P, hipStream_t st) {
     SmallGemmArgs a;
     const size_t slice_a = (size_t)pl.chunks * A.rows_pad * pl.row_bytes, slice_b = (size_t)pl.chunks * B.rows_pad * pl.row_bytes;
     a.sa = A.slices + (size_t)t * pl.s * slice_a;
@@ -310,9 +357,16 @@ hipError_t launch_pair_gemm_small(const Plan& pl, const Operand& A, const Operan
     a.da = A.deltas + (size_t)t * (A.rows_pad / LINK_ROWS) * pl.s;
     a.db = B.deltas + (size_t)t * (B.rows_pad / LINK_ROWS) * pl.s;
     a.order = order; a.pass = ps;
+    list_groups(order, ps, a.groups);
+    a.starts = check.starts;
+    a.ba = check.bound_a != nullptr ? check.bound_a + (size_t)t * (A.rows_pad / LINK_ROWS) * pl.s : nullptr;
+    a.bb = check.bound_b != nullptr ? check.bound_b + (size_t)t * (B.rows_pad / LINK_ROWS) * pl.s : nullptr;
+    a.pair_bound = pl.pair_bound;
+    a.sure = pl.run_limit;
+    a.unit = ldexpf(1.0f, -pl.p_frac);
     const int64_t blocks = (int64_t)ps.ngroups * a.quads_m * a.quads_n;
     if (blocks > 0x7FFFFFFF || pl.chunks * MAX_SLICES > 0x7FFFFFFF) return hipErrorInvalidValue;
-    a.work = work_order(blocks, 64, a.quads_m, order.run_limit);
+    a.work = work_order(blocks, 64, a.quads_m, a.quads_n, order.run_limit);
     const dim3 grid((unsigned)blocks), block(256);
     if (pl.fmt == FMT_FP16) hipLaunchKernelGGL((pair_gemm_small_kernel<FMT_FP16>), grid, block, 0, st, a);
     else if (pl.fmt == FMT_FP6) hipLaunchKernelGGL((pair_gemm_small_kernel<FMT_FP6>), grid, block, 0, st, a);

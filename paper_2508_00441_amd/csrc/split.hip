@@ -57,6 +57,7 @@ struct SplitVectors {
     int64_t rows, rows_pad;
     uint8_t* slices;       // null: count only, nothing is stored
     int32_t* exps;
+    int32_t* l1;           // sum |q| per slice, or null (FP16 slices only)
 };
 
 // A launch splits the vectors of up to two operands (same k, block length, format and slice count): the first wg_first
@@ -324,6 +325,17 @@ __device__ __forceinline__ V wave_max(V v) {
     return (V)__builtin_amdgcn_readlane((int)v, 63);
 }
 
+// The sum, in lane 63: the same steps; a row that a step leaves out adds zero.
+__device__ __forceinline__ int wave_sum(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);
+    return __builtin_amdgcn_readlane(v, 63);
+}
+
 // (At least four waves per SIMD, i.e. at most 128 registers: two 512-thread workgroups per CU, so that one computes while
 // the other waits at its barrier.)
 // A vector rarely fills its threads: a wave without elements in its second octet leaves that half of the work out, and with
@@ -354,6 +366,7 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
     const int64_t v_rows = second ? a.v[1].rows : a.v[0].rows, v_rows_pad = second ? a.v[1].rows_pad : a.v[0].rows_pad;
     uint8_t* const v_slices = second ? a.v[1].slices : a.v[0].slices;
     int32_t* const v_exps = second ? a.v[1].exps : a.v[0].exps;
+    int32_t* const v_l1 = second ? a.v[1].l1 : a.v[0].l1;
     const unsigned li = blockIdx.x - (second ? a.wg_first : 0u);     // index and count inside the operand's part of the
     const unsigned gl = second ? gridDim.x - a.wg_first : a.wg_first;   // grid; both multiples of 8, so li % 8 is the XCD
     const int64_t wg = (int64_t)(li & 7) * (gl >> 3) + (li >> 3);
@@ -375,6 +388,7 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
                 if (ke < padded) store_codes<FMT>(zero8, ke, dst, v_rows_pad, row, a.b);
             }
             if (tr == 0) v_exps[(t * a.s + p) * v_rows_pad + row] = 0;
+            if (tr == 0 && v_l1 != nullptr) v_l1[(t * a.s + p) * v_rows_pad + row] = 0;
         }
         return;
     }
@@ -537,9 +551,19 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
     }
     if (nonfinite) atomicOr(a.flags, 1);
 
+    // sum |q| of the slices, if wanted: a wave's share goes to LDS and is added up behind the barrier of the next exchange
+    __shared__ int l1_share[2][BLOCK / 64];
+    auto store_l1 = [&](int p) {
+        if (tr != 0) return;
+        const int w0 = threadIdx.x >> 6;
+        int sum = 0;
+        for (int w = 0; w < threads / 64; ++w) sum += l1_share[p & 1][w0 + w];
+        v_l1[(t * a.s + p) * v_rows_pad + row] = sum;
+    };
     int c_prev = 0;
     for (int p = 0; p < a.s; ++p) {
         cmax = vector_max(cmax, p);
+        if (v_l1 != nullptr && p > 0) store_l1(p - 1);
         if (v_slices == nullptr) {
             if (cmax != NO_ELEM && tr == 0) atomicMax(a.flags + 1, p + 1);      // count-only mode
         }
@@ -555,6 +579,7 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
         uint8_t* const dst_slice = v_slices + (size_t)((t * a.s + p) * a.chunks) * (size_t)v_rows_pad * ROWB;
         uint64_t rmax = 0;                                             // largest |remainder| of this thread's active elements
         int cdorm = NO_ELEM;                                           // largest cd of its still dormant elements
+        int l1 = 0;
         const int64_t round_bias = ((int64_t)1 << (F - 1)) - 1;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -562,16 +587,26 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
             int qs[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) qs[e] = slice_element(tv[8 * u + e], pk[8 * u + e], unit, rescale, F, round_bias, rmax, cdorm);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) l1 += qs[e] < 0 ? -qs[e] : qs[e];
             const int64_t ke = 8 * ((int64_t)tr + (int64_t)threads * u);
             if (ke < padded && v_slices != nullptr) store_codes<FMT>(qs, ke, dst_slice, v_rows_pad, row, a.b);
         }
         if (tr == 0 && v_slices != nullptr) v_exps[(t * a.s + p) * v_rows_pad + row] = c;
+        if (v_l1 != nullptr) {
+            const int share = wave_sum(l1);
+            if ((threadIdx.x & 63) == 0) l1_share[p & 1][threadIdx.x >> 6] = share;
+        }
         // this thread's candidate for the next exponent: remainders are rmax * 2^(unit - F)
         cmax = cdorm;
         if (rmax != 0) {
             const int ca = ceil_log2_scaled(rmax, unit, F);
             cmax = ca > cmax ? ca : cmax;
         }
+    }
+    if (v_l1 != nullptr) {
+        __syncthreads();
+        store_l1(a.s - 1);
     }
 }
 
@@ -861,9 +896,11 @@ __global__ void __launch_bounds__(256) export_slices_kernel(const uint8_t* __res
 struct DeltaOperand {
     const int32_t* exps;
     int32_t* deltas;
+    const int32_t* l1;
+    int32_t* bounds;
     int64_t rows, rows_pad;
 };
-__global__ void __launch_bounds__(256) delta_kernel(DeltaOperand o0, DeltaOperand o1, unsigned tiles_first, int s) {
+__global__ void __launch_bounds__(256) delta_kernel(DeltaOperand o0, DeltaOperand o1, unsigned tiles_first, int s, int b) {
     const bool second = blockIdx.x >= tiles_first;
     const int32_t* const exps = second ? o1.exps : o0.exps;
     int32_t* const deltas = second ? o1.deltas : o0.deltas;
@@ -883,6 +920,19 @@ __global__ void __launch_bounds__(256) delta_kernel(DeltaOperand o0, DeltaOperan
         if ((lane & 31) == 0) out[(size_t)p * groups] = same ? ref : DELTA_IRREGULAR;
     }
     if ((lane & 31) == 0) out[(size_t)(s - 1) * groups] = DELTA_IRREGULAR;
+    const int32_t* const l1 = second ? o1.l1 : o0.l1;
+    if (l1 == nullptr) return;
+    // Operand::bounds: 2^b times the largest sum |q| of the group
+    int32_t* const bounds = (second ? o1.bounds : o0.bounds) + (size_t)t * s * groups + group;
+    for (int p = 0; p < s; ++p) {
+        int most = l1[(size_t)(t * s + p) * rows_pad + row];
+#pragma unroll
+        for (int off = 1; off < 32; off <<= 1) {
+            const int o = __shfl_xor(most, off, 64);
+            most = o > most ? o : most;
+        }
+        if ((lane & 31) == 0) bounds[(size_t)p * groups] = most << b;
+    }
 }
 
 template <int U, int TPR>
@@ -935,7 +985,7 @@ SplitVectors split_vectors(const double* X, int64_t ldv, const Operand* op) {
     SplitVectors v;
     memset(&v, 0, sizeof(v));
     if (op == nullptr || op->rows == 0) return v;                                 // no vectors: no workgroups
-    v.X = X; v.ldv = ldv; v.rows = op->rows; v.rows_pad = op->rows_pad; v.slices = op->slices; v.exps = op->exps;
+    v.X = X; v.ldv = ldv; v.rows = op->rows; v.rows_pad = op->rows_pad; v.slices = op->slices; v.exps = op->exps; v.l1 = op->l1;
     return v;
 }
 }  // namespace
@@ -977,7 +1027,7 @@ hipError_t launch_count_slices(const double* X, int64_t ldv, const Plan& pl, int
     Operand op;
     op.rows = rows;
     op.rows_pad = (rows + TILE - 1) / TILE * TILE;
-    op.slices = nullptr; op.exps = nullptr; op.deltas = nullptr;
+    op.slices = nullptr; op.exps = nullptr; op.deltas = nullptr; op.l1 = nullptr; op.bounds = nullptr;
     return launch_split(X, ldv, &op, nullptr, 0, nullptr, cp, flags, st);
 }
 
@@ -986,10 +1036,10 @@ hipError_t launch_deltas(const Plan& pl, const Operand* op0, const Operand* op1,
     memset(o, 0, sizeof(o));
     const Operand* ops[2] = {op0, op1};
     for (int i = 0; i < 2; ++i)
-        if (ops[i] != nullptr && ops[i]->rows > 0) o[i] = DeltaOperand{ops[i]->exps, ops[i]->deltas, ops[i]->rows, ops[i]->rows_pad};
+        if (ops[i] != nullptr && ops[i]->rows > 0) o[i] = DeltaOperand{ops[i]->exps, ops[i]->deltas, ops[i]->l1, ops[i]->bounds, ops[i]->rows, ops[i]->rows_pad};
     const unsigned t0 = (unsigned)(o[0].rows_pad / TILE), t1 = (unsigned)(o[1].rows_pad / TILE);
     if (t0 + t1 == 0 || pl.T == 0 || pl.s == 0) return hipSuccess;
-    hipLaunchKernelGGL(delta_kernel, dim3(t0 + t1, (unsigned)pl.T), dim3(256), 0, st, o[0], o[1], t0, pl.s);
+    hipLaunchKernelGGL(delta_kernel, dim3(t0 + t1, (unsigned)pl.T), dim3(256), 0, st, o[0], o[1], t0, pl.s, pl.b);
     return hipGetLastError();
 }
 

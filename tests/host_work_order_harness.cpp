@@ -19,25 +19,34 @@ int work_items_cover(unsigned groups, unsigned blocks_m, unsigned blocks_n, int 
     return bad;
 }
 
-// 0 if the groups of the pass g_hi ... g_lo hold every pair of it once, each in its slot, none longer than len
+// 0 if the groups of the pass g_hi ... g_lo hold every pair of it once, each in its slot, none longer than len, start where
+// the accumulation expects them, and the list for the kernels holds the same groups, longest first
 int groups_cover(int s, int full, int len, int g_hi, int g_lo) {
     const PairOrder o{s, full, len};
     Pass ps{g_hi, g_lo, 0, 0};
     for (int g = g_hi; g >= g_lo; --g) { ps.npairs += diag_len(o, g); ps.ngroups += diag_groups(o, g); }
-    int seen[MAX_PAIRS] = {};
-    for (int gi = 0; gi < ps.ngroups; ++gi) {
-        const Group r = pass_group(o, ps, gi);
-        if (r.len < 1 || r.len > len) return 1;
-        int slot = 0, g = g_hi;
-        for (; g > r.p0 + r.q0; --g) slot += diag_len(o, g);
-        if (g < g_lo || slot + r.p0 - diag_first_p(o, g) != r.slot) return 2;
-        for (int j = 0; j < r.len; ++j) {
-            if (r.p0 + j > s || r.q0 - j < 1) return 3;
-            ++seen[r.slot + j];
+    static GroupList list;
+    list_groups(o, ps, list);
+    if (list.listed != (ps.ngroups <= MAX_LISTED_GROUPS ? ps.ngroups : 0)) return 5;
+    for (int listed = 0; listed < 2; ++listed) {
+        int seen[MAX_PAIRS] = {}, last = MAX_SLICES;
+        for (int gi = 0; gi < ps.ngroups; ++gi) {
+            const Group r = listed ? listed_group(list, o, ps, gi) : pass_group(o, ps, gi);
+            if (r.len < 1 || r.len > len) return 1;
+            if (listed && list.listed && r.len > last) return 6;
+            last = r.len;
+            int slot = 0, g = g_hi;
+            for (; g > r.p0 + r.q0; --g) slot += diag_len(o, g);
+            if (g < g_lo || slot + r.p0 - diag_first_p(o, g) != r.slot) return 2;
+            for (int j = 0; j < r.len; ++j) {
+                if (r.p0 + j > s || r.q0 - j < 1) return 3;
+                if (((r.p0 - diag_first_p(o, g) + j) % len == 0) != (j == 0)) return 7;
+                ++seen[r.slot + j];
+            }
         }
+        for (int z = 0; z < ps.npairs; ++z)
+            if (seen[z] != 1) return 4;
     }
-    for (int z = 0; z < ps.npairs; ++z)
-        if (seen[z] != 1) return 4;
     return 0;
 }
 

@@ -78,6 +78,10 @@ def test_small_block_kernels_use_no_fp64(tmp_path):
     assert len(bodies) == 5
     for body in bodies.values():
         assert "v_mfma_" in body and not re.search(F64, body)
+    measured = {n: b for n, b in _kernel_bodies("pair_gemm_measured.hip", tmp_path).items() if "pair_gemm_measured_kernel" in n}
+    assert len(measured) == 4
+    for body in measured.values():
+        assert "v_mfma_" in body and not re.search(F64, body) and "scratch_" not in body      # nothing spilled
     fine = {n: b for n, b in _kernel_bodies("accumulate.hip", tmp_path).items() if "accumulate_fine_kernel" in n}
     assert len(fine) == 6
     for name, body in fine.items():
