@@ -14,9 +14,10 @@
 // q is its rounding to an integer, the remainder is what is left, and moving to the next slice is a left shift
 // by c_p - c_(p+1).  Until then the element waits with its significand and exponent: with b <= 7 it is then smaller
 // than half the unit (q = 0); with wider slices it can already reach the unit, and is rounded in its integer form.
-// No FP64 instruction is executed.  Two forms of this element step: slices of at most 7 bits (FP8, FP6, INT8) work on
-// the upper 32-bit word of the fixed-point number (slice_element.hpp); FP16 slices, whose fixed-point form has fewer
-// than 53 fraction bits, keep the 64-bit step below (decode_element, slice_element).
+// No FP64 instruction is executed.  Two forms of this element step: slices of at most 7 bits (FP8, FP6, INT8, and FP16 in
+// blocks of 1024 elements and more) work on the upper 32-bit word of the fixed-point number (slice_element.hpp); wider FP16
+// slices, whose fixed-point form has fewer than 53 fraction bits, take the 64-bit step below (decode_element,
+// slice_element).  4096 + 4096 vectors of 4096 elements, nine FP16 slices of 6 bits: 0.33 ms with the 64-bit step, 0.24 ms with the 32-bit one.
 //
 // A vector is held in the registers of TPR threads (8*U consecutive elements per thread in U groups of
 // eight) for all s slices, so HBM sees each input element once and each slice code once.
@@ -249,6 +250,17 @@ __device__ __forceinline__ void store_fp8_codes_scaled(const int (&qs)[8], float
     *reinterpret_cast<uint2*>(dst) = v;
 }
 
+// FP16 codes of eight slice values (exact: q 2^-b with |q| <= 2^b is a normal number of the format, or zero)
+__device__ __forceinline__ void store_fp16_codes(const float (&f)[8], int64_t ke, uint8_t* dst_slice, int64_t v_rows_pad, int64_t row) {
+    constexpr int EPC = CHUNK_BYTES / 2;
+    uint4 w;
+    w.x = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(f[0], f[1]));
+    w.y = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(f[2], f[3]));
+    w.z = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(f[4], f[5]));
+    w.w = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(f[6], f[7]));
+    *reinterpret_cast<uint4*>(dst_slice + ((size_t)(ke / EPC) * v_rows_pad + row) * CHUNK_BYTES + (ke % EPC) * 2) = w;
+}
+
 // Where the eight 6-bit codes of one octet of a vector go inside a slice matrix: a 32-bit and a 16-bit store (see
 // store_codes).  The same for every slice, so a thread works it out once per octet.
 struct Fp6Slot {
@@ -441,10 +453,25 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
         return val;
     };
 
-    if constexpr (!FP16) {
+    // FP16: sum |q| of the slices, if wanted.  A wave's share goes to LDS and is added up behind the barrier of the next exchange.
+    __shared__ int l1_share[2][BLOCK / 64];
+    auto share_l1 = [&](int p, int mine) {
+        const int share = wave_sum(mine);
+        if ((threadIdx.x & 63) == 0) l1_share[p & 1][threadIdx.x >> 6] = share;
+    };
+    auto store_l1 = [&](int p) {
+        if (tr != 0) return;
+        const int w0 = threadIdx.x >> 6;
+        int sum = 0;
+        for (int w = 0; w < threads / 64; ++w) sum += l1_share[p & 1][w0 + w];
+        v_l1[(t * a.s + p) * v_rows_pad + row] = sum;
+    };
+
+    if (!FP16 || a.b <= 7) {
         // ---- slices of at most 7 bits: the element step on 32-bit words (slice_element.hpp)
         const int pos = F - 32, bias = (1 << (pos - 1)) - 1;
         const uint32_t keep = ~((1u << pos) - 1u);
+        const float code_unit = ldexpf(1.0f, -(pos + a.b));            // q * 2^pos * code_unit = q * 2^-b, the slice value
         const float code_scale = ldexpf(1.0f, pos + a.b);              // q * 2^pos / code_scale = q * 2^-b, the slice value
         Fp6Slot slots[FP6 ? U : 1];                                    // FP6 only: where each octet's codes go inside a slice matrix
         if constexpr (FP6) {
@@ -465,6 +492,7 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
         uint8_t* dst_slice = nullptr;
         int kmax, kmin;
         uint32_t cd_wait;
+        float l1 = 0.0f;                                               // FP16: sum |q| 2^-b of this thread's elements, exact
         // head of slice p: Eq. 4, the unit 2^(c-b) and the distance from the previous unit
         auto begin_slice = [&](int p) {
             cmax = vector_max(cmax, p);
@@ -479,11 +507,23 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
             kmax = KEY_NONE_MAX;
             kmin = KEY_NONE_MIN;
             cd_wait = 0;
+            if constexpr (FP16) {
+                if (v_l1 != nullptr && p > 0) store_l1(p - 1);
+                l1 = 0.0f;
+            }
         };
         auto store_octet = [&](int u, int (&qs)[8]) {                   // qs: q * 2^pos
             const int64_t ke = 8 * ((int64_t)tr + (int64_t)threads * u);
             if constexpr (FMT == FMT_FP8) {
                 if (ke < padded && v_slices != nullptr) store_fp8_codes_scaled(qs, code_scale, ke, dst_slice, v_rows_pad, row);
+            } else if constexpr (FP16) {
+                float f[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    f[e] = (float)qs[e] * code_unit;
+                    l1 += fabsf(f[e]);
+                }
+                if (ke < padded && v_slices != nullptr) store_fp16_codes(f, ke, dst_slice, v_rows_pad, row);
             } else if constexpr (FP6) {
                 if (ke < padded && v_slices != nullptr) store_fp6_codes_at_pos<FMT>(qs, pos, a.b, slots[u], dst_slice);
             } else {
@@ -493,6 +533,9 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
         // tail of slice p: the exponent goes out, the thread forms its candidate for the next one
         auto end_slice = [&](int p, bool settled) {
             if (tr == 0 && v_slices != nullptr) v_exps[(t * a.s + p) * v_rows_pad + row] = c;
+            if constexpr (FP16) {
+                if (v_l1 != nullptr) share_l1(p, (int)ldexpf(l1, a.b));
+            }
             bool needs_exact;
             cmax = narrow_candidate(kmax, kmin, unit, F, needs_exact);
             if (needs_exact) {                                         // the upper words cannot tell: all 64 bits of the remainders
@@ -536,10 +579,16 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
             }
             end_slice(p, true);
         }
+        if constexpr (FP16) {
+            if (v_l1 != nullptr) {
+                __syncthreads();
+                store_l1(a.s - 1);
+            }
+        }
         return;
     }
 
-    // ---- FP16 slices (more than 7 bits wide): element state as described at decode_element
+    // ---- FP16 slices of more than 7 bits (blocks of fewer than 1024 elements): element state as described at decode_element
     int64_t tv[8 * U];
     int pk[8 * U];
 #pragma unroll
@@ -551,15 +600,6 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
     }
     if (nonfinite) atomicOr(a.flags, 1);
 
-    // sum |q| of the slices, if wanted: a wave's share goes to LDS and is added up behind the barrier of the next exchange
-    __shared__ int l1_share[2][BLOCK / 64];
-    auto store_l1 = [&](int p) {
-        if (tr != 0) return;
-        const int w0 = threadIdx.x >> 6;
-        int sum = 0;
-        for (int w = 0; w < threads / 64; ++w) sum += l1_share[p & 1][w0 + w];
-        v_l1[(t * a.s + p) * v_rows_pad + row] = sum;
-    };
     int c_prev = 0;
     for (int p = 0; p < a.s; ++p) {
         cmax = vector_max(cmax, p);
@@ -593,10 +633,7 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
             if (ke < padded && v_slices != nullptr) store_codes<FMT>(qs, ke, dst_slice, v_rows_pad, row, a.b);
         }
         if (tr == 0 && v_slices != nullptr) v_exps[(t * a.s + p) * v_rows_pad + row] = c;
-        if (v_l1 != nullptr) {
-            const int share = wave_sum(l1);
-            if ((threadIdx.x & 63) == 0) l1_share[p & 1][threadIdx.x >> 6] = share;
-        }
+        if (v_l1 != nullptr) share_l1(p, l1);
         // this thread's candidate for the next exponent: remainders are rmax * 2^(unit - F)
         cmax = cdorm;
         if (rmax != 0) {
@@ -817,42 +854,23 @@ __global__ void __launch_bounds__(256) split_stream_kernel(SplitArgs a) {
     }
     int cmax = NO_ELEM;
     bool nonfinite = false;                                          // long_exponents_kernel has reported it
-    if constexpr (!FP16) {
-        const int pos = F - 32, bias = (1 << (pos - 1)) - 1;
-        const uint32_t keep = ~((1u << pos) - 1u);
-        uint64_t T[8];
-        int pk[8];
+    // Blocks this long leave FP16 slices 4 bits at most, so the 32-bit element step serves every format.
+    const int pos = F - 32, bias = (1 << (pos - 1)) - 1;
+    const uint32_t keep = ~((1u << pos) - 1u);
+    uint64_t T[8];
+    int pk[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) decode_narrow(bits[e], F, T[e], pk[e], cmax, nonfinite);
-        int unit_prev = 0;
-        for (int p = 0; p < a.s; ++p, dst_slice += slice_bytes) {
-            const int unit = exps[(int64_t)p * v.rows_pad] - a.b;
-            const int step16 = (unit_prev - unit) * 65536;
-            unit_prev = unit;
-            int kmax = KEY_NONE_MAX, kmin = KEY_NONE_MIN, qs[8];
-            uint32_t cd_wait = 0;
+    for (int e = 0; e < 8; ++e) decode_narrow(bits[e], F, T[e], pk[e], cmax, nonfinite);
+    int unit_prev = 0;
+    for (int p = 0; p < a.s; ++p, dst_slice += slice_bytes) {
+        const int unit = exps[(int64_t)p * v.rows_pad] - a.b;
+        const int step16 = (unit_prev - unit) * 65536;
+        unit_prev = unit;
+        int kmax = KEY_NONE_MAX, kmin = KEY_NONE_MIN, qs[8];
+        uint32_t cd_wait = 0;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) qs[e] = slice_narrow(T[e], pk[e], step16, pos, bias, keep, kmax, kmin, cd_wait) >> pos;
-            store_codes<FMT>(qs, ke, dst_slice, v.rows_pad, row, a.b);
-        }
-    } else {
-        int64_t tv[8];
-        int pk[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) decode_element(bits[e], F, tv[e], pk[e], cmax, nonfinite);
-        const int64_t round_bias = ((int64_t)1 << (F - 1)) - 1;
-        int c_prev = 0;
-        for (int p = 0; p < a.s; ++p, dst_slice += slice_bytes) {
-            const int c = exps[(int64_t)p * v.rows_pad], unit = c - a.b;
-            int rescale = p == 0 ? 0 : c_prev - c;
-            rescale = rescale < 0 ? 0 : (rescale > 63 ? 63 : rescale);
-            c_prev = c;
-            uint64_t rmax = 0;
-            int cdorm = NO_ELEM, qs[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) qs[e] = slice_element(tv[e], pk[e], unit, rescale, F, round_bias, rmax, cdorm);
-            store_codes<FMT>(qs, ke, dst_slice, v.rows_pad, row, a.b);
-        }
+        for (int e = 0; e < 8; ++e) qs[e] = slice_narrow(T[e], pk[e], step16, pos, bias, keep, kmax, kmin, cd_wait) >> pos;
+        store_codes<FMT>(qs, ke, dst_slice, v.rows_pad, row, a.b);
     }
 }
 
