@@ -52,7 +52,7 @@ struct AccArgs {
     int allow_chain;         // the GEMM kernel summed tile-wide runs
     const uint8_t* starts;   // measured runs (RunCheck), or null
     int merge;               // rule "runs": merge equal-scale products of an anti-diagonal element by element
-    const int32_t* da;       // deltas of the block: [s][rows_pad_a / 32]
+    const int32_t* da;       // deltas of the block: [s][rows_pad_a / 32]; null: formed here from the exponents
     const int32_t* db;       // [s][rows_pad_b / 32]
     PairOrder order;
     Pass pass;
@@ -106,9 +106,27 @@ __device__ __forceinline__ void accumulate_body(const AccArgs& a) {
     if (a.starts != nullptr)
         for (int z = tid; z < a.pass.npairs; z += 256) starts[z] = a.starts[((size_t)z * a.tiles_m * a.tiles_n + tile) * 64 + pos];
     // the deltas that decide where the GEMM kernel ended its runs at this position: fetched once, all at the same time
-    if (tid < a.order.s) linkA[tid] = a.da[(int64_t)tid * (a.rows_pad_a / LINK_ROWS) + m0 / LINK_ROWS];
+    if (a.da == nullptr) {
+        // (below, from the exponents in LDS)
+    } else if (tid < a.order.s) linkA[tid] = a.da[(int64_t)tid * (a.rows_pad_a / LINK_ROWS) + m0 / LINK_ROWS];
     else if (tid >= 64 && tid - 64 < a.order.s) linkB[tid - 64] = a.db[(int64_t)(tid - 64) * (a.rows_pad_b / LINK_ROWS) + n0 / LINK_ROWS];
     __syncthreads();
+
+    if (a.da == nullptr && a.starts == nullptr) {
+        // half a wave per slice: is c_p - c_(p+1) the same for all real rows / columns of the position?
+        for (int idx = tid; idx < a.order.s * 32; idx += 256) {
+            const int p = idx >> 5, r = idx & 31, half = lane & 32;
+            const bool last = p + 1 == a.order.s;
+            const int dA = last ? 0 : (p == 0 ? 0 : relA[p][r]) - relA[p + 1][r], dB = last ? 0 : (p == 0 ? 0 : relB[p][r]) - relB[p + 1][r];
+            const int refA = __shfl(dA, half, 64), refB = __shfl(dB, half, 64);
+            const uint64_t okA = __ballot(m0 + r >= a.m || dA == refA), okB = __ballot(n0 + r >= a.n || dB == refB);
+            if (r == 0) {
+                linkA[p] = !last && (uint32_t)(okA >> half) == 0xFFFFFFFFu ? refA : DELTA_IRREGULAR;
+                linkB[p] = !last && (uint32_t)(okB >> half) == 0xFFFFFFFFu ? refB : DELTA_IRREGULAR;
+            }
+        }
+        __syncthreads();
+    }
 
     const int ml = lane & 31;
     const int nl = g4 * 8 + (lane >> 5) * 4 + r0;
@@ -375,8 +393,8 @@ hipError_t launch_accumulate(const Plan& pl, const Operand& A, const Operand& B,
     a.allow_chain = chained ? 1 : 0;
     a.starts = starts;
     a.merge = (sum_rule == SUM_RUNS || accum_mode == ACC_EXACT) ? 1 : 0;
-    a.da = A.deltas + (size_t)t * (A.rows_pad / LINK_ROWS) * pl.s;
-    a.db = B.deltas + (size_t)t * (B.rows_pad / LINK_ROWS) * pl.s;
+    a.da = A.deltas != nullptr ? A.deltas + (size_t)t * (A.rows_pad / LINK_ROWS) * pl.s : nullptr;
+    a.db = B.deltas != nullptr ? B.deltas + (size_t)t * (B.rows_pad / LINK_ROWS) * pl.s : nullptr;
     a.order = order; a.pass = ps;
     a.read_S = !first_pass;
     a.write_S = !last_pass;

@@ -51,7 +51,8 @@ struct Operand {
     int32_t* bounds;      // [T][s][rows_pad/LINK_ROWS]  2^b times the largest l1 of the group (see RunCheck)
     int32_t* deltas;      // [T][s][rows_pad/LINK_ROWS]  per slice p and group of 32 vectors (one matrix-unit tile edge):
                           //                        c_p - c_(p+1) if that difference is the same for all real vectors of
-                          //                        the group, else DELTA_IRREGULAR (always for the last slice)
+                          //                        the group, else DELTA_IRREGULAR (always for the last slice); null:
+                          //                        the kernels form them from the exponents (128 x 128 blocks only)
 };
 
 constexpr int LINK_ROWS = 32;             // granularity of the equal-scale decision: one 32 x 32 matrix-unit tile
@@ -263,10 +264,11 @@ __host__ __device__ inline void acc_order_to_mn(int idx, int& m_in_tile, int& n_
 // ---- launchers (each enqueues on `st` and returns the launch status) ----------------------------------------
 hipError_t launch_transpose(const double* A, int64_t lda, int64_t m, int64_t k, double* At, hipStream_t st);
 
-// Vectors are contiguous: vector r of an operand starts at X + r*ldv and has k entries.  Writes the internal layout of
+// Vector r of an operand starts at X + r*ldv and has k entries, contiguous ones in the second operand, `es0` apart in the
+// first (1 for blocks beyond MAX_K_BLOCK_IN_REGISTERS).  Writes the internal layout of
 // up to two operands in one launch (a null Operand, or one without vectors, is skipped).  Blocks longer than
 // MAX_K_BLOCK_IN_REGISTERS take two launches: the exponents of all slices first, then the slices.
-hipError_t launch_split(const double* X0, int64_t ldv0, const Operand* op0, const double* X1, int64_t ldv1, const Operand* op1,
+hipError_t launch_split(const double* X0, int64_t ldv0, int64_t es0, const Operand* op0, const double* X1, int64_t ldv1, const Operand* op1,
                         const Plan& pl, int* flags, hipStream_t st);
 
 // Slices until every remainder is zero (paragraph before Eq. 4): atomicMax of the per-vector count into flags[1]

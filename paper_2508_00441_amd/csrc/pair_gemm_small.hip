@@ -36,8 +36,11 @@ struct SmallGemmArgs {
     int quads_m, quads_n;    // 128 x 128 blocks that hold real elements
     int allow_chain;
     WorkOrder work;
-    const int32_t* da;       // A deltas of the block: [s][rows_pad_a / 32]
+    const int32_t* da;       // A deltas of the block: [s][rows_pad_a / 32]; null: formed here from the exponents
     const int32_t* db;       // B deltas of the block: [s][rows_pad_b / 32]
+    const int32_t* ea;       // exponents of the block: [s][rows_pad_a]
+    const int32_t* eb;       // [s][rows_pad_b]
+    int64_t m, n;
     PairOrder order;
     Pass pass;
     GroupList groups;
@@ -97,8 +100,10 @@ __global__ void __launch_bounds__(256, 2) pair_gemm_small_kernel(const SmallGemm
     const int64_t groups_a = a.rows_pad_a / LINK_ROWS, groups_b = a.rows_pad_b / LINK_ROWS;
     const int32_t* const dA = a.da + (qm * 4 + wm * 2);
     const int32_t* const dB = a.db + (qn * 4 + wn * 2);
+    uint64_t links[2] = {0, 0};                        // without deltas: four bits per pair, formed below
     auto continue_mask = [&](int jp) -> unsigned {
         if (!a.allow_chain) return 0u;
+        if (a.da == nullptr) return (unsigned)(links[jp >> 4] >> (4 * (jp & 15))) & 0xFu;
         const v2s dav = *(delta2_ptr)(dA + (size_t)(p0 + jp) * groups_a);
         const v2s dbv = *(delta2_ptr)(dB + (size_t)(q0 - jp - 1) * groups_b);
         unsigned cont = 0;
@@ -262,6 +267,45 @@ __global__ void __launch_bounds__(256, 2) pair_gemm_small_kernel(const SmallGemm
         for (int j = 0; j < 2; ++j) zero_tile(acc[i][j]);
 #pragma unroll
     for (int st = 0; st < NSTAGE; ++st) issue_next(st);
+    if (a.da == nullptr && a.allow_chain) {
+        // Lane l has row l of the wave's 64 rows of A and column l of its 64 columns of B; the first stages are on their way
+        // meanwhile.  A launch of its own for the deltas (5 us) would be a tenth of the smallest calls.
+        const int64_t row = (int64_t)qm * QUAD + wm * 64 + lane, col = (int64_t)qn * QUAD + wn * 64 + lane;
+        const int32_t* const ea = a.ea + (size_t)p0 * a.rows_pad_a + row;
+        const int32_t* const eb = a.eb + (size_t)q0 * a.rows_pad_b + col;
+        int cA = ea[0], cB = eb[0];
+        auto same = [&](int d, int ref, bool pad, bool (&ok)[2]) {
+            const uint64_t mask = __ballot(pad || d == ref);
+            ok[0] = (uint32_t)mask == 0xFFFFFFFFu;
+            ok[1] = (uint32_t)(mask >> 32) == 0xFFFFFFFFu;
+        };
+        for (int j0 = 0; j0 + 1 < glen; j0 += 8) {
+            int nA[8], nB[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int j = j0 + u + 1 < glen ? j0 + u + 1 : glen - 1;
+                nA[u] = ea[(size_t)j * a.rows_pad_a];
+                nB[u] = *(eb - (size_t)j * a.rows_pad_b);
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int jp = j0 + u;
+                if (jp + 1 >= glen) break;
+                const int d_a = cA - nA[u], d_b = nB[u] - cB;          // deltas of slices p0 + jp and q0 - jp - 1
+                cA = nA[u];
+                cB = nB[u];
+                const int a0 = __builtin_amdgcn_readlane(d_a, 0), a1 = __builtin_amdgcn_readlane(d_a, 32);
+                const int b0 = __builtin_amdgcn_readlane(d_b, 0), b1 = __builtin_amdgcn_readlane(d_b, 32);
+                bool okA[2], okB[2];
+                same(d_a, lane < 32 ? a0 : a1, row >= a.m, okA);
+                same(d_b, lane < 32 ? b0 : b1, col >= a.n, okB);
+                const unsigned bits = (okA[0] && okB[0] && a0 == b0 ? 1u : 0u) | (okA[1] && okB[0] && a1 == b0 ? 2u : 0u) |
+                                      (okA[0] && okB[1] && a0 == b1 ? 4u : 0u) | (okA[1] && okB[1] && a1 == b1 ? 8u : 0u);
+                if (jp < 16) links[0] |= (uint64_t)bits << (4 * jp);
+                else links[1] |= (uint64_t)bits << (4 * (jp - 16));
+            }
+        }
+    }
     wait_and_barrier<(NSTAGE - 1) * LPW>();
     read_frags(0, 0, 0);
 
@@ -354,8 +398,11 @@ hipError_t launch_pair_gemm_small(const Plan& pl, const Operand& A, const Operan
     a.tiles_m = (int)pl.tiles_m; a.tiles_n = (int)pl.tiles_n;
     a.quads_m = (int)((pl.m + QUAD - 1) / QUAD); a.quads_n = (int)((pl.n + QUAD - 1) / QUAD);
     a.allow_chain = allow_chain ? 1 : 0;
-    a.da = A.deltas + (size_t)t * (A.rows_pad / LINK_ROWS) * pl.s;
-    a.db = B.deltas + (size_t)t * (B.rows_pad / LINK_ROWS) * pl.s;
+    a.da = A.deltas != nullptr ? A.deltas + (size_t)t * (A.rows_pad / LINK_ROWS) * pl.s : nullptr;
+    a.db = B.deltas != nullptr ? B.deltas + (size_t)t * (B.rows_pad / LINK_ROWS) * pl.s : nullptr;
+    a.ea = A.exps + (size_t)t * pl.s * A.rows_pad;
+    a.eb = B.exps + (size_t)t * pl.s * B.rows_pad;
+    a.m = pl.m; a.n = pl.n;
     a.order = order; a.pass = ps;
     list_groups(order, ps, a.groups);
     a.starts = check.starts;

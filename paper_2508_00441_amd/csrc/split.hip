@@ -53,8 +53,8 @@ typedef uint64_t two_doubles __attribute__((ext_vector_type(2), aligned(8)));
 
 // One operand of a split launch.
 struct SplitVectors {
-    const double* X;       // vector r starts at X + r*ldv
-    int64_t ldv;
+    const double* X;       // vector r starts at X + r*ldv, its elements are `es` apart
+    int64_t ldv, es;
     int64_t rows, rows_pad;
     uint8_t* slices;       // null: count only, nothing is stored
     int32_t* exps;
@@ -65,7 +65,7 @@ struct SplitVectors {
 // workgroups of the grid belong to v[0], the rest to v[1].
 struct SplitArgs {
     SplitVectors v[2];
-    unsigned wg_first;     // a multiple of 8
+    unsigned wg_first;     // a multiple of 64
     int64_t k, kb;
     int64_t chunks;        // chunks per block
     int s, b;
@@ -370,18 +370,18 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
     const int threads = WHOLE ? blockDim.x : TPR;     // per vector
     // Workgroups are handed to the eight XCDs (each with an L2 of its own) round-robin by their index.  Neighbouring
     // vectors share the cache lines of the slice layout (a line holds the 16-byte pieces of eight vectors in the
-    // FP6 planes, the 64-byte chunks of two vectors otherwise), so consecutive vectors go to workgroups of the SAME
-    // XCD, where the partial lines meet in one L2 before they are written back.  Each operand's share of the grid is a multiple of 8.
+    // FP6 planes, the 64-byte chunks of two vectors otherwise), so eight consecutive workgroups' worth of vectors go to the
+    // SAME XCD, where the partial lines meet in one L2 before they are written back; the next eight go to the next XCD, so that
+    // also an operand of few vectors is spread over all of them.  Each operand's share of the grid is a multiple of 64.
     const bool second = blockIdx.x >= a.wg_first;                    // which operand this workgroup works on
     const double* const vX = second ? a.v[1].X : a.v[0].X;
-    const int64_t v_ldv = second ? a.v[1].ldv : a.v[0].ldv;
+    const int64_t v_ldv = second ? a.v[1].ldv : a.v[0].ldv, es = second ? a.v[1].es : a.v[0].es;
     const int64_t v_rows = second ? a.v[1].rows : a.v[0].rows, v_rows_pad = second ? a.v[1].rows_pad : a.v[0].rows_pad;
     uint8_t* const v_slices = second ? a.v[1].slices : a.v[0].slices;
     int32_t* const v_exps = second ? a.v[1].exps : a.v[0].exps;
     int32_t* const v_l1 = second ? a.v[1].l1 : a.v[0].l1;
-    const unsigned li = blockIdx.x - (second ? a.wg_first : 0u);     // index and count inside the operand's part of the
-    const unsigned gl = second ? gridDim.x - a.wg_first : a.wg_first;   // grid; both multiples of 8, so li % 8 is the XCD
-    const int64_t wg = (int64_t)(li & 7) * (gl >> 3) + (li >> 3);
+    const unsigned li = blockIdx.x - (second ? a.wg_first : 0u);     // index inside the operand's part of the grid
+    const int64_t wg = (li & ~63u) + (li & 7) * 8 + ((li >> 3) & 7);
     const int64_t row = wg * RPB + threadIdx.x / TPR;
     const int64_t t = blockIdx.y;
     const int64_t k0 = t * a.kb;
@@ -414,11 +414,11 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
 
     bool nonfinite = false;
     int cmax = NO_ELEM;
-    const double* src = vX + row * v_ldv + k0;
+    const double* src = vX + row * v_ldv + k0 * es;
     // the eight FP64 bit patterns of octet u of this thread (zeros beyond the block)
     auto load_octet = [&](int u, uint64_t (&bits)[8]) {
         const int64_t ke = 8 * ((int64_t)tr + (int64_t)threads * u);
-        if (ke + 8 <= klen) {
+        if (es == 1 && ke + 8 <= klen) {
 #pragma unroll
             for (int h = 0; h < 4; ++h) {
                 const two_doubles w = *reinterpret_cast<const two_doubles*>(src + ke + 2 * h);
@@ -427,7 +427,7 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
             }
         } else {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) bits[e] = (ke + e < klen) ? __double_as_longlong(src[ke + e]) : 0ull;
+            for (int e = 0; e < 8; ++e) bits[e] = (ke + e < klen) ? __double_as_longlong(src[(ke + e) * es]) : 0ull;
         }
     };
     // does this wave hold elements of the block in octet u?  (wave-uniform)
@@ -999,25 +999,26 @@ hipError_t launch_transpose(const double* A, int64_t lda, int64_t m, int64_t k, 
 }
 
 namespace {
-SplitVectors split_vectors(const double* X, int64_t ldv, const Operand* op) {
+SplitVectors split_vectors(const double* X, int64_t ldv, int64_t es, const Operand* op) {
     SplitVectors v;
     memset(&v, 0, sizeof(v));
     if (op == nullptr || op->rows == 0) return v;                                 // no vectors: no workgroups
-    v.X = X; v.ldv = ldv; v.rows = op->rows; v.rows_pad = op->rows_pad; v.slices = op->slices; v.exps = op->exps; v.l1 = op->l1;
+    v.X = X; v.ldv = ldv; v.es = es; v.rows = op->rows; v.rows_pad = op->rows_pad; v.slices = op->slices; v.exps = op->exps; v.l1 = op->l1;
     return v;
 }
 }  // namespace
 
-hipError_t launch_split(const double* X0, int64_t ldv0, const Operand* op0, const double* X1, int64_t ldv1, const Operand* op1,
+hipError_t launch_split(const double* X0, int64_t ldv0, int64_t es0, const Operand* op0, const double* X1, int64_t ldv1, const Operand* op1,
                         const Plan& pl, int* flags, hipStream_t st) {
     SplitArgs a;
-    a.v[0] = split_vectors(X0, ldv0, op0);
-    a.v[1] = split_vectors(X1, ldv1, op1);
+    a.v[0] = split_vectors(X0, ldv0, es0, op0);
+    a.v[1] = split_vectors(X1, ldv1, 1, op1);
     a.wg_first = 0;
     a.k = pl.k; a.kb = pl.kb; a.chunks = pl.chunks; a.s = pl.s; a.b = pl.b; a.flags = flags;
     if (a.v[0].rows_pad + a.v[1].rows_pad == 0 || pl.T == 0) return hipSuccess;
     const int64_t vectors = (a.v[0].rows_pad + a.v[1].rows_pad) * pl.T;
     const int fmt = pl.fmt;
+    if (pl.kb > MAX_K_BLOCK_IN_REGISTERS && es0 != 1) return hipErrorInvalidValue;
     if (pl.kb > MAX_K_BLOCK_IN_REGISTERS) return launch_split_long(a, fmt, pl.T, st);
     const int64_t octets = pl.chunks * pl.epc / 8;                              // per vector and block, padded
     // sixteen elements per thread (U = 2) is the measured optimum: more elements per thread cost registers and with
@@ -1046,7 +1047,7 @@ hipError_t launch_count_slices(const double* X, int64_t ldv, const Plan& pl, int
     op.rows = rows;
     op.rows_pad = (rows + TILE - 1) / TILE * TILE;
     op.slices = nullptr; op.exps = nullptr; op.deltas = nullptr; op.l1 = nullptr; op.bounds = nullptr;
-    return launch_split(X, ldv, &op, nullptr, 0, nullptr, cp, flags, st);
+    return launch_split(X, ldv, 1, &op, nullptr, 0, nullptr, cp, flags, st);
 }
 
 hipError_t launch_deltas(const Plan& pl, const Operand* op0, const Operand* op1, hipStream_t st) {

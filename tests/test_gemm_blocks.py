@@ -87,3 +87,28 @@ def test_small_block_kernels_use_no_fp64(tmp_path):
     for name, body in fine.items():
         if "ILi0E" not in name:                          # mode 0 is the hardware FP64 sum
             assert not re.search(F64, body), name
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fmt,m,n,k,s,mode", [("fp8", 130, 70, 100, 20, "triangle"), ("fp8", 65, 97, 200, 12, "full"), ("fp6", 33, 160, 64, 20, "triangle"),
+                                              ("int8", 128, 31, 300, 18, "triangle"), ("fp8", 31, 33, 17, 32, "triangle")])
+def test_long_groups_of_regular_ladders_match_oracle(fmt, m, n, k, s, mode):
+    """One-binade rows (every scale difference the same) with an irregular row and column among them, the last tile partly
+    padding: runs as long as the groups, formed from exponents that the GEMM kernel compares itself."""
+    torch = pytest.importorskip("torch")
+    from paper_2508_00441_amd import device
+    rng = np.random.default_rng(m + n + k)
+    A = inputs.full_mantissa_one_binade(m, k, rng) * np.where(rng.random((m, k)) < 0.5, -1.0, 1.0) * np.ldexp(1.0, rng.integers(-9, 9, m))[:, None]
+    B = inputs.full_mantissa_one_binade(k, n, rng) * np.where(rng.random((k, n)) < 0.5, -1.0, 1.0)
+    A[m // 2, :] = inputs.phi_matrix(1, k, 3.0, rng)[0]
+    B[:, n - 1] = inputs.phi_matrix(1, k, 3.0, rng)[0]
+    Ad, Bd = device.to_device_colmajor(A), device.to_device_colmajor(B)
+    fid, ps = lib.SLICE_FORMATS[fmt], lib.PAIR_SETS[mode]
+    ws = device.Workspace.for_problem(m, n, k, fid, s, 0, pair_set=ps)
+    for accum, rule in (("hw", "runs"), ("emu", "runs"), ("exact", "exact")):
+        Cd = torch.full((n, m), float("nan"), dtype=torch.float64, device="cuda")
+        lib.ozaki_dgemm_ex(m, n, k, Ad, m, Bd, k, Cd, m, fid, s, 0, lib.ACCUM_MODES[accum], ps, lib.SUM_RUNS, 0)
+        assert lib.ozaki_last_device_status() == 0
+        want = oz.ozaki_dgemm(A, B, fmt, s, 0, mode=mode, accumulate=rule)
+        assert np.array_equal(np.ascontiguousarray(Cd.cpu().numpy().T).view(np.uint64), want.view(np.uint64)), accum
+    ws.close()
