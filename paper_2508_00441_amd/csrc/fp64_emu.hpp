@@ -31,6 +31,14 @@ OZAKI_HD int clz64(uint64_t v) {
 #endif
 }
 
+OZAKI_HD int clz32(uint32_t v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __clz((int)v);
+#else
+    return __builtin_clz(v);
+#endif
+}
+
 constexpr uint64_t F64_SIGN = 0x8000000000000000ull;
 constexpr uint64_t F64_FRAC = 0x000FFFFFFFFFFFFFull;
 constexpr uint64_t F64_HIDDEN = 0x0010000000000000ull;
@@ -160,11 +168,7 @@ struct RoundedSum {
     OZAKI_HD bool add(int v, int e2) {                          // same for a 32-bit term: cheaper bit count
         if (v == 0) return true;
         const uint32_t av = (uint32_t)(v < 0 ? -v : v);
-#if defined(__HIP_DEVICE_COMPILE__)
-        return add_bits((int64_t)v, e2, 32 - __clz((int)av));
-#else
-        return add_bits((int64_t)v, e2, 32 - __builtin_clz(av));
-#endif
+        return add_bits((int64_t)v, e2, 32 - clz32(av));
     }
     // v != 0 with nv significant bits
     OZAKI_HD bool add_bits(int64_t v, int e2, int nv) {
@@ -200,10 +204,13 @@ struct RoundedSum {
         // Round t to 53 significant bits, ties to even, on the two's-complement number itself.  The bit count is
         // taken from t with its bits flipped if negative (|t| - 1): that is the bit count of |t| except for a negative
         // power of two, which then keeps one bit more -- it is exact either way and stays within |x| <= 2^53.
-        const uint64_t flipped = (uint64_t)(t ^ (t >> 63));
-        const int drop = 11 - clz64(flipped | 1);               // bits beyond 53
+        // |t| < 2^63, so the upper word decides whether there are more than 53 bits, and at most 10 are dropped: the bit
+        // count and the rounding constant are 32-bit operations.
+        const uint32_t hi = (uint32_t)((uint64_t)t >> 32), flipped = hi ^ (uint32_t)((int32_t)hi >> 31);
+        const int drop = 11 - clz32(flipped | 1u);              // bits beyond 53; not positive if there are none
         if (drop > 0) {
-            x = (t + (((int64_t)1 << (drop - 1)) - 1) + ((t >> drop) & 1)) >> drop;      // may reach +-2^53
+            const uint32_t half = (1u << (drop - 1)) - 1u + (((uint32_t)t >> drop) & 1u);
+            x = (t + (int64_t)half) >> drop;                    // may reach +-2^53
             ex = e + drop;
         } else {
             x = t;
