@@ -654,7 +654,7 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
 // (long_exponents_kernel, remainder_key), from the elements alone, and with them known every element is sliced on its own
 // (split_stream_kernel), with no exchange between threads and no state in memory: the block is read two or three times
 // instead of once, plus 24 bytes of state, per slice.  256 + 320 vectors of 65536 elements, 11 FP8 slices: 6.3 ms with the
-// state in memory, 0.53 ms so.
+// state in memory, 0.49 ms so.
 
 // How far an element's remainder at unit 2^u is from zero, in 2^-32 of the unit and rounded up: the key of the maximum in
 // Eq. 4.  The remainder of mm * 2^E is the distance of its fraction f = mm 2^-sh mod 1 (sh = u - E) from the nearest
@@ -857,20 +857,46 @@ __global__ void __launch_bounds__(256) split_stream_kernel(SplitArgs a) {
     // Blocks this long leave FP16 slices 4 bits at most, so the 32-bit element step serves every format.
     const int pos = F - 32, bias = (1 << (pos - 1)) - 1;
     const uint32_t keep = ~((1u << pos) - 1u);
+    const float code_scale = ldexpf(1.0f, pos + a.b), code_unit = ldexpf(1.0f, -(pos + a.b));
+    const Fp6Slot slot = fp6_slot(ke, v.rows_pad, row);
+    auto store = [&](const int (&qs)[8]) {                           // qs: q * 2^pos
+        if constexpr (FMT == FMT_FP8) {
+            store_fp8_codes_scaled(qs, code_scale, ke, dst_slice, v.rows_pad, row);
+        } else if constexpr (FMT == FMT_INT8) {
+            store_int8_codes_at_pos(qs, pos, ke, dst_slice, v.rows_pad, row);
+        } else if constexpr (FP16) {
+            float f[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) f[e] = (float)qs[e] * code_unit;
+            store_fp16_codes(f, ke, dst_slice, v.rows_pad, row);
+        } else {
+            store_fp6_codes_at_pos<FMT>(qs, pos, a.b, slot, dst_slice);
+        }
+    };
     uint64_t T[8];
     int pk[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) decode_narrow(bits[e], F, T[e], pk[e], cmax, nonfinite);
-    int unit_prev = 0;
-    for (int p = 0; p < a.s; ++p, dst_slice += slice_bytes) {
+    int unit_prev = 0, kmax = KEY_NONE_MAX, kmin = KEY_NONE_MIN, p = 0;
+    // while some element of the wave waits for its unit, then one shift for all (as in split_kernel)
+    for (bool settled = false; p < a.s && !settled; ++p, dst_slice += slice_bytes) {
         const int unit = exps[(int64_t)p * v.rows_pad] - a.b;
         const int step16 = (unit_prev - unit) * 65536;
         unit_prev = unit;
-        int kmax = KEY_NONE_MAX, kmin = KEY_NONE_MIN, qs[8];
+        int qs[8];
         uint32_t cd_wait = 0;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) qs[e] = slice_narrow(T[e], pk[e], step16, pos, bias, keep, kmax, kmin, cd_wait) >> pos;
-        store_codes<FMT>(qs, ke, dst_slice, v.rows_pad, row, a.b);
+        for (int e = 0; e < 8; ++e) qs[e] = slice_narrow(T[e], pk[e], step16, pos, bias, keep, kmax, kmin, cd_wait);
+        store(qs);
+        settled = __ballot(cd_wait != 0) == 0ull;
+    }
+    for (; p < a.s; ++p, dst_slice += slice_bytes) {
+        const int unit = exps[(int64_t)p * v.rows_pad] - a.b, step = unit_prev - unit;
+        unit_prev = unit;
+        int qs[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) qs[e] = slice_narrow_active(T[e], step, pos, bias, keep, kmax, kmin);
+        store(qs);
     }
 }
 
