@@ -37,7 +37,7 @@ namespace ozaki {
 namespace {
 
 struct AccArgs {
-    const float* P;          // [nz][tiles_n][tiles_m][TILE_ELEMS] FP32 (or INT32) words
+    const float* P;          // [nz][quads_n][quads_m][QUAD_ELEMS] FP32 (or INT32) words
     uint64_t* S;             // running block sum, word w of an element at S[w * plane + element] (may be null when unused)
     double* C;
     int64_t ldc;
@@ -46,6 +46,7 @@ struct AccArgs {
     int64_t rows_pad_a, rows_pad_b;
     int64_t m, n;
     int tiles_m, tiles_n;
+    int quads_m, quads_n;
     int two_b;               // 2b: a term is (stored product) * 2^(p_frac - two_b) * 2^e
     int p_frac;              // the stored products are integer multiples of 2^-p_frac (2b; 2b - 2 for FP6 codes; 0 for INT32)
     int read_S, write_S, add_to_C;
@@ -130,8 +131,8 @@ __device__ __forceinline__ void accumulate_body(const AccArgs& a) {
 
     const int ml = lane & 31;
     const int nl = g4 * 8 + (lane >> 5) * 4 + r0;
-    const size_t tile_off = (size_t)tile * TILE_ELEMS + (size_t)pos * 1024 + (size_t)(g4 * 64 + lane) * 4 + r0;
-    const size_t pair_stride = (size_t)a.tiles_m * a.tiles_n * TILE_ELEMS;
+    const size_t tile_off = ((size_t)(tn * 2 + wn) * a.quads_m + tm * 2 + wm) * QUAD_ELEMS + (size_t)sub * 1024 + (size_t)(g4 * 64 + lane) * 4 + r0;
+    const size_t pair_stride = (size_t)a.quads_m * a.quads_n * QUAD_ELEMS;
 
     // the block sum of this thread's elements, in the representation of the mode
     double Sd[R];                                     // HW
@@ -294,7 +295,7 @@ struct ExportArgs {
     float* out;
     uint8_t* run_len;
     int64_t m, n;
-    int tiles_m, tiles_n;
+    int quads_m, quads_n;
     float factor;            // FP32 products: the exact power of two that undoes the FP6 code scaling
     int p_is_int;
     int allow_chain;
@@ -305,7 +306,7 @@ struct ExportArgs {
     Pass pass;
 };
 __global__ void __launch_bounds__(256) export_products_kernel(const ExportArgs a) {
-    const size_t pair_stride = (size_t)a.tiles_m * a.tiles_n * TILE_ELEMS;
+    const size_t pair_stride = (size_t)a.quads_m * a.quads_n * QUAD_ELEMS;
     const int z = blockIdx.y;
     // the pair of slot z: anti-diagonal g, position pos in it
     int g = a.pass.g_hi, pos = z;
@@ -313,11 +314,11 @@ __global__ void __launch_bounds__(256) export_products_kernel(const ExportArgs a
     const int len = diag_len(a.order, g);
     const int p = diag_first_p(a.order, g) + pos - 1, q = g - p - 2;      // 0-based slice indices
     for (size_t gi = (size_t)blockIdx.x * 256 + threadIdx.x; gi < pair_stride; gi += (size_t)gridDim.x * 256) {
-        const int tile = (int)(gi / TILE_ELEMS), idx = (int)(gi % TILE_ELEMS);
-        const int tn = tile / a.tiles_m, tm = tile - tn * a.tiles_m;
+        const int block = (int)(gi / QUAD_ELEMS), idx = (int)(gi % QUAD_ELEMS);
+        const int qn = block / a.quads_m, qm = block - qn * a.quads_m;
         int ml, nl;
         acc_order_to_mn(idx, ml, nl);
-        const int64_t mi = (int64_t)tm * TILE + ml, nj = (int64_t)tn * TILE + nl;
+        const int64_t mi = (int64_t)qm * QUAD + ml, nj = (int64_t)qn * QUAD + nl;
         if (mi >= a.m || nj >= a.n) continue;
         const int32_t* dA = a.da + mi / LINK_ROWS;
         const int32_t* dB = a.db + nj / LINK_ROWS;
@@ -388,6 +389,7 @@ hipError_t launch_accumulate(const Plan& pl, const Operand& A, const Operand& B,
     a.eb = B.exps + (size_t)t * pl.s * B.rows_pad;
     a.rows_pad_a = A.rows_pad; a.rows_pad_b = B.rows_pad;
     a.m = pl.m; a.n = pl.n; a.tiles_m = (int)pl.tiles_m; a.tiles_n = (int)pl.tiles_n;
+    a.quads_m = (int)pl.quads_m; a.quads_n = (int)pl.quads_n;
     a.two_b = 2 * pl.b;
     a.p_frac = pl.p_frac;
     a.allow_chain = chained ? 1 : 0;
@@ -427,7 +429,7 @@ hipError_t launch_export_products(const Plan& pl, const Operand& A, const Operan
     if (ps.npairs <= 0 || pl.m == 0 || pl.n == 0) return hipSuccess;
     ExportArgs a;
     a.P = P; a.out = out; a.run_len = run_len_out;
-    a.m = pl.m; a.n = pl.n; a.tiles_m = (int)pl.tiles_m; a.tiles_n = (int)pl.tiles_n;
+    a.m = pl.m; a.n = pl.n; a.quads_m = (int)pl.quads_m; a.quads_n = (int)pl.quads_n;
     a.factor = ldexpf(1.0f, pl.p_is_int ? 0 : pl.p_frac - 2 * pl.b);
     a.p_is_int = pl.p_is_int;
     a.allow_chain = chained ? 1 : 0;
@@ -435,7 +437,7 @@ hipError_t launch_export_products(const Plan& pl, const Operand& A, const Operan
     a.db = B.deltas + (size_t)t * (B.rows_pad / LINK_ROWS) * pl.s;
     a.ga = A.rows_pad / LINK_ROWS; a.gb = B.rows_pad / LINK_ROWS;
     a.order = order; a.pass = ps;
-    dim3 grid(grid_for(pl.tiles_m * pl.tiles_n * (int64_t)TILE_ELEMS), (unsigned)ps.npairs);
+    dim3 grid(grid_for(pl.quads_m * pl.quads_n * (int64_t)QUAD_ELEMS), (unsigned)ps.npairs);
     hipLaunchKernelGGL(export_products_kernel, grid, dim3(256), 0, st, a);
     return hipGetLastError();
 }

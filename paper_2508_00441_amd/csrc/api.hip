@@ -93,7 +93,7 @@ void choose_gemm(Plan& pl, int pairs, bool measured_runs) {
     pl.group_len = most;
     const int64_t tiles = pl.tiles_m * pl.tiles_n;
     if (tiles == 0 || tiles >= 256) return;
-    const int64_t quads = ((pl.m + QUAD - 1) / QUAD) * ((pl.n + QUAD - 1) / QUAD);
+    const int64_t quads = pl.quads_m * pl.quads_n;
     const int longest_diag = pairs < pl.s ? pairs : pl.s, shortest = most > 1 ? 2 : 1;
     double best = 1e300;
     for (int small = 0; small < 2; ++small) {
@@ -148,6 +148,8 @@ int make_plan(int64_t m, int64_t n, int64_t k, int fmt, int s, int64_t k_block, 
     pl.run_limit = rl < 1 ? 1 : rl > MAX_SLICES ? MAX_SLICES : (int)rl;
     pl.tiles_m = (m + TILE - 1) / TILE;
     pl.tiles_n = (n + TILE - 1) / TILE;
+    pl.quads_m = (m + QUAD - 1) / QUAD;
+    pl.quads_n = (n + QUAD - 1) / QUAD;
     pl.m_pad = pl.tiles_m * TILE;
     pl.n_pad = pl.tiles_n * TILE;
     choose_gemm(pl, pl.npairs, false);
@@ -183,8 +185,12 @@ size_t fixed_bytes(const Plan& pl) {
            slices_bytes(pl, pl.n_pad) + exps_bytes(pl, pl.m_pad) + exps_bytes(pl, pl.n_pad) + deltas_bytes(pl, pl.m_pad) +
            deltas_bytes(pl, pl.n_pad);
 }
+// The documented sizes count a product with whole 256 x 256 tiles, and the running block sum between passes with the three
+// words of the exact mode whatever the mode; carve() packs closer (stored_bytes, sum_plane_bytes), so that more products of a
+// small workspace stay resident and fewer passes are needed.
 size_t pair_bytes(const Plan& pl) { return (size_t)pl.m_pad * pl.n_pad * sizeof(float); }
-// running block sum between passes: room for the three words of the exact mode whatever the mode
+size_t stored_bytes(const Plan& pl) { return (size_t)pl.quads_m * pl.quads_n * QUAD_ELEMS * sizeof(float); }
+size_t sum_plane_bytes(const Plan& pl) { return 2 * stored_bytes(pl); }
 size_t sum_bytes(const Plan& pl) { return (size_t)pl.m_pad * pl.n_pad * sizeof(uint64_t) * SUM_WORDS_MAX; }
 
 size_t recommended_bytes(const Plan& pl) {
@@ -204,7 +210,8 @@ size_t minimum_bytes(const Plan& pl) {
 size_t product_bytes(const Plan& pl) { return align_up((size_t)pl.m * pl.n * sizeof(double)); }
 
 // Places every buffer in the work memory; returns false if it does not fit.
-bool carve(const Plan& pl, Carve& c, bool want_product, WorkMem wm) {
+// sum_words: 64-bit words per element of a running block sum in the call's mode.
+bool carve(const Plan& pl, Carve& c, bool want_product, int sum_words, WorkMem wm) {
     uint8_t* const ws = wm.ptr;
     const size_t ws_bytes = wm.bytes;
     if (!ws) return false;
@@ -226,21 +233,22 @@ bool carve(const Plan& pl, Carve& c, bool want_product, WorkMem wm) {
     c.W = nullptr;
     if (want_product) { c.W = reinterpret_cast<double*>(ws + off); off += product_bytes(pl); }
     if (off > ws_bytes) return false;
-    const size_t rest = ws_bytes - off, pb = pair_bytes(pl);
+    const size_t rest = ws_bytes - off, pb = pair_bytes(pl), stored = stored_bytes(pl);
     if (pb == 0) { c.S = nullptr; c.P = nullptr; c.chunk_pairs = pl.npairs; return true; }
-    if (rest >= (size_t)pl.npairs * pb) {
+    const bool all_documented = rest >= (size_t)pl.npairs * pb;
+    if (!all_documented && rest < sum_bytes(pl) + (size_t)pl.s * pb) return false;      // below the documented minimum
+    if (rest >= (size_t)pl.npairs * stored) {
         c.S = nullptr;
         c.P = reinterpret_cast<float*>(ws + off);
         c.chunk_pairs = pl.npairs;
         return true;
     }
-    if (rest < sum_bytes(pl) + (size_t)pl.s * pb) return false;
     c.S = reinterpret_cast<uint64_t*>(ws + off);
-    off += sum_bytes(pl);
+    off += (size_t)sum_words * sum_plane_bytes(pl);
     c.P = reinterpret_cast<float*>(ws + off);
-    size_t fit = (ws_bytes - off) / pb;
+    const size_t fit = (ws_bytes - off) / stored;                                           // at least the documented s
     c.chunk_pairs = fit > (size_t)pl.npairs ? pl.npairs : (int)fit;
-    return c.chunk_pairs >= pl.s;
+    return true;
 }
 
 // Measured runs (RunCheck) where run_limit cuts anti-diagonals, and the buffers they need.  These live in memory whose own
@@ -261,7 +269,7 @@ RunCheck place_run_check(const Plan& pl, Carve& c) {
     if ((from_slices ? ba + bb : 0) + starts > room) return none;
     if (!from_slices) return RunCheck{at, nullptr, nullptr};
     const size_t la = exps_bytes(pl, pl.m_pad), lb = exps_bytes(pl, pl.n_pad);
-    if (la + lb > (size_t)c.chunk_pairs * pair_bytes(pl)) return none;
+    if (la + lb > (size_t)c.chunk_pairs * stored_bytes(pl)) return none;
     c.A.l1 = reinterpret_cast<int32_t*>(c.P);
     c.B.l1 = reinterpret_cast<int32_t*>(reinterpret_cast<uint8_t*>(c.P) + la);
     c.A.bounds = reinterpret_cast<int32_t*>(at);
@@ -380,7 +388,7 @@ int dgemm_core(const Plan& plan, double alpha, const double* A, int64_t lda, con
     const bool scaled = !(alpha == 1.0 && beta == 0.0);
     Carve c;
     c.W = nullptr;
-    if ((k > 0 || scaled) && !carve(plan, c, scaled, wm)) return OZAKI_STATUS_WORKSPACE;
+    if ((k > 0 || scaled) && !carve(plan, c, scaled, o.accum_mode == OZAKI_ACCUM_EXACT_FIXED ? SUM_WORDS_MAX : 1, wm)) return OZAKI_STATUS_WORKSPACE;
     Plan pl = plan;
     // the plain rule adds every product on its own, so the matrix unit must not sum across pairs
     const bool chained = o.sum_rule == OZAKI_SUM_RUNS || o.accum_mode == OZAKI_ACCUM_EXACT_FIXED;
@@ -662,7 +670,7 @@ int ozaki_split(int is_B, int64_t rows, int64_t k, const double* X, int64_t ldx,
     if (!slices_out) return -9;
     if (!exps_out) return -10;
     Carve c;
-    if (!carve(pl, c, false, context_workspace())) return OZAKI_STATUS_WORKSPACE;
+    if (!carve(pl, c, false, 1, context_workspace())) return OZAKI_STATUS_WORKSPACE;
     int rc = run_split(pl, c, X, ldx, X, ldx, !is_B, is_B != 0);
     if (rc) return rc;
     hipStream_t stream = ctx().stream;
@@ -727,7 +735,7 @@ int ozaki_pair_products(int64_t m, int64_t n, int64_t k, const double* A, int64_
     if (ldb < k) return -7;
     if (!P_out) return -13;
     Carve c;
-    if (!carve(pl, c, false, context_workspace())) return OZAKI_STATUS_WORKSPACE;
+    if (!carve(pl, c, false, 1, context_workspace())) return OZAKI_STATUS_WORKSPACE;
     if (c.chunk_pairs < pl.npairs) choose_gemm(pl, c.chunk_pairs, false);
     hipStream_t stream = ctx().stream;
     const PairOrder order = order_of(pl);

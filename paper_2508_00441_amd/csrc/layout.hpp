@@ -14,8 +14,9 @@ constexpr int64_t MAX_K_BLOCK_IN_REGISTERS = 16384;     // longer blocks: split_
 constexpr int TILE = 256;
 constexpr int CHUNK_BYTES = 64;           // bytes of the inner dimension per row staged per pipeline step (FP8, FP16)
 constexpr int CHUNK_BYTES_FP6 = 48;       // the same 64 inner indices as 6-bit codes
-constexpr int TILE_ELEMS = TILE * TILE;
-constexpr int QUAD = 128;                 // edge of a workgroup's block in the small-problem GEMM kernel
+constexpr int QUAD = 128;                 // edge of a block of the product storage: a workgroup's share in the small-problem GEMM
+                                          // kernel, a wave's in the other one
+constexpr int QUAD_ELEMS = QUAD * QUAD;
 
 // slice formats (values of ozaki_slice_format)
 constexpr int FMT_FP8 = 0, FMT_FP16 = 1, FMT_FP6 = 2, FMT_FP6_E3M2 = 3, FMT_INT8 = 4;     // FMT_FP6 is E2M3
@@ -79,6 +80,7 @@ struct Plan {
     int pair_bound;       // kb * 4^b: no partial sum of a pair product is larger (FP32 formats: at most 2^24)
     int group_len;        // pairs per group of the GEMM kernel, <= run_limit, or s with measured runs (PairOrder::run_limit of the launches)
     int64_t tiles_m, tiles_n;
+    int64_t quads_m, quads_n;    // 128 x 128 blocks that hold elements of C
     int64_t m_pad, n_pad;
     int small_tiles;      // 1: the GEMMs run in 128 x 128 blocks (launch_pair_gemm_small)
     int p_is_int;         // 1: the stored products are INT32 words (INT8 slices), 0: FP32
@@ -228,7 +230,7 @@ __host__ __device__ inline WorkOrder work_order(int64_t total, int per_xcd, int6
 // before.  The bound is kb 4^b where run_limit >= 2; where a single pair may fill the window (FP16 with the widest slices) it
 // is 2^b sum |q| over a vector, from the slicing, the smaller of the two operands' maxima over the tile's 32 vectors.  Which
 // pairs start a run is then data; the GEMM kernel writes it down for the accumulation, a byte per product slot and tile:
-// starts[slot][tile_n][tile_m][position in the order of the product storage], 1 if the slot holds a run's sum.
+// starts[slot][tile_n][tile_m][wave of the 256 x 256 kernel * 16 + sub], 1 if the slot holds a run's sum.
 struct RunCheck {
     uint8_t* starts;          // null: runs of at most run_limit pairs, decided from the deltas alone
     const int32_t* bound_a;   // [T][s][rows_pad_a / LINK_ROWS] bounds of the slices' pair products, or null: pair_bound for all
@@ -247,18 +249,17 @@ __host__ __device__ inline bool pair_linked(const int32_t* dA, int64_t ga, const
 }
 
 // ---- pair-product storage ("accumulator order") ------------------------------------------------------------
-// The FP32 product of one pair is stored tile by tile, [tile_n][tile_m][TILE_ELEMS], and inside a tile in
-// the order the matrix unit leaves it in the registers of the workgroup's four waves:
-//     float index = ((((wave*16 + sub)*4 + a)*64 + lane)*4 + r
-//     wave = wn*2 + wm (wn, wm in {0,1});  sub = ti*4 + tj (ti, tj in 0..3)
-//     column of C (n) = tile_n*256 + wn*128 + ti*32 + a*8 + (lane/32)*4 + r
-//     row    of C (m) = tile_m*256 + wm*128 + tj*32 + lane%32
+// The FP32 product of one pair is stored in blocks of 128 x 128, [block_n][block_m][QUAD_ELEMS], only the blocks that hold
+// elements of C, and inside a block in the order the matrix unit leaves it in the registers of a wave:
+//     float index = ((sub*4 + a)*64 + lane)*4 + r
+//     sub = ti*4 + tj (ti, tj in 0..3)
+//     column of C (n) = block_n*128 + ti*32 + a*8 + (lane/32)*4 + r
+//     row    of C (m) = block_m*128 + tj*32 + lane%32
 // Every wave-wide store / load of this buffer is one contiguous kilobyte.
-__host__ __device__ inline void acc_order_to_mn(int idx, int& m_in_tile, int& n_in_tile) {
-    int r = idx & 3, lane = (idx >> 2) & 63, a = (idx >> 8) & 3, sub = (idx >> 10) & 15, wave = idx >> 14;
-    int ti = sub >> 2, tj = sub & 3, wn = wave >> 1, wm = wave & 1;
-    n_in_tile = wn * 128 + ti * 32 + a * 8 + (lane >> 5) * 4 + r;
-    m_in_tile = wm * 128 + tj * 32 + (lane & 31);
+__host__ __device__ inline void acc_order_to_mn(int idx, int& m_in_block, int& n_in_block) {
+    int r = idx & 3, lane = (idx >> 2) & 63, a = (idx >> 8) & 3, sub = idx >> 10;
+    n_in_block = (sub >> 2) * 32 + a * 8 + (lane >> 5) * 4 + r;
+    m_in_block = (sub & 3) * 32 + (lane & 31);
 }
 
 // ---- launchers (each enqueues on `st` and returns the launch status) ----------------------------------------
@@ -281,7 +282,7 @@ hipError_t launch_export_slices(const Plan& pl, const Operand& op, void* out, hi
 // Fills Operand::deltas from Operand::exps, for up to two operands in one launch.
 hipError_t launch_deltas(const Plan& pl, const Operand* op0, const Operand* op1, hipStream_t st);
 
-// Products of the pairs of pass `ps` of block t into P ([ps.npairs][tiles_n][tiles_m][TILE_ELEMS] floats).  With
+// Products of the pairs of pass `ps` of block t into P ([ps.npairs][quads_n][quads_m][QUAD_ELEMS] floats).  With
 // allow_chain, consecutive pairs of a group that are linked for a tile (pair_linked) form a run whose exact sum is
 // stored in the slot of the run's first pair; the slots of the other pairs of the run are left untouched.
 hipError_t launch_pair_gemm(const Plan& pl, const Operand& A, const Operand& B, const PairOrder& order, const Pass& ps,
@@ -292,7 +293,7 @@ hipError_t launch_pair_gemm_small(const Plan& pl, const Operand& A, const Operan
 
 // Accumulate the pairs of pass `ps` of block t.  S_io: running block sum in accumulator order (read unless the
 // pass is the block's first, written unless it is the last): one 64-bit word per element (FP64 bits), three in the
-// exact mode, word w of element e at S_io[w * tiles * TILE_ELEMS + e].  On the last pass the block sum is rescaled by
+// exact mode, word w of element e at S_io[w * quads * QUAD_ELEMS + e].  On the last pass the block sum is rescaled by
 // the first-slice exponents and stored to C (t == 0) or added to C (t > 0).  `chained`: the products were written
 // with allow_chain; starts: RunCheck::starts of that launch.  sum_rule SUM_PLAIN: every product is added on its own.
 hipError_t launch_accumulate(const Plan& pl, const Operand& A, const Operand& B, const PairOrder& order, const Pass& ps,

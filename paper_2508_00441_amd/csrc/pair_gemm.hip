@@ -21,6 +21,7 @@ hipError_t launch_pair_gemm(const Plan& pl, const Operand& A, const Operand& B, 
     a.P = P;
     a.rows_pad_a = A.rows_pad; a.rows_pad_b = B.rows_pad; a.chunks = pl.chunks;
     a.tiles_m = (int)pl.tiles_m; a.tiles_n = (int)pl.tiles_n;
+    a.quads_m = (int)pl.quads_m; a.quads_n = (int)pl.quads_n;
     a.allow_chain = allow_chain ? 1 : 0;
     a.da = A.deltas + (size_t)t * (A.rows_pad / LINK_ROWS) * pl.s;
     a.db = B.deltas + (size_t)t * (B.rows_pad / LINK_ROWS) * pl.s;

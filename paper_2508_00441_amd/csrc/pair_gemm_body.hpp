@@ -51,10 +51,11 @@ namespace ozaki {
 struct GemmArgs {
     const uint8_t* sa;       // A slices of the block: [s][chunks][rows_pad_a][row bytes]
     const uint8_t* sb;       // B slices of the block
-    float* P;                // [nz][tiles_n][tiles_m][TILE_ELEMS]
+    float* P;                // [nz][quads_n][quads_m][QUAD_ELEMS]
     int64_t rows_pad_a, rows_pad_b;
     int64_t chunks;
     int tiles_m, tiles_n;
+    int quads_m, quads_n;
     int allow_chain;
     WorkOrder work;
     const int32_t* da;       // A deltas of the block: [s][rows_pad_a / 32]
@@ -232,9 +233,12 @@ __device__ __forceinline__ void pair_gemm_body(const GemmArgs& a) {
     // the wave's part of the product slot `slot`, MFMA tile (i, j): 4 KiB contiguous, 16 bytes per lane and quarter.
     // The tile's base address is wave-uniform (it stays in scalar registers), the lane adds a 32-bit byte offset.
     const unsigned lane_bytes = (unsigned)lane * 16u;
+    // A wave whose 128 x 128 block lies outside the matrix has nothing to store.
+    const int qn = tn * 2 + wn, qm = tm * 2 + wm;
+    const bool has_block = qn < a.quads_n && qm < a.quads_m;
     auto store_tile = [&](int slot, int i, int j, const acc_t& t) {
-        char* base = reinterpret_cast<char*>(a.P + ((size_t)(slot * a.tiles_n + tn) * a.tiles_m + tm) * TILE_ELEMS + (size_t)wave * 16384 +
-                                             (size_t)(i * 4 + j) * 1024);
+        if (!has_block) return;
+        char* base = reinterpret_cast<char*>(a.P + ((size_t)(slot * a.quads_n + qn) * a.quads_m + qm) * QUAD_ELEMS + (size_t)(i * 4 + j) * 1024);
 #pragma unroll
         for (int g4 = 0; g4 < 4; ++g4) {
             acc4_t v = {t[4 * g4], t[4 * g4 + 1], t[4 * g4 + 2], t[4 * g4 + 3]};

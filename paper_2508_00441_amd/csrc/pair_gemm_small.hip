@@ -29,10 +29,10 @@ typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 struct SmallGemmArgs {
     const uint8_t* sa;       // A slices of the block: [s][chunks][rows_pad_a][row bytes]
     const uint8_t* sb;       // B slices of the block
-    float* P;                // [nz][tiles_n][tiles_m][TILE_ELEMS]
+    float* P;                // [nz][quads_n][quads_m][QUAD_ELEMS]
     int64_t rows_pad_a, rows_pad_b;
     int chunks;
-    int tiles_m, tiles_n;    // 256 x 256 tiles: the product layout
+    int tiles_m, tiles_n;    // 256 x 256 tiles: the layout of the run starts
     int quads_m, quads_n;    // 128 x 128 blocks that hold real elements
     int allow_chain;
     WorkOrder work;
@@ -191,11 +191,10 @@ __global__ void __launch_bounds__(256, 2) pair_gemm_small_kernel(const SmallGemm
 #pragma unroll
         for (int r = 0; r < 16; ++r) t[r] = 0;
     };
-    // 32 x 32 tile (i, j) of the wave inside the 256 x 256 tile's accumulator order: the block is the part of "wave"
-    // (qn & 1) * 2 + (qm & 1) there, the tile its sub-tile (wn * 2 + i) * 4 + (wm * 2 + j)
+    // 32 x 32 tile (i, j) of the wave is sub-tile (wn * 2 + i) * 4 + (wm * 2 + j) of the block
     const unsigned lane_bytes = (unsigned)lane * 16u;
-    const size_t block_at = ((size_t)(qn >> 1) * a.tiles_m + (qm >> 1)) * TILE_ELEMS + (size_t)((qn & 1) * 2 + (qm & 1)) * 16384;
-    const size_t pair_stride = (size_t)a.tiles_n * a.tiles_m * TILE_ELEMS;
+    const size_t block_at = ((size_t)qn * a.quads_m + qm) * QUAD_ELEMS;
+    const size_t pair_stride = (size_t)a.quads_n * a.quads_m * QUAD_ELEMS;
     auto store_tile = [&](int slot, int i, int j, const acc_t& t) {
         char* base = reinterpret_cast<char*>(a.P + (size_t)slot * pair_stride + block_at + (size_t)((wn * 2 + i) * 4 + wm * 2 + j) * 1024);
 #pragma unroll
@@ -396,7 +395,7 @@ hipError_t launch_pair_gemm_small(const Plan& pl, const Operand& A, const Operan
     a.P = P;
     a.rows_pad_a = A.rows_pad; a.rows_pad_b = B.rows_pad; a.chunks = (int)pl.chunks;
     a.tiles_m = (int)pl.tiles_m; a.tiles_n = (int)pl.tiles_n;
-    a.quads_m = (int)((pl.m + QUAD - 1) / QUAD); a.quads_n = (int)((pl.n + QUAD - 1) / QUAD);
+    a.quads_m = (int)pl.quads_m; a.quads_n = (int)pl.quads_n;
     a.allow_chain = allow_chain ? 1 : 0;
     a.da = A.deltas != nullptr ? A.deltas + (size_t)t * (A.rows_pad / LINK_ROWS) * pl.s : nullptr;
     a.db = B.deltas != nullptr ? B.deltas + (size_t)t * (B.rows_pad / LINK_ROWS) * pl.s : nullptr;

@@ -82,6 +82,8 @@ def test_small_block_kernels_use_no_fp64(tmp_path):
     assert len(measured) == 4
     for body in measured.values():
         assert "v_mfma_" in body and not re.search(F64, body) and "scratch_" not in body      # nothing spilled
+    exponents = [b for n, b in _kernel_bodies("split.hip", tmp_path).items() if "long_exponents_kernel" in n]
+    assert len(exponents) == 1 and not re.search(F64, exponents[0])
     fine = {n: b for n, b in _kernel_bodies("accumulate.hip", tmp_path).items() if "accumulate_fine_kernel" in n}
     assert len(fine) == 6
     for name, body in fine.items():
