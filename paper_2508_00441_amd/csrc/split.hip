@@ -647,6 +647,132 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
     }
 }
 
+// Blocks of at most 256 elements, slices of at most 7 bits: a wave per vector, four elements per lane.  (With eight, half the
+// lanes of split_kernel are idle there and a thread's serial chain, which is what these launches take, is twice as long:
+// 256 + 256 vectors of 256 elements, 12 FP8 slices: 13.5 -> 10 us; 256 + 8192 of 256: 50 -> 30 us.)  The steps are those of split_kernel.
+template <int FMT>
+__global__ void __launch_bounds__(256) slice_short_kernel(SplitArgs a) {
+    constexpr bool FP6 = fmt_is_fp6(FMT);
+    constexpr int ROWB = FP6 ? CHUNK_BYTES_FP6 : CHUNK_BYTES;
+    const int lane = threadIdx.x & 63;
+    const bool second = blockIdx.x >= a.wg_first;
+    const SplitVectors& v = second ? a.v[1] : a.v[0];
+    const unsigned li = blockIdx.x - (second ? a.wg_first : 0u);     // dealt to the XCDs as in split_kernel
+    const int64_t row = ((int64_t)((li & ~63u) + (li & 7) * 8 + ((li >> 3) & 7))) * 4 + (threadIdx.x >> 6);
+    const int64_t t = blockIdx.y;
+    int64_t klen = a.k - t * a.kb;
+    if (klen > a.kb) klen = a.kb;
+    if (row >= v.rows) klen = 0;                                     // a padding vector: zero codes, c = 0
+    const int ke = 4 * lane;
+    const bool stores = ke < a.chunks * CHUNK_BYTES;
+    const int F = 60 - a.b, pos = F - 32, bias = (1 << (pos - 1)) - 1;
+    const uint32_t keep = ~((1u << pos) - 1u);
+    const float code_scale = ldexpf(1.0f, pos + a.b);
+    const double* const src = v.X + row * v.ldv + t * a.kb * v.es;
+    uint64_t bits[4];
+    if (v.es == 1 && ke + 4 <= klen) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const two_doubles w = *reinterpret_cast<const two_doubles*>(src + ke + 2 * h);
+            bits[2 * h] = w.x;
+            bits[2 * h + 1] = w.y;
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bits[e] = (ke + e < klen) ? (uint64_t)__double_as_longlong(src[(ke + e) * v.es]) : 0ull;
+    }
+    uint64_t T[4];
+    int pk[4], cmax = NO_ELEM;
+    bool nonfinite = false;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) decode_narrow(bits[e], F, T[e], pk[e], cmax, nonfinite);
+    if (nonfinite) atomicOr(a.flags, 1);
+
+    const size_t slice_bytes = (size_t)a.chunks * v.rows_pad * ROWB;
+    uint8_t* dst_slice = v.slices + (size_t)(t * a.s) * slice_bytes;
+    // FP6: an even lane stores the 48 bits of its own four codes and its neighbour's
+    const Fp6Slot slot = fp6_slot(ke & ~7, v.rows_pad, row);
+    const size_t at = ((size_t)(ke / CHUNK_BYTES) * v.rows_pad + row) * CHUNK_BYTES + ke % CHUNK_BYTES;
+    auto store = [&](const int (&qs)[4]) {                           // qs: q * 2^pos
+        if constexpr (FP6) {
+            constexpr int K = FMT == FMT_FP6_E3M2 ? 3 : 4;
+            const int down = pos - (K - a.b);
+            uint32_t w = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t mag = (uint32_t)(qs[e] < 0 ? -qs[e] : qs[e]) >> down, sign = ((uint32_t)qs[e] >> 26) & 32u;
+                w |= ((FMT == FMT_FP6_E3M2 ? (uint32_t)((0xCBA986420ull >> (4 * mag)) & 0xFull) : mag) | sign) << (6 * e);
+            }
+            const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0xB1, 0xF, 0xF, false);     // the other lane of the pair
+            if (stores && (lane & 1) == 0) {
+                const uint64_t w48 = (uint64_t)w | ((uint64_t)next << 24);
+                *reinterpret_cast<uint32_t*>(dst_slice + slot.at32) = slot.low32 ? (uint32_t)w48 : (uint32_t)(w48 >> 16);
+                *reinterpret_cast<uint16_t*>(dst_slice + slot.at16) = slot.low32 ? (uint16_t)(w48 >> 32) : (uint16_t)w48;
+            }
+        } else {
+            uint32_t w = 0;
+            if constexpr (FMT == FMT_FP8) {
+                typedef short short2v __attribute__((ext_vector_type(2)));
+                short2v r = {0, 0};
+                r = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(r, (float)qs[0], (float)qs[1], code_scale, false);
+                r = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(r, (float)qs[2], (float)qs[3], code_scale, true);
+                w = __builtin_bit_cast(uint32_t, r);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w |= __builtin_amdgcn_ubfe((uint32_t)qs[e], pos, 8) << (8 * e);
+            }
+            if (stores) *reinterpret_cast<uint32_t*>(dst_slice + at) = w;
+        }
+    };
+    int unit_prev = 0, unit = 0, step = 0, kmax, kmin;
+    uint32_t cd_wait;
+    auto begin_slice = [&](int p) {
+        cmax = wave_max(cmax);
+        const int c = (cmax == NO_ELEM) ? 0 : cmax;
+        unit = c - a.b;
+        step = unit_prev - unit;
+        unit_prev = unit;
+        kmax = KEY_NONE_MAX;
+        kmin = KEY_NONE_MIN;
+        cd_wait = 0;
+        if (lane == 0) v.exps[(t * a.s + p) * v.rows_pad + row] = c;
+    };
+    auto end_slice = [&](bool settled) {
+        bool needs_exact;
+        cmax = narrow_candidate(kmax, kmin, unit, F, needs_exact);
+        if (needs_exact) {
+            uint64_t mx = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint64_t ar = (settled || pk[i] == 0) ? narrow_abs(T[i]) : 0ull;
+                mx = ar > mx ? ar : mx;
+            }
+            cmax = narrow_candidate_exact(mx, unit, F);
+        }
+        const int cw = (int)cd_wait - CD_BIAS;
+        cmax = (cd_wait != 0 && cw > cmax) ? cw : cmax;
+        dst_slice += slice_bytes;
+    };
+    int p = 0;
+    for (bool settled = false; p < a.s && !settled; ++p) {
+        begin_slice(p);
+        int qs[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) qs[e] = slice_narrow(T[e], pk[e], step * 65536, pos, bias, keep, kmax, kmin, cd_wait);
+        store(qs);
+        settled = __ballot(cd_wait != 0) == 0ull;
+        end_slice(false);
+    }
+    for (; p < a.s; ++p) {
+        begin_slice(p);
+        int qs[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) qs[e] = slice_narrow_active(T[e], step, pos, bias, keep, kmax, kmin);
+        store(qs);
+        end_slice(true);
+    }
+}
+
 // ---- Blocks too long for the registers of one workgroup --------------------------------------------------------
 // The remainders need not be carried from slice to slice: x^(p) differs from x by a multiple of the previous unit, which
 // is an even multiple of this one (every remainder is at most half a unit, so the units 2^u_p shrink by b+1 bits or more),
@@ -996,6 +1122,17 @@ hipError_t launch_split_cfg(const SplitArgs& a_in, int fmt, int64_t T, hipStream
     return hipGetLastError();
 }
 
+hipError_t launch_split_short(const SplitArgs& a_in, int fmt, int64_t T, hipStream_t st) {
+    SplitArgs a = a_in;
+    a.wg_first = (unsigned)(a.v[0].rows_pad / 4);
+    const dim3 grid(a.wg_first + (unsigned)(a.v[1].rows_pad / 4), (unsigned)T), block(256);
+    if (fmt == FMT_FP6) hipLaunchKernelGGL((slice_short_kernel<FMT_FP6>), grid, block, 0, st, a);
+    else if (fmt == FMT_FP6_E3M2) hipLaunchKernelGGL((slice_short_kernel<FMT_FP6_E3M2>), grid, block, 0, st, a);
+    else if (fmt == FMT_INT8) hipLaunchKernelGGL((slice_short_kernel<FMT_INT8>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((slice_short_kernel<FMT_FP8>), grid, block, 0, st, a);
+    return hipGetLastError();
+}
+
 // blocks too long for the register-resident kernel: exponents first (one workgroup per vector and block), then the slices
 hipError_t launch_split_long(const SplitArgs& a_in, int fmt, int64_t T, hipStream_t st) {
     SplitArgs a = a_in;
@@ -1049,6 +1186,7 @@ hipError_t launch_split(const double* X0, int64_t ldv0, int64_t es0, const Opera
     const int64_t octets = pl.chunks * pl.epc / 8;                              // per vector and block, padded
     // sixteen elements per thread (U = 2) is the measured optimum: more elements per thread cost registers and with
     // them the occupancy that hides the latency of the dependent integer chains (64 per thread: one wave per SIMD)
+    if (octets <= 32 && fmt != FMT_FP16 && (a.v[0].slices != nullptr || a.v[1].slices != nullptr)) return launch_split_short(a, fmt, pl.T, st);
     if (octets <= 64) return launch_split_cfg<1, 64>(a, fmt, pl.T, st);
     // a small problem (few vectors) is bound by the length of a thread's dependent chain, not by throughput: eight
     // elements per thread there (1024 x 1024: 0.080 -> 0.065 ms for both operands; no gain from 2048 vectors on)

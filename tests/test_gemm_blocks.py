@@ -82,8 +82,10 @@ def test_small_block_kernels_use_no_fp64(tmp_path):
     assert len(measured) == 4
     for body in measured.values():
         assert "v_mfma_" in body and not re.search(F64, body) and "scratch_" not in body      # nothing spilled
-    exponents = [b for n, b in _kernel_bodies("split.hip", tmp_path).items() if "long_exponents_kernel" in n]
-    assert len(exponents) == 1 and not re.search(F64, exponents[0])
+    slicing = _kernel_bodies("split.hip", tmp_path)
+    for name, count in (("long_exponents_kernel", 1), ("slice_short_kernel", 4)):
+        hit = [b for n, b in slicing.items() if name in n]
+        assert len(hit) == count and not any(re.search(F64, b) for b in hit)
     fine = {n: b for n, b in _kernel_bodies("accumulate.hip", tmp_path).items() if "accumulate_fine_kernel" in n}
     assert len(fine) == 6
     for name, body in fine.items():
