@@ -1,12 +1,11 @@
-// C ABI of libozaki: contexts, argument checks, the planner (Eq. 1-3), workspace carve-up and the kernel sequence.
+// C ABI of libozaki: contexts, argument checks and the kernel sequence (the planner is plan.hpp).
 #include <stdio.h>
 #include <string.h>
 
 #include <new>
 #include <vector>
 
-#include "../../include/ozaki_dgemm.h"
-#include "layout.hpp"
+#include "plan.hpp"
 
 using namespace ozaki;
 
@@ -43,255 +42,11 @@ static __device__ __align__(256) unsigned char static_scratch[OZAKI_STATIC_SCRAT
 constexpr int MAX_DEVICES = 64;
 uint8_t* static_scratch_ptr[MAX_DEVICES] = {};
 
-constexpr size_t ALIGN = 256;
-constexpr size_t FLAG_BYTES = 256;
-constexpr size_t P_BUDGET = (size_t)160 << 30;        // resident pair products: well inside the 288 GB of one GPU
-size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
-
 int fail_hip(hipError_t e) {
     ctx().last_hip_error = (int)e;
     return OZAKI_STATUS_HIP_ERROR;
 }
 #define HIP_TRY(expr) do { hipError_t e_ = (expr); if (e_ != hipSuccess) return fail_hip(e_); } while (0)
-
-// Exact window of the matrix unit's accumulator, in units of the product of two slice units: |sum| <= window is exact.
-int64_t exact_window(int fmt) { return fmt == OZAKI_SLICE_INT8 ? ((int64_t)1 << 31) - 1 : (int64_t)1 << 24; }
-
-// Largest b <= m2 with kb * 4^b <= window (Eq. 1-3 with Type1 = FP64, Type3 = FP32 / INT32); -1 if none.
-int slice_bits(int64_t kb, int fmt) {
-    // significand bits with the hidden one: E4M3 and E2M3 have three fraction bits, E3M2 two; an INT8 byte holds |q| <= 2^6
-    const int m2 = fmt == OZAKI_SLICE_FP16 ? 11 : fmt == OZAKI_SLICE_FP6_E3M2 ? 3 : fmt == OZAKI_SLICE_INT8 ? 6 : 4;
-    const int64_t window = exact_window(fmt);
-    for (int b = m2; b >= 0; --b)
-        if (kb <= (window >> (2 * b))) return b;
-    return -1;
-}
-
-bool format_ok(int fmt) { return fmt >= OZAKI_SLICE_FP8_E4M3 && fmt <= OZAKI_SLICE_INT8; }
-
-// Groups of at most `len` pairs in a pass of `pairs` products (pl.npairs: all of them).
-int64_t groups_in_pass(const Plan& pl, int pairs, int len) {
-    const int64_t q = pl.s / len, r = pl.s % len, triangle = len * q * (q + 1) / 2 + r * (q + 1);   // sum of ceil(L / len), L = 1 ... s
-    const int64_t all = pl.full ? 2 * triangle - (pl.s + len - 1) / len : triangle;
-    return pairs >= pl.npairs ? all : (all * pairs + pl.npairs - 1) / pl.npairs;
-}
-
-// How the GEMMs of a pass of `pairs` products run: 256 x 256 or 128 x 128 blocks, and the length of the groups.  Any choice
-// gives the same bits (the accumulation kernel merges equal-scale products of an anti-diagonal element by element whatever
-// the grouping).  Long groups store fewer products, shorter ones and smaller blocks give a problem of few tiles enough
-// workgroups to keep 256 compute units busy.  The estimate below, in microseconds, was fitted to measurements from 256^3 to
-// 256 x 2048 x 8192 (FP8): a 64-byte stage takes 0.62 in a 256 x 256 block (0.58 where they do not fill the chip), 0.25 in a
-// 128 x 128 block alone on its compute unit and 0.42 where two share one; a workgroup costs 5 resp. 3 on top (filling the load
-// ring, storing), a stored product its bytes twice through memory, an entry of the accumulation lists 0.2; with more
-// workgroups than slots the last ones add part of a group's time, less where whole anti-diagonals run from long to short.
-// GEMM + accumulation before this rule and the smaller blocks, and with them: 256^3 49 -> 26, 512^3 emulated 91 -> 42,
-// 600 x 600 x 1000 161 -> 59, 1000 x 777 x 1301 214 -> 135, 400 x 3000 x 2000 348 -> 256 us.  From 256 tiles on long groups of the
-// large blocks are always the choice.
-void choose_gemm(Plan& pl, int pairs, bool measured_runs) {
-    const int most = measured_runs || pl.run_limit > pl.s ? pl.s : pl.run_limit;
-    pl.small_tiles = 0;
-    pl.group_len = most;
-    const int64_t tiles = pl.tiles_m * pl.tiles_n;
-    if (tiles == 0 || tiles >= 256) return;
-    const int64_t quads = pl.quads_m * pl.quads_n;
-    const int longest_diag = pairs < pl.s ? pairs : pl.s, shortest = most > 1 ? 2 : 1;
-    double best = 1e300;
-    for (int small = 0; small < 2; ++small) {
-        const int64_t blocks = small ? quads : tiles, slots = small ? 512 : 256;
-        for (int len = most; len >= shortest; len = len > 8 ? (len + 1) / 2 : len - 1) {
-            const int64_t ngroups = groups_in_pass(pl, pairs, len), wgs = ngroups * blocks;
-            const double stage = small ? (wgs <= 256 ? 0.25 : 0.42) : 0.62, fixed = small ? 3.0 : 5.0;
-            const double longest = (len < longest_diag ? len : longest_diag) * (double)pl.chunks * (small ? stage : 0.58);
-            double t = longest + fixed;
-            if (wgs > slots) {
-                const double even = ((double)pairs * blocks * pl.chunks * stage + wgs * fixed) / slots + (len == pl.s ? 0.2 : small ? 0.5 : 0.4) * longest;
-                if (even > t) t = even;
-            }
-            t += ngroups * (0.2 + blocks * (small ? 0.0146 : 0.0583) * 2.0);      // 64 resp. 256 KiB at 4.5 TB/s
-            if (t < best) {
-                best = t;
-                pl.small_tiles = small;
-                pl.group_len = len;
-            }
-        }
-    }
-}
-
-// Builds the plan; returns 0 or a status / negative argument index in the numbering of ozaki_dgemm.
-int make_plan(int64_t m, int64_t n, int64_t k, int fmt, int s, int64_t k_block, bool full, Plan& pl) {
-    if (m < 0) return -1;
-    if (n < 0) return -2;
-    if (k < 0) return -3;
-    if (!format_ok(fmt)) return -10;
-    if (s < 0) return -11;
-    if (k_block < 0) return -12;
-    memset(&pl, 0, sizeof(pl));
-    pl.m = m; pl.n = n; pl.k = k; pl.fmt = fmt;
-    pl.epc = fmt == OZAKI_SLICE_FP16 ? CHUNK_BYTES / 2 : CHUNK_BYTES;
-    pl.row_bytes = fmt_is_fp6(fmt) ? CHUNK_BYTES_FP6 : CHUNK_BYTES;
-    pl.kb = (k_block == 0 || k_block > k) ? k : k_block;
-    if (pl.kb < 1) pl.kb = 1;
-    pl.b = slice_bits(pl.kb, fmt);
-    if (pl.b < 0) return OZAKI_STATUS_INFEASIBLE;
-    pl.rho = 53 - pl.b;
-    pl.s = s == 0 ? (61 + pl.b) / (pl.b + 1) : s;
-    if (pl.s > MAX_SLICES) return OZAKI_STATUS_SLICE_COUNT;
-    pl.T = k == 0 ? 0 : (k + pl.kb - 1) / pl.kb;
-    pl.p_frac = 2 * pl.b - (fmt == OZAKI_SLICE_FP6_E2M3 ? 2 : 0);
-    pl.p_is_int = fmt == OZAKI_SLICE_INT8 ? 1 : 0;
-    if (pl.p_is_int) pl.p_frac = 0;               // the stored words are the integers themselves
-    pl.chunks = (pl.kb + pl.epc - 1) / pl.epc;
-    pl.full = full ? 1 : 0;
-    pl.npairs = full ? pl.s * pl.s : pl.s * (pl.s + 1) / 2;
-    const int64_t rl = exact_window(fmt) / (pl.kb << (2 * pl.b));
-    pl.pair_bound = (int)(pl.kb << (2 * pl.b));
-    pl.run_limit = rl < 1 ? 1 : rl > MAX_SLICES ? MAX_SLICES : (int)rl;
-    pl.tiles_m = (m + TILE - 1) / TILE;
-    pl.tiles_n = (n + TILE - 1) / TILE;
-    pl.quads_m = (m + QUAD - 1) / QUAD;
-    pl.quads_n = (n + QUAD - 1) / QUAD;
-    pl.m_pad = pl.tiles_m * TILE;
-    pl.n_pad = pl.tiles_n * TILE;
-    choose_gemm(pl, pl.npairs, false);
-    return 0;
-}
-
-struct WorkMem {
-    uint8_t* ptr;
-    size_t bytes;
-};
-
-struct Carve {
-    int* flags;
-    double* At;
-    Operand A, B;
-    double* W;            // m x n product buffer of the scaled call (null otherwise)
-    uint64_t* S;
-    float* P;
-    int chunk_pairs;
-};
-
-size_t slices_bytes(const Plan& pl, int64_t rows_pad) { return align_up((size_t)pl.T * pl.s * pl.chunks * rows_pad * pl.row_bytes); }
-size_t exps_bytes(const Plan& pl, int64_t rows_pad) { return align_up((size_t)pl.T * pl.s * rows_pad * sizeof(int32_t)); }
-size_t deltas_bytes(const Plan& pl, int64_t rows_pad) { return align_up((size_t)pl.T * (rows_pad / LINK_ROWS) * pl.s * sizeof(int32_t)); }
-// Blocks beyond MAX_K_BLOCK_IN_REGISTERS: 12 bytes per (padded) element of the operands, part of the documented sizes.  No
-// kernel needs them any more.
-size_t long_block_reserve(const Plan& pl) {
-    if (pl.kb <= MAX_K_BLOCK_IN_REGISTERS) return 0;
-    return align_up((size_t)(pl.m + pl.n) * pl.T * pl.chunks * pl.epc * 12);
-}
-size_t fixed_bytes(const Plan& pl) {
-    return FLAG_BYTES + align_up((size_t)pl.m * pl.k * sizeof(double)) + long_block_reserve(pl) + slices_bytes(pl, pl.m_pad) +
-           slices_bytes(pl, pl.n_pad) + exps_bytes(pl, pl.m_pad) + exps_bytes(pl, pl.n_pad) + deltas_bytes(pl, pl.m_pad) +
-           deltas_bytes(pl, pl.n_pad);
-}
-// The documented sizes count a product with whole 256 x 256 tiles, and the running block sum between passes with the three
-// words of the exact mode whatever the mode; carve() packs closer (stored_bytes, sum_plane_bytes), so that more products of a
-// small workspace stay resident and fewer passes are needed.
-size_t pair_bytes(const Plan& pl) { return (size_t)pl.m_pad * pl.n_pad * sizeof(float); }
-size_t stored_bytes(const Plan& pl) { return (size_t)pl.quads_m * pl.quads_n * QUAD_ELEMS * sizeof(float); }
-size_t sum_plane_bytes(const Plan& pl) { return 2 * stored_bytes(pl); }
-size_t sum_bytes(const Plan& pl) { return (size_t)pl.m_pad * pl.n_pad * sizeof(uint64_t) * SUM_WORDS_MAX; }
-
-size_t recommended_bytes(const Plan& pl) {
-    const size_t all = (size_t)pl.npairs * pair_bytes(pl);
-    if (all <= P_BUDGET) return fixed_bytes(pl) + all;
-    size_t fit = P_BUDGET / pair_bytes(pl);
-    if (fit < (size_t)pl.s) fit = pl.s;
-    return fixed_bytes(pl) + sum_bytes(pl) + fit * pair_bytes(pl);
-}
-// The pair list is processed in passes that end at anti-diagonal boundaries (a run of equal-scale products
-// never spans two passes), so the smallest workspace holds the longest anti-diagonal: s products.
-size_t minimum_bytes(const Plan& pl) {
-    if (pl.npairs == 1) return fixed_bytes(pl) + pair_bytes(pl);
-    return fixed_bytes(pl) + sum_bytes(pl) + (size_t)pl.s * pair_bytes(pl);
-}
-
-size_t product_bytes(const Plan& pl) { return align_up((size_t)pl.m * pl.n * sizeof(double)); }
-
-// Places every buffer in the work memory; returns false if it does not fit.
-// sum_words: 64-bit words per element of a running block sum in the call's mode.
-bool carve(const Plan& pl, Carve& c, bool want_product, int sum_words, WorkMem wm) {
-    uint8_t* const ws = wm.ptr;
-    const size_t ws_bytes = wm.bytes;
-    if (!ws) return false;
-    size_t off = 0;
-    c.flags = reinterpret_cast<int*>(ws);
-    off += FLAG_BYTES;
-    c.At = reinterpret_cast<double*>(ws + off);
-    off += align_up((size_t)pl.m * pl.k * sizeof(double));
-    off += long_block_reserve(pl);
-    c.A.rows = pl.m; c.A.rows_pad = pl.m_pad;
-    c.B.rows = pl.n; c.B.rows_pad = pl.n_pad;
-    c.A.slices = ws + off; off += slices_bytes(pl, pl.m_pad);
-    c.B.slices = ws + off; off += slices_bytes(pl, pl.n_pad);
-    c.A.exps = reinterpret_cast<int32_t*>(ws + off); off += exps_bytes(pl, pl.m_pad);
-    c.B.exps = reinterpret_cast<int32_t*>(ws + off); off += exps_bytes(pl, pl.n_pad);
-    c.A.deltas = reinterpret_cast<int32_t*>(ws + off); off += deltas_bytes(pl, pl.m_pad);
-    c.B.deltas = reinterpret_cast<int32_t*>(ws + off); off += deltas_bytes(pl, pl.n_pad);
-    c.A.l1 = c.B.l1 = c.A.bounds = c.B.bounds = nullptr;
-    c.W = nullptr;
-    if (want_product) { c.W = reinterpret_cast<double*>(ws + off); off += product_bytes(pl); }
-    if (off > ws_bytes) return false;
-    const size_t rest = ws_bytes - off, pb = pair_bytes(pl), stored = stored_bytes(pl);
-    if (pb == 0) { c.S = nullptr; c.P = nullptr; c.chunk_pairs = pl.npairs; return true; }
-    const bool all_documented = rest >= (size_t)pl.npairs * pb;
-    if (!all_documented && rest < sum_bytes(pl) + (size_t)pl.s * pb) return false;      // below the documented minimum
-    if (rest >= (size_t)pl.npairs * stored) {
-        c.S = nullptr;
-        c.P = reinterpret_cast<float*>(ws + off);
-        c.chunk_pairs = pl.npairs;
-        return true;
-    }
-    c.S = reinterpret_cast<uint64_t*>(ws + off);
-    off += (size_t)sum_words * sum_plane_bytes(pl);
-    c.P = reinterpret_cast<float*>(ws + off);
-    const size_t fit = (ws_bytes - off) / stored;                                           // at least the documented s
-    c.chunk_pairs = fit > (size_t)pl.npairs ? pl.npairs : (int)fit;
-    return true;
-}
-
-// Measured runs (RunCheck) where run_limit cuts anti-diagonals, and the buffers they need.  These live in memory whose own
-// contents are not needed at the time: the transposed A is dead once the operands are sliced (bounds, starts), the products
-// are not there yet while they are (l1).  Without room the runs keep to run_limit.  Anti-diagonals cut in two at most are
-// left so: looking at the accumulators then costs as much as the fewer products give (8192^3, 16 FP8 slices, run_limit 8:
-// GEMMs 46.6 -> 47.0 ms, accumulation 1.97 -> 1.78 ms).  Where every pair was stored on its own: 8192^3 FP16 in blocks of 1024
-// 57.8 -> 36.6 ms, in blocks of 4096 43.5 -> 37.9 ms, 2048^3 in blocks of 1024 1.36 -> 0.88 ms.
-RunCheck place_run_check(const Plan& pl, Carve& c) {
-    RunCheck none{nullptr, nullptr, nullptr};
-    if (pl.p_is_int || 2 * pl.run_limit >= pl.s) return none;
-    const bool from_slices = pl.run_limit == 1;            // a pair may fill the window: bounds from the slicing kernel
-    if (from_slices && (pl.fmt != OZAKI_SLICE_FP16 || pl.kb > MAX_K_BLOCK_IN_REGISTERS)) return none;
-    uint8_t* const at = reinterpret_cast<uint8_t*>(c.At);
-    const size_t room = align_up((size_t)pl.m * pl.k * sizeof(double));
-    const size_t ba = deltas_bytes(pl, pl.m_pad), bb = deltas_bytes(pl, pl.n_pad);
-    const size_t starts = (size_t)c.chunk_pairs * pl.tiles_m * pl.tiles_n * 64;
-    if ((from_slices ? ba + bb : 0) + starts > room) return none;
-    if (!from_slices) return RunCheck{at, nullptr, nullptr};
-    const size_t la = exps_bytes(pl, pl.m_pad), lb = exps_bytes(pl, pl.n_pad);
-    if (la + lb > (size_t)c.chunk_pairs * stored_bytes(pl)) return none;
-    c.A.l1 = reinterpret_cast<int32_t*>(c.P);
-    c.B.l1 = reinterpret_cast<int32_t*>(reinterpret_cast<uint8_t*>(c.P) + la);
-    c.A.bounds = reinterpret_cast<int32_t*>(at);
-    c.B.bounds = reinterpret_cast<int32_t*>(at + ba);
-    return RunCheck{at + ba + bb, c.A.bounds, c.B.bounds};
-}
-
-PairOrder order_of(const Plan& pl) { return PairOrder{pl.s, pl.full, pl.group_len}; }
-
-// The pass that starts at anti-diagonal g_hi: as many whole anti-diagonals as fit into `capacity` products (at
-// least one: the carve-up guarantees room for the longest anti-diagonal).
-Pass next_pass(const PairOrder& o, int g_hi, int capacity) {
-    Pass ps{g_hi, g_hi, 0, 0};
-    for (int g = g_hi; g >= 2; --g) {
-        const int len = diag_len(o, g);
-        if (ps.npairs > 0 && ps.npairs + len > capacity) break;
-        ps.g_lo = g;
-        ps.npairs += len;
-        ps.ngroups += diag_groups(o, g);
-    }
-    return ps;
-}
 
 // ---- profiling spans -------------------------------------------------------------------------------------------
 hipEvent_t take_event(Context& c) {
@@ -386,19 +141,15 @@ int dgemm_core(const Plan& plan, double alpha, const double* A, int64_t lda, con
     if (m == 0 || n == 0) return 0;
     hipStream_t st = ctx().stream;
     const bool scaled = !(alpha == 1.0 && beta == 0.0);
-    Carve c;
-    c.W = nullptr;
-    if ((k > 0 || scaled) && !carve(plan, c, scaled, o.accum_mode == OZAKI_ACCUM_EXACT_FIXED ? SUM_WORDS_MAX : 1, wm)) return OZAKI_STATUS_WORKSPACE;
-    Plan pl = plan;
     // the plain rule adds every product on its own, so the matrix unit must not sum across pairs
     const bool chained = o.sum_rule == OZAKI_SUM_RUNS || o.accum_mode == OZAKI_ACCUM_EXACT_FIXED;
-    RunCheck check{nullptr, nullptr, nullptr};
-    if (k > 0) {
-        if (chained) check = place_run_check(pl, c);
-        // several passes: each is a launch of its own
-        if (check.starts != nullptr || c.chunk_pairs < pl.npairs) choose_gemm(pl, c.chunk_pairs, check.starts != nullptr);
-        if (pl.small_tiles && c.A.l1 == nullptr) c.A.deltas = c.B.deltas = nullptr;      // a launch less
-    }
+    Route r;
+    r.c.W = nullptr;
+    if ((k > 0 || scaled) && !place_call(plan, scaled, o.accum_mode == OZAKI_ACCUM_EXACT_FIXED ? SUM_WORDS_MAX : 1, chained, true, wm, r))
+        return OZAKI_STATUS_WORKSPACE;
+    const Plan& pl = r.pl;
+    const Carve& c = r.c;
+    const RunCheck& check = r.check;
     double* const out = scaled ? c.W : C;
     const int64_t ldo = scaled ? (m > 1 ? m : 1) : ldc;
     if (k == 0) {
