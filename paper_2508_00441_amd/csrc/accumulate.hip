@@ -302,6 +302,8 @@ struct ExportArgs {
     const int32_t* da;
     const int32_t* db;
     int64_t ga, gb;          // groups of 32 vectors per slice in da / db
+    const uint8_t* starts;   // measured runs (RunCheck), or null: decided from the deltas
+    int tiles_m, tiles_n;    // layout of starts
     PairOrder order;
     Pass pass;
 };
@@ -322,10 +324,16 @@ __global__ void __launch_bounds__(256) export_products_kernel(const ExportArgs a
         if (mi >= a.m || nj >= a.n) continue;
         const int32_t* dA = a.da + mi / LINK_ROWS;
         const int32_t* dB = a.db + nj / LINK_ROWS;
+        const size_t tiles = (size_t)a.tiles_m * a.tiles_n;
+        const size_t place = ((size_t)(qn >> 1) * a.tiles_m + (qm >> 1)) * 64 + ((qn & 1) * 2 + (qm & 1)) * 16 + (idx >> 10);
+        auto starts_at = [&](int j) -> bool {                                   // pair j of the anti-diagonal behind this one
+            if (a.starts != nullptr) return a.starts[(size_t)(z + j) * tiles * 64 + place] != 0;
+            return starts_run(a.order, a.allow_chain, dA, a.ga, dB, a.gb, pos + j, p + j, q - j);
+        };
         int run = 0;
-        if (starts_run(a.order, a.allow_chain, dA, a.ga, dB, a.gb, pos, p, q)) {
+        if (starts_at(0)) {
             run = 1;
-            while (pos + run < len && !starts_run(a.order, a.allow_chain, dA, a.ga, dB, a.gb, pos + run, p + run, q - run)) ++run;
+            while (pos + run < len && !starts_at(run)) ++run;
         }
         const size_t o = ((size_t)z * a.n + nj) * a.m + mi;
         const uint32_t w = reinterpret_cast<const uint32_t*>(a.P)[(size_t)z * pair_stride + gi];
@@ -425,7 +433,8 @@ hipError_t launch_accumulate(const Plan& pl, const Operand& A, const Operand& B,
 }
 
 hipError_t launch_export_products(const Plan& pl, const Operand& A, const Operand& B, const PairOrder& order, const Pass& ps,
-                                  bool chained, int64_t t, const float* P, float* out, uint8_t* run_len_out, hipStream_t st) {
+                                  bool chained, const uint8_t* starts, int64_t t, const float* P, float* out, uint8_t* run_len_out,
+                                  hipStream_t st) {
     if (ps.npairs <= 0 || pl.m == 0 || pl.n == 0) return hipSuccess;
     ExportArgs a;
     a.P = P; a.out = out; a.run_len = run_len_out;
@@ -436,6 +445,7 @@ hipError_t launch_export_products(const Plan& pl, const Operand& A, const Operan
     a.da = A.deltas + (size_t)t * (A.rows_pad / LINK_ROWS) * pl.s;
     a.db = B.deltas + (size_t)t * (B.rows_pad / LINK_ROWS) * pl.s;
     a.ga = A.rows_pad / LINK_ROWS; a.gb = B.rows_pad / LINK_ROWS;
+    a.starts = starts; a.tiles_m = (int)pl.tiles_m; a.tiles_n = (int)pl.tiles_n;
     a.order = order; a.pass = ps;
     dim3 grid(grid_for(pl.quads_m * pl.quads_n * (int64_t)QUAD_ELEMS), (unsigned)ps.npairs);
     hipLaunchKernelGGL(export_products_kernel, grid, dim3(256), 0, st, a);

@@ -474,8 +474,8 @@ int ozaki_pair_products(int64_t m, int64_t n, int64_t k, const double* A, int64_
                         int slice_format, int num_slices, int64_t k_block, int pair_set, int chained, void* P_out,
                         uint8_t* run_len_out) {
     if (pair_set != OZAKI_PAIRS_TRIANGLE && pair_set != OZAKI_PAIRS_ALL) return -11;
-    Plan pl;
-    int st = make_plan(m, n, k, slice_format, num_slices, k_block, pair_set == OZAKI_PAIRS_ALL, pl);
+    Plan plan;
+    int st = make_plan(m, n, k, slice_format, num_slices, k_block, pair_set == OZAKI_PAIRS_ALL, plan);
     if (st < 0) return st == -10 ? -8 : st == -11 ? -9 : st == -12 ? -10 : st;
     if (st != 0) return st;
     if (num_slices < 1) return -9;
@@ -485,20 +485,26 @@ int ozaki_pair_products(int64_t m, int64_t n, int64_t k, const double* A, int64_
     if (!B) return -6;
     if (ldb < k) return -7;
     if (!P_out) return -13;
-    Carve c;
-    if (!carve(pl, c, false, 1, context_workspace())) return OZAKI_STATUS_WORKSPACE;
-    if (c.chunk_pairs < pl.npairs) choose_gemm(pl, c.chunk_pairs, false);
+    Route r;
+    if (!place_call(plan, false, 1, chained != 0, chained == 2, context_workspace(), r)) return OZAKI_STATUS_WORKSPACE;
+    const Plan& pl = r.pl;
+    const Carve& c = r.c;
     hipStream_t stream = ctx().stream;
     const PairOrder order = order_of(pl);
     int rc = run_split(pl, c, A, lda, B, ldb, true, true);
     if (rc) return rc;
+    // the export reads the links from the deltas also where the GEMM kernel formed them itself
+    Operand ea = c.A, eb = c.B;
+    ea.deltas = r.deltas_a;
+    eb.deltas = r.deltas_b;
+    if (c.A.deltas == nullptr) HIP_TRY(launch_deltas(pl, &ea, &eb, stream));
     for (int64_t t = 0; t < pl.T; ++t) {
         int z0 = 0;
         for (int g_hi = order_top_diag(order); g_hi >= 2;) {
             const Pass ps = next_pass(order, g_hi, c.chunk_pairs);
             const size_t at = ((size_t)t * pl.npairs + z0) * (size_t)m * n;
-            HIP_TRY(launch_pair_gemm(pl, c.A, c.B, order, ps, chained != 0, RunCheck{nullptr, nullptr, nullptr}, t, c.P, stream));
-            HIP_TRY(launch_export_products(pl, c.A, c.B, order, ps, chained != 0, t, c.P, static_cast<float*>(P_out) + at,
+            HIP_TRY(launch_pair_gemm(pl, c.A, c.B, order, ps, chained != 0, r.check, t, c.P, stream));
+            HIP_TRY(launch_export_products(pl, ea, eb, order, ps, chained != 0, r.check.starts, t, c.P, static_cast<float*>(P_out) + at,
                                            run_len_out ? run_len_out + at : nullptr, stream));
             z0 += ps.npairs;
             g_hi = ps.g_lo - 1;

@@ -304,9 +304,10 @@ hipError_t launch_accumulate(const Plan& pl, const Operand& A, const Operand& B,
 // P in accumulator order -> [nz][n][m] column-major matrices (verification export): FP32 values of Eq. 10-11, or INT32
 // integers for INT8 slices.  run_len_out (may be null): for every element and pair slot of the pass, how many pairs'
 // products the slot holds summed (1 without chaining; 0: the pair's product is part of an earlier slot's sum, and
-// `out` gets 0 there).
+// `out` gets 0 there).  chained, starts: as in launch_accumulate; without starts the operands' deltas are needed.
 hipError_t launch_export_products(const Plan& pl, const Operand& A, const Operand& B, const PairOrder& order, const Pass& ps,
-                                  bool chained, int64_t t, const float* P, float* out, uint8_t* run_len_out, hipStream_t st);
+                                  bool chained, const uint8_t* starts, int64_t t, const float* P, float* out, uint8_t* run_len_out,
+                                  hipStream_t st);
 
 // C = alpha * W + beta * C element by element (one rounding per operation, no fused multiply-add; beta == 0: C is not
 // read), W and C column-major m x n.

@@ -1,0 +1,28 @@
+// Host build of the planner (plan.hpp): which blocks, groups and runs a call takes.
+#include "../paper_2508_00441_amd/csrc/plan.hpp"
+
+using namespace ozaki;
+
+extern "C" {
+
+// The route of a DGEMM call without rounding modes of its own (one word per running sum) in `bytes` of work memory (0: the
+// documented size, -1: the documented minimum).  route: small_tiles, group_len, run_limit, measured, bounds from the slices,
+// products per pass.  Returns the planner's status.
+int plan_route(int64_t m, int64_t n, int64_t k, int fmt, int s, int64_t k_block, int full, int chained, int64_t bytes, int64_t route[6]) {
+    Plan plan;
+    const int st = make_plan(m, n, k, fmt, s, k_block, full != 0, plan);
+    if (st != 0) return st;
+    const size_t size = bytes > 0 ? (size_t)bytes : bytes < 0 ? minimum_bytes(plan) : recommended_bytes(plan);
+    Route r;
+    if (!place_call(plan, false, 1, chained != 0, true, WorkMem{reinterpret_cast<uint8_t*>((uintptr_t)1 << 40), size}, r))
+        return OZAKI_STATUS_WORKSPACE;
+    route[0] = r.pl.small_tiles;
+    route[1] = r.pl.group_len;
+    route[2] = r.pl.run_limit;
+    route[3] = r.check.starts != nullptr;
+    route[4] = r.check.bound_a != nullptr;
+    route[5] = r.c.chunk_pairs;
+    return 0;
+}
+
+}  // extern "C"
