@@ -211,15 +211,19 @@ __host__ __device__ inline WorkItem work_item(unsigned b, unsigned total, const 
     it.bm = strip_rows * strip + (in - it.bn * height);
     return it;
 }
-// The order for a launch of `total` workgroups of which `per_xcd` run at a time on an XCD.  Measured against the plain order:
-// 4096^3 FP8 4.08 -> 4.01 ms, 2048^3 FP16 in blocks of 1024 0.83 -> 0.78 ms, 600 x 600 x 1000 (128 x 128 blocks) 43 -> 35 us.
-// The plain order stays where it already gives every XCD a compact patch (32 block rows: four of them per XCD; strips
-// lose 2.5 % at 16384^2 FP16 there) and where a launch has few rounds of groups of unequal length (1024^3, all pairs:
-// 112 us plain, 138 us in strips, because a unit's XCD waits for its longest group), also when a group of 256 x 256 blocks has
-// fewer of them than an XCD runs at a time (1024 x 1024 x 8192: 0.49 ms plain, 0.55 to 0.62 in strips).
-__host__ __device__ inline WorkOrder work_order(int64_t total, int per_xcd, int64_t blocks_m, int64_t blocks_n, int group_len) {
-    if (blocks_m % 32 == 0 || (group_len > (per_xcd == 32 ? 4 : 6) && total < 64 * (int64_t)per_xcd)) return WorkOrder{0, 0};
-    if (per_xcd == 32 && blocks_m * blocks_n < 32) return WorkOrder{0, 0};
+// The order for a launch of `total` workgroups of which `per_xcd` run at a time on an XCD: strips from about two rounds of workgroups
+// on (128 x 128 blocks 2, 256 x 256 blocks 2.5, four where a pair has fewer than eight stages).  What they save is traffic between
+// the L2s and the memory behind them, a panel per workgroup and stage or more in the plain order: 5 x 23 blocks of 128 x 128,
+// 24 stages, 121 products in 2415 workgroups (4.7 rounds) 576 -> 290 us; 14 x 6 blocks of 256 x 256, 112 FP16 stages, 4.6 rounds
+// 1.58 -> 1.31 ms; 4096^3 FP8 4.08 -> 4.01 ms.  Over 700 random problems strips take 0.7 to 0.9 of the plain time with 128 x 128
+// blocks and 0.92 to 0.97 with 256 x 256 blocks at two to four rounds, 0.63 to 0.8 and 0.75 to 0.9 from eight rounds on, whatever the
+// length of the groups; with few rounds a unit's XCD waits for its longest group while others are idle (1.0 to 1.2 of the plain time), and
+// short pairs are bound by their stores (0.95 to 1.05 below four rounds).  The plain order also stays where it already gives
+// every XCD a compact patch by itself: at 32 block rows, four of them per XCD (128 x 128 blocks: 1.0 to 1.1 of the plain time
+// there; 16384^2 FP16: 2.5 % longer).  40, 44, 48, 52 and 56 block rows of 256: strips, equal to the plain order or up to 6 % faster.
+__host__ __device__ inline WorkOrder work_order(int64_t total, int per_xcd, int64_t blocks_m, int64_t chunks) {
+    const int half_rounds = chunks < 8 ? 8 : per_xcd == 32 ? 5 : 4;
+    if (blocks_m % 32 == 0 || 2 * total < half_rounds * 8 * (int64_t)per_xcd) return WorkOrder{0, 0};
     return WorkOrder{per_xcd, blocks_m > 8 ? 4 : 8};
 }
 
