@@ -146,6 +146,12 @@ __host__ __device__ inline Group pass_group(const PairOrder& o, const Pass& ps, 
     return Group{1, 1, 0, 0};
 }
 
+inline int longest_group(const PairOrder& o, const Pass& ps) {
+    int longest = 1;
+    for (int g = ps.g_hi; g >= ps.g_lo; --g) longest = diag_len(o, g) > longest ? diag_len(o, g) : longest;
+    return longest < o.run_limit ? longest : o.run_limit;
+}
+
 // The groups of a pass in the order in which workgroups take them, longest first (a long group that starts last would be
 // the launch's tail), packed for the kernel arguments: p0 | q0 << 6 | len << 12 | slot << 18.  A pass of more groups than fit
 // goes in accumulation order.
@@ -211,19 +217,25 @@ __host__ __device__ inline WorkItem work_item(unsigned b, unsigned total, const 
     it.bm = strip_rows * strip + (in - it.bn * height);
     return it;
 }
-// The order for a launch of `total` workgroups of which `per_xcd` run at a time on an XCD: strips from about two rounds of workgroups
-// on (128 x 128 blocks 2, 256 x 256 blocks 2.5, four where a pair has fewer than eight stages).  What they save is traffic between
-// the L2s and the memory behind them, a panel per workgroup and stage or more in the plain order: 5 x 23 blocks of 128 x 128,
-// 24 stages, 121 products in 2415 workgroups (4.7 rounds) 576 -> 290 us; 14 x 6 blocks of 256 x 256, 112 FP16 stages, 4.6 rounds
-// 1.58 -> 1.31 ms; 4096^3 FP8 4.08 -> 4.01 ms.  Over 700 random problems strips take 0.7 to 0.9 of the plain time with 128 x 128
-// blocks and 0.92 to 0.97 with 256 x 256 blocks at two to four rounds, 0.63 to 0.8 and 0.75 to 0.9 from eight rounds on, whatever the
-// length of the groups; with few rounds a unit's XCD waits for its longest group while others are idle (1.0 to 1.2 of the plain time), and
-// short pairs are bound by their stores (0.95 to 1.05 below four rounds).  The plain order also stays where it already gives
-// every XCD a compact patch by itself: at 32 block rows, four of them per XCD (128 x 128 blocks: 1.0 to 1.1 of the plain time
-// there; 16384^2 FP16: 2.5 % longer).  40, 44, 48, 52 and 56 block rows of 256: strips, equal to the plain order or up to 6 % faster.
-__host__ __device__ inline WorkOrder work_order(int64_t total, int per_xcd, int64_t blocks_m, int64_t chunks) {
-    const int half_rounds = chunks < 8 ? 8 : per_xcd == 32 ? 5 : 4;
-    if (blocks_m % 32 == 0 || 2 * total < half_rounds * 8 * (int64_t)per_xcd) return WorkOrder{0, 0};
+// The order for a launch of `groups` groups of `pairs` pairs together, none longer than `len`, over blocks_m x blocks_n blocks; `per_xcd`
+// workgroups run at a time on an XCD: strips from about two rounds of workgroups on (128 x 128 blocks 2, 256 x 256 blocks 2.5, four where
+// a pair has fewer than eight stages).  What they save is traffic between the L2s and the memory behind them, a panel per
+// workgroup and stage or more in the plain order: 5 x 23 blocks of 128 x 128, 24 stages, 121 products in 2415 workgroups
+// (4.7 rounds) 576 -> 290 us; 14 x 6 blocks of 256 x 256, 112 FP16 stages, 4.6 rounds 1.58 -> 1.31 ms; 4096^3 FP8 4.08 -> 4.01 ms.
+// Over 700 random problems strips take 0.7 to 0.9 of the plain time with 128 x 128 blocks and 0.92 to 0.97 with 256 x 256
+// blocks at two to four rounds, 0.63 to 0.8 and 0.75 to 0.9 from eight rounds on, whatever the length of the groups.  With fewer rounds
+// a unit's XCD waits for its longest group while others are idle (1.0 to 1.2 of the plain time), except in 128 x 128 blocks where the
+// groups are of nearly equal length and the plain order spreads every group over all XCDs (a number of blocks that is no
+// multiple of eight): there strips pay from 0.75 rounds on if pairs are long (12 x 3 blocks, 64 FP16 stages, groups of two:
+// 679 -> 510 us; 7 x 4 blocks 226 -> 165; 3 x 3 blocks, 128 stages, single pairs: 316 -> 209).  Short pairs are bound by their stores
+// (0.95 to 1.05 below four rounds).  The plain order also stays where it already gives every XCD a compact patch by itself: at
+// 32 block rows, four of them per XCD (128 x 128 blocks: 1.0 to 1.1 of the plain time there; 16384^2 FP16: 2.5 % longer).
+// 40, 44, 48, 52 and 56 block rows of 256: strips, equal to the plain order or up to 6 % faster.
+__host__ __device__ inline WorkOrder work_order(double groups, double pairs, int len, int per_xcd, int64_t blocks_m, int64_t blocks_n, int64_t chunks) {
+    const double rounds = groups * (double)(blocks_m * blocks_n) / (8 * per_xcd);
+    const bool small = per_xcd == 64, even = pairs >= 0.7 * len * groups && (blocks_m * blocks_n) % 8 != 0;
+    const double least = chunks < 8 ? 4.0 : !small ? 2.5 : even && chunks >= 32 ? 0.75 : 2.0;
+    if (blocks_m % 32 == 0 || rounds < least) return WorkOrder{0, 0};
     return WorkOrder{per_xcd, blocks_m > 8 ? 4 : 8};
 }
 

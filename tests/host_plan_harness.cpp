@@ -25,9 +25,13 @@ int plan_route(int64_t m, int64_t n, int64_t k, int fmt, int s, int64_t k_block,
     return 0;
 }
 
-// 1: strips, 0: the plain order, for a launch of `groups` groups of blocks_m x blocks_n blocks of 256 (small: 128)
-int order_of_launch(int small, int64_t groups, int64_t blocks_m, int64_t blocks_n, int64_t chunks) {
-    return work_order(groups * blocks_m * blocks_n, small ? 64 : 32, blocks_m, chunks).unit != 0;
+// 1: strips, 0: the plain order, for a launch of groups of `len` pairs and less over the anti-diagonals of s slices, in blocks_m x blocks_n
+// blocks of 256 (small: 128)
+int order_of_launch(int small, int s, int full, int len, int64_t blocks_m, int64_t blocks_n, int64_t chunks) {
+    const PairOrder o{s, full, len};
+    Pass ps{order_top_diag(o), 2, 0, 0};
+    for (int g = ps.g_hi; g >= 2; --g) { ps.npairs += diag_len(o, g); ps.ngroups += diag_groups(o, g); }
+    return work_order(ps.ngroups, ps.npairs, longest_group(o, ps), small ? 64 : 32, blocks_m, blocks_n, chunks).unit != 0;
 }
 
 }  // extern "C"
