@@ -1,6 +1,7 @@
 // The planner: Eq. 1-3, the work memory's carve-up and the route of a call (blocks, groups of pairs, runs, passes).  Host code
 // without a call to the runtime, so that host programs can ask which route a call takes.
 #pragma once
+#include <math.h>
 #include <string.h>
 
 #include "../../include/ozaki_dgemm.h"
@@ -28,45 +29,108 @@ inline int slice_bits(int64_t kb, int fmt) {
 
 inline bool format_ok(int fmt) { return fmt >= OZAKI_SLICE_FP8_E4M3 && fmt <= OZAKI_SLICE_INT8; }
 
-// Groups of at most `len` pairs in a pass of `pairs` products (pl.npairs: all of them).
-inline int64_t groups_in_pass(const Plan& pl, int pairs, int len) {
-    const int64_t q = pl.s / len, r = pl.s % len, triangle = len * q * (q + 1) / 2 + r * (q + 1);   // sum of ceil(L / len), L = 1 ... s
-    const int64_t all = pl.full ? 2 * triangle - (pl.s + len - 1) / len : triangle;
-    return pairs >= pl.npairs ? all : (all * pairs + pl.npairs - 1) / pl.npairs;
+// What a GEMM launch takes per 64-byte stage, in microseconds: a 128 x 128 block alone on its compute unit and one of two that
+// share it, a 256 x 256 block.
+struct StageTimes {
+    double small_alone, small_shared, large;
+};
+inline StageTimes stage_times(int fmt) {
+    if (fmt_is_fp6(fmt)) return {0.23, 0.34, 0.41};
+    if (fmt == FMT_FP16) return {0.24, 0.42, 0.64};
+    if (fmt == FMT_INT8) return {0.29, 0.45, 0.63};
+    return {0.255, 0.44, 0.55};
 }
 
 // How the GEMMs of a pass of `pairs` products run: 256 x 256 or 128 x 128 blocks, and the length of the groups.  Any choice
 // gives the same bits (the accumulation kernel merges equal-scale products of an anti-diagonal element by element whatever
 // the grouping).  Long groups store fewer products, shorter ones and smaller blocks give a problem of few tiles enough
-// workgroups to keep 256 compute units busy.  The estimate below, in microseconds, was fitted to measurements from 256^3 to
-// 256 x 2048 x 8192 (FP8): a 64-byte stage takes 0.62 in a 256 x 256 block (0.58 where they do not fill the chip), 0.25 in a
-// 128 x 128 block alone on its compute unit and 0.42 where two share one; a workgroup costs 5 resp. 3 on top (filling the load
-// ring, storing), a stored product its bytes twice through memory, an entry of the accumulation lists 0.2; with more
-// workgroups than slots the last ones add part of a group's time, less where whole anti-diagonals run from long to short.
-// GEMM + accumulation before this rule and the smaller blocks, and with them: 256^3 49 -> 26, 512^3 emulated 91 -> 42,
-// 600 x 600 x 1000 161 -> 59, 1000 x 777 x 1301 214 -> 135, 400 x 3000 x 2000 348 -> 256 us.  From 256 tiles on long groups of the
-// large blocks are always the choice.
-inline void choose_gemm(Plan& pl, int pairs, bool measured_runs) {
+// workgroups to keep 256 compute units evenly busy.  The estimate of GEMM + accumulation below, in microseconds, is the least that
+// covers
+//   - a workgroup's own stages (stage_times) and, added to the fourth power, the panels that the workgroups in flight fetch
+//     beyond the L2s: 20 TB/s while the slices fit the memory-side cache, 11.5 TB/s beyond it.  Panels per workgroup and stage:
+//     rows + columns over the area of what an XCD has in flight of a group, at most two;
+//   - more workgroups than slots: the even share of all stages, but at least as many rounds of every length as the workgroups
+//     of that length or more need, and up to two rounds the last ones behind the shortest of the first; then a sixth of a group
+//     for the uneven end (not for 256 x 256 blocks in the plain order, longest first over all XCDs);
+//   - filling the load ring and storing, per round; the products stored and read again.
+// Measured on 720 random problems of fewer than 256 tiles, all formats, every block size and length, the constants fitted to two
+// thirds of them: the choice takes 1.022 of the best one's time on average (1.028 on the other third), 1.23 at worst; the estimate
+// before it, FP8's times for every format, no panels, group lengths of two and more and not all of them, 1.082 and 1.94.  From 256 tiles
+// on long groups of the large blocks are always the choice.
+inline void choose_gemm(Plan& pl, int pairs, bool chained, bool measured_runs) {
     const int most = measured_runs || pl.run_limit > pl.s ? pl.s : pl.run_limit;
     pl.small_tiles = 0;
     pl.group_len = most;
-    const int64_t tiles = pl.tiles_m * pl.tiles_n;
+    const int64_t tiles = pl.tiles_m * pl.tiles_n, quads = pl.quads_m * pl.quads_n;
     if (tiles == 0 || tiles >= 256) return;
-    const int64_t quads = pl.quads_m * pl.quads_n;
-    const int longest_diag = pairs < pl.s ? pairs : pl.s, shortest = most > 1 ? 2 : 1;
+    const StageTimes us = stage_times(pl.fmt);
+    const double part = pairs < pl.npairs ? (double)pairs / pl.npairs : 1.0;              // of the groups of all pairs
+    const double chunks = (double)pl.chunks, slices_mb = 1e-6 * pl.s * chunks * pl.row_bytes * (double)(pl.m_pad + pl.n_pad);
+    const double mb_per_us = slices_mb < 160.0 ? 20.0 : 11.5;
     double best = 1e300;
-    for (int small = 0; small < 2; ++small) {
-        const int64_t blocks = small ? quads : tiles, slots = small ? 512 : 256;
-        for (int len = most; len >= shortest; len = len > 8 ? (len + 1) / 2 : len - 1) {
-            const int64_t ngroups = groups_in_pass(pl, pairs, len), wgs = ngroups * blocks;
-            const double stage = small ? (wgs <= 256 ? 0.25 : 0.42) : 0.62, fixed = small ? 3.0 : 5.0;
-            const double longest = (len < longest_diag ? len : longest_diag) * (double)pl.chunks * (small ? stage : 0.58);
-            double t = longest + fixed;
-            if (wgs > slots) {
-                const double even = ((double)pairs * blocks * pl.chunks * stage + wgs * fixed) / slots + (len == pl.s ? 0.2 : small ? 0.5 : 0.4) * longest;
-                if (even > t) t = even;
+    for (int len = most; len >= 1; --len) {
+        int count[MAX_SLICES + 1] = {};                          // groups of each length
+        for (int diag = 1; diag <= pl.s; ++diag) {
+            const int times = pl.full && diag < pl.s ? 2 : 1;
+            count[len] += times * (diag / len);
+            if (diag % len != 0) count[diag % len] += times;
+        }
+        for (int small = 0; small < 2; ++small) {
+            const int64_t bm = small ? pl.quads_m : pl.tiles_m, bn = small ? pl.quads_n : pl.tiles_n;
+            const double blocks = (double)(bm * bn), slots = small ? 512.0 : 256.0;
+            double ngroups = 0.0, line = 0.0;                    // line: the longest line of groups on one slot, in pairs
+            for (int l = len; l >= 1; --l) {
+                ngroups += part * count[l];
+                const double bound = ceil(ngroups * blocks / slots) * l;
+                if (bound > line) line = bound;
             }
-            t += ngroups * (0.2 + blocks * (small ? 0.0146 : 0.0583) * 2.0);      // 64 resp. 256 KiB at 4.5 TB/s
+            const double wgs = ngroups * blocks;
+            if (wgs > slots && wgs <= 2.0 * slots) {             // the last ones start where the shortest of the first ones end
+                double last = 0.0;
+                for (int l = len; l >= 1; --l) {
+                    last += part * count[l] * blocks;
+                    if (count[l] == 0 || last <= slots) continue;
+                    double first = 0.0;
+                    int before = len;
+                    for (int f = len; f >= 1 && first < 2.0 * slots + 1.0 - last; --f) {
+                        first += part * count[f] * blocks;
+                        if (count[f] != 0) before = f;
+                    }
+                    if (l + before > line) line = l + before;
+                }
+            }
+            const WorkOrder work = work_order(ngroups, part * pl.npairs, len, small ? 64 : 32, bm, bn, pl.chunks);
+            double rows, cols, in_flight;                        // of a group, on one XCD
+            if (work.unit == 0) {
+                const int64_t stride = bm % 8 == 0 ? 8 : bm % 4 == 0 ? 4 : bm % 2 == 0 ? 2 : 1;
+                in_flight = blocks > 8.0 ? blocks / 8.0 : 1.0;
+                rows = (double)(bm / stride);
+                cols = (double)bn;
+                if (rows > in_flight) rows = in_flight;
+                if (cols > in_flight) cols = in_flight;
+            } else if (blocks >= work.unit) {
+                rows = (double)(bm < work.height ? bm : work.height);
+                cols = work.unit / rows < (double)bn ? work.unit / rows : (double)bn;
+                in_flight = rows * cols;
+            } else {
+                rows = (double)bm;
+                cols = (double)bn;
+                in_flight = blocks;
+            }
+            const double panels = (rows + cols) / in_flight < 2.0 ? (rows + cols) / in_flight : 2.0;
+            const double fetch = panels * 1e-6 * (small ? QUAD : TILE) * pl.row_bytes * (wgs < slots ? wgs : slots) / mb_per_us;
+            const double own = !small ? us.large : wgs <= 256.0 ? us.small_alone : us.small_shared;
+            const double stage = sqrt(sqrt(own * own * own * own + fetch * fetch * fetch * fetch)), fixed = small ? 2.2 : 6.0;
+            double t;
+            if (wgs <= slots) {
+                t = len * chunks * stage + fixed;
+            } else {
+                const double even = part * pl.npairs * blocks / slots;
+                if (even > line) line = even;
+                t = (line + (work.unit == 0 && !small ? 0.0 : 0.17 * len)) * chunks * stage + ceil(wgs / slots) * fixed;
+            }
+            const double stored = chained ? ngroups : part * pl.npairs;
+            t += stored * (0.015 * blocks * (small ? 0.25 : 1.0) + 0.18 + 0.014 * (double)quads);
             if (t < best) {
                 best = t;
                 pl.small_tiles = small;
@@ -111,7 +175,6 @@ inline int make_plan(int64_t m, int64_t n, int64_t k, int fmt, int s, int64_t k_
     pl.quads_n = (n + QUAD - 1) / QUAD;
     pl.m_pad = pl.tiles_m * TILE;
     pl.n_pad = pl.tiles_n * TILE;
-    choose_gemm(pl, pl.npairs, false);
     return 0;
 }
 
@@ -251,8 +314,7 @@ inline bool place_call(const Plan& plan, bool want_product, int sum_words, bool 
     r.check = RunCheck{nullptr, nullptr, nullptr};
     if (!carve(plan, r.c, want_product, sum_words, wm)) return false;
     if (chained && measured) r.check = place_run_check(r.pl, r.c);
-    // several passes: each is a launch of its own
-    if (r.check.starts != nullptr || r.c.chunk_pairs < r.pl.npairs) choose_gemm(r.pl, r.c.chunk_pairs, r.check.starts != nullptr);
+    choose_gemm(r.pl, r.c.chunk_pairs, chained, r.check.starts != nullptr);               // of one pass: each is a launch of its own
     r.deltas_a = r.c.A.deltas;
     r.deltas_b = r.c.B.deltas;
     if (r.pl.small_tiles && r.c.A.l1 == nullptr) r.c.A.deltas = r.c.B.deltas = nullptr;      // a launch less

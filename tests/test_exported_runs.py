@@ -1,6 +1,8 @@
-"""The product export in the launch configuration of ozaki_dgemm (chained = 2): runs beyond the window's worst case, blocks and
-groups as the DGEMM takes them.  Every run joins consecutive pairs of equal scale, its stored word is the exact sum, and no
-partial sum leaves the window."""
+"""Runs beyond the window's worst case, in the launch configuration of ozaki_dgemm (product export with chained = 2) and in the DGEMM
+itself.  The cases take the route that they are for, which the planner says on the host: 256 x 256 or 128 x 128 blocks, groups
+longer than the worst case allows, bounds from the slices or the same for every pair.  One half of the vectors are regular
+(long runs must form), the other half have slices that fill the window (runs must break).  Sampled rows and columns from both
+halves and from the edges are compared with the oracle: a vector is sliced on its own, so is every entry of the product."""
 import numpy as np
 import pytest
 
@@ -8,67 +10,99 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
+import planner  # noqa: E402
 from oracle import formats  # noqa: E402
 from oracle import ozaki_oracle as oz  # noqa: E402
 from paper_2508_00441_amd import binding as lib, device  # noqa: E402
-from test_gpu_parity import _as_device_words, _oracle_products, _recipe  # noqa: E402
+from test_gpu_parity import _as_device_words  # noqa: E402
 
 
-def export(A, B, fmt, s, k_block, mode, chained, minimum=False):
-    """(products, run lengths) as numpy arrays [T][pairs][n][m]"""
-    m, k = A.shape
-    n = B.shape[1]
-    T, npairs = oz.make_plan(k, fmt, k_block).num_blocks, len(oz.pair_order(s, mode))
-    Ad, Bd = device.to_device_colmajor(A), device.to_device_colmajor(B)
-    ws = device.Workspace.for_problem(m, n, k, lib.SLICE_FORMATS[fmt], s, k_block, pair_set=lib.PAIR_SETS[mode], minimum=minimum)
-    P = torch.full((T, npairs, n, m), -77, dtype=torch.int32 if fmt == "int8" else torch.float32, device="cuda")
-    L = torch.full((T, npairs, n, m), 99, dtype=torch.uint8, device="cuda")
-    lib.ozaki_pair_products(m, n, k, Ad, m, Bd, k, lib.SLICE_FORMATS[fmt], s, k_block, P, pair_set=lib.PAIR_SETS[mode], chained=chained, run_len_out=L)
-    assert lib.ozaki_last_device_status() == 0
-    ws.close()
-    return P.cpu().numpy(), L.cpu().numpy().astype(np.int64)
+def _vectors(count, k, b, gen):
+    """count x k: regular vectors (one binade, full significands, random signs), from count // 2 on vectors whose slices are all
+    +-2^b: 1 - 2^-(b+1) + 2^-2(b+1) - ..., a tie at every slice that rounds up to 2^b; every third of those cancels half way."""
+    X = (torch.randint(0, 1 << 52, (count, k), generator=gen, device="cuda") | (1023 << 52)).view(torch.float64)
+    X *= torch.randint(0, 2, (count, k), generator=gen, device="cuda", dtype=torch.int8) * 2 - 1
+    half = count // 2
+    X[half:] = sum((-1.0) ** i * 2.0 ** (-i * (b + 1)) for i in range(5))
+    X[half + 2::3, : k // 2] *= -1.0
+    return X
 
 
-# fmt, m, n, k, k_block, s, mode, inputs, runs beyond the worst case expected (None: as the groups allow)
-CASES = [
-    ("fp16", 260, 130, 700, 256, 5, "triangle", "u110", True),     # a pair may fill the window: bounds from the slices
-    ("fp16", 130, 70, 2048, 1024, 6, "full", "binade", True),
-    ("fp16", 100, 150, 4096, 0, 5, "triangle", "u110", True),      # window of one pair at b = 6
-    ("fp16", 100, 150, 2100, 0, 5, "triangle", "u110", True),
-    ("fp8", 70, 140, 32768, 0, 7, "triangle", "binade", None),     # window of two pairs: bounds k_block 4^b; few tiles, short groups
-    ("fp6", 140, 70, 32768, 0, 7, "triangle", "binade", None),
-    ("fp6_e3m2", 70, 40, 65536, 0, 9, "triangle", "binade", None),  # four pairs
-    ("fp8", 300, 270, 520, 0, 8, "triangle", "phi1", False),       # windows that hold every anti-diagonal
-    ("fp8", 130, 100, 200, 0, 12, "full", "binade", False),
-    ("int8", 130, 100, 520, 0, 7, "triangle", "phi1", False),
+def _sample(count, rng):
+    half = count // 2
+    fixed = [0, min(31, half - 1), half - 1, half, count - 1]
+    return np.unique(fixed + list(rng.integers(0, half, 9)) + list(rng.integers(half, count, 9)))
+
+
+# format, m, n, k, k_block, s, mode, 128 x 128 blocks?, bounds from the slices?
+BEYOND = [
+    ("fp16", 700, 650, 600, 256, 7, "triangle", 1, 1), ("fp16", 1300, 1200, 1024, 0, 7, "full", 0, 1), ("fp16", 1300, 1200, 2048, 0, 7, "full", 0, 0),
+    ("fp16", 2900, 380, 2048, 0, 9, "full", 1, 0), ("fp16", 2100, 1100, 4096, 0, 8, "full", 0, 1),
+    ("fp8", 2010, 1900, 32768, 0, 7, "triangle", 0, 0), ("fp8", 640, 640, 32768, 0, 9, "triangle", 1, 0), ("fp8", 100, 2600, 32768, 0, 7, "full", 1, 0),
+    ("fp6", 2010, 1900, 32768, 0, 7, "triangle", 0, 0), ("fp6", 640, 640, 32768, 0, 9, "triangle", 1, 0),
+    ("fp6_e3m2", 3000, 384, 65536, 0, 11, "full", 0, 0), ("fp6_e3m2", 100, 2600, 131072, 0, 7, "full", 1, 0),
 ]
 
 
-@pytest.mark.parametrize("fmt,m,n,k,k_block,s,mode,recipe,beyond", CASES)
-def test_runs_of_the_dgemm_are_exact(fmt, m, n, k, k_block, s, mode, recipe, beyond):
-    A, B = _recipe(recipe, m, n, k, seed=m + 2 * n + k)
-    plan, blocks = _oracle_products(A, B, fmt, s, k_block, mode)
+@pytest.mark.parametrize("fmt,m,n,k,k_block,s,mode,small,from_slices", BEYOND)
+def test_runs_beyond_the_worst_case(fmt, m, n, k, k_block, s, mode, small, from_slices):
+    way = planner.route(m, n, k, fmt, s, k_block, mode)
+    assert way.measured and way.small == small and way.bounds_from_slices == from_slices and way.group_len > way.run_limit, way
+    assert from_slices == (way.run_limit == 1)
+    plan = oz.make_plan(k, fmt, k_block)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(m + 2 * n + k)
+    A, Bt = _vectors(m, k, plan.b, gen), _vectors(n, k, plan.b, gen)
+    rng = np.random.default_rng(k)
+    rows, cols = _sample(m, rng), _sample(n, rng)
+    Ah, Bh = A[torch.from_numpy(rows).cuda()].cpu().numpy(), Bt[torch.from_numpy(cols).cuda()].cpu().numpy().T.copy()
+    pick = (torch.from_numpy(cols).cuda()[:, None], torch.from_numpy(rows).cuda()[None, :])
+    Ad = A.T.contiguous()
+    del A
+    fid, ps = lib.SLICE_FORMATS[fmt], lib.PAIR_SETS[mode]
+    ws = device.Workspace.for_problem(m, n, k, fid, s, k_block, pair_set=ps)
+    C = {}
+    for accum in ("hw", "exact"):
+        Cd = torch.full((n, m), float("nan"), dtype=torch.float64, device="cuda")
+        print(f"{fmt} {m}x{n}x{k} {accum}", flush=True)
+        lib.ozaki_dgemm_ex(m, n, k, Ad, m, Bt, k, Cd, m, fid, s, k_block, lib.ACCUM_MODES[accum], ps, lib.SUM_RUNS, 0)
+        assert lib.ozaki_last_device_status() == 0
+        C[accum] = Cd[pick].cpu().numpy().T
     pairs = oz.pair_order(s, mode)
+    P = torch.full((plan.num_blocks, len(pairs), n, m), -77.0, dtype=torch.float32, device="cuda")
+    L = torch.full((plan.num_blocks, len(pairs), n, m), 99, dtype=torch.uint8, device="cuda")
+    print(f"{fmt} {m}x{n}x{k} export", flush=True)
+    lib.ozaki_pair_products(m, n, k, Ad, m, Bt, k, fid, s, k_block, P, pair_set=ps, chained=2, run_len_out=L)
+    assert lib.ozaki_last_device_status() == 0
+    Pn, Ln = P[:, :, pick[0], pick[1]].cpu().numpy(), L[:, :, pick[0], pick[1]].cpu().numpy().astype(np.int64)
+    ws.close()
+
+    for accum, rule in (("hw", "runs"), ("exact", "exact")):
+        want = oz.ozaki_dgemm(Ah, Bh, fmt, s, k_block, mode=mode, accumulate=rule)
+        assert np.array_equal(np.ascontiguousarray(C[accum]).view(np.uint64), want.view(np.uint64)), accum
+    _, blocks = oz.ozaki_dgemm(Ah, Bh, fmt, s, k_block, mode=mode, return_blocks=True)
     window = formats.EXACT_WINDOW[fmt]
-    limit = max(1, min(32, window // (plan.k_block << (2 * plan.b))))
-    for minimum in (False, True):                     # all products resident, and one pass per anti-diagonal
-        Pn, Ln = export(A, B, fmt, s, k_block, mode, 2, minimum)
-        longest = 0
-        for t, br in enumerate(blocks):
-            covered = np.zeros((len(pairs), n, m), dtype=np.int64)
-            for z, (p, q) in enumerate(pairs):
-                run = Ln[t, z]
-                longest = max(longest, int(run.max()))
-                scale = br.c_a[p - 1][None, :] + br.c_b[q - 1][:, None]
-                total = np.zeros((n, m), dtype=np.int64)
-                for j in range(int(run.max())):
-                    inside = run > j
-                    pj, qj = pairs[z + j]
-                    assert (pj, qj) == (p + j, q - j), (t, z, j)                         # one anti-diagonal, consecutive
-                    assert np.array_equal((br.c_a[pj - 1][None, :] + br.c_b[qj - 1][:, None])[inside], scale[inside]), (t, z, j)
-                    total += np.where(inside, br.products[z + j].T, 0)
-                    assert np.abs(total).max() <= window, (t, z, j)
-                    covered[z + j] += inside
-                assert np.array_equal(Pn[t, z], _as_device_words(total.T, fmt, plan.b)), (t, z)
-            assert covered.min() == 1 and covered.max() == 1, t                          # every pair in exactly one run
-        assert beyond is None or (longest > limit) == beyond, (longest, limit)
+    regular = np.outer(cols < n // 2 // 32 * 32, rows < m // 2 // 32 * 32)            # 32 x 32 tiles of regular vectors only
+    longest = cut = 0
+    for t, br in enumerate(blocks):
+        covered = np.zeros((len(pairs), len(cols), len(rows)), dtype=np.int64)
+        for z, (p, q) in enumerate(pairs):
+            run = Ln[t, z]
+            longest = max(longest, int(run[regular].max()))
+            scale = br.c_a[p - 1][None, :] + br.c_b[q - 1][:, None]
+            total = np.zeros(run.shape, dtype=np.int64)
+            for j in range(int(run.max())):
+                inside = run > j
+                pj, qj = pairs[z + j]
+                assert (pj, qj) == (p + j, q - j), (t, z, j)                         # one anti-diagonal, consecutive
+                assert np.array_equal((br.c_a[pj - 1][None, :] + br.c_b[qj - 1][:, None])[inside], scale[inside]), (t, z, j)
+                total += np.where(inside, br.products[z + j].T, 0)
+                assert np.abs(total).max() <= window, (t, z, j)
+                covered[z + j] += inside
+            assert np.array_equal(Pn[t, z], _as_device_words(total.T, fmt, plan.b)), (t, z)
+            # the run ends although the scale goes on: the window was full, or the group ended
+            if z + int(run.max()) < len(pairs):
+                cut = max(cut, int(np.abs(total).max()))
+        assert covered.min() == 1 and covered.max() == 1, t                          # every pair in exactly one run
+    assert longest > way.run_limit, (longest, way)
+    assert 2 * cut >= window, (cut, window)                                          # sums that fill the window were there
