@@ -315,6 +315,10 @@ inline bool place_call(const Plan& plan, bool want_product, int sum_words, bool 
     if (!carve(plan, r.c, want_product, sum_words, wm)) return false;
     if (chained && measured) r.check = place_run_check(r.pl, r.c);
     choose_gemm(r.pl, r.c.chunk_pairs, chained, r.check.starts != nullptr);               // of one pass: each is a launch of its own
+    if (r.pl.group_len <= r.pl.run_limit) {                                               // no group passes the worst case: nothing to measure
+        r.check = RunCheck{nullptr, nullptr, nullptr};
+        r.c.A.l1 = r.c.B.l1 = r.c.A.bounds = r.c.B.bounds = nullptr;
+    }
     r.deltas_a = r.c.A.deltas;
     r.deltas_b = r.c.B.deltas;
     if (r.pl.small_tiles && r.c.A.l1 == nullptr) r.c.A.deltas = r.c.B.deltas = nullptr;      // a launch less
