@@ -39,8 +39,8 @@ def test_groups_of_a_pass_hold_every_pair_once(host_order):
                         assert host_order.groups_cover(s, full, length, g_hi, g_lo) == 0, (s, full, length, g_hi, g_lo)
 
 
-# m, n around the block edges; k of one chunk, an odd and an even number of chunks, a ragged last one; the last two are
-# shapes that take the 256 x 256 blocks although they have few tiles
+# m, n around the block edges; k of one chunk, an odd and an even number of chunks, a ragged last one.  Which blocks these few
+# tiles take is the planner's choice; test_large_blocks_match_oracle has the shapes that take 256 x 256
 SHAPES = [(127, 129, 64), (128, 128, 65), (129, 127, 200), (1, 385, 320), (257, 100, 33), (96, 1500, 1000), (520, 500, 2100), (700, 900, 800)]
 
 
@@ -66,6 +66,41 @@ def test_block_edges_match_oracle(fmt, m, n, k):
             assert lib.ozaki_last_device_status() == 0
             got = np.ascontiguousarray(Cd.cpu().numpy().T)
             assert np.array_equal(got.view(np.uint64), want[rule].view(np.uint64)), (minimum, accum, rule)
+        ws.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fmt", ["fp8", "fp6", "fp6_e3m2", "int8", "fp16"])
+@pytest.mark.parametrize("m,n,k,s,mode", [(4097, 3900, 300, 6, "triangle"), (3969, 4225, 129, 5, "full"), (8191, 2049, 64, 7, "triangle")])
+def test_large_blocks_match_oracle(fmt, m, n, k, s, mode):
+    """256 x 256 blocks in every format, from 256 tiles on: numbers of 128 x 128 blocks odd (waves without a block to store), odd,
+    even and single stages per pair, a ragged last one; strips and the plain order (32 block rows).  Rows and columns from both
+    sides of the tile edges are compared: a vector is sliced on its own, so is every entry of the product."""
+    torch = pytest.importorskip("torch")
+    import planner
+    from paper_2508_00441_amd import device
+    rng = np.random.default_rng(m + n + k)
+    A, B = inputs.phi_pair(m, n, k, 2.0, seed=m + 3 * n + k)
+    sample = lambda count: np.unique(np.concatenate([np.arange(0, 3), [127, 128, 255, 256, count - 130, count - 129, count - 1], rng.integers(0, count, 30)]))
+    rows, cols = sample(m), sample(n)
+    A[m // 2:, :] = np.ldexp(inputs.full_mantissa_one_binade(m - m // 2, k, rng), 3)           # half of the tiles with long runs
+    B[:, n // 2:] = inputs.full_mantissa_one_binade(k, n - n // 2, rng)
+    Ad, Bd = device.to_device_colmajor(A), device.to_device_colmajor(B)
+    fid, ps = lib.SLICE_FORMATS[fmt], lib.PAIR_SETS[mode]
+    want = {rule: oz.ozaki_dgemm(A[rows], B[:, cols], fmt, s, 0, mode=mode, accumulate=rule) for rule in ("runs", "plain")}
+    for minimum in (False, True):
+        assert planner.route(m, n, k, fmt, s, 0, mode, minimum=minimum).small == 0
+        ws = device.Workspace.for_problem(m, n, k, fid, s, 0, pair_set=ps, minimum=minimum)
+        ws.buf.fill_(0xFF)                            # NaN patterns wherever nothing is written
+        ws.buf[:256].zero_()
+        for accum, rule in (("hw", "runs"), ("emu", "plain")):
+            Cd = torch.full((n, m), float("nan"), dtype=torch.float64, device="cuda")
+            print(f"{fmt} {m}x{n}x{k} minimum={minimum} {accum} {rule}", flush=True)
+            lib.ozaki_dgemm_ex(m, n, k, Ad, m, Bd, k, Cd, m, fid, s, 0, lib.ACCUM_MODES[accum], ps, lib.SUM_RULES[rule], 0)
+            assert lib.ozaki_last_device_status() == 0
+            got = Cd[torch.from_numpy(cols).cuda()[:, None], torch.from_numpy(rows).cuda()[None, :]].cpu().numpy().T
+            assert np.array_equal(np.ascontiguousarray(got).view(np.uint64), want[rule].view(np.uint64)), (minimum, accum, rule)
+            assert bool(torch.isfinite(Cd).all())
         ws.close()
 
 

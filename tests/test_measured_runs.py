@@ -1,6 +1,6 @@
-"""Runs beyond the window's worst case: where the slices' own size allows it, the matrix unit keeps summing.  Inputs whose
-products fill the window exactly (the runs must break), random ones (they must not change a bit), every route to the
-accumulation."""
+"""Block lengths and slice counts around the window: inputs whose products fill it exactly, random ones, every route to the
+accumulation.  These problems have few tiles, so that the planner mostly keeps their groups within the worst case; the
+cases whose groups pass it, so that the accumulators are looked at, are in test_exported_runs.py."""
 import numpy as np
 import pytest
 
