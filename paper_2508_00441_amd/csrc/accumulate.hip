@@ -6,8 +6,8 @@
 // Rule "runs": inside an anti-diagonal, consecutive pairs with the same e form a run.  A run is summed exactly (an
 // integer in units of 2^-2b: at most 32 products of at most 2^24, or 2^31 for INT8 slices, units each) and added to
 // the block sum S with ONE rounded FP64 addition.  The GEMM kernel has already formed part of these sums in the
-// matrix unit's accumulators, as far as the exact window of Eq. 11 reaches (groups of at most run_limit pairs) and
-// where a whole 32 x 32 tile shares the scale; the rest is merged here, element by element.  Rule "plain": every
+// matrix unit's accumulators, as far as the exact window of Eq. 11 reaches (in the worst case, or measured: RunCheck in
+// layout.hpp) and where a whole 32 x 32 tile shares the scale; the rest is merged here, element by element.  Rule "plain": every
 // product is added with its own rounded addition (the GEMM kernel then stores every pair on its own).  Then
 //     C   = S * 2^(cA_1(i) + cB_1(j))            first block
 //     C  += S * 2^(cA_1(i) + cB_1(j))            later blocks (one more FP64 addition)
@@ -65,7 +65,7 @@ struct AccArgs {
 // p, q 0-based slice indices of the pair.
 __device__ __forceinline__ bool starts_run(const PairOrder& o, int allow_chain, const int32_t* dA, int64_t ga, const int32_t* dB,
                                            int64_t gb, int pos, int p, int q) {
-    return pos % o.run_limit == 0 || !(allow_chain && pair_linked(dA, ga, dB, gb, p - 1, q + 1));
+    return pos % o.group_len == 0 || !(allow_chain && pair_linked(dA, ga, dB, gb, p - 1, q + 1));
 }
 
 // R elements per thread: 4 (one workgroup per 32 x 32 position) or 1 (four workgroups per position, each eight of its
@@ -161,7 +161,7 @@ __device__ __forceinline__ void accumulate_body(const AccArgs& a) {
     // (an anti-diagonal has at most 32 pairs).
     if (tid < 64) {
         int count = 0, slot0 = 0;
-        const bool group_start = tid % a.order.run_limit == 0;
+        const bool group_start = tid % a.order.group_len == 0;
         for (int g = a.pass.g_hi; g >= a.pass.g_lo; --g) {
             const int len = diag_len(a.order, g);
             bool start = false;

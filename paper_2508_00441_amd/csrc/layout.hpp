@@ -78,7 +78,7 @@ struct Plan {
     int run_limit;        // floor(window / (kb * 4^b)): equal-scale pair products that may be summed exactly in the
                           // matrix unit's accumulators (window 2^24 for FP32, 2^31 - 1 for INT32)
     int pair_bound;       // kb * 4^b: no partial sum of a pair product is larger (FP32 formats: at most 2^24)
-    int group_len;        // pairs per group of the GEMM kernel, <= run_limit, or s with measured runs (PairOrder::run_limit of the launches)
+    int group_len;        // pairs per group of the GEMM kernel (choose_gemm): at most run_limit, with measured runs at most s
     int64_t tiles_m, tiles_n;
     int64_t quads_m, quads_n;    // 128 x 128 blocks that hold elements of C
     int64_t m_pad, n_pad;
@@ -89,14 +89,14 @@ struct Plan {
 // The slice pairs (p, q), 1-based, and their accumulation order: anti-diagonals g = p + q from the least
 // significant (largest g) down to g = 2, p ascending inside one.  Triangle mode uses the pairs with p + q <= s + 1,
 // full mode all s * s.  Consecutive pairs of an anti-diagonal with equal scale are summed exactly before the FP64
-// addition; the matrix unit can do that for as many pairs as fit the exact FP32 window (Plan::run_limit), so every
-// anti-diagonal is cut into groups of at most run_limit consecutive pairs (Plan::group_len, never more than the
-// window), the unit of work of the GEMM kernel; pairs are numbered z = 0, 1, ... in this order.  Everything below
-// is a closed form of (s, full, run_limit), evaluated on the host and in the kernels.
+// addition; the matrix unit can do that for as many pairs as surely fit the exact window (Plan::run_limit), or, with measured
+// runs (RunCheck), for as many as its accumulators leave room for.  Every anti-diagonal is cut into groups of at most group_len
+// consecutive pairs (Plan::group_len), the unit of work of the GEMM kernel; pairs are numbered z = 0, 1, ... in this order.
+// Everything below is a closed form of (s, full, group_len), evaluated on the host and in the kernels.
 struct PairOrder {
     int s;
     int full;
-    int run_limit;        // pairs per group
+    int group_len;        // pairs per group
 };
 __host__ __device__ inline int order_top_diag(const PairOrder& o) { return o.full ? 2 * o.s : o.s + 1; }
 __host__ __device__ inline int diag_first_p(const PairOrder& o, int g) { return g - o.s > 1 ? g - o.s : 1; }
@@ -104,11 +104,11 @@ __host__ __device__ inline int diag_len(const PairOrder& o, int g) {
     const int hi = g - 1 < o.s ? g - 1 : o.s;
     return hi - diag_first_p(o, g) + 1;
 }
-__host__ __device__ inline int diag_groups(const PairOrder& o, int g) { return (diag_len(o, g) + o.run_limit - 1) / o.run_limit; }
+__host__ __device__ inline int diag_groups(const PairOrder& o, int g) { return (diag_len(o, g) + o.group_len - 1) / o.group_len; }
 // First position of group i of an anti-diagonal of `len` pairs: whole groups, then the rest.  (Cuts of equal length would even
 // out the workgroups, but groups of neighbouring anti-diagonals that start at the same slice read the same panels side by
 // side: 1024 x 1024 x 8192 takes 0.51 ms with these cuts, 0.56 ms with equal ones.)
-__host__ __device__ inline int group_first(const PairOrder& o, int len, int i) { return i * o.run_limit < len ? i * o.run_limit : len; }
+__host__ __device__ inline int group_first(const PairOrder& o, int len, int i) { return i * o.group_len < len ? i * o.group_len : len; }
 __host__ __device__ inline int order_num_groups(const PairOrder& o) {
     int n = 0;
     for (int g = order_top_diag(o); g >= 2; --g) n += diag_groups(o, g);
@@ -149,7 +149,7 @@ __host__ __device__ inline Group pass_group(const PairOrder& o, const Pass& ps, 
 inline int longest_group(const PairOrder& o, const Pass& ps) {
     int longest = 1;
     for (int g = ps.g_hi; g >= ps.g_lo; --g) longest = diag_len(o, g) > longest ? diag_len(o, g) : longest;
-    return longest < o.run_limit ? longest : o.run_limit;
+    return longest < o.group_len ? longest : o.group_len;
 }
 
 // The groups of a pass in the order in which workgroups take them, longest first (a long group that starts last would be
@@ -255,8 +255,8 @@ struct RunCheck {
 
 // True if, for every element of a 32 x 32 tile, pair (p+1, q-1) carries the same scale factor 2^(cA + cB) as pair
 // (p, q) (0-based slice indices): then the two products can be summed in the accumulator of the matrix unit
-// (a group has at most run_limit pairs, so the sum stays inside the exact window).  a: the delta of slice p of the
-// tile's 32 rows of A, b: the delta of slice q - 1 of its 32 columns of B.
+// (that the sum stays inside the exact window is another matter: groups of at most run_limit pairs, or RunCheck).  a: the delta
+// of slice p of the tile's 32 rows of A, b: the delta of slice q - 1 of its 32 columns of B.
 __host__ __device__ inline bool deltas_link(int a, int b) { return a != DELTA_IRREGULAR && a == b; }
 // dA / dB: Operand::deltas of the block, advanced to the tile's group of rows of A / columns of B; ga / gb: groups per
 // slice (rows_pad / LINK_ROWS) of the two operands.

@@ -13,9 +13,9 @@
 // group of pairs (consecutive pairs of an anti-diagonal, streamed through one continuous pipeline); each wave owns
 // 128 x 128 (4 x 4 MFMA tiles of 32 x 32, 256 accumulator registers per lane).  Whether the product of the next pair
 // keeps accumulating on top of the current one is decided per 32 x 32 MFMA tile: it does where all 32 rows of A and all
-// 32 columns of B concerned carry the same scale factor for both pairs (exact, because a group never exceeds the
-// window of Eq. 11); a tile that does not is stored and cleared, so one irregular row costs one 4 KiB store, not the
-// workgroup's 256 KiB.  The
+// 32 columns of B concerned carry the same scale factor for both pairs (exact, because a group's worst case stays inside the
+// window of Eq. 11, or because the accumulators have been looked at: MEASURED below); a tile that does not is stored and
+// cleared, so one irregular row costs one 4 KiB store, not the workgroup's 256 KiB.  The
 // matrix unit's "row" operand is the B slice (index n), its "column" operand the A slice (index m), so that
 // the lanes of a wave run along m, the contiguous direction of column-major C.
 //
@@ -139,8 +139,8 @@ __device__ __forceinline__ void pair_gemm_body(const GemmArgs& a) {
     const int chunks = (int)a.chunks;
     // Whether pair jp+1 of the group keeps accumulating on top of pair jp is decided per MFMA tile (i, j) of the wave,
     // when pair jp is complete: it does if all 32 rows of A and all 32 columns of B behind the tile carry the same scale
-    // factor for both pairs (pair_linked; the sum stays inside the exact window because a group has at most run_limit
-    // pairs).  The rows of A behind tile column j are the 32-vector group tm*8 + wm*4 + j, the columns of B behind
+    // factor for both pairs (pair_linked; without MEASURED a group has at most run_limit pairs, whose sum stays inside the
+    // exact window whatever the data).  The rows of A behind tile column j are the 32-vector group tm*8 + wm*4 + j, the columns of B behind
     // tile row i the group tn*8 + wn*4 + i.  The deltas of the wave's four groups are 16 contiguous bytes per slice and
     // are read through the scalar cache (they were written by an earlier kernel and the addresses are wave-uniform), so
     // they stay out of the vector-memory counter that paces the load ring.

@@ -1,4 +1,4 @@
-// Slice-pair GEMMs for problems with too few 256 x 256 tiles to fill the chip (see pair_gemm.hip for the method).
+// Slice-pair GEMMs for problems with too few 256 x 256 tiles to fill the chip (see pair_gemm_body.hpp for the method).
 //
 // A workgroup of four waves computes a 128 x 128 block of the product for one group of pairs, each wave 64 x 64 (2 x 2
 // MFMA tiles, 64 accumulator registers per lane).  Against the 256 x 256 kernel this costs twice the L2 -> LDS bytes per
@@ -6,7 +6,7 @@
 // stage takes a quarter of the time, and rows and columns beyond the matrix are padded to 128 instead of 256.  Products
 // are stored in the same layout: a 128 x 128 block is what one wave of the 256 x 256 kernel owns.
 //
-// The pipeline is the one of pair_gemm.hip: direct-to-LDS loads through a ring of NSTAGE stages, fragments read one
+// The pipeline is the one of pair_gemm_body.hpp: direct-to-LDS loads through a ring of NSTAGE stages, fragments read one
 // k-step ahead.  Two waves load the B slices (the matrix unit's "row" operand), two the A slices.
 #include <math.h>
 
@@ -93,7 +93,7 @@ __global__ void __launch_bounds__(256, 2) pair_gemm_small_kernel(const SmallGemm
     const int glen = grp.len, p0 = grp.p0 - 1, q0 = grp.q0 - 1;       // 0-based slice indices from here on
     const int chunks = a.chunks;
 
-    // Run continuation per 32 x 32 tile, as in pair_gemm.hip; the wave's two row groups and two column groups are eight
+    // Run continuation per 32 x 32 tile, as in pair_gemm_body.hpp; the wave's two row groups and two column groups are eight
     // contiguous bytes each per slice, read through the scalar cache.
     typedef int v2s __attribute__((ext_vector_type(2)));
     typedef const __attribute__((address_space(4))) v2s* delta2_ptr;
@@ -115,7 +115,7 @@ __global__ void __launch_bounds__(256, 2) pair_gemm_small_kernel(const SmallGemm
         return cont;
     };
 
-    // Measured runs, as in pair_gemm.hip
+    // Measured runs, as in pair_gemm_body.hpp
     auto drop_full_tiles = [&](unsigned cont, const v2s& bav, const v2s& bbv, const auto& acc) -> unsigned {
 #pragma unroll
         for (int i = 0; i < 2; ++i)
@@ -161,7 +161,7 @@ __global__ void __launch_bounds__(256, 2) pair_gemm_small_kernel(const SmallGemm
 #pragma unroll
         for (int i = 0; i < LPW; ++i) piece[i] = first_row * BK + (size_t)(half * LPW + i) * 1024 + goff;
     }
-    // A slices of a group lie back to back; B slices are walked backwards (see pair_gemm.hip)
+    // A slices of a group lie back to back; B slices are walked backwards (see pair_gemm_body.hpp)
     const int64_t d_wrap = is_x ? -(int64_t)((size_t)(2 * chunks - 1) * cs) : (int64_t)cs;
     const int lds_at = (is_x ? 0 : OPERAND_BYTES) + half * LPW * 1024;
     const int total = glen * chunks;
@@ -222,7 +222,7 @@ __global__ void __launch_bounds__(256, 2) pair_gemm_small_kernel(const SmallGemm
             const unsigned y8 = (unsigned)(uintptr_t)OZAKI_LPTR(base + OPERAND_BYTES + 4096 + fg * 1024 + yrow * 8);
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                unsigned ax = x8 + i * 32 * 8, ay = y8 + i * 32 * 8;      // an address register of its own each, see pair_gemm.hip
+                unsigned ax = x8 + i * 32 * 8, ay = y8 + i * 32 * 8;      // an address register of its own each, see pair_gemm_body.hpp
                 asm volatile("" : "+v"(ax), "+v"(ay));
                 const v4i xlo = *reinterpret_cast<const v4i*>(x16 + i * 32 * 16);
                 const v2i xhi = *reinterpret_cast<const __attribute__((address_space(3))) v2i*>((uintptr_t)ax);

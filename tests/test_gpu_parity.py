@@ -383,7 +383,7 @@ def test_dgemm_matches_oracle(fmt, m, n, k, k_block, s, phi):
 @pytest.mark.parametrize("fmt,k_block", [("fp8", 0), ("fp6", 0), ("fp16", 256)])
 def test_operands_off_the_16_byte_boundary_with_odd_leading_dimensions(fmt, k_block):
     """A, B and C start one element (8 bytes) past a 16-byte boundary and have odd leading dimensions: the split
-    kernel's two-element loads are not allowed there, the result must not change."""
+    kernel's two-element loads are 8 bytes off their size there, the result must not change."""
     m, n, k, s = 270, 140, 600, 9
     A, B = inputs.phi_pair(m, n, k, 1.0, seed=99)
     lda, ldb, ldc = m + 1, k + 1, m + 1
@@ -609,7 +609,7 @@ def test_memory_capped_call_works_in_panels_and_gives_the_same_bits():
                                            ("int8", 40, 33, 131072, 8, 6), ("fp16", 40, 20, 65536, 9, 4)])
 def test_unblocked_inner_dimensions_beyond_the_register_kernel(fmt, m, n, k, s, b):
     """Table 2's last rows run as printed: k = 65536 (b = 4) and k = 131072 (b = 3) without inner blocking; the
-    slicing then streams through the vectors with its state in work memory."""
+    slicing then finds the exponents of all slices first and slices every chunk on its own."""
     assert lib.ozaki_plan(k, FMT[fmt])[1] == b == oz.make_plan(k, fmt).b
     A, B = inputs.phi_pair(m, n, k, 1.0, seed=k % 1000 + m)
     Ad, Bd = _upload(A, B)

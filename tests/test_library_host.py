@@ -86,7 +86,7 @@ def test_workspace_sizes():
     assert lib.ozaki_workspace_bytes(16, 16, 16, 5, 4, 0) == 0          # bad format
     assert lib.ozaki_workspace_bytes(16, 16, 1 << 25, 0, 4, 0) == 0     # no slice width is exact for a block this long
     assert lib.ozaki_workspace_bytes(16, 16, 1 << 25, 0, 4, 8192) > 0
-    # blocks beyond the register-resident slicing kernel need its streaming state: 12 bytes per (padded) element
+    # blocks beyond the register-resident slicing kernel: the documented sizes keep a reserve of 12 bytes per (padded) element
     long_ws = lib.ozaki_workspace_bytes(16, 16, 1 << 20, 0, 4, 0)
     assert long_ws > lib.ozaki_workspace_bytes(16, 16, 1 << 20, 0, 4, 16384) + 12 * 32 * (1 << 20) - (1 << 20)
     assert lib.ozaki_workspace_bytes(16, 16, 16, 0, 33, 0) == 0         # more slices than the library takes
