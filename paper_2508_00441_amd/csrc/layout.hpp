@@ -217,26 +217,51 @@ __host__ __device__ inline WorkItem work_item(unsigned b, unsigned total, const 
     it.bm = strip_rows * strip + (in - it.bn * height);
     return it;
 }
+// Slice panels that an XCD fetches per workgroup and stage, of the two that a workgroup reads: rows + columns over the area of what it
+// has in flight of one group, in strips and in the plain order (every eighth block, block rows fastest).
+inline double strip_panels(int64_t blocks_m, int64_t blocks_n, const WorkOrder& o) {
+    if (blocks_m * blocks_n < o.unit) return (double)(blocks_m + blocks_n) / (double)(blocks_m * blocks_n);
+    const double rows = (double)(blocks_m < o.height ? blocks_m : o.height), cols = o.unit / rows < (double)blocks_n ? o.unit / rows : (double)blocks_n;
+    return (rows + cols) / (rows * cols);
+}
+inline double plain_panels(int64_t blocks_m, int64_t blocks_n) {
+    const int64_t blocks = blocks_m * blocks_n, stride = blocks_m % 8 == 0 ? 8 : blocks_m % 4 == 0 ? 4 : blocks_m % 2 == 0 ? 2 : 1;
+    const double in_flight = blocks > 8 ? blocks / 8.0 : 1.0, rows = (double)(blocks_m / stride), cols = (double)blocks_n;
+    return ((rows < in_flight ? rows : in_flight) + (cols < in_flight ? cols : in_flight)) / in_flight;
+}
+
 // The order for a launch of `groups` groups of `pairs` pairs together, none longer than `len`, over blocks_m x blocks_n blocks; `per_xcd`
-// workgroups run at a time on an XCD: strips from about two rounds of workgroups on (128 x 128 blocks 2, 256 x 256 blocks 2.5, four where
-// a pair has fewer than eight stages).  What they save is traffic between the L2s and the memory behind them, a panel per
-// workgroup and stage or more in the plain order: 5 x 23 blocks of 128 x 128, 24 stages, 121 products in 2415 workgroups
-// (4.7 rounds) 576 -> 290 us; 14 x 6 blocks of 256 x 256, 112 FP16 stages, 4.6 rounds 1.58 -> 1.31 ms; 4096^3 FP8 4.08 -> 4.01 ms.
-// Over 700 random problems strips take 0.7 to 0.9 of the plain time with 128 x 128 blocks and 0.92 to 0.97 with 256 x 256
-// blocks at two to four rounds, 0.63 to 0.8 and 0.75 to 0.9 from eight rounds on, whatever the length of the groups.  With fewer rounds
-// a unit's XCD waits for its longest group while others are idle (1.0 to 1.2 of the plain time), except in 128 x 128 blocks where the
-// groups are of nearly equal length and the plain order spreads every group over all XCDs (a number of blocks that is no
-// multiple of eight): there strips pay from 0.75 rounds on if pairs are long (12 x 3 blocks, 64 FP16 stages, groups of two:
-// 679 -> 510 us; 7 x 4 blocks 226 -> 165; 3 x 3 blocks, 128 stages, single pairs: 316 -> 209).  Short pairs are bound by their stores
-// (0.95 to 1.05 below four rounds).  The plain order also stays where it already gives every XCD a compact patch by itself: at
-// 32 block rows, four of them per XCD (128 x 128 blocks: 1.0 to 1.1 of the plain time there; 16384^2 FP16: 2.5 % longer).
-// 40, 44, 48, 52 and 56 block rows of 256: strips, equal to the plain order or up to 6 % faster.
-__host__ __device__ inline WorkOrder work_order(double groups, double pairs, int len, int per_xcd, int64_t blocks_m, int64_t blocks_n, int64_t chunks) {
-    const double rounds = groups * (double)(blocks_m * blocks_n) / (8 * per_xcd);
-    const bool small = per_xcd == 64, even = pairs >= 0.7 * len * groups && (blocks_m * blocks_n) % 8 != 0;
-    const double least = chunks < 8 ? 4.0 : !small ? 2.5 : even && chunks >= 32 ? 0.75 : 2.0;
-    if (blocks_m % 32 == 0 || rounds < least) return WorkOrder{0, 0};
-    return WorkOrder{per_xcd, blocks_m > 8 ? 4 : 8};
+// workgroups run at a time on an XCD.  Strips save traffic between the L2s and the memory behind them, a panel per workgroup
+// and stage or more: 5 x 23 blocks of 128 x 128, 24 stages, 121 products in 2415 workgroups (4.7 rounds) 576 -> 290 us;
+// 14 x 6 blocks of 256 x 256, 112 FP16 stages, 4.6 rounds 1.58 -> 1.31 ms; 4096^3 FP8 4.08 -> 4.01 ms.  In 700 random problems they
+// take 0.7 to 0.9 of the plain time with 128 x 128 blocks and 0.92 to 0.97 with 256 x 256 blocks at two to four rounds of
+// workgroups, 0.63 to 0.8 and 0.75 to 0.9 from eight rounds on, whatever the length of the groups.  What they cost: a unit's
+// XCD waits for its longest group while others are idle, 1.0 to 1.2 of the plain time with few rounds.  Hence
+//   - 128 x 128 blocks from 2 rounds on, 256 x 256 blocks from 2.5; where a group has a multiple of eight blocks, so that the plain
+//     order keeps a block on its XCD from group to group, from 2.5 and 4 (8 x 8 blocks of 256 x 256, 32 FP16 stages, 3.25
+//     rounds: strips 6 % slower);
+//   - pairs of fewer than eight stages, which are bound by their stores, from 4 (0.95 to 1.05 below);
+//   - 128 x 128 blocks, pairs of 16 stages and more, where strips fetch less than a panel and the plain order 1.5 or more: from 0.6
+//     in groups of equal length (0.85 of the longest on average), from 0.75 at 0.7 (0.76 to 0.89 of the plain time on average, 1.1
+//     to 1.25 below; 5 x 5 blocks, groups of two to five: 72 -> 47, 62 -> 51, 60 -> 49, 54 -> 50 us; 12 x 3 blocks, 64 FP16
+//     stages, groups of two: 679 -> 510); from 0.35 to 0.5, where no two workgroups share a compute unit and so none waits, if it
+//     is 0.6 against 1.9 (passes of 21 to 24 pairs in groups of three, 5 x 5 blocks: the call 120 -> 116 us).
+// The plain order also stays where it already gives every XCD a compact patch by itself: at 32 block rows, four of them per XCD
+// (128 x 128 blocks: 1.0 to 1.1 of the plain time there; 16384^2 FP16: 2.5 % longer).  40, 44, 48, 52 and 56 block rows of 256:
+// strips, equal to the plain order or up to 6 % faster.
+inline WorkOrder work_order(int64_t pairs, int64_t groups, int len, int per_xcd, int64_t blocks_m, int64_t blocks_n, int64_t chunks) {
+    const WorkOrder plain{0, 0}, strips{per_xcd, blocks_m > 8 ? 4 : 8};
+    const int64_t blocks = blocks_m * blocks_n;
+    const double rounds = (double)(groups * blocks) / (8 * per_xcd);
+    const bool small = per_xcd == 64, keeps_xcd = blocks % 8 == 0;
+    double least = small ? (keeps_xcd ? 2.5 : 2.0) : (keeps_xcd ? 4.0 : 2.5);
+    if (chunks < 8) least = 4.0;
+    if (small && !keeps_xcd && chunks >= 16 && 10 * pairs >= 7 * len * groups) {
+        const double in_strips = strip_panels(blocks_m, blocks_n, strips), in_plain = plain_panels(blocks_m, blocks_n);
+        if (in_strips < 1.0 && in_plain >= 1.5) least = 20 * pairs >= 17 * len * groups ? 0.6 : 0.75;
+        if (in_strips < 0.6 && in_plain >= 1.9 && rounds <= 0.5) least = 0.35;
+    }
+    return blocks_m % 32 == 0 || rounds < least ? plain : strips;
 }
 
 // Runs longer than run_limit pairs ("measured" runs).  run_limit assumes that every product of slice entries is as large as it

@@ -35,7 +35,7 @@ hipError_t launch_pair_gemm(const Plan& pl, const Operand& A, const Operand& B, 
     a.unit = ldexpf(1.0f, -pl.p_frac);
     const int64_t blocks = (int64_t)ps.ngroups * pl.tiles_m * pl.tiles_n;
     if (blocks > 0x7FFFFFFF || pl.chunks > 0x7FFFFFFF) return hipErrorInvalidValue;
-    a.work = work_order(ps.ngroups, ps.npairs, longest_group(order, ps), 32, a.tiles_m, a.tiles_n, pl.chunks);
+    a.work = work_order(ps.npairs, ps.ngroups, longest_group(order, ps), 32, a.tiles_m, a.tiles_n, pl.chunks);
     if (check.starts != nullptr) return launch_pair_gemm_measured(a, pl.fmt, (unsigned)blocks, st);
     if (pl.fmt == FMT_FP16) hipLaunchKernelGGL((pair_gemm_kernel<FMT_FP16>), dim3((unsigned)blocks), dim3(256), 0, st, a);
     else if (pl.fmt == FMT_FP6) hipLaunchKernelGGL((pair_gemm_kernel<FMT_FP6>), dim3((unsigned)blocks), dim3(256), 0, st, a);

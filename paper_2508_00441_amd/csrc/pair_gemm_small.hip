@@ -412,7 +412,7 @@ hipError_t launch_pair_gemm_small(const Plan& pl, const Operand& A, const Operan
     a.unit = ldexpf(1.0f, -pl.p_frac);
     const int64_t blocks = (int64_t)ps.ngroups * a.quads_m * a.quads_n;
     if (blocks > 0x7FFFFFFF || pl.chunks * MAX_SLICES > 0x7FFFFFFF) return hipErrorInvalidValue;
-    a.work = work_order(ps.ngroups, ps.npairs, longest_group(order, ps), 64, a.quads_m, a.quads_n, pl.chunks);
+    a.work = work_order(ps.npairs, ps.ngroups, longest_group(order, ps), 64, a.quads_m, a.quads_n, pl.chunks);
     const dim3 grid((unsigned)blocks), block(256);
     if (pl.fmt == FMT_FP16) hipLaunchKernelGGL((pair_gemm_small_kernel<FMT_FP16>), grid, block, 0, st, a);
     else if (pl.fmt == FMT_FP6) hipLaunchKernelGGL((pair_gemm_small_kernel<FMT_FP6>), grid, block, 0, st, a);

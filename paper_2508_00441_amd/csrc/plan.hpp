@@ -29,115 +29,117 @@ inline int slice_bits(int64_t kb, int fmt) {
 
 inline bool format_ok(int fmt) { return fmt >= OZAKI_SLICE_FP8_E4M3 && fmt <= OZAKI_SLICE_INT8; }
 
+// The pass that starts at anti-diagonal g_hi: as many whole anti-diagonals as fit into `capacity` products (at
+// least one: the carve-up guarantees room for the longest anti-diagonal).
+inline Pass next_pass(const PairOrder& o, int g_hi, int capacity) {
+    Pass ps{g_hi, g_hi, 0, 0};
+    for (int g = g_hi; g >= 2; --g) {
+        const int len = diag_len(o, g);
+        if (ps.npairs > 0 && ps.npairs + len > capacity) break;
+        ps.g_lo = g;
+        ps.npairs += len;
+        ps.ngroups += diag_groups(o, g);
+    }
+    return ps;
+}
+
 // What a GEMM launch takes per 64-byte stage, in microseconds: a 128 x 128 block alone on its compute unit and one of two that
 // share it, a 256 x 256 block.
 struct StageTimes {
     double small_alone, small_shared, large;
 };
 inline StageTimes stage_times(int fmt) {
-    if (fmt_is_fp6(fmt)) return {0.23, 0.34, 0.41};
-    if (fmt == FMT_FP16) return {0.24, 0.42, 0.64};
-    if (fmt == FMT_INT8) return {0.29, 0.45, 0.63};
-    return {0.255, 0.44, 0.55};
+    if (fmt_is_fp6(fmt)) return {0.20, 0.35, 0.39};
+    if (fmt == FMT_FP16) return {0.24, 0.41, 0.61};
+    if (fmt == FMT_INT8) return {0.25, 0.45, 0.60};
+    return {0.24, 0.44, 0.53};
 }
 
-// How the GEMMs of a pass of `pairs` products run: 256 x 256 or 128 x 128 blocks, and the length of the groups.  Any choice
-// gives the same bits (the accumulation kernel merges equal-scale products of an anti-diagonal element by element whatever
-// the grouping).  Long groups store fewer products, shorter ones and smaller blocks give a problem of few tiles enough
-// workgroups to keep 256 compute units evenly busy.  The estimate of GEMM + accumulation below, in microseconds, is the least that
-// covers
+// How the GEMMs run whose products are stored `pairs` at a time (several passes, each a launch of its own, if that is not all of
+// them): 256 x 256 or 128 x 128 blocks, and the length of the groups.  Any choice gives the same bits (the accumulation kernel
+// merges equal-scale products of an anti-diagonal element by element whatever the grouping).  Long groups store fewer products,
+// shorter ones and smaller blocks give a problem of few tiles enough workgroups to keep 256 compute units evenly busy.  The
+// estimate of GEMM + accumulation, in microseconds (pass_time), is the least that covers
 //   - a workgroup's own stages (stage_times) and, added to the fourth power, the panels that the workgroups in flight fetch
-//     beyond the L2s: 20 TB/s while the slices fit the memory-side cache, 11.5 TB/s beyond it.  Panels per workgroup and stage:
-//     rows + columns over the area of what an XCD has in flight of a group, at most two;
+//     beyond the L2s (strip_panels, plain_panels): 20 TB/s while the slices fit the memory-side cache, 17 TB/s beyond it (not
+//     what the memory delivers: groups that start at the same slice share a panel);
 //   - more workgroups than slots: the even share of all stages, but at least as many rounds of every length as the workgroups
 //     of that length or more need, and up to two rounds the last ones behind the shortest of the first; then a sixth of a group
 //     for the uneven end (not for 256 x 256 blocks in the plain order, longest first over all XCDs);
 //   - filling the load ring and storing, per round; the products stored and read again.
 // Measured on 720 random problems of fewer than 256 tiles, all formats, every block size and length, the constants fitted to two
-// thirds of them: the choice takes 1.022 of the best one's time on average (1.028 on the other third), 1.23 at worst; the estimate
-// before it, FP8's times for every format, no panels, group lengths of two and more and not all of them, 1.082 and 1.94.  From 256 tiles
-// on long groups of the large blocks are always the choice.
+// thirds of them: the choice takes 1.020 of the best one's time on average (1.029 on the other third), 1.23 at worst, on 70 more
+// with inner dimensions of 8192 to 65536 1.05 and 1.39; the estimate before it (FP8's times for every format, no panels, group
+// lengths of two and more and not all of them) 1.082 and 1.94.  From 256 tiles on long groups of the large blocks are always the choice.
+inline double pass_time(const Plan& pl, const StageTimes& us, bool small, int len, const Pass& ps, bool chained) {
+    const PairOrder order{pl.s, pl.full, len};
+    int count[MAX_SLICES + 1] = {}, longest = 1;                 // groups of each length
+    for (int g = ps.g_hi; g >= ps.g_lo; --g) {
+        const int diag = diag_len(order, g), most = diag < len ? diag : len;
+        count[len] += diag / len;
+        if (diag % len != 0) ++count[diag % len];
+        if (most > longest) longest = most;
+    }
+    const int64_t bm = small ? pl.quads_m : pl.tiles_m, bn = small ? pl.quads_n : pl.tiles_n;
+    const int64_t blocks = bm * bn, slots = small ? 512 : 256;
+    int64_t wgs = 0, line = 0;                                   // line: the longest line of groups on one slot, in pairs
+    for (int l = longest; l >= 1; --l) {
+        wgs += count[l] * blocks;
+        const int64_t bound = (wgs + slots - 1) / slots * l;
+        if (bound > line) line = bound;
+    }
+    if (wgs > slots && wgs <= 2 * slots) {                       // the last ones start where the shortest of the first ones end
+        int64_t last = 0;
+        for (int l = longest; l >= 1; --l) {
+            last += count[l] * blocks;
+            if (count[l] == 0 || last <= slots) continue;
+            int64_t first = 0;
+            int before = longest;
+            for (int f = longest; f >= 1 && first < 2 * slots + 1 - last; --f) {
+                first += count[f] * blocks;
+                if (count[f] != 0) before = f;
+            }
+            if (l + before > line) line = l + before;
+        }
+    }
+    const WorkOrder work = work_order(ps.npairs, wgs / blocks, longest, small ? 64 : 32, bm, bn, pl.chunks);
+    const double fetched = work.unit == 0 ? plain_panels(bm, bn) : strip_panels(bm, bn, work), panels = fetched < 2.0 ? fetched : 2.0;
+    const double slices_mb = 1e-6 * pl.s * (double)pl.chunks * pl.row_bytes * (double)(pl.m_pad + pl.n_pad);
+    const double fetch = panels * 1e-6 * (small ? QUAD : TILE) * pl.row_bytes * (double)(wgs < slots ? wgs : slots) / (slices_mb < 160.0 ? 20.0 : 17.0);
+    const double own = !small ? us.large : wgs <= 256 ? us.small_alone : us.small_shared;
+    const double stage = sqrt(sqrt(own * own * own * own + fetch * fetch * fetch * fetch)), fixed = small ? 2.2 : 6.0;
+    double pairs = longest;                                      // in line on the slot that ends last
+    if (wgs > slots) {
+        const double even = (double)ps.npairs * blocks / slots;
+        pairs = (even > line ? even : (double)line) + (work.unit == 0 && !small ? 0.0 : 0.17 * longest);
+    }
+    const double rounds = (double)((wgs + slots - 1) / slots), stored = chained ? (double)(wgs / blocks) : (double)ps.npairs;
+    return pairs * pl.chunks * stage + rounds * fixed + stored * (0.015 * blocks * (small ? 0.25 : 1.0) + 0.18 + 0.014 * (double)(pl.quads_m * pl.quads_n));
+}
+
 inline void choose_gemm(Plan& pl, int pairs, bool chained, bool measured_runs) {
     const int most = measured_runs || pl.run_limit > pl.s ? pl.s : pl.run_limit;
     pl.small_tiles = 0;
     pl.group_len = most;
-    const int64_t tiles = pl.tiles_m * pl.tiles_n, quads = pl.quads_m * pl.quads_n;
+    const int64_t tiles = pl.tiles_m * pl.tiles_n;
     if (tiles == 0 || tiles >= 256) return;
     const StageTimes us = stage_times(pl.fmt);
-    const double part = pairs < pl.npairs ? (double)pairs / pl.npairs : 1.0;              // of the groups of all pairs
-    const double chunks = (double)pl.chunks, slices_mb = 1e-6 * pl.s * chunks * pl.row_bytes * (double)(pl.m_pad + pl.n_pad);
-    const double mb_per_us = slices_mb < 160.0 ? 20.0 : 11.5;
     double best = 1e300;
-    for (int len = most; len >= 1; --len) {
-        int count[MAX_SLICES + 1] = {};                          // groups of each length
-        for (int diag = 1; diag <= pl.s; ++diag) {
-            const int times = pl.full && diag < pl.s ? 2 : 1;
-            count[len] += times * (diag / len);
-            if (diag % len != 0) count[diag % len] += times;
-        }
+    for (int len = most; len >= 1; --len)
         for (int small = 0; small < 2; ++small) {
-            const int64_t bm = small ? pl.quads_m : pl.tiles_m, bn = small ? pl.quads_n : pl.tiles_n;
-            const double blocks = (double)(bm * bn), slots = small ? 512.0 : 256.0;
-            double ngroups = 0.0, line = 0.0;                    // line: the longest line of groups on one slot, in pairs
-            for (int l = len; l >= 1; --l) {
-                ngroups += part * count[l];
-                const double bound = ceil(ngroups * blocks / slots) * l;
-                if (bound > line) line = bound;
+            const PairOrder order{pl.s, pl.full, len};
+            double t = 0.0;
+            for (int g_hi = order_top_diag(order); g_hi >= 2 && t < best;) {
+                const Pass ps = next_pass(order, g_hi, pairs);
+                t += pass_time(pl, us, small != 0, len, ps, chained);
+                g_hi = ps.g_lo - 1;
             }
-            const double wgs = ngroups * blocks;
-            if (wgs > slots && wgs <= 2.0 * slots) {             // the last ones start where the shortest of the first ones end
-                double last = 0.0;
-                for (int l = len; l >= 1; --l) {
-                    last += part * count[l] * blocks;
-                    if (count[l] == 0 || last <= slots) continue;
-                    double first = 0.0;
-                    int before = len;
-                    for (int f = len; f >= 1 && first < 2.0 * slots + 1.0 - last; --f) {
-                        first += part * count[f] * blocks;
-                        if (count[f] != 0) before = f;
-                    }
-                    if (l + before > line) line = l + before;
-                }
-            }
-            const WorkOrder work = work_order(ngroups, part * pl.npairs, len, small ? 64 : 32, bm, bn, pl.chunks);
-            double rows, cols, in_flight;                        // of a group, on one XCD
-            if (work.unit == 0) {
-                const int64_t stride = bm % 8 == 0 ? 8 : bm % 4 == 0 ? 4 : bm % 2 == 0 ? 2 : 1;
-                in_flight = blocks > 8.0 ? blocks / 8.0 : 1.0;
-                rows = (double)(bm / stride);
-                cols = (double)bn;
-                if (rows > in_flight) rows = in_flight;
-                if (cols > in_flight) cols = in_flight;
-            } else if (blocks >= work.unit) {
-                rows = (double)(bm < work.height ? bm : work.height);
-                cols = work.unit / rows < (double)bn ? work.unit / rows : (double)bn;
-                in_flight = rows * cols;
-            } else {
-                rows = (double)bm;
-                cols = (double)bn;
-                in_flight = blocks;
-            }
-            const double panels = (rows + cols) / in_flight < 2.0 ? (rows + cols) / in_flight : 2.0;
-            const double fetch = panels * 1e-6 * (small ? QUAD : TILE) * pl.row_bytes * (wgs < slots ? wgs : slots) / mb_per_us;
-            const double own = !small ? us.large : wgs <= 256.0 ? us.small_alone : us.small_shared;
-            const double stage = sqrt(sqrt(own * own * own * own + fetch * fetch * fetch * fetch)), fixed = small ? 2.2 : 6.0;
-            double t;
-            if (wgs <= slots) {
-                t = len * chunks * stage + fixed;
-            } else {
-                const double even = part * pl.npairs * blocks / slots;
-                if (even > line) line = even;
-                t = (line + (work.unit == 0 && !small ? 0.0 : 0.17 * len)) * chunks * stage + ceil(wgs / slots) * fixed;
-            }
-            const double stored = chained ? ngroups : part * pl.npairs;
-            t += stored * (0.015 * blocks * (small ? 0.25 : 1.0) + 0.18 + 0.014 * (double)quads);
             if (t < best) {
                 best = t;
                 pl.small_tiles = small;
                 pl.group_len = len;
             }
         }
-    }
 }
 
 // Builds the plan; returns 0 or a status / negative argument index in the numbering of ozaki_dgemm.
@@ -326,19 +328,5 @@ inline bool place_call(const Plan& plan, bool want_product, int sum_words, bool 
 }
 
 inline PairOrder order_of(const Plan& pl) { return PairOrder{pl.s, pl.full, pl.group_len}; }
-
-// The pass that starts at anti-diagonal g_hi: as many whole anti-diagonals as fit into `capacity` products (at
-// least one: the carve-up guarantees room for the longest anti-diagonal).
-inline Pass next_pass(const PairOrder& o, int g_hi, int capacity) {
-    Pass ps{g_hi, g_hi, 0, 0};
-    for (int g = g_hi; g >= 2; --g) {
-        const int len = diag_len(o, g);
-        if (ps.npairs > 0 && ps.npairs + len > capacity) break;
-        ps.g_lo = g;
-        ps.npairs += len;
-        ps.ngroups += diag_groups(o, g);
-    }
-    return ps;
-}
 
 }  // namespace ozaki

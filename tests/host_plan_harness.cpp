@@ -31,7 +31,7 @@ int order_of_launch(int small, int s, int full, int len, int64_t blocks_m, int64
     const PairOrder o{s, full, len};
     Pass ps{order_top_diag(o), 2, 0, 0};
     for (int g = ps.g_hi; g >= 2; --g) { ps.npairs += diag_len(o, g); ps.ngroups += diag_groups(o, g); }
-    return work_order(ps.ngroups, ps.npairs, longest_group(o, ps), small ? 64 : 32, blocks_m, blocks_n, chunks).unit != 0;
+    return work_order(ps.npairs, ps.ngroups, longest_group(o, ps), small ? 64 : 32, blocks_m, blocks_n, chunks).unit != 0;
 }
 
 }  // extern "C"

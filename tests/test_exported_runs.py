@@ -38,8 +38,8 @@ def _sample(count, rng):
 BEYOND = [
     ("fp16", 700, 650, 600, 256, 7, "triangle", 1, 1), ("fp16", 1300, 1200, 1024, 0, 7, "full", 0, 1), ("fp16", 1300, 1200, 2048, 0, 7, "full", 0, 0),
     ("fp16", 2900, 380, 2048, 0, 9, "full", 1, 0), ("fp16", 2100, 1100, 4096, 0, 8, "full", 0, 1),
-    ("fp8", 2010, 1900, 32768, 0, 7, "triangle", 0, 0), ("fp8", 640, 640, 32768, 0, 9, "triangle", 1, 0), ("fp8", 100, 2600, 32768, 0, 7, "full", 1, 0),
-    ("fp6", 2010, 1900, 32768, 0, 7, "triangle", 0, 0), ("fp6", 640, 640, 32768, 0, 9, "triangle", 1, 0),
+    ("fp8", 2010, 1900, 32768, 0, 7, "triangle", 0, 0), ("fp8", 900, 120, 32768, 0, 11, "triangle", 1, 0), ("fp8", 100, 2600, 32768, 0, 7, "full", 1, 0),
+    ("fp6", 2010, 1900, 32768, 0, 7, "triangle", 0, 0), ("fp6", 900, 120, 32768, 0, 11, "triangle", 1, 0),
     ("fp6_e3m2", 3000, 384, 65536, 0, 11, "full", 0, 0), ("fp6_e3m2", 100, 2600, 131072, 0, 7, "full", 1, 0),
 ]
 
