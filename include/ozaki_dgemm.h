@@ -304,12 +304,13 @@ int ozaki_count_slices(int is_B, int64_t rows, int64_t k, const double* X, int64
  *   chained     0: every pair is multiplied on its own (the kernel's run formation is switched off).
  *               1: run formation on: where all elements of a 32 x 32 tile share the scale of consecutive pairs of an
  *               anti-diagonal, the matrix unit keeps accumulating and ONE slot receives the exact sum of the run.
- *               Runs hold at most floor(window / (k_block 4^b)) pairs (at least one), whose sum is inside the exact
- *               window (2^24; INT8: 2^31 - 1) whatever the data.
- *               2: the launch configuration of ozaki_dgemm with OZAKI_SUM_RUNS in this workspace.  It can differ from 1
- *               where that limit would cut the longest anti-diagonal into three runs or more (not for INT8): there the
- *               matrix unit sums on as long as the accumulators, together with a bound on every partial sum of the
- *               next pair, stay inside the window, so that the length of a run depends on the data.
+ *               Every anti-diagonal is cut into groups of floor(window / (k_block 4^b)) pairs (at least one), whose sum is
+ *               inside the exact window (2^24; INT8: 2^31 - 1) whatever the data; a run ends with its group.
+ *               2: the launch configuration of ozaki_dgemm with OZAKI_SUM_RUNS in this workspace.  Its groups are shorter
+ *               where that is faster, and longer where the limit of 1 would cut the longest anti-diagonal into three
+ *               groups or more (not for INT8): there the matrix unit sums on as long as the accumulators, together with
+ *               a bound on every partial sum of the next pair, stay inside the window, so that the length of a run
+ *               depends on the data.
  *   P_out       DEVICE: [T][pairs][n][m] 4-byte words: for block t and pair index z (pairs in accumulation order:
  *               anti-diagonals g = p+q from the largest down to 2, p ascending within one), an m x n column-major
  *               matrix (leading dimension m).  FP32 value sum_kk sliceA_p(i,kk) * sliceB_q(kk,j), the slices being

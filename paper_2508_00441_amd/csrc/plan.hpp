@@ -310,13 +310,15 @@ struct Route {
     int32_t* deltas_a;    // where the deltas would go
     int32_t* deltas_b;
 };
-// chained: the matrix unit may sum pairs; measured: also beyond the window's worst case.  False if the memory does not hold it.
-inline bool place_call(const Plan& plan, bool want_product, int sum_words, bool chained, bool measured, WorkMem wm, Route& r) {
+// chained: the matrix unit may sum pairs.  as_dgemm: as the DGEMM does, beyond the window's worst case where measured runs apply, in the
+// groups that take the least time; otherwise in the longest groups of the worst case.  False if the memory does not hold it.
+inline bool place_call(const Plan& plan, bool want_product, int sum_words, bool chained, bool as_dgemm, WorkMem wm, Route& r) {
     r.pl = plan;
     r.check = RunCheck{nullptr, nullptr, nullptr};
     if (!carve(plan, r.c, want_product, sum_words, wm)) return false;
-    if (chained && measured) r.check = place_run_check(r.pl, r.c);
+    if (chained && as_dgemm) r.check = place_run_check(r.pl, r.c);
     choose_gemm(r.pl, r.c.chunk_pairs, chained, r.check.starts != nullptr);               // of one pass: each is a launch of its own
+    if (chained && !as_dgemm) r.pl.group_len = r.pl.run_limit < r.pl.s ? r.pl.run_limit : r.pl.s;
     if (r.pl.group_len <= r.pl.run_limit) {                                               // no group passes the worst case: nothing to measure
         r.check = RunCheck{nullptr, nullptr, nullptr};
         r.c.A.l1 = r.c.B.l1 = r.c.A.bounds = r.c.B.bounds = nullptr;

@@ -106,3 +106,29 @@ def test_runs_beyond_the_worst_case(fmt, m, n, k, k_block, s, mode, small, from_
         assert covered.min() == 1 and covered.max() == 1, t                          # every pair in exactly one run
     assert longest > way.run_limit, (longest, way)
     assert 2 * cut >= window, (cut, window)                                          # sums that fill the window were there
+
+
+@pytest.mark.parametrize("fmt,m,n,k,s,mode", [("int8", 257, 100, 3000, 8, "full"), ("fp8", 130, 70, 8192, 12, "triangle"), ("fp16", 70, 130, 512, 5, "triangle")])
+def test_runs_of_the_worst_case_are_as_long_as_it_allows(fmt, m, n, k, s, mode):
+    """chained = 1: groups of as many pairs as surely fit the window, whatever groups the DGEMM would take."""
+    plan = oz.make_plan(k, fmt, 0)
+    limit = max(1, min(s, formats.EXACT_WINDOW[fmt] // (plan.k_block << (2 * plan.b))))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(k)
+    A, Bt = _vectors(m, k, plan.b, gen), _vectors(n, k, plan.b, gen)
+    Ad = A.T.contiguous()
+    pairs = oz.pair_order(s, mode)
+    for minimum in (False, True):
+        ws = device.Workspace.for_problem(m, n, k, lib.SLICE_FORMATS[fmt], s, 0, pair_set=lib.PAIR_SETS[mode], minimum=minimum)
+        P = torch.empty((1, len(pairs), n, m), dtype=torch.float32, device="cuda")
+        L = torch.full((1, len(pairs), n, m), 99, dtype=torch.uint8, device="cuda")
+        lib.ozaki_pair_products(m, n, k, Ad, m, Bt, k, lib.SLICE_FORMATS[fmt], s, 0, P, pair_set=lib.PAIR_SETS[mode], chained=1, run_len_out=L)
+        assert lib.ozaki_last_device_status() == 0
+        ws.close()
+        regular = L[0, :, : n // 2 // 32 * 32, : m // 2 // 32 * 32].amax(dim=(1, 2)).cpu().numpy()
+        for z, (p, q) in enumerate(pairs):
+            first = p - max(1, p + q - s)                      # position in the anti-diagonal
+            left = min(s, p + q - 1) - p + 1                   # pairs from here to its end
+            if first % limit == 0:
+                assert 1 <= regular[z] <= min(limit, left), (z, p, q)
+        assert regular.max() == limit, (regular.max(), limit)
