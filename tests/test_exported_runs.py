@@ -14,7 +14,7 @@ import planner  # noqa: E402
 from oracle import formats  # noqa: E402
 from oracle import ozaki_oracle as oz  # noqa: E402
 from paper_2508_00441_amd import binding as lib, device  # noqa: E402
-from test_gpu_parity import _as_device_words  # noqa: E402
+from test_gpu_parity import _as_device_words, _recipe  # noqa: E402
 
 
 def _vectors(count, k, b, gen):
@@ -32,6 +32,35 @@ def _sample(count, rng):
     half = count // 2
     fixed = [0, min(31, half - 1), half - 1, half, count - 1]
     return np.unique(fixed + list(rng.integers(0, half, 9)) + list(rng.integers(half, count, 9)))
+
+
+def check_export(Pn, Ln, Ah, Bh, fmt, s, k_block, mode, counted):
+    """Words and run lengths [T][pairs][n][m] of the columns of Bh and the rows of Ah: every run joins consecutive pairs of one
+    anti-diagonal and equal scale, its word is the exact sum, no partial sum leaves the window, every pair is in one run.
+    Returns the longest run among the entries `counted` and the largest sum."""
+    plan = oz.make_plan(Ah.shape[1], fmt, k_block)
+    pairs, window = oz.pair_order(s, mode), formats.EXACT_WINDOW[fmt]
+    _, blocks = oz.ozaki_dgemm(Ah, Bh, fmt, s, k_block, mode=mode, return_blocks=True)
+    longest = largest = 0
+    for t, br in enumerate(blocks):
+        covered = np.zeros(Ln.shape[1:], dtype=np.int64)
+        for z, (p, q) in enumerate(pairs):
+            run = Ln[t, z]
+            longest = max(longest, int(run[counted].max()))
+            scale = br.c_a[p - 1][None, :] + br.c_b[q - 1][:, None]
+            total = np.zeros(run.shape, dtype=np.int64)
+            for j in range(int(run.max())):
+                inside = run > j
+                pj, qj = pairs[z + j]
+                assert (pj, qj) == (p + j, q - j), (t, z, j)
+                assert np.array_equal((br.c_a[pj - 1][None, :] + br.c_b[qj - 1][:, None])[inside], scale[inside]), (t, z, j)
+                total += np.where(inside, br.products[z + j].T, 0)
+                assert np.abs(total).max() <= window, (t, z, j)
+                covered[z + j] += inside
+            largest = max(largest, int(np.abs(total).max()))
+            assert np.array_equal(Pn[t, z], _as_device_words(total.T, fmt, plan.b)), (t, z)
+        assert covered.min() == 1 and covered.max() == 1, t
+    return longest, largest
 
 
 # format, m, n, k, k_block, s, mode, 128 x 128 blocks?, bounds from the slices?
@@ -80,32 +109,10 @@ def test_runs_beyond_the_worst_case(fmt, m, n, k, k_block, s, mode, small, from_
     for accum, rule in (("hw", "runs"), ("exact", "exact")):
         want = oz.ozaki_dgemm(Ah, Bh, fmt, s, k_block, mode=mode, accumulate=rule)
         assert np.array_equal(np.ascontiguousarray(C[accum]).view(np.uint64), want.view(np.uint64)), accum
-    _, blocks = oz.ozaki_dgemm(Ah, Bh, fmt, s, k_block, mode=mode, return_blocks=True)
-    window = formats.EXACT_WINDOW[fmt]
     regular = np.outer(cols < n // 2 // 32 * 32, rows < m // 2 // 32 * 32)            # 32 x 32 tiles of regular vectors only
-    longest = cut = 0
-    for t, br in enumerate(blocks):
-        covered = np.zeros((len(pairs), len(cols), len(rows)), dtype=np.int64)
-        for z, (p, q) in enumerate(pairs):
-            run = Ln[t, z]
-            longest = max(longest, int(run[regular].max()))
-            scale = br.c_a[p - 1][None, :] + br.c_b[q - 1][:, None]
-            total = np.zeros(run.shape, dtype=np.int64)
-            for j in range(int(run.max())):
-                inside = run > j
-                pj, qj = pairs[z + j]
-                assert (pj, qj) == (p + j, q - j), (t, z, j)                         # one anti-diagonal, consecutive
-                assert np.array_equal((br.c_a[pj - 1][None, :] + br.c_b[qj - 1][:, None])[inside], scale[inside]), (t, z, j)
-                total += np.where(inside, br.products[z + j].T, 0)
-                assert np.abs(total).max() <= window, (t, z, j)
-                covered[z + j] += inside
-            assert np.array_equal(Pn[t, z], _as_device_words(total.T, fmt, plan.b)), (t, z)
-            # the run ends although the scale goes on: the window was full, or the group ended
-            if z + int(run.max()) < len(pairs):
-                cut = max(cut, int(np.abs(total).max()))
-        assert covered.min() == 1 and covered.max() == 1, t                          # every pair in exactly one run
+    longest, largest = check_export(Pn, Ln, Ah, Bh, fmt, s, k_block, mode, regular)
     assert longest > way.run_limit, (longest, way)
-    assert 2 * cut >= window, (cut, window)                                          # sums that fill the window were there
+    assert 2 * largest >= formats.EXACT_WINDOW[fmt], largest                         # sums that fill the window were there
 
 
 @pytest.mark.parametrize("fmt,m,n,k,s,mode", [("int8", 257, 100, 3000, 8, "full"), ("fp8", 130, 70, 8192, 12, "triangle"), ("fp16", 70, 130, 512, 5, "triangle")])
@@ -132,3 +139,24 @@ def test_runs_of_the_worst_case_are_as_long_as_it_allows(fmt, m, n, k, s, mode):
             if first % limit == 0:
                 assert 1 <= regular[z] <= min(limit, left), (z, p, q)
         assert regular.max() == limit, (regular.max(), limit)
+
+
+@pytest.mark.parametrize("fmt,m,n,k,k_block,s,mode,recipe", [
+    ("fp8", 300, 270, 520, 0, 8, "triangle", "phi4"), ("fp8", 130, 100, 200, 0, 12, "full", "binade"), ("fp6", 257, 130, 1000, 384, 9, "full", "u110"),
+    ("fp6_e3m2", 130, 300, 64, 0, 14, "triangle", "binade"), ("int8", 130, 257, 300, 0, 8, "full", "binade"), ("fp16", 260, 130, 700, 256, 5, "triangle", "u110")])
+def test_groups_of_the_dgemm(fmt, m, n, k, k_block, s, mode, recipe):
+    """chained = 2 on few tiles: links that the 128 x 128 kernel forms from the exponents, irregular vectors among regular ones, one
+    pass and several."""
+    A, B = _recipe(recipe, m, n, k, seed=m + 2 * n + k)
+    Ad, Bd = device.to_device_colmajor(A), device.to_device_colmajor(B)
+    fid, ps = lib.SLICE_FORMATS[fmt], lib.PAIR_SETS[mode]
+    shape = (oz.make_plan(k, fmt, k_block).num_blocks, len(oz.pair_order(s, mode)), n, m)
+    for minimum in (False, True):
+        assert planner.route(m, n, k, fmt, s, k_block, mode, minimum=minimum).small
+        ws = device.Workspace.for_problem(m, n, k, fid, s, k_block, pair_set=ps, minimum=minimum)
+        P = torch.full(shape, -77, dtype=torch.int32 if fmt == "int8" else torch.float32, device="cuda")
+        L = torch.full(shape, 99, dtype=torch.uint8, device="cuda")
+        lib.ozaki_pair_products(m, n, k, Ad, m, Bd, k, fid, s, k_block, P, pair_set=ps, chained=2, run_len_out=L)
+        assert lib.ozaki_last_device_status() == 0
+        ws.close()
+        check_export(P.cpu().numpy(), L.cpu().numpy().astype(np.int64), A, B, fmt, s, k_block, mode, np.ones((n, m), dtype=bool))
