@@ -240,6 +240,8 @@ inline double plain_panels(int64_t blocks_m, int64_t blocks_n) {
 //   - 128 x 128 blocks from 2 rounds on, 256 x 256 blocks from 2.5; where a group has a multiple of eight blocks, so that the plain
 //     order keeps a block on its XCD from group to group, from 2.5 and 4 (8 x 8 blocks of 256 x 256, 32 FP16 stages, 3.25
 //     rounds: strips 6 % slower);
+//   - results of one row or column of blocks, where strips too fetch a panel and more: from 3 (128 x 128 blocks, pairs of 32 stages and more: 2), a multiple of eight blocks 6 (1.1 to 1.25
+//     of the plain time before; 56 x 1 blocks of 128 x 128, groups of nine pairs, 2.6 rounds: 178 us plain, 226 in strips);
 //   - pairs of fewer than eight stages, which are bound by their stores, from 4 (0.95 to 1.05 below);
 //   - 128 x 128 blocks, pairs of 16 stages and more, where strips fetch less than a panel and the plain order 1.5 or more: from 0.6
 //     in groups of equal length (0.85 of the longest on average), from 0.75 at 0.7 (0.76 to 0.89 of the plain time on average, 1.1
@@ -254,10 +256,11 @@ inline WorkOrder work_order(int64_t pairs, int64_t groups, int len, int per_xcd,
     const int64_t blocks = blocks_m * blocks_n;
     const double rounds = (double)(groups * blocks) / (8 * per_xcd);
     const bool small = per_xcd == 64, keeps_xcd = blocks % 8 == 0;
+    const double in_strips = strip_panels(blocks_m, blocks_n, strips), in_plain = plain_panels(blocks_m, blocks_n);
     double least = small ? (keeps_xcd ? 2.5 : 2.0) : (keeps_xcd ? 4.0 : 2.5);
-    if (chunks < 8) least = 4.0;
+    if (in_strips >= 1.0) least = keeps_xcd ? 6.0 : small && chunks >= 32 ? 2.0 : 3.0;
+    if (chunks < 8 && least < 4.0) least = 4.0;
     if (small && !keeps_xcd && chunks >= 16 && 10 * pairs >= 7 * len * groups) {
-        const double in_strips = strip_panels(blocks_m, blocks_n, strips), in_plain = plain_panels(blocks_m, blocks_n);
         if (in_strips < 1.0 && in_plain >= 1.5) least = 20 * pairs >= 17 * len * groups ? 0.6 : 0.75;
         if (in_strips < 0.6 && in_plain >= 1.9 && rounds <= 0.5) least = 0.35;
     }
