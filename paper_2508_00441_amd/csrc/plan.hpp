@@ -68,7 +68,7 @@ inline StageTimes stage_times(int fmt) {
 //     for the uneven end (not for 256 x 256 blocks in the plain order, longest first over all XCDs);
 //   - filling the load ring and storing, per round; the products stored and read again.
 // Measured on 720 random problems of fewer than 256 tiles, all formats, every block size and length, the constants fitted to two
-// thirds of them: the choice takes 1.020 of the best one's time on average (1.029 on the other third), 1.23 at worst, on 70 more
+// thirds of them: the choice takes 1.020 of the best one's time on average (1.029 on the other third), 1.27 at worst, on 70 more
 // with inner dimensions of 8192 to 65536 1.05 and 1.39; the estimate before it (FP8's times for every format, no panels, group
 // lengths of two and more and not all of them) 1.082 and 1.94.  From 256 tiles on long groups of the large blocks are always the choice.
 inline double pass_time(const Plan& pl, const StageTimes& us, bool small, int len, const Pass& ps, bool chained) {
