@@ -8,23 +8,21 @@
 // Eq. 5-6 obtain q through (x + sigma) - sigma with sigma = 0.75 * 2^(rho+c) in FP64: x + sigma lies in the
 // binade whose unit in the last place is 2^(rho+c-53) = 2^(c-b), sigma is an even multiple of that unit,
 // so the FP64 addition rounds x to the nearest multiple of 2^(c-b) with ties to even q, and the
-// subtraction of sigma is exact.  The kernel computes the same q with integers: once an element is within
-// reach of the current unit it is kept as the signed 64-bit fixed-point number x^(p) / 2^(c-b) with 60-b
-// fraction bits, which holds the element and every later remainder exactly (|x^(p)| <= 2^c bounds it by 2^60);
-// q is its rounding to an integer, the remainder is what is left, and moving to the next slice is a left shift
-// by c_p - c_(p+1).  Until then the element waits with its significand and exponent: with b <= 7 it is then smaller
-// than half the unit (q = 0); with wider slices it can already reach the unit, and is rounded in its integer form.
-// No FP64 instruction is executed.  Two forms of this element step: slices of at most 7 bits (FP8, FP6, INT8, and FP16 in
-// blocks of 1024 elements and more) work on the upper 32-bit word of the fixed-point number (slice_element.hpp); wider FP16
-// slices, whose fixed-point form has fewer than 53 fraction bits, take the 64-bit step below (decode_element,
-// slice_element).  4096 + 4096 vectors of 4096 elements, nine FP16 slices of 6 bits: 0.33 ms with the 64-bit step, 0.24 ms with the 32-bit one.
-//
-// A vector is held in the registers of TPR threads (8*U consecutive elements per thread in U groups of
-// eight) for all s slices, so HBM sees each input element once and each slice code once.
+// subtraction of sigma is exact.  The kernels compute the same q with integers; no FP64 instruction is executed.
+//   * Slices of at most 7 bits (FP8, FP6, INT8, FP16 in blocks of more than 256 elements): all slices of an element are read off one
+//     96-bit fixed-point number as long as the units follow the regular ladder (slice_digits.hpp, slice_vectors); blocks beyond
+//     16384 elements in two kernels (long_exponents_kernel, split_stream_kernel), the second of which carries the remainders from
+//     slice to slice where the units are off the ladder (slice_element.hpp).
+//   * Wider FP16 slices: slice by slice, once an element is within reach of the current unit as the signed 64-bit number
+//     x^(p) / 2^(c-b) with 60-b fraction bits, until then as its significand and exponent (decode_element, slice_element).
+// HBM sees each input element once (long blocks: two or three times) and each slice code once.
 #include <string.h>
 
 #include "layout.hpp"
+#include "slice_digits.hpp"
 #include "slice_element.hpp"
+
+#include <type_traits>
 
 namespace ozaki {
 
@@ -69,45 +67,12 @@ struct SplitArgs {
     int64_t k, kb;
     int64_t chunks;        // chunks per block
     int s, b;
+    DigitLadder ladder;    // of b
     int* flags;            // [0]: non-finite input seen; [1]: slice count (count-only mode)
 };
 
 constexpr int NO_ELEM = -(1 << 30);
 static_assert(NO_ELEM == NO_CANDIDATE, "the two slicers share the reduction");
-
-// Type2 codes of the two values q0 * 2^-b and q1 * 2^-b (|q| <= 2^b), packed low/high.  The hardware FP32 -> FP8
-// (OCP E4M3 on gfx950) and FP32 -> FP16 conversions are exact here because every such value is a normal number of
-// the format; FP32 arithmetic is not FP64 arithmetic, so the integer-only property of the slicer is about FP64.
-template <int FMT>
-__device__ __forceinline__ uint32_t encode_type2_pair(int q0, int q1, int b) {
-    if (FMT == FMT_INT8) return ((uint32_t)q0 & 0xFFu) | (((uint32_t)q1 & 0xFFu) << 8);     // the integers themselves, |q| <= 64
-    const float f0 = ldexpf((float)q0, -b), f1 = ldexpf((float)q1, -b);
-    if (FMT == FMT_FP16) {
-        typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-        const h2 h = {(_Float16)f0, (_Float16)f1};
-        return __builtin_bit_cast(uint32_t, h);                       // q = 0 gives +0.0, code 0
-    } else {
-        const uint32_t w = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(f0, f1, 0, false) & 0xFFFFu;
-        return w;
-    }
-}
-
-// FP6 E2M3 code of q * 2^-(b-1), twice the slice value (|q| <= 2^b, b <= 4): with q' = q * 2^(4-b) the value is q'/8,
-// and for magnitudes 0..16 the code (subnormals 0..7, normals 8..15 with exponent field 1, 16 = 2.0) is the magnitude
-// itself; bit 5 is the sign.
-__device__ __forceinline__ uint32_t encode_e2m3(int q, int b) {
-    const int v = q << (4 - b);
-    const uint32_t mag = (uint32_t)(v < 0 ? -v : v);
-    return mag | (v < 0 ? 32u : 0u);
-}
-
-// FP6 E3M2 code of q * 2^-b (|q| <= 2^b, b <= 3): with q' = q * 2^(3-b) the value is q'/8; the codes (exponent field
-// << 2 | fraction) of the magnitudes 0 .. 8 are 0 (zero), 2 (subnormal 2/16), 4, 6, 8, 9, 10, 11, 12; bit 5 is the sign.
-__device__ __forceinline__ uint32_t encode_e3m2(int q, int b) {
-    const int v = q << (3 - b);
-    const uint32_t mag = (uint32_t)(v < 0 ? -v : v);
-    return (uint32_t)((0xCBA986420ull >> (4 * mag)) & 0xFull) | (v < 0 ? 32u : 0u);
-}
 
 constexpr int ACTIVE = 0x7FFF;
 
@@ -180,55 +145,19 @@ __device__ __forceinline__ int slice_element(int64_t& tv, int& pk, int unit, int
     return q;
 }
 
-// Stores the Type2 codes of eight consecutive inner indices ke .. ke+7 of vector `row` into slice matrix dst_slice
-// (internal layout, see layout.hpp).
-template <int FMT>
-__device__ __forceinline__ void store_codes(const int (&qs)[8], int64_t ke, uint8_t* dst_slice, int64_t v_rows_pad, int64_t row, int b) {
-    constexpr bool FP16 = FMT == FMT_FP16;
-    constexpr bool FP6 = fmt_is_fp6(FMT);
-    constexpr int EPC = FP16 ? CHUNK_BYTES / 2 : CHUNK_BYTES;
-    constexpr int ROWB = FP6 ? CHUNK_BYTES_FP6 : CHUNK_BYTES;
-    if constexpr (FP6) {
-        // eight 6-bit codes = 48 bits: octet j of the 24-byte string of k-group g, i.e. bytes
-        // 6j .. 6j+5 of the string, whose first 16 bytes live in the 16-byte plane of g and the rest in the
-        // 8-byte plane (see layout.hpp).  Written as one 32-bit and one 16-bit store, both naturally aligned.
-        uint64_t w48 = 0;
+// FP16 codes of the eight slice values qs[e] * 2^-b of consecutive inner indices ke .. ke+7 of vector `row`.  The hardware FP32 ->
+// FP16 and FP32 -> FP8 (OCP E4M3 on gfx950) conversions are exact in this file because every slice value is a normal number of its
+// format, or zero (code 0); FP32 arithmetic is not FP64 arithmetic, so the integer-only property of the slicer is about FP64.
+__device__ __forceinline__ void store_wide_codes(const int (&qs)[8], int64_t ke, uint8_t* dst_slice, int64_t v_rows_pad, int64_t row, int b) {
+    constexpr int EPC = CHUNK_BYTES / 2;
+    uint32_t w[4];
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
-            w48 |= (uint64_t)(FMT == FMT_FP6_E3M2 ? encode_e3m2(qs[e], b) : encode_e2m3(qs[e], b)) << (6 * e);
-        const int64_t kc = ke / EPC;
-        const int o = (int)((ke % EPC) / 8), g = o >> 2, j = o & 3;
-        uint8_t* const chunk = dst_slice + (size_t)kc * v_rows_pad * ROWB;
-        uint8_t* const p16 = chunk + ((size_t)g * v_rows_pad + row) * 16;
-        uint8_t* const p8 = chunk + (size_t)v_rows_pad * 32 + ((size_t)g * v_rows_pad + row) * 8;
-        uint8_t* d32 = j == 0 ? p16 : j == 1 ? p16 + 8 : j == 2 ? p16 + 12 : p8 + 4;
-        uint8_t* d16 = j == 0 ? p16 + 4 : j == 1 ? p16 + 6 : j == 2 ? p8 : p8 + 2;
-        const bool low32 = (j & 1) == 0;                   // bytes 6j.. start 4-byte aligned for even j
-        *reinterpret_cast<uint32_t*>(d32) = low32 ? (uint32_t)w48 : (uint32_t)(w48 >> 16);
-        *reinterpret_cast<uint16_t*>(d16) = low32 ? (uint16_t)(w48 >> 32) : (uint16_t)w48;
-    } else {
-        uint32_t c2[4];                                            // two codes each
-#pragma unroll
-        for (int e = 0; e < 4; ++e) c2[e] = encode_type2_pair<FMT>(qs[2 * e], qs[2 * e + 1], b);
-        const int64_t kc = ke / EPC;
-        uint8_t* dst = dst_slice + ((size_t)kc * v_rows_pad + row) * CHUNK_BYTES + (ke % EPC) * (FP16 ? 2 : 1);
-        if (FP16) {
-            uint4 w;
-            w.x = c2[0];
-            w.y = c2[1];
-            w.z = c2[2];
-            w.w = c2[3];
-            *reinterpret_cast<uint4*>(dst) = w;
-        } else {
-            uint2 w;
-            w.x = c2[0] | (c2[1] << 16);
-            w.y = c2[2] | (c2[3] << 16);
-            *reinterpret_cast<uint2*>(dst) = w;
-        }
-    }
+    for (int h = 0; h < 4; ++h)
+        w[h] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(ldexpf((float)qs[2 * h], -b), ldexpf((float)qs[2 * h + 1], -b)));
+    *reinterpret_cast<uint4*>(dst_slice + ((size_t)(ke / EPC) * v_rows_pad + row) * CHUNK_BYTES + (ke % EPC) * 2) = uint4{w[0], w[1], w[2], w[3]};
 }
 
-// The same for FP8 codes of the eight values qs[e] / scale (integers times a power of two, scale a power of two): the
+// FP8 codes of the eight values qs[e] / scale (integers times a power of two, scale a power of two): the
 // scaled FP32 -> FP8 pair conversion of gfx950 divides by the scale, so the slice integer is converted from where it
 // sits in the slicer's upper word, without a shift or a separate scaling.  Exact for the same reason as above.
 __device__ __forceinline__ void store_fp8_codes_scaled(const int (&qs)[8], float scale, int64_t ke, uint8_t* dst_slice, int64_t v_rows_pad,
@@ -337,6 +266,18 @@ __device__ __forceinline__ V wave_max(V v) {
     return (V)__builtin_amdgcn_readlane((int)v, 63);
 }
 
+// The bitwise OR, in the same steps
+__device__ __forceinline__ uint32_t wave_or(uint32_t v) {
+    auto step = [](uint32_t x, int y) { return x | (uint32_t)y; };
+    v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0xB1, 0xF, 0xF, false));
+    v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x4E, 0xF, 0xF, false));
+    v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x141, 0xF, 0xF, false));
+    v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x140, 0xF, 0xF, false));
+    v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x142, 0xA, 0xF, false));
+    v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x143, 0xC, 0xF, false));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
 // The sum, in lane 63: the same steps; a row that a step leaves out adds zero.
 __device__ __forceinline__ int wave_sum(int v) {
     v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false);
@@ -348,265 +289,44 @@ __device__ __forceinline__ int wave_sum(int v) {
     return __builtin_amdgcn_readlane(v, 63);
 }
 
-// (At least four waves per SIMD, i.e. at most 128 registers: two 512-thread workgroups per CU, so that one computes while
-// the other waits at its barrier.)
-// A vector rarely fills its threads: a wave without elements in its second octet leaves that half of the work out, and with
-// one octet per thread (U = 1, TPR = 256) the launch has only the waves that hold elements (4096 + 4096 vectors of 4097
-// elements, nine FP8 slices: 0.40 ms with every octet worked on, 0.35 ms so; 0.36 ms with fewer waves per workgroup there too,
-// whose number should stay a multiple of the four SIMDs).
-template <int U, int TPR, int FMT>
-__global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu_waves_per_eu(4))) split_kernel(SplitArgs a) {
-    constexpr bool FP16 = FMT == FMT_FP16;
-    constexpr bool FP6 = fmt_is_fp6(FMT);
-    constexpr int BLOCK = TPR < 256 ? 256 : TPR;
-    constexpr int RPB = BLOCK / TPR;                  // vectors per workgroup
-    constexpr int EPC = FP16 ? CHUNK_BYTES / 2 : CHUNK_BYTES;   // elements per chunk
-    constexpr int ROWB = FP6 ? CHUNK_BYTES_FP6 : CHUNK_BYTES;   // bytes per vector and chunk
-    constexpr bool WHOLE = RPB == 1;                  // the workgroup is one vector, of blockDim.x <= TPR threads
-    constexpr int MAX_WAVES = TPR / 64;
-    __shared__ int red[2][BLOCK / 64];
-
-    const int tr = WHOLE ? threadIdx.x : threadIdx.x % TPR;
-    const int threads = WHOLE ? blockDim.x : TPR;     // per vector
-    // Workgroups are handed to the eight XCDs (each with an L2 of its own) round-robin by their index.  Neighbouring
-    // vectors share the cache lines of the slice layout (a line holds the 16-byte pieces of eight vectors in the
-    // FP6 planes, the 64-byte chunks of two vectors otherwise), so eight consecutive workgroups' worth of vectors go to the
-    // SAME XCD, where the partial lines meet in one L2 before they are written back; the next eight go to the next XCD, so that
-    // also an operand of few vectors is spread over all of them.  Each operand's share of the grid is a multiple of 64.
-    const bool second = blockIdx.x >= a.wg_first;                    // which operand this workgroup works on
-    const double* const vX = second ? a.v[1].X : a.v[0].X;
-    const int64_t v_ldv = second ? a.v[1].ldv : a.v[0].ldv, es = second ? a.v[1].es : a.v[0].es;
-    const int64_t v_rows = second ? a.v[1].rows : a.v[0].rows, v_rows_pad = second ? a.v[1].rows_pad : a.v[0].rows_pad;
-    uint8_t* const v_slices = second ? a.v[1].slices : a.v[0].slices;
-    int32_t* const v_exps = second ? a.v[1].exps : a.v[0].exps;
-    int32_t* const v_l1 = second ? a.v[1].l1 : a.v[0].l1;
-    const unsigned li = blockIdx.x - (second ? a.wg_first : 0u);     // index inside the operand's part of the grid
-    const int64_t wg = (li & ~63u) + (li & 7) * 8 + ((li >> 3) & 7);
-    const int64_t row = wg * RPB + threadIdx.x / TPR;
-    const int64_t t = blockIdx.y;
-    const int64_t k0 = t * a.kb;
+// FP16 slices of more than 7 bits (blocks of at most 256 elements): a wave per vector, eight elements per lane, the 64-bit element
+// step (see decode_element).
+__global__ void __launch_bounds__(256) slice_wide_kernel(SplitArgs a) {
+    constexpr int EPC = CHUNK_BYTES / 2;
+    const int lane = threadIdx.x & 63;
+    const bool second = blockIdx.x >= a.wg_first;
+    const SplitVectors& v = second ? a.v[1] : a.v[0];
+    const unsigned li = blockIdx.x - (second ? a.wg_first : 0u);     // dealt to the XCDs as in slice_vectors
+    const int64_t row = (int64_t)((li & ~63u) + (li & 7) * 8 + ((li >> 3) & 7)) * 4 + (threadIdx.x >> 6);
+    const int64_t t = blockIdx.y, k0 = t * a.kb, padded = a.chunks * EPC;
     int64_t klen = a.k - k0;
     if (klen > a.kb) klen = a.kb;
-    if (row >= v_rows) klen = 0;                      // padding vectors are all zero
-    const int64_t padded = a.chunks * EPC;
-    if (wg * RPB >= v_rows) {                         // padding vectors only: zero codes and c = 0 in every slice
-        if (v_slices == nullptr) return;
-        const int zero8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        for (int p = 0; p < a.s; ++p) {
-            uint8_t* const dst = v_slices + (size_t)((t * a.s + p) * a.chunks) * (size_t)v_rows_pad * ROWB;
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int64_t ke = 8 * ((int64_t)tr + (int64_t)threads * u);
-                if (ke < padded) store_codes<FMT>(zero8, ke, dst, v_rows_pad, row, a.b);
-            }
-            if (tr == 0) v_exps[(t * a.s + p) * v_rows_pad + row] = 0;
-            if (tr == 0 && v_l1 != nullptr) v_l1[(t * a.s + p) * v_rows_pad + row] = 0;
-        }
-        return;
-    }
-    if (WHOLE && MAX_WAVES > 1) {
-        if (threadIdx.x < 2 * MAX_WAVES) red[threadIdx.x / MAX_WAVES][threadIdx.x % MAX_WAVES] = NO_ELEM;
-        __syncthreads();
-    }
-    // Fixed-point scale of the working representation: an active element holds T = x^(p) / 2^(c_p - b) * 2^F as a
-    // signed 64-bit integer.  |x^(p)| <= 2^(c_p) bounds |T| by 2^(b+F) = 2^60.
-    const int F = 60 - a.b;
-
+    if (row >= v.rows) klen = 0;                                     // padding vectors are all zero
+    const int F = 60 - a.b, ke = 8 * lane;
+    const double* const src = v.X + row * v.ldv + k0 * v.es;
     bool nonfinite = false;
     int cmax = NO_ELEM;
-    const double* src = vX + row * v_ldv + k0 * es;
-    // the eight FP64 bit patterns of octet u of this thread (zeros beyond the block)
-    auto load_octet = [&](int u, uint64_t (&bits)[8]) {
-        const int64_t ke = 8 * ((int64_t)tr + (int64_t)threads * u);
-        if (es == 1 && ke + 8 <= klen) {
+    int64_t tv[8];
+    int pk[8];
+    uint64_t bits[8];
+    if (v.es == 1 && ke + 8 <= klen) {
 #pragma unroll
-            for (int h = 0; h < 4; ++h) {
-                const two_doubles w = *reinterpret_cast<const two_doubles*>(src + ke + 2 * h);
-                bits[2 * h] = w.x;
-                bits[2 * h + 1] = w.y;
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) bits[e] = (ke + e < klen) ? __double_as_longlong(src[(ke + e) * es]) : 0ull;
+        for (int h = 0; h < 4; ++h) {
+            const two_doubles w = *reinterpret_cast<const two_doubles*>(src + ke + 2 * h);
+            bits[2 * h] = w.x;
+            bits[2 * h + 1] = w.y;
         }
-    };
-    // does this wave hold elements of the block in octet u?  (wave-uniform)
-    auto wave_has = [&](int u) -> bool {
-        return 8 * ((int64_t)__builtin_amdgcn_readfirstlane(tr & ~63) + (int64_t)threads * u) < padded;
-    };
-    // Eq. 4: c = max over the vector of ceil(log2 |x_i|); each thread contributes the maximum over its elements
-    // (from the decoded inputs for the first slice, from the remainders afterwards)
-    auto vector_max = [&](int val, int p) -> int {
-        static_assert(TPR >= 64, "a wave never holds parts of two vectors");
-        val = wave_max(val);
-        if (MAX_WAVES > 1) {
-            const int wave = threadIdx.x >> 6;
-            if ((threadIdx.x & 63) == 0) red[p & 1][wave] = val;
-            __syncthreads();
-            const int w0 = (wave / MAX_WAVES) * MAX_WAVES;
+    } else {
 #pragma unroll
-            for (int w = 0; w < MAX_WAVES; ++w) {                    // entries of waves that are not there never change
-                const int o = red[p & 1][w0 + w];
-                val = o > val ? o : val;
-            }
-        }
-        return val;
-    };
-
-    // FP16: sum |q| of the slices, if wanted.  A wave's share goes to LDS and is added up behind the barrier of the next exchange.
-    __shared__ int l1_share[2][BLOCK / 64];
-    auto share_l1 = [&](int p, int mine) {
-        const int share = wave_sum(mine);
-        if ((threadIdx.x & 63) == 0) l1_share[p & 1][threadIdx.x >> 6] = share;
-    };
-    auto store_l1 = [&](int p) {
-        if (tr != 0) return;
-        const int w0 = threadIdx.x >> 6;
-        int sum = 0;
-        for (int w = 0; w < threads / 64; ++w) sum += l1_share[p & 1][w0 + w];
-        v_l1[(t * a.s + p) * v_rows_pad + row] = sum;
-    };
-
-    if (!FP16 || a.b <= 7) {
-        // ---- slices of at most 7 bits: the element step on 32-bit words (slice_element.hpp)
-        const int pos = F - 32, bias = (1 << (pos - 1)) - 1;
-        const uint32_t keep = ~((1u << pos) - 1u);
-        const float code_unit = ldexpf(1.0f, -(pos + a.b));            // q * 2^pos * code_unit = q * 2^-b, the slice value
-        const float code_scale = ldexpf(1.0f, pos + a.b);              // q * 2^pos / code_scale = q * 2^-b, the slice value
-        Fp6Slot slots[FP6 ? U : 1];                                    // FP6 only: where each octet's codes go inside a slice matrix
-        if constexpr (FP6) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) slots[u] = fp6_slot(8 * ((int64_t)tr + (int64_t)threads * u), v_rows_pad, row);
-        }
-        uint64_t T[8 * U];                                             // element state, see slice_element.hpp
-        int pk[8 * U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            uint64_t bits[8];
-            load_octet(u, bits);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) decode_narrow(bits[e], F, T[8 * u + e], pk[8 * u + e], cmax, nonfinite);
-        }
-        if (nonfinite) atomicOr(a.flags, 1);
-        int unit_prev = 0, unit = 0, c = 0, step = 0;
-        uint8_t* dst_slice = nullptr;
-        int kmax, kmin;
-        uint32_t cd_wait;
-        float l1 = 0.0f;                                               // FP16: sum |q| 2^-b of this thread's elements, exact
-        // head of slice p: Eq. 4, the unit 2^(c-b) and the distance from the previous unit
-        auto begin_slice = [&](int p) {
-            cmax = vector_max(cmax, p);
-            // count-only mode (slicing until the remainder is zero, paragraph before Eq. 4): something is left before
-            // the (p+1)-th slice, so this vector needs at least p + 1 of them
-            if (v_slices == nullptr && cmax != NO_ELEM && tr == 0) atomicMax(a.flags + 1, p + 1);
-            c = (cmax == NO_ELEM) ? 0 : cmax;
-            unit = c - a.b;
-            step = unit_prev - unit;
-            unit_prev = unit;
-            dst_slice = v_slices + (size_t)((t * a.s + p) * a.chunks) * (size_t)v_rows_pad * ROWB;
-            kmax = KEY_NONE_MAX;
-            kmin = KEY_NONE_MIN;
-            cd_wait = 0;
-            if constexpr (FP16) {
-                if (v_l1 != nullptr && p > 0) store_l1(p - 1);
-                l1 = 0.0f;
-            }
-        };
-        auto store_octet = [&](int u, int (&qs)[8]) {                   // qs: q * 2^pos
-            const int64_t ke = 8 * ((int64_t)tr + (int64_t)threads * u);
-            if constexpr (FMT == FMT_FP8) {
-                if (ke < padded && v_slices != nullptr) store_fp8_codes_scaled(qs, code_scale, ke, dst_slice, v_rows_pad, row);
-            } else if constexpr (FP16) {
-                float f[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    f[e] = (float)qs[e] * code_unit;
-                    l1 += fabsf(f[e]);
-                }
-                if (ke < padded && v_slices != nullptr) store_fp16_codes(f, ke, dst_slice, v_rows_pad, row);
-            } else if constexpr (FP6) {
-                if (ke < padded && v_slices != nullptr) store_fp6_codes_at_pos<FMT>(qs, pos, a.b, slots[u], dst_slice);
-            } else {
-                if (ke < padded && v_slices != nullptr) store_int8_codes_at_pos(qs, pos, ke, dst_slice, v_rows_pad, row);
-            }
-        };
-        // tail of slice p: the exponent goes out, the thread forms its candidate for the next one
-        auto end_slice = [&](int p, bool settled) {
-            if (tr == 0 && v_slices != nullptr) v_exps[(t * a.s + p) * v_rows_pad + row] = c;
-            if constexpr (FP16) {
-                if (v_l1 != nullptr) share_l1(p, (int)ldexpf(l1, a.b));
-            }
-            bool needs_exact;
-            cmax = narrow_candidate(kmax, kmin, unit, F, needs_exact);
-            if (needs_exact) {                                         // the upper words cannot tell: all 64 bits of the remainders
-                uint64_t mx = 0;
-#pragma unroll
-                for (int i = 0; i < 8 * U; ++i) {
-                    const uint64_t ar = (settled || pk[i] == 0) ? narrow_abs(T[i]) : 0ull;
-                    mx = ar > mx ? ar : mx;
-                }
-                cmax = narrow_candidate_exact(mx, unit, F);
-            }
-            const int cw = (int)cd_wait - CD_BIAS;
-            cmax = (cd_wait != 0 && cw > cmax) ? cw : cmax;
-        };
-        // first the slices during which some element of this wave still waits ...
-        int p = 0;
-        for (bool settled = false; p < a.s && !settled; ++p) {
-            begin_slice(p);
-            const int step16 = step * 65536;
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (u > 0 && !wave_has(u)) break;
-                int qs[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) qs[e] = slice_narrow(T[8 * u + e], pk[8 * u + e], step16, pos, bias, keep, kmax, kmin, cd_wait);
-                store_octet(u, qs);
-            }
-            settled = __ballot(cd_wait != 0) == 0ull;
-            end_slice(p, false);
-        }
-        // ... then the rest: every element is in fixed-point form, one shift for all, no control words
-        for (; p < a.s; ++p) {
-            begin_slice(p);
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (u > 0 && !wave_has(u)) break;
-                int qs[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) qs[e] = slice_narrow_active(T[8 * u + e], step, pos, bias, keep, kmax, kmin);
-                store_octet(u, qs);
-            }
-            end_slice(p, true);
-        }
-        if constexpr (FP16) {
-            if (v_l1 != nullptr) {
-                __syncthreads();
-                store_l1(a.s - 1);
-            }
-        }
-        return;
+        for (int e = 0; e < 8; ++e) bits[e] = (ke + e < klen) ? (uint64_t)__double_as_longlong(src[(ke + e) * v.es]) : 0ull;
     }
-
-    // ---- FP16 slices of more than 7 bits (blocks of fewer than 1024 elements): element state as described at decode_element
-    int64_t tv[8 * U];
-    int pk[8 * U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        uint64_t bits[8];
-        load_octet(u, bits);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) decode_element(bits[e], F, tv[8 * u + e], pk[8 * u + e], cmax, nonfinite);
-    }
+    for (int e = 0; e < 8; ++e) decode_element(bits[e], F, tv[e], pk[e], cmax, nonfinite);
     if (nonfinite) atomicOr(a.flags, 1);
-
     int c_prev = 0;
     for (int p = 0; p < a.s; ++p) {
-        cmax = vector_max(cmax, p);
-        if (v_l1 != nullptr && p > 0) store_l1(p - 1);
-        if (v_slices == nullptr) {
-            if (cmax != NO_ELEM && tr == 0) atomicMax(a.flags + 1, p + 1);      // count-only mode
-        }
+        cmax = wave_max(cmax);
+        if (v.slices == nullptr && cmax != NO_ELEM && lane == 0) atomicMax(a.flags + 1, p + 1);      // count-only mode
         const int c = (cmax == NO_ELEM) ? 0 : cmax;
         const int unit = c - a.b;                                      // the slice's unit is 2^(c-b)
         // remainders of active elements were left in units of the previous slice: rescale them to this one (a
@@ -614,26 +334,24 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
         int rescale = p == 0 ? 0 : c_prev - c;
         rescale = rescale < 0 ? 0 : (rescale > 63 ? 63 : rescale);
         c_prev = c;
-
-        // ---- Eq. 5-8 element by element, eight codes per store
-        uint8_t* const dst_slice = v_slices + (size_t)((t * a.s + p) * a.chunks) * (size_t)v_rows_pad * ROWB;
         uint64_t rmax = 0;                                             // largest |remainder| of this thread's active elements
         int cdorm = NO_ELEM;                                           // largest cd of its still dormant elements
-        int l1 = 0;
+        int l1 = 0, qs[8];
         const int64_t round_bias = ((int64_t)1 << (F - 1)) - 1;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (u > 0 && !wave_has(u)) break;
-            int qs[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) qs[e] = slice_element(tv[8 * u + e], pk[8 * u + e], unit, rescale, F, round_bias, rmax, cdorm);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) l1 += qs[e] < 0 ? -qs[e] : qs[e];
-            const int64_t ke = 8 * ((int64_t)tr + (int64_t)threads * u);
-            if (ke < padded && v_slices != nullptr) store_codes<FMT>(qs, ke, dst_slice, v_rows_pad, row, a.b);
+        for (int e = 0; e < 8; ++e) {
+            qs[e] = slice_element(tv[e], pk[e], unit, rescale, F, round_bias, rmax, cdorm);
+            l1 += qs[e] < 0 ? -qs[e] : qs[e];
         }
-        if (tr == 0 && v_slices != nullptr) v_exps[(t * a.s + p) * v_rows_pad + row] = c;
-        if (v_l1 != nullptr) share_l1(p, l1);
+        if (v.slices != nullptr) {
+            uint8_t* const dst_slice = v.slices + (size_t)((t * a.s + p) * a.chunks) * (size_t)v.rows_pad * CHUNK_BYTES;
+            if (ke < padded) store_wide_codes(qs, ke, dst_slice, v.rows_pad, row, a.b);
+            if (lane == 0) v.exps[(t * a.s + p) * v.rows_pad + row] = c;
+        }
+        if (v.l1 != nullptr) {
+            l1 = wave_sum(l1);
+            if (lane == 0) v.l1[(t * a.s + p) * v.rows_pad + row] = l1;
+        }
         // this thread's candidate for the next exponent: remainders are rmax * 2^(unit - F)
         cmax = cdorm;
         if (rmax != 0) {
@@ -641,179 +359,338 @@ __global__ void __launch_bounds__((TPR < 256 ? 256 : TPR)) __attribute__((amdgpu
             cmax = ca > cmax ? ca : cmax;
         }
     }
-    if (v_l1 != nullptr) {
-        __syncthreads();
-        store_l1(a.s - 1);
-    }
 }
 
-// Blocks of at most 256 elements, slices of at most 7 bits: a wave per vector, four elements per lane.  (With eight, half the
-// lanes of split_kernel are idle there and a thread's serial chain, which is what these launches take, is twice as long:
-// 256 + 256 vectors of 256 elements, 12 FP8 slices: 13.5 -> 10 us; 256 + 8192 of 256: 50 -> 30 us.)  The steps are those of split_kernel.
-template <int FMT>
-__global__ void __launch_bounds__(256) slice_short_kernel(SplitArgs a) {
-    constexpr bool FP6 = fmt_is_fp6(FMT);
-    constexpr int ROWB = FP6 ? CHUNK_BYTES_FP6 : CHUNK_BYTES;
-    const int lane = threadIdx.x & 63;
-    const bool second = blockIdx.x >= a.wg_first;
-    const SplitVectors& v = second ? a.v[1] : a.v[0];
-    const unsigned li = blockIdx.x - (second ? a.wg_first : 0u);     // dealt to the XCDs as in split_kernel
-    const int64_t row = ((int64_t)((li & ~63u) + (li & 7) * 8 + ((li >> 3) & 7))) * 4 + (threadIdx.x >> 6);
-    const int64_t t = blockIdx.y;
-    int64_t klen = a.k - t * a.kb;
-    if (klen > a.kb) klen = a.kb;
-    if (row >= v.rows) klen = 0;                                     // a padding vector: zero codes, c = 0
-    const int ke = 4 * lane;
-    const bool stores = ke < a.chunks * CHUNK_BYTES;
-    const int F = 60 - a.b, pos = F - 32, bias = (1 << (pos - 1)) - 1;
-    const uint32_t keep = ~((1u << pos) - 1u);
-    const float code_scale = ldexpf(1.0f, pos + a.b);
-    const double* const src = v.X + row * v.ldv + t * a.kb * v.es;
-    uint64_t bits[4];
-    if (v.es == 1 && ke + 4 <= klen) {
+// Type2 codes of G consecutive slice integers (G = 8, or 4 in blocks of at most 256 elements), stored where the layout wants them.
+// scale: 2^b, code_unit: 2^-b.  at: byte offset of the codes inside a slice matrix, slot the same for FP6 (an even lane of a pair
+// with G = 4 stores its own four codes and its neighbour's).
+template <int FMT, int G>
+__device__ __forceinline__ void store_slice_codes(const int (&q)[G], bool stores, int b, float scale, float code_unit, uint8_t* dst_slice, size_t at,
+                                                  const Fp6Slot& slot) {
+    if constexpr (fmt_is_fp6(FMT)) {
+        constexpr int K = FMT == FMT_FP6_E3M2 ? 3 : 4;
+        uint32_t c[G];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const two_doubles w = *reinterpret_cast<const two_doubles*>(src + ke + 2 * h);
-            bits[2 * h] = w.x;
-            bits[2 * h + 1] = w.y;
+        for (int e = 0; e < G; ++e) {
+            // The magnitude in eighths is at most 16 (8); as unsigned numbers the smaller of v and 32 - v is v, or 32 (the sign) + |v|.
+            // For E2M3 that is the code (see store_fp6_codes_at_pos), for E3M2 magnitudes up to 4 count twice, others are 4 more.
+            const int v = q[e] << (K - b);
+            c[e] = digit_min((uint32_t)v, 32u - (uint32_t)v);
+            if constexpr (FMT == FMT_FP6_E3M2) c[e] += digit_min(c[e] & 31u, 4u);
+        }
+        uint32_t lo32, hi16;
+        if constexpr (G == 8) {
+            lo32 = c[0] | (c[1] << 6) | (c[2] << 12) | (c[3] << 18) | (c[4] << 24) | (c[5] << 30);
+            hi16 = (c[5] >> 2) | (c[6] << 4) | (c[7] << 10);
+        } else {
+            const uint32_t w = c[0] | (c[1] << 6) | (c[2] << 12) | (c[3] << 18);
+            const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0xB1, 0xF, 0xF, false);     // the other lane of the pair
+            lo32 = w | (next << 24);
+            hi16 = next >> 8;
+        }
+        if (stores) {
+            *reinterpret_cast<uint32_t*>(dst_slice + slot.at32) = slot.low32 ? lo32 : (lo32 >> 16) | (hi16 << 16);
+            *reinterpret_cast<uint16_t*>(dst_slice + slot.at16) = (uint16_t)(slot.low32 ? hi16 : lo32);
+        }
+    } else if constexpr (FMT == FMT_FP16) {
+        uint32_t w[G / 2];
+#pragma unroll
+        for (int h = 0; h < G / 2; ++h)
+            w[h] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz((float)q[2 * h] * code_unit, (float)q[2 * h + 1] * code_unit));
+        if (stores) {
+#pragma unroll
+            for (int h = 0; h < G / 8; ++h) *reinterpret_cast<uint4*>(dst_slice + at + 16 * h) = uint4{w[4 * h], w[4 * h + 1], w[4 * h + 2], w[4 * h + 3]};
         }
     } else {
+        uint32_t w[G / 4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) bits[e] = (ke + e < klen) ? (uint64_t)__double_as_longlong(src[(ke + e) * v.es]) : 0ull;
-    }
-    uint64_t T[4];
-    int pk[4], cmax = NO_ELEM;
-    bool nonfinite = false;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) decode_narrow(bits[e], F, T[e], pk[e], cmax, nonfinite);
-    if (nonfinite) atomicOr(a.flags, 1);
-
-    const size_t slice_bytes = (size_t)a.chunks * v.rows_pad * ROWB;
-    uint8_t* dst_slice = v.slices + (size_t)(t * a.s) * slice_bytes;
-    // FP6: an even lane stores the 48 bits of its own four codes and its neighbour's
-    const Fp6Slot slot = fp6_slot(ke & ~7, v.rows_pad, row);
-    const size_t at = ((size_t)(ke / CHUNK_BYTES) * v.rows_pad + row) * CHUNK_BYTES + ke % CHUNK_BYTES;
-    auto store = [&](const int (&qs)[4]) {                           // qs: q * 2^pos
-        if constexpr (FP6) {
-            constexpr int K = FMT == FMT_FP6_E3M2 ? 3 : 4;
-            const int down = pos - (K - a.b);
-            uint32_t w = 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const uint32_t mag = (uint32_t)(qs[e] < 0 ? -qs[e] : qs[e]) >> down, sign = ((uint32_t)qs[e] >> 26) & 32u;
-                w |= ((FMT == FMT_FP6_E3M2 ? (uint32_t)((0xCBA986420ull >> (4 * mag)) & 0xFull) : mag) | sign) << (6 * e);
-            }
-            const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0xB1, 0xF, 0xF, false);     // the other lane of the pair
-            if (stores && (lane & 1) == 0) {
-                const uint64_t w48 = (uint64_t)w | ((uint64_t)next << 24);
-                *reinterpret_cast<uint32_t*>(dst_slice + slot.at32) = slot.low32 ? (uint32_t)w48 : (uint32_t)(w48 >> 16);
-                *reinterpret_cast<uint16_t*>(dst_slice + slot.at16) = slot.low32 ? (uint16_t)(w48 >> 32) : (uint16_t)w48;
-            }
-        } else {
-            uint32_t w = 0;
+        for (int h = 0; h < G / 4; ++h) {
+            const int* const v = q + 4 * h;
             if constexpr (FMT == FMT_FP8) {
                 typedef short short2v __attribute__((ext_vector_type(2)));
                 short2v r = {0, 0};
-                r = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(r, (float)qs[0], (float)qs[1], code_scale, false);
-                r = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(r, (float)qs[2], (float)qs[3], code_scale, true);
-                w = __builtin_bit_cast(uint32_t, r);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) w |= __builtin_amdgcn_ubfe((uint32_t)qs[e], pos, 8) << (8 * e);
+                r = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(r, (float)v[0], (float)v[1], scale, false);
+                r = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(r, (float)v[2], (float)v[3], scale, true);
+                w[h] = __builtin_bit_cast(uint32_t, r);
+            } else {                                                 // the lowest byte of each
+                w[h] = __builtin_amdgcn_perm((uint32_t)v[1], (uint32_t)v[0], 0x0C0C0400u) | __builtin_amdgcn_perm((uint32_t)v[3], (uint32_t)v[2], 0x04000C0Cu);
             }
-            if (stores) *reinterpret_cast<uint32_t*>(dst_slice + at) = w;
+        }
+        if (stores) {
+            if constexpr (G == 8) *reinterpret_cast<uint2*>(dst_slice + at) = uint2{w[0], w[1]};
+            else *reinterpret_cast<uint32_t*>(dst_slice + at) = w[0];
+        }
+    }
+}
+
+// Slices of at most 7 bits (FP8, FP6, INT8, FP16 in blocks of 1024 elements and more) of blocks of up to 16384 elements, along
+// ladders of units (slice_digits.hpp): the largest element gives the first exponent, one OR over the vector tells how many of the
+// following slices keep to the ladder, and these are read off each element's 96-bit number without any exchange; where a vector
+// leaves the ladder, the next exponent is found from the remainders and another ladder starts there (the inputs are read again).
+// What bounds it: memory, mostly.  About 60 integer instructions per element and 5 per element and slice, against 22 per element and
+// slice and a maximum over the vector for each slice when the remainders were carried from slice to slice: 2 x 4096 vectors of 4096,
+// 13 FP8 slices, 265 -> 160 us (704 MB: 4.4 of the 4.7 TB/s of a large copy); 2 x 8192 of 8192, 16 slices, 1300 -> 960 us; 2 x 256 of
+// 256, 12 slices, 9.5 -> 6.5 us; 96 + 6000 of 4097, 9 INT8 slices, 245 -> 152 us.  FP6 slices, whose 16- and 8-byte pieces of a
+// vector lie in three planes, take 330 us as before at 2 x 4096 of 4096.
+// U groups of G consecutive elements per thread.  Several waves per vector: the workgroup is one vector and has only the waves that
+// hold elements; one wave: four vectors per workgroup, no barrier.
+template <int U, int TPR, int G, int FMT>
+__device__ __forceinline__ void slice_vectors(const SplitArgs& a) {
+    constexpr bool FP16 = FMT == FMT_FP16;
+    constexpr int EPC = FP16 ? CHUNK_BYTES / 2 : CHUNK_BYTES;
+    constexpr int ROWB = fmt_is_fp6(FMT) ? CHUNK_BYTES_FP6 : CHUNK_BYTES;
+    constexpr bool WHOLE = TPR > 64;
+    constexpr int RPB = WHOLE ? 1 : 4, WAVES = TPR / 64;
+    __shared__ uint32_t red_key[2][WAVES], red_proof[3][WAVES];
+    __shared__ int l1_share[FP16 && WHOLE ? MAX_SLICES : 1][WAVES];
+
+    const int tr = WHOLE ? threadIdx.x : threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int threads = WHOLE ? blockDim.x : 64;
+    // Workgroups are handed to the eight XCDs (each with an L2 of its own) round-robin by their index.  Neighbouring
+    // vectors share the cache lines of the slice layout (a line holds the 16-byte pieces of eight vectors in the
+    // FP6 planes, the 64-byte chunks of two vectors otherwise), so eight consecutive workgroups' worth of vectors go to the
+    // SAME XCD, where the partial lines meet in one L2 before they are written back; the next eight go to the next XCD, so that
+    // also an operand of few vectors is spread over all of them.  Each operand's share of the grid is a multiple of 64.
+    const bool second = blockIdx.x >= a.wg_first;
+    const SplitVectors& v = second ? a.v[1] : a.v[0];
+    const unsigned li = blockIdx.x - (second ? a.wg_first : 0u);
+    const int64_t row = (int64_t)((li & ~63u) + (li & 7) * 8 + ((li >> 3) & 7)) * RPB + (WHOLE ? 0 : wave);
+    const int64_t t = blockIdx.y, k0 = t * a.kb, padded = a.chunks * EPC;
+    int64_t klen = a.k - k0;
+    if (klen > a.kb) klen = a.kb;
+    if (row >= v.rows) klen = 0;                                     // a padding vector: zero codes, c = 0
+    const DigitLadder l = a.ladder;
+    const float scale = ldexpf(1.0f, a.b), code_unit = ldexpf(1.0f, -a.b);
+    const size_t slice_bytes = (size_t)a.chunks * v.rows_pad * ROWB;
+    uint8_t* dst_slice = v.slices + (size_t)(t * a.s) * slice_bytes;
+    const double* const src = v.X + row * v.ldv + k0 * v.es;
+    struct Group {
+        uint64_t bits[G];
+        uint32_t limb[3][G];
+        size_t at;
+        Fp6Slot slot;
+    };
+    Group first_group, second_group;                                 // (two variables: an array of them does not stay in single registers)
+    auto each_group = [&](auto f) {
+        f(0, first_group);
+        if constexpr (U > 1) f(1, second_group);
+    };
+    static_assert(U <= 2, "groups per thread");
+    auto first_of = [&](int u) -> int64_t { return G * ((int64_t)tr + (int64_t)threads * u); };
+    // does this wave hold elements of the block in group u?  (wave-uniform)
+    auto wave_has = [&](int u) -> bool { return u == 0 || G * ((int64_t)__builtin_amdgcn_readfirstlane(tr & ~63) + (int64_t)threads * u) < padded; };
+    auto load_group = [&](int u, uint64_t (&bits)[G]) {
+        int64_t ke = first_of(u);
+        asm volatile("" : "+v"(ke));                                 // (a second reading works its addresses out again: they would spill)
+        if (v.es == 1 && ke + G <= klen) {
+#pragma unroll
+            for (int h = 0; h < G / 2; ++h) {
+                const two_doubles w = *reinterpret_cast<const two_doubles*>(src + ke + 2 * h);
+                bits[2 * h] = w.x;
+                bits[2 * h + 1] = w.y;
+            }
+        } else {
+            const double* at_e = src + ke * v.es;
+            const int rest = (int)(klen - ke < G ? klen - ke : G);
+#pragma unroll
+            for (int e = 0; e < G; ++e) {
+                bits[e] = e < rest ? (uint64_t)__double_as_longlong(*at_e) : 0ull;
+                at_e += v.es;
+                asm volatile("" : "+v"(at_e));                       // one address at a time
+            }
         }
     };
-    int unit_prev = 0, unit = 0, step = 0, kmax, kmin;
-    uint32_t cd_wait;
-    auto begin_slice = [&](int p) {
-        cmax = wave_max(cmax);
-        const int c = (cmax == NO_ELEM) ? 0 : cmax;
-        unit = c - a.b;
-        step = unit_prev - unit;
-        unit_prev = unit;
-        kmax = KEY_NONE_MAX;
-        kmin = KEY_NONE_MIN;
-        cd_wait = 0;
-        if (lane == 0) v.exps[(t * a.s + p) * v.rows_pad + row] = c;
-    };
-    auto end_slice = [&](bool settled) {
-        bool needs_exact;
-        cmax = narrow_candidate(kmax, kmin, unit, F, needs_exact);
-        if (needs_exact) {
-            uint64_t mx = 0;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint64_t ar = (settled || pk[i] == 0) ? narrow_abs(T[i]) : 0ull;
-                mx = ar > mx ? ar : mx;
-            }
-            cmax = narrow_candidate_exact(mx, unit, F);
+    auto vector_max = [&](uint32_t key, int slot) -> uint32_t {
+        key = wave_max(key);
+        if constexpr (WHOLE) {
+            if ((tr & 63) == 0) red_key[slot][wave] = key;
+            __syncthreads();
+            for (int w = 0; w < threads / 64; ++w) key = red_key[slot][w] > key ? red_key[slot][w] : key;
         }
-        const int cw = (int)cd_wait - CD_BIAS;
-        cmax = (cd_wait != 0 && cw > cmax) ? cw : cmax;
-        dst_slice += slice_bytes;
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)key);
     };
-    int p = 0;
-    for (bool settled = false; p < a.s && !settled; ++p) {
-        begin_slice(p);
-        int qs[4];
+    each_group([&](int u, Group& g) {
+        const int64_t ke = first_of(u);
+        if constexpr (fmt_is_fp6(FMT)) g.slot = fp6_slot(ke & ~(int64_t)7, v.rows_pad, row);
+        g.at = ((size_t)(ke / EPC) * v.rows_pad + row) * CHUNK_BYTES + (size_t)(ke % EPC) * (FP16 ? 2 : 1);
+    });
+
+    uint32_t key = 0;
+    each_group([&](int u, Group& g) {
+        load_group(u, g.bits);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) qs[e] = slice_narrow(T[e], pk[e], step * 65536, pos, bias, keep, kmax, kmin, cd_wait);
-        store(qs);
-        settled = __ballot(cd_wait != 0) == 0ull;
-        end_slice(false);
-    }
-    for (; p < a.s; ++p) {
-        begin_slice(p);
-        int qs[4];
+        for (int e = 0; e < G; ++e) {
+            const uint32_t k = magnitude_key(g.bits[e]);
+            key = k > key ? k : key;
+        }
+    });
+    if (key >= 0x7FF00000u) atomicOr(a.flags, 1);                    // infinity or NaN
+    key = vector_max(key, 0);
+    bool left = key != 0;                                            // is there a remainder?
+    int c = 0;
+    if (left && key >= 0x100000u) {
+        c = magnitude_exponent(key);
+    } else if (left) {                                               // subnormal numbers only
+        uint32_t sub = 0;
+        each_group([&](int, Group& g) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) qs[e] = slice_narrow_active(T[e], step, pos, bias, keep, kmax, kmin);
-        store(qs);
-        end_slice(true);
+            for (int e = 0; e < G; ++e) {
+                uint64_t bit = g.bits[e];
+                asm volatile("" : "+v"(bit));
+                const uint32_t k = exponent_key(bit & 0x000FFFFFFFFFFFFFull, -1074);
+                sub = k > sub ? k : sub;
+            }
+        });
+        c = (int)vector_max(sub, 1) - CD_BIAS;
     }
+
+    auto clear = [&](Group& g) {
+#pragma unroll
+        for (int e = 0; e < G; ++e) g.limb[0][e] = g.limb[1][e] = g.limb[2][e] = 0;
+    };
+    for (int p = 0;;) {
+        int levels = 3 * l.per_limb;
+        if (left) {
+            uint32_t proof[3] = {0, 0, 0};
+            auto form = [&](auto beyond) {
+                each_group([&](int u, Group& g) {
+                    if (!wave_has(u)) {
+                        clear(g);
+                        return;
+                    }
+#pragma unroll
+                    for (int e = 0; e < G; ++e) {
+                        uint32_t x[3], w[3];
+                        uint64_t bit = g.bits[e];
+                        asm volatile("" : "+v"(bit));                // keeps what the two forms share from being worked out for all elements at once
+                        digit_number<decltype(beyond)::value>(bit, c, l, x);
+                        digit_limbs(x, l, w);
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) {
+                            g.limb[i][e] = w[i];
+                            proof[i] |= digit_proof(w[i]);
+                        }
+                        // two elements at a time: with all of them in flight the compiler runs out of registers
+                        if (e & 1) __builtin_amdgcn_sched_barrier(0);
+                    }
+                });
+            };
+            if (p > 0 || c < -1021) form(std::true_type{});
+            else form(std::false_type{});
+#pragma unroll
+            for (int i = 0; i < 3; ++i) proof[i] = wave_or(proof[i]);
+            if constexpr (WHOLE) {
+                if ((tr & 63) == 0) {
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) red_proof[i][wave] = proof[i];
+                }
+                __syncthreads();
+                for (int w = 0; w < threads / 64; ++w) {
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) proof[i] |= red_proof[i][w];
+                }
+#pragma unroll
+                for (int i = 0; i < 3; ++i) proof[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)proof[i]);
+            }
+            levels = digit_levels(proof, l);
+        } else {
+            each_group([&](int, Group& g) { clear(g); });
+        }
+        levels = levels < a.s - p ? levels : a.s - p;
+        if (v.slices == nullptr) {
+            // count-only mode (slicing until the remainder is zero, paragraph before Eq. 4): something is left before the last
+            // of these slices
+            if (left && tr == 0) atomicMax(a.flags + 1, p + levels);
+        } else {
+            if (tr < levels) v.exps[(t * a.s + p + tr) * v.rows_pad + row] = left ? c - tr * l.step : 0;
+            auto store_limb = [&](auto i) {
+                const int rest = levels - i * l.per_limb, fields = rest < l.per_limb ? rest : l.per_limb;
+                for (int d = 0; d < fields; ++d, dst_slice += slice_bytes) {
+                    int l1 = 0;
+                    each_group([&](int u, Group& g) {
+                        if (!wave_has(u)) return;
+                        int q[G];
+#pragma unroll
+                        for (int e = 0; e < G; ++e) {
+                            q[e] = digit_of(g.limb[i][e], d, l.step);
+                            if constexpr (FP16) l1 += q[e] < 0 ? -q[e] : q[e];
+                        }
+                        const bool stores = first_of(u) < padded && (G == 8 || !fmt_is_fp6(FMT) || (tr & 1) == 0);
+                        store_slice_codes<FMT, G>(q, stores, a.b, scale, code_unit, dst_slice, g.at, g.slot);
+                    });
+                    if constexpr (FP16) {
+                        if (v.l1 != nullptr) {                       // sum |q| of the slice
+                            const int at_slice = p + i * l.per_limb + d;
+                            l1 = wave_sum(l1);
+                            if constexpr (WHOLE) {
+                                if ((tr & 63) == 0) l1_share[at_slice][wave] = l1;
+                            } else {
+                                if (tr == 0) v.l1[(t * a.s + at_slice) * v.rows_pad + row] = l1;
+                            }
+                        }
+                    }
+                }
+            };
+            store_limb(std::integral_constant<int, 0>{});
+            store_limb(std::integral_constant<int, 1>{});
+            store_limb(std::integral_constant<int, 2>{});
+        }
+        p += levels;
+        if (p >= a.s) break;
+        if (left) {
+            uint32_t next = 0;
+            const int unit = c - (levels - 1) * l.step - a.b;
+            each_group([&](int u, Group& g) {
+                load_group(u, g.bits);
+#pragma unroll
+                for (int e = 0; e < G; ++e) {
+                    uint64_t bit = g.bits[e];
+                    asm volatile("" : "+v"(bit));
+                    const uint32_t k = remainder_key(bit, unit);
+                    next = k > next ? k : next;
+                    if (e & 1) __builtin_amdgcn_sched_barrier(0);
+                }
+            });
+            next = vector_max(next, 1);
+            left = next != 0;
+            c = (int)next - CD_BIAS;
+        }
+    }
+    if constexpr (FP16 && WHOLE) {
+        if (v.l1 != nullptr) {
+            __syncthreads();
+            if (tr < a.s) {
+                int sum = 0;
+                for (int w = 0; w < threads / 64; ++w) sum += l1_share[tr][w];
+                v.l1[(t * a.s + tr) * v.rows_pad + row] = sum;
+            }
+        }
+    }
+}
+
+template <int U, int TPR, int FMT>
+__global__ void __launch_bounds__((TPR < 128 ? 256 : TPR)) __attribute__((amdgpu_waves_per_eu(U == 1 ? 4 : 3))) split_kernel(SplitArgs a) {
+    slice_vectors<U, TPR, 8, FMT>(a);
+}
+// Blocks of at most 256 elements: four elements per lane (with eight, half the lanes are idle and a thread's chain is twice as long)
+template <int FMT>
+__global__ void __launch_bounds__(256) slice_short_kernel(SplitArgs a) {
+    slice_vectors<1, 64, 4, FMT>(a);
 }
 
 // ---- Blocks too long for the registers of one workgroup --------------------------------------------------------
-// The remainders need not be carried from slice to slice: x^(p) differs from x by a multiple of the previous unit, which
-// is an even multiple of this one (every remainder is at most half a unit, so the units 2^u_p shrink by b+1 bits or more),
-// hence  x^(p+1) = x - (x rounded to a multiple of 2^u_p, ties to even)  directly from x.  So the exponents come first
-// (long_exponents_kernel, remainder_key), from the elements alone, and with them known every element is sliced on its own
-// (split_stream_kernel), with no exchange between threads and no state in memory: the block is read two or three times
-// instead of once, plus 24 bytes of state, per slice.  256 + 320 vectors of 65536 elements, 11 FP8 slices: 6.3 ms with the
-// state in memory, 0.49 ms so.
+// x^(p) differs from x by a multiple of the previous unit, which is an even multiple of this one (every remainder is at most half a
+// unit, so the units 2^u_p shrink by b+1 bits or more), hence  x^(p+1) = x - (x rounded to a multiple of 2^u_p, ties to even)
+// directly from x.  So the exponents come first, from the elements alone (long_exponents_kernel), and with them known every element
+// is sliced on its own (split_stream_kernel), with no exchange between threads and no state in memory.  256 + 320 vectors of 65536
+// elements, 11 FP8 slices: exponents 212 us when every slice's key was formed from the whole block, 71 us now (302 MB read once at
+// 4.7 TB/s: 64 us); slices 247 us carrying remainders, 228 us now (855 MB with the padding vectors: 182 us).
 
-// How far an element's remainder at unit 2^u is from zero, in 2^-32 of the unit and rounded up: the key of the maximum in
-// Eq. 4.  The remainder of mm * 2^E is the distance of its fraction f = mm 2^-sh mod 1 (sh = u - E) from the nearest
-// integer; f is taken to 64 bits with the lowest one sticky.  With hi, lo its words, f < 1/2 gives hi + (lo != 0), f >= 1/2
-// gives the same of 2^64 - f, which is -hi whether lo is zero or not.
-__device__ __forceinline__ uint32_t fraction_key(uint64_t f) {
-    const int hi = (int)(uint32_t)(f >> 32);
-    const uint32_t up = (uint32_t)hi + ((uint32_t)f != 0 ? 1u : 0u);
-    return hi < 0 ? 0u - (uint32_t)hi : up;
-}
-__device__ __forceinline__ uint64_t unit_fraction(uint64_t mm, int sh) {
-    if (sh <= 0) return 0;                                           // a multiple of the unit
-    if (sh <= 64) return mm << (64 - sh);
-    const int r = sh - 64;                                           // far below the unit: cut, with a sticky lowest bit
-    const uint64_t cut = r < 64 ? mm >> r : 0;
-    return cut | ((r < 64 ? (cut << r) != mm : mm != 0) ? 1u : 0u);
-}
-// |remainder| at unit 2^(E + sh), in units of 2^E: exact
-__device__ __forceinline__ uint64_t remainder_abs(uint64_t mm, int sh) {
-    if (sh <= 0) return 0;
-    if (sh > 54) return mm;
-    const uint64_t low = mm & ((1ull << sh) - 1), up = (1ull << sh) - low;
-    return low < up ? low : up;
-}
-
-constexpr int LEVELS = 12;            // units tried per reading of the block
-
-// Eq. 4 for all slices of one vector and block.  With enough elements a unit's largest remainder is nearly half the unit, so
-// that the next unit is b+1 bits down: the keys of the next LEVELS units of that ladder are formed in one reading, and the
-// ladder is followed as far as the keys confirm it; the first exponent off it is known from them too, and another reading
-// starts there.
+// Eq. 4 for all slices of one vector and block: the largest element in one reading, then ladder by ladder (slice_digits.hpp) the
+// slices that the elements prove to keep to it.  The proofs need not see the whole block: the second reading stops as soon as every
+// slice is confirmed, as a rule after the first 8192 elements.
 __global__ void __launch_bounds__(1024) long_exponents_kernel(SplitArgs a) {
-    __shared__ uint32_t red[LEVELS][16];
+    __shared__ uint32_t red_key[16], red_proof[2][3][16];
     const int tid = threadIdx.x, wave = tid >> 6;
     const bool second = blockIdx.x >= a.wg_first;
     const SplitVectors& v = second ? a.v[1] : a.v[0];
@@ -827,118 +704,91 @@ __global__ void __launch_bounds__(1024) long_exponents_kernel(SplitArgs a) {
         return;
     }
     const double* const src = v.X + row * v.ldv + t * a.kb;
-    // maximum over the workgroup of `count` keys per thread, left in red[0 .. count-1][0]
-    auto block_max = [&](uint32_t (&keys)[LEVELS], int count) {
-        __syncthreads();                                             // the previous maxima have been read
-#pragma unroll
-        for (int j = 0; j < LEVELS; ++j) {
-            if (j < count) {
-                const uint32_t m = wave_max(keys[j]);
-                if ((tid & 63) == 0) red[j][wave] = m;
-            }
-        }
-        __syncthreads();
-        if (tid < LEVELS) {
-            uint32_t m = red[tid][0];
-#pragma unroll
-            for (int w = 1; w < 16; ++w) m = red[tid][w] > m ? red[tid][w] : m;
-            red[tid][0] = m;
-        }
-        __syncthreads();
-    };
-    // f(mm, E) for every element of the block, four 16-byte loads in flight per thread
-    auto for_each = [&](auto f) {
-        auto one = [&](uint64_t w) {
-            const int e11 = (int)((w >> 52) & 0x7FF);
-            uint64_t mm = w & 0x000FFFFFFFFFFFFFull;
-            if (e11 != 0) mm |= 0x0010000000000000ull;
-            f(mm, e11 != 0 ? e11 - 1075 : -1074);
-        };
-        int64_t i = 0;
-        for (; i + 8192 <= klen; i += 8192) {
+    const DigitLadder l = a.ladder;
+    // f(bits) for the elements i .. i + 8191, four 16-byte loads in flight per thread
+    auto for_chunk = [&](int64_t i, auto f) {
+        if (i + 8192 <= klen) {
             two_doubles w[4];
 #pragma unroll
             for (int h = 0; h < 4; ++h) w[h] = *reinterpret_cast<const two_doubles*>(src + i + h * 2048 + 2 * tid);
 #pragma unroll
             for (int h = 0; h < 4; ++h) {
-                one(w[h].x);
-                one(w[h].y);
+                f(w[h].x);
+                f(w[h].y);
             }
+        } else {
+            for (i += tid; i < klen; i += 1024) f((uint64_t)__double_as_longlong(src[i]));
         }
-        for (i += tid; i < klen; i += 1024) one((uint64_t)__double_as_longlong(src[i]));
+    };
+    auto block_max = [&](uint32_t key) -> uint32_t {
+        __syncthreads();                                             // the previous maximum has been read
+        key = wave_max(key);
+        if ((tid & 63) == 0) red_key[wave] = key;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < 16; ++w) key = red_key[w] > key ? red_key[w] : key;
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)key);
+    };
+    auto largest_remainder = [&](int unit) -> uint32_t {
+        uint32_t key = 0;
+        for (int64_t i = 0; i < klen; i += 8192)
+            for_chunk(i, [&](uint64_t w) {
+                const uint32_t k = remainder_key(w, unit);
+                key = k > key ? k : key;
+            });
+        return block_max(key);
     };
 
-    uint32_t keys[LEVELS];
-#pragma unroll
-    for (int j = 0; j < LEVELS; ++j) keys[j] = 0;
-    bool nonfinite = false;
-    auto exponent_key = [&](uint64_t mm, int E) -> uint32_t {         // ceil log2 of a non-zero mm * 2^E, biased; 0 for zero
-        return mm == 0 ? 0u : (uint32_t)(E + bit_length_u64(mm) - (((mm & (mm - 1)) == 0) ? 1 : 0) + CD_BIAS);
-    };
-    for_each([&](uint64_t mm, int E) {
-        nonfinite |= E == 0x7FF - 1075;
-        const uint32_t key = exponent_key(mm, E);
-        keys[0] = key > keys[0] ? key : keys[0];
-    });
-    if (nonfinite) atomicOr(a.flags, 1);
-    block_max(keys, 1);
-    int p = 0, c = 0;
-    bool left = red[0][0] != 0;                                      // is there a remainder before slice p?
-    const bool any = left;
-    if (left) c = (int)red[0][0] - CD_BIAS;
-    if (exps != nullptr && tid == 0) exps[0] = c;
-    while (left && p + 1 < a.s) {
-        const int unit0 = c - a.b, step = a.b + 1;
-        const int levels = a.s - 1 - p < LEVELS ? a.s - 1 - p : LEVELS;
-#pragma unroll
-        for (int j = 0; j < LEVELS; ++j) keys[j] = 0;
-        for_each([&](uint64_t mm, int E) {
-            const int sh = unit0 - E;
-            if (sh <= 64) {
-                uint64_t f = unit_fraction(mm, sh);
-#pragma unroll
-                for (int j = 0; j < LEVELS; ++j) {
-                    const uint32_t key = fraction_key(f);
-                    keys[j] = key > keys[j] ? key : keys[j];
-                    f <<= step;
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < LEVELS; ++j) {
-                    const uint32_t key = fraction_key(unit_fraction(mm, sh - j * step));
-                    keys[j] = key > keys[j] ? key : keys[j];
-                }
-            }
+    uint32_t top = 0;
+    for (int64_t i = 0; i < klen; i += 8192)
+        for_chunk(i, [&](uint64_t w) {
+            const uint32_t k = magnitude_key(w);
+            top = k > top ? k : top;
         });
-        block_max(keys, levels);
-        for (int j = 0; j < levels; ++j) {
-            const uint32_t key = red[j][0];
-            const int unit = unit0 - j * step;
-            left = key != 0;
-            if (!left) break;
-            if (key > 1) {
-                c = unit - 32 + bit_length_u32(key - 1);             // smallest c with key * 2^(unit-32) <= 2^c
-            } else {
-                // every remainder is at most 2^-32 of the unit: look at all their bits
-                uint32_t exact[LEVELS];
+    if (top >= 0x7FF00000u) atomicOr(a.flags, 1);                    // infinity or NaN
+    top = block_max(top);
+    bool left = top != 0;                                            // is there a remainder before slice p?
+    int c = 0, p = 0;
+    if (left) c = top >= 0x100000u ? magnitude_exponent(top) : (int)largest_remainder(2000) - CD_BIAS;      // 2^2000: x itself
+    while (left && p < a.s) {
+        uint32_t proof[3] = {0, 0, 0};
+        const int wanted = a.s - p < 3 * l.per_limb ? a.s - p : 3 * l.per_limb;
+        int levels = 1;
+        for (int64_t i = 0, turn = 0; i < klen && levels < wanted; i += 8192, turn ^= 1) {
+            for_chunk(i, [&](uint64_t w) {
+                uint32_t x[3], limb[3];
+                digit_number<true>(w, c, l, x);
+                digit_limbs(x, l, limb);
 #pragma unroll
-                for (int i = 0; i < LEVELS; ++i) exact[i] = 0;
-                for_each([&](uint64_t mm, int E) {
-                    const uint32_t k = exponent_key(remainder_abs(mm, unit - E), E);
-                    exact[0] = k > exact[0] ? k : exact[0];
-                });
-                block_max(exact, 1);
-                c = (int)red[0][0] - CD_BIAS;
+                for (int j = 0; j < 3; ++j) proof[j] |= digit_proof(limb[j]);
+            });
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                const uint32_t m = wave_or(proof[j]);
+                if ((tid & 63) == 0) red_proof[turn][j][wave] = m;
             }
-            ++p;
-            if (exps != nullptr && tid == 0) exps[(int64_t)p * v.rows_pad] = c;
-            if (key == 1 || c - a.b != unit - step) break;           // off the ladder (or its keys are overwritten): read again
+            __syncthreads();                                         // (the other buffer's readers are behind the previous one)
+            uint32_t all[3] = {0, 0, 0};
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+#pragma unroll
+                for (int w = 0; w < 16; ++w) all[j] |= red_proof[turn][j][w];
+                all[j] = (uint32_t)__builtin_amdgcn_readfirstlane((int)all[j]);
+            }
+            levels = digit_levels(all, l);
         }
+        levels = levels < wanted ? levels : wanted;
+        if (exps != nullptr && tid < levels) exps[(int64_t)(p + tid) * v.rows_pad] = c - tid * l.step;
+        p += levels;
+        if (p >= a.s) break;
+        const uint32_t next = largest_remainder(c - (levels - 1) * l.step - a.b);
+        left = next != 0;
+        c = (int)next - CD_BIAS;
     }
     // nothing left: the remaining slices are zero (c := 0); without slices to write, report how many there are
-    if (exps != nullptr && !left)
-        for (int i = p + 1 + tid; i < a.s; i += 1024) exps[(int64_t)i * v.rows_pad] = 0;
-    if (v.slices == nullptr && tid == 0 && any) atomicMax(a.flags + 1, p + 1);
+    if (exps != nullptr)
+        for (int i = p + tid; i < a.s; i += 1024) exps[(int64_t)i * v.rows_pad] = 0;
+    if (v.slices == nullptr && tid == 0 && p > 0) atomicMax(a.flags + 1, p);
 }
 
 // All slices of one chunk (64 inner indices; FP16: 32) of 32 (64) consecutive vectors, with the exponents known: eight
@@ -977,6 +827,39 @@ __global__ void __launch_bounds__(256) split_stream_kernel(SplitArgs a) {
     } else {
 #pragma unroll
         for (int e = 0; e < 8; ++e) bits[e] = (ke + e < klen) ? (uint64_t)__double_as_longlong(src[ke + e]) : 0ull;
+    }
+    // Where the units of all slices follow one ladder (the usual case), the slices are read off one number per element.
+    {
+        const int c0 = exps[0];
+        bool on_ladder = a.s <= 3 * a.ladder.per_limb && c0 >= -1021;
+        for (int p = 1; p < a.s; ++p) on_ladder = on_ladder && exps[(int64_t)p * v.rows_pad] == c0 - p * a.ladder.step;
+        if (__all(on_ladder || row >= v.rows)) {
+            const DigitLadder l = a.ladder;
+            uint32_t limb[3][8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                uint32_t x[3], w[3];
+                digit_number<false>(bits[e], c0, l, x);
+                digit_limbs(x, l, w);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) limb[i][e] = w[i];
+                if (e & 1) __builtin_amdgcn_sched_barrier(0);
+            }
+            const float scale = ldexpf(1.0f, a.b), unit_value = ldexpf(1.0f, -a.b);
+            const Fp6Slot at6 = fp6_slot(ke, v.rows_pad, row);
+            const size_t at = ((size_t)kc * v.rows_pad + row) * CHUNK_BYTES + (size_t)(threadIdx.x % OCTETS) * (FP16 ? 16 : 8);
+            int rest = a.s;
+#pragma unroll
+            for (int i = 0; i < 3; ++i, rest -= l.per_limb) {
+                for (int d = 0; d < l.per_limb && d < rest; ++d, dst_slice += slice_bytes) {
+                    int q[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) q[e] = digit_of(limb[i][e], d, l.step);
+                    store_slice_codes<FMT, 8>(q, true, a.b, scale, unit_value, dst_slice, at, at6);
+                }
+            }
+            return;
+        }
     }
     int cmax = NO_ELEM;
     bool nonfinite = false;                                          // long_exponents_kernel has reported it
@@ -1107,18 +990,17 @@ __global__ void __launch_bounds__(256) delta_kernel(DeltaOperand o0, DeltaOperan
 
 template <int U, int TPR>
 hipError_t launch_split_cfg(const SplitArgs& a_in, int fmt, int64_t T, hipStream_t st) {
-    constexpr int BLOCK = TPR < 256 ? 256 : TPR;
-    constexpr int RPB = BLOCK / TPR;
+    constexpr int RPB = TPR == 64 ? 4 : 1;
     SplitArgs a = a_in;
-    a.wg_first = (unsigned)(a.v[0].rows_pad / RPB);                     // rows_pad is a multiple of 256, RPB <= 4
+    a.wg_first = (unsigned)(a.v[0].rows_pad / RPB);                     // rows_pad is a multiple of 256
     dim3 grid(a.wg_first + (unsigned)(a.v[1].rows_pad / RPB), (unsigned)T);
     const int64_t octets = a.chunks * (fmt == FMT_FP16 ? CHUNK_BYTES / 2 : CHUNK_BYTES) / 8;
-    const unsigned threads = RPB == 1 && U == 1 ? (unsigned)((octets + 64 * U - 1) / (64 * U)) * 64u : BLOCK;
-    if (fmt == FMT_FP16) hipLaunchKernelGGL((split_kernel<U, TPR, FMT_FP16>), grid, dim3(threads), 0, st, a);
-    else if (fmt == FMT_FP6) hipLaunchKernelGGL((split_kernel<U, TPR, FMT_FP6>), grid, dim3(threads), 0, st, a);
-    else if (fmt == FMT_FP6_E3M2) hipLaunchKernelGGL((split_kernel<U, TPR, FMT_FP6_E3M2>), grid, dim3(threads), 0, st, a);
-    else if (fmt == FMT_INT8) hipLaunchKernelGGL((split_kernel<U, TPR, FMT_INT8>), grid, dim3(threads), 0, st, a);
-    else hipLaunchKernelGGL((split_kernel<U, TPR, FMT_FP8>), grid, dim3(threads), 0, st, a);
+    const dim3 block(RPB == 4 ? 256u : (unsigned)((octets + 64 * U - 1) / (64 * U)) * 64u);
+    if (fmt == FMT_FP16) hipLaunchKernelGGL((split_kernel<U, TPR, FMT_FP16>), grid, block, 0, st, a);
+    else if (fmt == FMT_FP6) hipLaunchKernelGGL((split_kernel<U, TPR, FMT_FP6>), grid, block, 0, st, a);
+    else if (fmt == FMT_FP6_E3M2) hipLaunchKernelGGL((split_kernel<U, TPR, FMT_FP6_E3M2>), grid, block, 0, st, a);
+    else if (fmt == FMT_INT8) hipLaunchKernelGGL((split_kernel<U, TPR, FMT_INT8>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((split_kernel<U, TPR, FMT_FP8>), grid, block, 0, st, a);
     return hipGetLastError();
 }
 
@@ -1126,7 +1008,8 @@ hipError_t launch_split_short(const SplitArgs& a_in, int fmt, int64_t T, hipStre
     SplitArgs a = a_in;
     a.wg_first = (unsigned)(a.v[0].rows_pad / 4);
     const dim3 grid(a.wg_first + (unsigned)(a.v[1].rows_pad / 4), (unsigned)T), block(256);
-    if (fmt == FMT_FP6) hipLaunchKernelGGL((slice_short_kernel<FMT_FP6>), grid, block, 0, st, a);
+    if (fmt == FMT_FP16) hipLaunchKernelGGL(slice_wide_kernel, grid, block, 0, st, a);
+    else if (fmt == FMT_FP6) hipLaunchKernelGGL((slice_short_kernel<FMT_FP6>), grid, block, 0, st, a);
     else if (fmt == FMT_FP6_E3M2) hipLaunchKernelGGL((slice_short_kernel<FMT_FP6_E3M2>), grid, block, 0, st, a);
     else if (fmt == FMT_INT8) hipLaunchKernelGGL((slice_short_kernel<FMT_INT8>), grid, block, 0, st, a);
     else hipLaunchKernelGGL((slice_short_kernel<FMT_FP8>), grid, block, 0, st, a);
@@ -1177,30 +1060,27 @@ hipError_t launch_split(const double* X0, int64_t ldv0, int64_t es0, const Opera
     a.v[0] = split_vectors(X0, ldv0, es0, op0);
     a.v[1] = split_vectors(X1, ldv1, 1, op1);
     a.wg_first = 0;
-    a.k = pl.k; a.kb = pl.kb; a.chunks = pl.chunks; a.s = pl.s; a.b = pl.b; a.flags = flags;
+    a.k = pl.k; a.kb = pl.kb; a.chunks = pl.chunks; a.s = pl.s; a.b = pl.b; a.ladder = digit_ladder(pl.b); a.flags = flags;
     if (a.v[0].rows_pad + a.v[1].rows_pad == 0 || pl.T == 0) return hipSuccess;
-    const int64_t vectors = (a.v[0].rows_pad + a.v[1].rows_pad) * pl.T;
     const int fmt = pl.fmt;
     if (pl.kb > MAX_K_BLOCK_IN_REGISTERS && es0 != 1) return hipErrorInvalidValue;
     if (pl.kb > MAX_K_BLOCK_IN_REGISTERS) return launch_split_long(a, fmt, pl.T, st);
     const int64_t octets = pl.chunks * pl.epc / 8;                              // per vector and block, padded
-    // sixteen elements per thread (U = 2) is the measured optimum: more elements per thread cost registers and with
-    // them the occupancy that hides the latency of the dependent integer chains (64 per thread: one wave per SIMD)
-    if (octets <= 32 && fmt != FMT_FP16 && (a.v[0].slices != nullptr || a.v[1].slices != nullptr)) return launch_split_short(a, fmt, pl.T, st);
+    // Eight elements per thread while a workgroup has threads for them, sixteen beyond: with two exchanges per vector the waves are
+    // not held up by each other, and 80 registers let six of them share a SIMD (sixteen elements need 130).  Both operands, us:
+    // 16384 + 8192 vectors of 1024, 13 FP8 slices: 116, 120 with sixteen per lane and no barrier; 96 + 6000 of 4097, 9 INT8 slices:
+    // 152 and 217; 2 x 8192 of 8192, 16 FP8 slices: 990 and 960 (1024 threads of eight leave a CU no second workgroup).
+    if (fmt == FMT_FP16 ? pl.b > 7 : octets <= 32) return launch_split_short(a, fmt, pl.T, st);
     if (octets <= 64) return launch_split_cfg<1, 64>(a, fmt, pl.T, st);
-    // a small problem (few vectors) is bound by the length of a thread's dependent chain, not by throughput: eight
-    // elements per thread there (1024 x 1024: 0.080 -> 0.065 ms for both operands; no gain from 2048 vectors on)
-    if (vectors <= 2048) {
-        if (octets <= 128) return launch_split_cfg<1, 128>(a, fmt, pl.T, st);
-        if (octets <= 256) return launch_split_cfg<1, 256>(a, fmt, pl.T, st);
-    }
-    if (octets <= 128) return launch_split_cfg<2, 64>(a, fmt, pl.T, st);
-    if (octets <= 256) return launch_split_cfg<2, 128>(a, fmt, pl.T, st);
-    if (octets <= 512) return launch_split_cfg<2, 256>(a, fmt, pl.T, st);
+    if (octets <= 128) return launch_split_cfg<1, 128>(a, fmt, pl.T, st);
+    if (octets <= 256) return launch_split_cfg<1, 256>(a, fmt, pl.T, st);
+    if (octets <= 512) return launch_split_cfg<1, 512>(a, fmt, pl.T, st);
+    if (octets <= 768) return launch_split_cfg<1, 1024>(a, fmt, pl.T, st);
     if (octets <= 1024) return launch_split_cfg<2, 512>(a, fmt, pl.T, st);
+    if (octets <= 1536) return launch_split_cfg<2, 768>(a, fmt, pl.T, st);
     if (octets <= 2048) return launch_split_cfg<2, 1024>(a, fmt, pl.T, st);
-    // 32 elements per thread would cover blocks of up to 32768 elements, but at the 128 registers a thread of a
-    // 1024-thread workgroup has, that variant lives on more than a hundred spilled registers; such blocks are streamed
+    // 32 elements per thread would cover blocks of up to 32768 elements, but not in the 128 registers a thread of a
+    // 1024-thread workgroup has; such blocks are streamed
     return hipErrorInvalidValue;
 }
 
