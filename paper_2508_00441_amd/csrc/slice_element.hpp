@@ -1,4 +1,5 @@
-// The per-element step of the slicer for slices at most 7 bits wide (FP8, FP6, INT8, FP16 in long blocks): Eq. 5-8 of
+// The per-element step of the slicer that carries remainders from slice to slice (blocks beyond 16384 elements whose units leave the
+// ladder of slice_digits.hpp), for slices at most 7 bits wide: Eq. 5-8 of
 // the paper on a 64-bit fixed-point number held as two 32-bit words, so that the rounding, the subtraction and the
 // bookkeeping for the next exponent are 32-bit integer operations.
 //

@@ -669,7 +669,7 @@ __device__ __forceinline__ void slice_vectors(const SplitArgs& a) {
 }
 
 template <int U, int TPR, int FMT>
-__global__ void __launch_bounds__((TPR < 128 ? 256 : TPR)) __attribute__((amdgpu_waves_per_eu(U == 1 ? 4 : 3))) split_kernel(SplitArgs a) {
+__global__ void __launch_bounds__((TPR < 128 ? 256 : TPR)) __attribute__((amdgpu_waves_per_eu(U == 2 ? 3 : TPR == 1024 ? 6 : 5))) split_kernel(SplitArgs a) {
     slice_vectors<U, TPR, 8, FMT>(a);
 }
 // Blocks of at most 256 elements: four elements per lane (with eight, half the lanes are idle and a thread's chain is twice as long)
