@@ -50,6 +50,10 @@ struct AccArgs {
     int two_b;               // 2b: a term is (stored product) * 2^(p_frac - two_b) * 2^e
     int p_frac;              // the stored products are integer multiples of 2^-p_frac (2b; 2b - 2 for FP6 codes; 0 for INT32)
     int read_S, write_S, add_to_C;
+    const double* W;         // add_to_C: what the block is added to (C itself, or the product so far)
+    int64_t ldw;
+    uint64_t alpha, beta;    // SCALED: the result is fl(fl(alpha * P) + fl(beta * C)), of fl(alpha * P) without reading C
+    int use_beta;
     int allow_chain;         // the GEMM kernel summed tile-wide runs
     const uint8_t* starts;   // measured runs (RunCheck), or null
     int merge;               // rule "runs": merge equal-scale products of an anti-diagonal element by element
@@ -68,9 +72,25 @@ __device__ __forceinline__ bool starts_run(const PairOrder& o, int allow_chain, 
     return pos % o.group_len == 0 || !(allow_chain && pair_linked(dA, ga, dB, gb, p - 1, q + 1));
 }
 
+// fl(fl(alpha * w) + fl(beta * c)), or fl(alpha * w) alone: the scaling around the product, with the FP64
+// multiplication and addition in hardware or emulated (Section 4.2).
+template <bool EMU>
+__device__ __forceinline__ uint64_t scaled_result(uint64_t alpha, uint64_t w, uint64_t beta, int use_beta, uint64_t c) {
+    if constexpr (EMU) {
+        uint64_t t = fp64_mul_emulated(alpha, w);
+        if (use_beta) t = fp64_add_emulated(t, fp64_mul_emulated(beta, c));
+        return t;
+    } else {
+        double t = __dmul_rn(__longlong_as_double((long long)alpha), __longlong_as_double((long long)w));
+        if (use_beta) t = __dadd_rn(t, __dmul_rn(__longlong_as_double((long long)beta), __longlong_as_double((long long)c)));
+        return (uint64_t)__double_as_longlong(t);
+    }
+}
+
 // R elements per thread: 4 (one workgroup per 32 x 32 position) or 1 (four workgroups per position, each eight of its
 // columns).  DEPTH product loads are kept in flight per thread.
-template <int MODE, bool PINT, int R, int DEPTH>
+// SCALED: the last step of the last block of a product C = alpha * (A B) + beta * C.
+template <int MODE, bool PINT, int R, int DEPTH, bool SCALED>
 __device__ __forceinline__ void accumulate_body(const AccArgs& a) {
     static_assert(R == 4 || R == 1, "a thread reads 16 bytes or one word of a stored product");
     constexpr bool HW = MODE == ACC_HW, EMU = MODE == ACC_EMU, EXACT = MODE == ACC_EXACT;
@@ -95,6 +115,47 @@ __device__ __forceinline__ void accumulate_body(const AccArgs& a) {
     const int64_t m0 = (int64_t)tm * TILE + wm * 128 + tj * 32;       // first row of C of this 32 x 32 position
     const int64_t n0 = (int64_t)tn * TILE + wn * 128 + ti * 32;       // first column
     if (m0 >= a.m || n0 >= a.n) return;               // padding only
+
+    const int ml = lane & 31;
+    const int nl = g4 * 8 + (lane >> 5) * 4 + r0;
+    const size_t tile_off = ((size_t)(tn * 2 + wn) * a.quads_m + tm * 2 + wm) * QUAD_ELEMS + (size_t)sub * 1024 + (size_t)(g4 * 64 + lane) * 4 + r0;
+    const size_t pair_stride = (size_t)a.quads_m * a.quads_n * QUAD_ELEMS;
+    struct Words { uint32_t w[R]; };
+    auto load_slot = [&](unsigned slot) -> Words {
+        const float* src = a.P + (size_t)slot * pair_stride + tile_off;
+        if constexpr (R == 4) {
+            const uint4 v = *reinterpret_cast<const uint4*>(src);
+            return Words{{v.x, v.y, v.z, v.w}};
+        } else {
+            return Words{{*reinterpret_cast<const uint32_t*>(src)}};
+        }
+    };
+    // The first pair of every group starts a run, whatever the exponents: the first DEPTH of those products are asked for now, and
+    // are the ones needed where the GEMM kernel stored nothing else (regular ladders).
+    Words v[DEPTH];
+    if (a.pass.npairs > 0) {
+        int g = a.pass.g_hi, len = diag_len(a.order, g), at = 0, slot = 0;      // the group at position `at` of anti-diagonal g, whose first slot is `slot`
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            v[d] = load_slot((unsigned)(slot + at));                  // (past the last group: once more the last one)
+            if (at + a.order.group_len < len) {
+                at += a.order.group_len;
+            } else if (g > a.pass.g_lo) {
+                slot += len;
+                len = diag_len(a.order, --g);
+                at = 0;
+            }
+        }
+    }
+
+    uint64_t c_old[SCALED ? R : 1];                   // the C of a scaled product, asked for early as well
+    if constexpr (SCALED) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int64_t mi = m0 + ml, nj = n0 + nl + r;
+            c_old[r] = a.use_beta && mi < a.m && nj < a.n ? reinterpret_cast<const uint64_t*>(a.C)[mi + nj * a.ldc] : 0;
+        }
+    }
 
     // exponents of the 32 rows and 32 columns: slot 0 keeps the first-slice exponent, slots p >= 1 the difference to it
     for (int idx = tid; idx < a.order.s * 32; idx += 256) {
@@ -128,11 +189,6 @@ __device__ __forceinline__ void accumulate_body(const AccArgs& a) {
         }
         __syncthreads();
     }
-
-    const int ml = lane & 31;
-    const int nl = g4 * 8 + (lane >> 5) * 4 + r0;
-    const size_t tile_off = ((size_t)(tn * 2 + wn) * a.quads_m + tm * 2 + wm) * QUAD_ELEMS + (size_t)sub * 1024 + (size_t)(g4 * 64 + lane) * 4 + r0;
-    const size_t pair_stride = (size_t)a.quads_m * a.quads_n * QUAD_ELEMS;
 
     // the block sum of this thread's elements, in the representation of the mode
     double Sd[R];                                     // HW
@@ -194,7 +250,6 @@ __device__ __forceinline__ void accumulate_body(const AccArgs& a) {
     // kernel this is the element-wise rule "consecutive pairs of an anti-diagonal with equal scale are summed exactly".
     run_t run_sum[R] = {};
     int run_e[R] = {};
-    struct Words { uint32_t w[R]; };
     auto process = [&](uint32_t entry, const Words& v) {
         const int p = (entry >> 12) & 63, q = (entry >> 18) & 63;
         const bool first = (entry >> 24) & 1;
@@ -213,21 +268,13 @@ __device__ __forceinline__ void accumulate_body(const AccArgs& a) {
             }
         }
     };
-    auto load_run = [&](int i) -> Words {
-        const uint32_t entry = entries[i < n_runs ? i : n_runs - 1];
-        const float* src = a.P + (size_t)(entry & 0xFFFu) * pair_stride + tile_off;
-        if constexpr (R == 4) {
-            const uint4 v = *reinterpret_cast<const uint4*>(src);
-            return Words{{v.x, v.y, v.z, v.w}};
-        } else {
-            return Words{{*reinterpret_cast<const uint32_t*>(src)}};
-        }
-    };
+    auto load_run = [&](int i) -> Words { return load_slot(entries[i < n_runs ? i : n_runs - 1] & 0xFFFu); };
     // DEPTH loads in flight per thread; the loop is unrolled by DEPTH so that each load keeps its registers
     if (n_runs > 0) {
-        Words v[DEPTH];
+        if (n_runs != a.pass.ngroups) {                               // not the products asked for above
 #pragma unroll
-        for (int d = 0; d < DEPTH; ++d) v[d] = load_run(d);
+            for (int d = 0; d < DEPTH; ++d) v[d] = load_run(d);
+        }
         int i = 0;
         for (; i + DEPTH <= n_runs; i += DEPTH) {
 #pragma unroll
@@ -265,28 +312,35 @@ __device__ __forceinline__ void accumulate_body(const AccArgs& a) {
         const int64_t nj = n0 + nl + r;
         if (nj >= a.n) continue;
         const int base = baseA + relB[0][nl + r];
+        uint64_t* const dst = reinterpret_cast<uint64_t*>(a.C) + mi + nj * a.ldc;
+        uint64_t v;
         if constexpr (HW) {
-            double* dst = a.C + mi + nj * a.ldc;
-            double v = ldexp(Sd[r], base);
-            if (a.add_to_C) v = *dst + v;
-            *dst = v;
+            double d = ldexp(Sd[r], base);
+            if (a.add_to_C) d = a.W[mi + nj * a.ldw] + d;
+            v = (uint64_t)__double_as_longlong(d);
         } else {
-            uint64_t* dst = reinterpret_cast<uint64_t*>(a.C) + mi + nj * a.ldc;
-            uint64_t v;
             if constexpr (EMU) v = fp64_scale_pow2_emulated(E[r].value(), base);
             else v = X[r].round_to_fp64(base - a.two_b - EXACT_WINDOW_BITS);
-            if (a.add_to_C) v = fp64_add_emulated(*dst, v);
-            *dst = v;
+            if (a.add_to_C) v = fp64_add_emulated(reinterpret_cast<const uint64_t*>(a.W)[mi + nj * a.ldw], v);
         }
+        if constexpr (SCALED) v = scaled_result<!HW>(a.alpha, v, a.beta, a.use_beta, c_old[r]);
+        *dst = v;
     }
 }
 
 template <int MODE, bool PINT>
-__global__ void __launch_bounds__(256) accumulate_kernel(const AccArgs a) { accumulate_body<MODE, PINT, 4, 4>(a); }
+__global__ void __launch_bounds__(256) accumulate_kernel(const AccArgs a) { accumulate_body<MODE, PINT, 4, 4, false>(a); }
 
 // Few elements: a quarter of the work per thread
 template <int MODE, bool PINT>
-__global__ void __launch_bounds__(256) accumulate_fine_kernel(const AccArgs a) { accumulate_body<MODE, PINT, 1, 8>(a); }
+__global__ void __launch_bounds__(256) accumulate_fine_kernel(const AccArgs a) { accumulate_body<MODE, PINT, 1, 8, false>(a); }
+
+// The last block of a scaled product: combined with C here, without a pass of its own over the product and C (1000 x 777, integer
+// only: 8.6 us).
+template <int MODE, bool PINT>
+__global__ void __launch_bounds__(256) accumulate_scaled_kernel(const AccArgs a) { accumulate_body<MODE, PINT, 4, 4, true>(a); }
+template <int MODE, bool PINT>
+__global__ void __launch_bounds__(256) accumulate_scaled_fine_kernel(const AccArgs a) { accumulate_body<MODE, PINT, 1, 8, true>(a); }
 
 // Verification export: one thread per stored word; grid.y = pair slot of the pass.  Writes the plain column-major
 // matrices and, if asked, the number of pairs each slot sums for the element (see launch_export_products).
@@ -350,25 +404,15 @@ __global__ void __launch_bounds__(256) add_emulated_kernel(const uint64_t* a, co
         out[i] = fp64_add_emulated(a[i], b[i]);
 }
 
-// C = fl(fl(alpha * W) + fl(beta * C)), or C = fl(alpha * W) without reading C when use_beta == 0: the scaling
-// around the product, with the FP64 multiplication and addition in hardware or emulated (Section 4.2).
+// The same as a pass of its own: products without an inner dimension.
 template <bool EMU>
 __global__ void __launch_bounds__(256) axpby_kernel(uint64_t alpha, uint64_t beta, int use_beta, const uint64_t* __restrict__ W,
                                                     int64_t ldw, uint64_t* C, int64_t ldc, int64_t m, int64_t n) {
     const int64_t total = m * n;
     for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * 256) {
         const int64_t i = idx % m, j = idx / m;
-        const uint64_t w = W[i + j * ldw];
         uint64_t* dst = C + i + j * ldc;
-        if constexpr (EMU) {
-            uint64_t t = fp64_mul_emulated(alpha, w);
-            if (use_beta) t = fp64_add_emulated(t, fp64_mul_emulated(beta, *dst));
-            *dst = t;
-        } else {
-            double t = __dmul_rn(__longlong_as_double((long long)alpha), __longlong_as_double((long long)w));
-            if (use_beta) t = __dadd_rn(t, __dmul_rn(__longlong_as_double((long long)beta), __longlong_as_double((long long)*dst)));
-            *dst = (uint64_t)__double_as_longlong(t);
-        }
+        *dst = scaled_result<EMU>(alpha, W[i + j * ldw], beta, use_beta, use_beta ? *dst : 0);
     }
 }
 
@@ -389,7 +433,8 @@ unsigned grid_for(int64_t work_items) {
 
 hipError_t launch_accumulate(const Plan& pl, const Operand& A, const Operand& B, const PairOrder& order, const Pass& ps,
                              bool first_pass, bool last_pass, int64_t t, const float* P, uint64_t* S_io,
-                             double* C, int64_t ldc, int accum_mode, int sum_rule, bool chained, const uint8_t* starts, hipStream_t st) {
+                             double* C, int64_t ldc, const ScaledResult* scaled, int accum_mode, int sum_rule, bool chained, const uint8_t* starts,
+                             hipStream_t st) {
     if (pl.tiles_m == 0 || pl.tiles_n == 0) return hipSuccess;
     AccArgs a;
     a.P = P; a.S = S_io; a.C = C; a.ldc = ldc;
@@ -409,6 +454,14 @@ hipError_t launch_accumulate(const Plan& pl, const Operand& A, const Operand& B,
     a.read_S = !first_pass;
     a.write_S = !last_pass;
     a.add_to_C = t > 0;
+    a.W = C; a.ldw = ldc;
+    a.alpha = a.beta = 0; a.use_beta = 0;
+    if (scaled != nullptr) {
+        a.C = scaled->C; a.ldc = scaled->ldc;
+        memcpy(&a.alpha, &scaled->alpha, 8);
+        memcpy(&a.beta, &scaled->beta, 8);
+        a.use_beta = scaled->beta != 0.0;
+    }
     const int64_t blocks = pl.tiles_m * pl.tiles_n * 64;
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
     // With few positions a thread's serial chain (four elements per stored run, a round trip to memory per four runs) is the
@@ -420,15 +473,19 @@ hipError_t launch_accumulate(const Plan& pl, const Operand& A, const Operand& B,
         if (fine) hipLaunchKernelGGL(fine_kernel, grid, block, 0, st, a);
         else hipLaunchKernelGGL(coarse_kernel, grid, block, 0, st, a);
     };
-    if (pl.p_is_int) {
-        if (accum_mode == ACC_EXACT) launch(accumulate_kernel<ACC_EXACT, true>, accumulate_fine_kernel<ACC_EXACT, true>);
-        else if (accum_mode == ACC_EMU) launch(accumulate_kernel<ACC_EMU, true>, accumulate_fine_kernel<ACC_EMU, true>);
-        else launch(accumulate_kernel<ACC_HW, true>, accumulate_fine_kernel<ACC_HW, true>);
-    } else {
-        if (accum_mode == ACC_EXACT) launch(accumulate_kernel<ACC_EXACT, false>, accumulate_fine_kernel<ACC_EXACT, false>);
-        else if (accum_mode == ACC_EMU) launch(accumulate_kernel<ACC_EMU, false>, accumulate_fine_kernel<ACC_EMU, false>);
-        else launch(accumulate_kernel<ACC_HW, false>, accumulate_fine_kernel<ACC_HW, false>);
-    }
+    auto launch_mode = [&](auto mode, auto pint) {
+        constexpr int M = decltype(mode)::value;
+        constexpr bool I = decltype(pint)::value;
+        if (scaled != nullptr) launch(accumulate_scaled_kernel<M, I>, accumulate_scaled_fine_kernel<M, I>);
+        else launch(accumulate_kernel<M, I>, accumulate_fine_kernel<M, I>);
+    };
+    auto launch_words = [&](auto pint) {
+        if (accum_mode == ACC_EXACT) launch_mode(std::integral_constant<int, ACC_EXACT>{}, pint);
+        else if (accum_mode == ACC_EMU) launch_mode(std::integral_constant<int, ACC_EMU>{}, pint);
+        else launch_mode(std::integral_constant<int, ACC_HW>{}, pint);
+    };
+    if (pl.p_is_int) launch_words(std::true_type{});
+    else launch_words(std::false_type{});
     return hipGetLastError();
 }
 

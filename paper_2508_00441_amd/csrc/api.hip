@@ -133,7 +133,7 @@ int check_dgemm_args(int64_t m, int64_t n, int64_t k, const double* A, int64_t l
 }
 
 // One Ozaki product on (a panel of) the operands: C = alpha * (A B) + beta * C.  (alpha, beta) = (1, 0): the product
-// goes straight to C.  Otherwise it goes to the work memory's product buffer and one more kernel combines it with C.
+// goes straight to C.  Otherwise the last accumulation combines it with C (earlier blocks of k go to the work memory).
 // The arguments have been checked and the plan made (check_dgemm_args).
 int dgemm_core(const Plan& plan, double alpha, const double* A, int64_t lda, const double* B, int64_t ldb, double beta, double* C,
                int64_t ldc, const Options& o, WorkMem wm) {
@@ -152,8 +152,10 @@ int dgemm_core(const Plan& plan, double alpha, const double* A, int64_t lda, con
     const RunCheck& check = r.check;
     double* const out = scaled ? c.W : C;
     const int64_t ldo = scaled ? (m > 1 ? m : 1) : ldc;
+    const ScaledResult result = {alpha, beta, C, ldc};
     if (k == 0) {
         HIP_TRY(launch_fill_zero_f64(out, ldo, m, n, st));
+        if (scaled) HIP_TRY(launch_axpby(alpha, beta, c.W, ldo, C, ldc, m, n, o.accum_mode != OZAKI_ACCUM_FP64_HW, st));
     } else {
         const PairOrder order = order_of(pl);
         int rc = run_split(pl, c, A, lda, B, ldb, true, true);
@@ -167,16 +169,13 @@ int dgemm_core(const Plan& plan, double alpha, const double* A, int64_t lda, con
                 }
                 {
                     Phase ph(2);
+                    const bool last = ps.g_lo == 2 && t + 1 == pl.T;
                     HIP_TRY(launch_accumulate(pl, c.A, c.B, order, ps, g_hi == order_top_diag(order), ps.g_lo == 2, t, c.P, c.S, out,
-                                              ldo, o.accum_mode, o.sum_rule, chained, check.starts, st));
+                                              ldo, scaled && last ? &result : nullptr, o.accum_mode, o.sum_rule, chained, check.starts, st));
                 }
                 g_hi = ps.g_lo - 1;
             }
         }
-    }
-    if (scaled) {
-        Phase ph(2);
-        HIP_TRY(launch_axpby(alpha, beta, c.W, ldo, C, ldc, m, n, o.accum_mode != OZAKI_ACCUM_FP64_HW, st));
     }
     return 0;
 }

@@ -335,15 +335,24 @@ hipError_t launch_pair_gemm(const Plan& pl, const Operand& A, const Operand& B, 
 hipError_t launch_pair_gemm_small(const Plan& pl, const Operand& A, const Operand& B, const PairOrder& order, const Pass& ps,
                                   bool allow_chain, const RunCheck& check, int64_t t, float* P, hipStream_t st);
 
+// C = alpha * (A B) + beta * C, formed where the last block's sum is added (one rounding per operation, no fused multiply-add;
+// beta == 0: C is not read).
+struct ScaledResult {
+    double alpha, beta;
+    double* C;
+    int64_t ldc;
+};
+
 // Accumulate the pairs of pass `ps` of block t.  S_io: running block sum in accumulator order (read unless the
 // pass is the block's first, written unless it is the last): one 64-bit word per element (FP64 bits), three in the
 // exact mode, word w of element e at S_io[w * quads * QUAD_ELEMS + e].  On the last pass the block sum is rescaled by
-// the first-slice exponents and stored to C (t == 0) or added to C (t > 0).  `chained`: the products were written
+// the first-slice exponents and stored to C (t == 0) or added to C (t > 0); with `scaled` (last pass of the last block) that sum
+// is the product of a scaled call, combined into scaled->C, and C is only read.  `chained`: the products were written
 // with allow_chain; starts: RunCheck::starts of that launch.  sum_rule SUM_PLAIN: every product is added on its own.
 hipError_t launch_accumulate(const Plan& pl, const Operand& A, const Operand& B, const PairOrder& order, const Pass& ps,
                              bool first_pass, bool last_pass, int64_t t, const float* P, uint64_t* S_io,
-                             double* C, int64_t ldc, int accum_mode, int sum_rule, bool chained, const uint8_t* starts,
-                             hipStream_t st);
+                             double* C, int64_t ldc, const ScaledResult* scaled, int accum_mode, int sum_rule, bool chained,
+                             const uint8_t* starts, hipStream_t st);
 
 // P in accumulator order -> [nz][n][m] column-major matrices (verification export): FP32 values of Eq. 10-11, or INT32
 // integers for INT8 slices.  run_len_out (may be null): for every element and pair slot of the pass, how many pairs'
