@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJDIR = os.path.join(CSRC, "_build")
 LIB = os.path.join(HERE, "libozaki.so")
-SOURCES = ["api.hip", "split.hip", "pair_gemm.hip", "pair_gemm_measured.hip", "pair_gemm_small.hip", "accumulate.hip"]
+SOURCES = ["api.hip", "split.hip", "pair_gemm.hip", "pair_gemm_fp8.hip", "pair_gemm_measured.hip", "pair_gemm_small.hip", "accumulate.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -8,6 +8,16 @@ namespace {
 template <int FMT>
 __global__ void __launch_bounds__(256) pair_gemm_kernel(const GemmArgs a) { pair_gemm_body<FMT, false>(a); }
 
+// FP8: the kernel of pair_gemm_fp8.hip, whose k-steps take two stages, for problems that keep the matrix unit busy (from 256 tiles
+// on: 2 - 5 % faster; 16 tiles: 2 - 6 % slower, figures there).  An odd number of stages is filled up to an even one, which costs
+// more than the kernel gains below some fifty.
+bool fp8_long_steps(int64_t tiles, int64_t chunks) { return tiles >= 256 && (chunks % 2 == 0 || chunks >= 64); }
+
+// Products of this size pass the caches on their way to the accumulation whatever the kernel does: their stores need not push the slices
+// out of the L2s.  16384 x 8192 x 1024 FP8: GEMM 8.83 -> 8.39 ms; 4096^2 FP6, all pairs: GEMM 4.11 -> 4.07, accumulation 0.594 -> 0.564 ms;
+// smaller ones are read back from the caches (2048^2 FP16: accumulation 55 -> 62 us with such stores).
+constexpr double STREAMED_PRODUCT_BYTES = 512.0 * (1 << 20);
+
 }  // namespace
 
 hipError_t launch_pair_gemm(const Plan& pl, const Operand& A, const Operand& B, const PairOrder& order, const Pass& ps,
@@ -36,6 +46,8 @@ hipError_t launch_pair_gemm(const Plan& pl, const Operand& A, const Operand& B, 
     const int64_t blocks = (int64_t)ps.ngroups * pl.tiles_m * pl.tiles_n;
     if (blocks > 0x7FFFFFFF || pl.chunks > 0x7FFFFFFF) return hipErrorInvalidValue;
     a.work = work_order(ps.npairs, ps.ngroups, longest_group(order, ps), 32, a.tiles_m, a.tiles_n, pl.chunks);
+    a.streamed = (double)ps.ngroups * (double)(pl.quads_m * pl.quads_n) * QUAD_ELEMS * 4.0 >= STREAMED_PRODUCT_BYTES;
+    if (pl.fmt == FMT_FP8 && fp8_long_steps(pl.tiles_m * pl.tiles_n, pl.chunks)) return launch_pair_gemm_fp8(a, check.starts != nullptr, (unsigned)blocks, st);
     if (check.starts != nullptr) return launch_pair_gemm_measured(a, pl.fmt, (unsigned)blocks, st);
     if (pl.fmt == FMT_FP16) hipLaunchKernelGGL((pair_gemm_kernel<FMT_FP16>), dim3((unsigned)blocks), dim3(256), 0, st, a);
     else if (pl.fmt == FMT_FP6) hipLaunchKernelGGL((pair_gemm_kernel<FMT_FP6>), dim3((unsigned)blocks), dim3(256), 0, st, a);

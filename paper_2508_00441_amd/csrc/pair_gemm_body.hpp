@@ -69,6 +69,7 @@ struct GemmArgs {
     int pair_bound;
     int sure;                // pairs of a group whose sum is inside the window whatever the data
     float unit;              // 2^-p_frac, the unit of the stored sums
+    int streamed;            // the products are more than the caches hold: non-temporal stores
 };
 
 namespace {
@@ -239,10 +240,20 @@ __device__ __forceinline__ void pair_gemm_body(const GemmArgs& a) {
     auto store_tile = [&](int slot, int i, int j, const acc_t& t) {
         if (!has_block) return;
         char* base = reinterpret_cast<char*>(a.P + ((size_t)(slot * a.quads_n + qn) * a.quads_m + qm) * QUAD_ELEMS + (size_t)(i * 4 + j) * 1024);
+        if (a.streamed) {
+            asm volatile("" ::: "memory");            // keeps these stores apart from the ordinary ones (merged, they would be ordinary)
 #pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-            acc4_t v = {t[4 * g4], t[4 * g4 + 1], t[4 * g4 + 2], t[4 * g4 + 3]};
-            *reinterpret_cast<acc4_t*>(base + g4 * 1024 + lane_bytes) = v;
+            for (int g4 = 0; g4 < 4; ++g4) {
+                const acc4_t v = {t[4 * g4], t[4 * g4 + 1], t[4 * g4 + 2], t[4 * g4 + 3]};
+                __builtin_nontemporal_store(v, reinterpret_cast<acc4_t*>(base + g4 * 1024 + lane_bytes));
+            }
+            asm volatile("" ::: "memory");
+        } else {
+#pragma unroll
+            for (int g4 = 0; g4 < 4; ++g4) {
+                const acc4_t v = {t[4 * g4], t[4 * g4 + 1], t[4 * g4 + 2], t[4 * g4 + 3]};
+                *reinterpret_cast<acc4_t*>(base + g4 * 1024 + lane_bytes) = v;
+            }
         }
     };
 
@@ -441,5 +452,7 @@ __device__ __forceinline__ void pair_gemm_body(const GemmArgs& a) {
 
 // pair_gemm_measured.hip
 hipError_t launch_pair_gemm_measured(const GemmArgs& a, int fmt, unsigned blocks, hipStream_t st);
+// pair_gemm_fp8.hip
+hipError_t launch_pair_gemm_fp8(const GemmArgs& a, bool measured, unsigned blocks, hipStream_t st);
 
 }  // namespace ozaki
