@@ -131,9 +131,11 @@ __device__ __forceinline__ void accumulate_body(const AccArgs& a) {
         }
     };
     // The first pair of every group starts a run, whatever the exponents: the first DEPTH of those products are asked for now, and
-    // are the ones needed where the GEMM kernel stored nothing else (regular ladders).
+    // are the ones needed where the GEMM kernel stored nothing else (regular ladders).  4096^2, hardware sum: 220 -> 184 us.  Few
+    // positions, whose launches are a chain of latencies of other kinds, gain nothing and pay for the list (600^2: 12.9 -> 13.5 us).
+    constexpr bool EARLY = R == 4;
     Words v[DEPTH];
-    if (a.pass.npairs > 0) {
+    if (EARLY && a.pass.npairs > 0) {
         int g = a.pass.g_hi, len = diag_len(a.order, g), at = 0, slot = 0;      // the group at position `at` of anti-diagonal g, whose first slot is `slot`
 #pragma unroll
         for (int d = 0; d < DEPTH; ++d) {
@@ -271,7 +273,7 @@ __device__ __forceinline__ void accumulate_body(const AccArgs& a) {
     auto load_run = [&](int i) -> Words { return load_slot(entries[i < n_runs ? i : n_runs - 1] & 0xFFFu); };
     // DEPTH loads in flight per thread; the loop is unrolled by DEPTH so that each load keeps its registers
     if (n_runs > 0) {
-        if (n_runs != a.pass.ngroups) {                               // not the products asked for above
+        if (!EARLY || n_runs != a.pass.ngroups) {                             // not the products asked for above
 #pragma unroll
             for (int d = 0; d < DEPTH; ++d) v[d] = load_run(d);
         }

@@ -1067,7 +1067,7 @@ hipError_t launch_split(const double* X0, int64_t ldv0, int64_t es0, const Opera
     if (pl.kb > MAX_K_BLOCK_IN_REGISTERS) return launch_split_long(a, fmt, pl.T, st);
     const int64_t octets = pl.chunks * pl.epc / 8;                              // per vector and block, padded
     // Eight elements per thread while a workgroup has threads for them, sixteen beyond: with two exchanges per vector the waves are
-    // not held up by each other, and 80 registers let six of them share a SIMD (sixteen elements need 130).  Both operands, us:
+    // not held up by each other, and 80 to 86 registers let five or six of them share a SIMD (sixteen elements need 130).  Both operands, us:
     // 16384 + 8192 vectors of 1024, 13 FP8 slices: 116, 120 with sixteen per lane and no barrier; 96 + 6000 of 4097, 9 INT8 slices:
     // 152 and 217; 2 x 8192 of 8192, 16 FP8 slices: 990 and 960 (1024 threads of eight leave a CU no second workgroup).
     if (fmt == FMT_FP16 ? pl.b > 7 : octets <= 32) return launch_split_short(a, fmt, pl.T, st);
