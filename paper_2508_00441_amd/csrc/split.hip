@@ -9,13 +9,14 @@
 // binade whose unit in the last place is 2^(rho+c-53) = 2^(c-b), sigma is an even multiple of that unit,
 // so the FP64 addition rounds x to the nearest multiple of 2^(c-b) with ties to even q, and the
 // subtraction of sigma is exact.  The kernels compute the same q with integers; no FP64 instruction is executed.
-//   * Slices of at most 7 bits (FP8, FP6, INT8, FP16 in blocks of more than 256 elements): all slices of an element are read off one
-//     96-bit fixed-point number as long as the units follow the regular ladder (slice_digits.hpp, slice_vectors); blocks beyond
-//     16384 elements in two kernels (long_exponents_kernel, split_stream_kernel), the second of which carries the remainders from
-//     slice to slice where the units are off the ladder (slice_element.hpp).
+//   * Slices of at most 7 bits, blocks of up to 16384 elements: the slices of an element are read off one 96-bit fixed-point number, and the exponents of all of
+//     them off one OR over the vector (slice_digits.hpp, slice_vectors).
+//   * Longer blocks in two kernels (long_exponents_kernel, split_stream_kernel), the second of which carries the remainders from
+//     slice to slice where the units do not follow the regular ladder (slice_element.hpp).
 //   * Wider FP16 slices: slice by slice, once an element is within reach of the current unit as the signed 64-bit number
 //     x^(p) / 2^(c-b) with 60-b fraction bits, until then as its significand and exponent (decode_element, slice_element).
-// HBM sees each input element once (long blocks: two or three times) and each slice code once.
+// HBM sees each input element once (long blocks: two or three times; a vector whose slices reach below 96 bits once more per 96) and
+// each slice code once.
 #include <string.h>
 
 #include "layout.hpp"
@@ -70,9 +71,6 @@ struct SplitArgs {
     DigitLadder ladder;    // of b
     int* flags;            // [0]: non-finite input seen; [1]: slice count (count-only mode)
 };
-
-constexpr int NO_ELEM = -(1 << 30);
-static_assert(NO_ELEM == NO_CANDIDATE, "the two slicers share the reduction");
 
 constexpr int ACTIVE = 0x7FFF;
 
@@ -250,33 +248,28 @@ __device__ __forceinline__ int ceil_log2_scaled(uint64_t v, int unit, int F) {
     return unit - F + L - (((v & (v - 1)) == 0) ? 1 : 0);
 }
 
-// Maximum over the 64 lanes of a wave (of int or uint32_t), returned to all of them: data-parallel-primitive steps inside rows of 16 lanes
-// (swap inside pairs, pairs inside quads, mirror the half rows, mirror the rows), then the last lane of a row is
-// passed on to the next row(s), and lane 63 holds the maximum.
-template <typename V>
-__device__ __forceinline__ V wave_max(V v) {
-    static_assert(sizeof(V) == 4, "one register per lane");
-    auto step = [](V x, int y) { return (V)y > x ? (V)y : x; };
-    v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0xB1, 0xF, 0xF, false));      // quad_perm [1,0,3,2]
-    v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x4E, 0xF, 0xF, false));      // quad_perm [2,3,0,1]
-    v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x141, 0xF, 0xF, false));     // row_half_mirror
-    v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x140, 0xF, 0xF, false));     // row_mirror
-    v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x142, 0xA, 0xF, false));     // row_bcast15 into rows 1 and 3
-    v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x143, 0xC, 0xF, false));     // row_bcast31 into rows 2 and 3
-    return (V)__builtin_amdgcn_readlane((int)v, 63);
-}
-
-// The bitwise OR, in the same steps
-__device__ __forceinline__ uint32_t wave_or(uint32_t v) {
-    auto step = [](uint32_t x, int y) { return x | (uint32_t)y; };
-    v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0xB1, 0xF, 0xF, false));
-    v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x4E, 0xF, 0xF, false));
-    v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x141, 0xF, 0xF, false));
-    v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x140, 0xF, 0xF, false));
-    v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x142, 0xA, 0xF, false));
-    v = step(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x143, 0xC, 0xF, false));
+// Maximum and bitwise OR over the 64 lanes of a wave, returned to all of them: data-parallel-primitive steps inside rows of 16 lanes
+// (swap inside pairs, pairs inside quads, mirror the half rows, mirror the rows), then the last lane of a row is passed on to the next
+// row(s), and lane 63 holds the result.  A row that a step leaves out takes part with 0, which lets the compiler make one instruction of
+// the move and the operation.
+template <typename F>
+__device__ __forceinline__ uint32_t wave_combine(uint32_t v, F f) {
+    v = f(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true));       // quad_perm [1,0,3,2]
+    v = f(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true));       // quad_perm [2,3,0,1]
+    v = f(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true));      // row_half_mirror
+    v = f(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, true));      // row_mirror
+    v = f(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false));     // row_bcast15 into rows 1 and 3
+    v = f(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false));     // row_bcast31 into rows 2 and 3
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+    return wave_combine(v, [](uint32_t x, uint32_t y) { return x > y ? x : y; });
+}
+__device__ __forceinline__ uint32_t wave_or(uint32_t v) {
+    return wave_combine(v, [](uint32_t x, uint32_t y) { return x | y; });
+}
+
+__device__ __forceinline__ int wave_max(int v) { return (int)(wave_max((uint32_t)v ^ 0x80000000u) ^ 0x80000000u); }
 
 // The sum, in lane 63: the same steps; a row that a step leaves out adds zero.
 __device__ __forceinline__ int wave_sum(int v) {
@@ -305,7 +298,7 @@ __global__ void __launch_bounds__(256) slice_wide_kernel(SplitArgs a) {
     const int F = 60 - a.b, ke = 8 * lane;
     const double* const src = v.X + row * v.ldv + k0 * v.es;
     bool nonfinite = false;
-    int cmax = NO_ELEM;
+    int cmax = NO_CANDIDATE;
     int64_t tv[8];
     int pk[8];
     uint64_t bits[8];
@@ -326,8 +319,8 @@ __global__ void __launch_bounds__(256) slice_wide_kernel(SplitArgs a) {
     int c_prev = 0;
     for (int p = 0; p < a.s; ++p) {
         cmax = wave_max(cmax);
-        if (v.slices == nullptr && cmax != NO_ELEM && lane == 0) atomicMax(a.flags + 1, p + 1);      // count-only mode
-        const int c = (cmax == NO_ELEM) ? 0 : cmax;
+        if (v.slices == nullptr && cmax != NO_CANDIDATE && lane == 0) atomicMax(a.flags + 1, p + 1);      // count-only mode
+        const int c = (cmax == NO_CANDIDATE) ? 0 : cmax;
         const int unit = c - a.b;                                      // the slice's unit is 2^(c-b)
         // remainders of active elements were left in units of the previous slice: rescale them to this one (a
         // left shift, exact and inside 2^60 because every remainder is at most 2^c; 0 << anything stays 0)
@@ -335,7 +328,7 @@ __global__ void __launch_bounds__(256) slice_wide_kernel(SplitArgs a) {
         rescale = rescale < 0 ? 0 : (rescale > 63 ? 63 : rescale);
         c_prev = c;
         uint64_t rmax = 0;                                             // largest |remainder| of this thread's active elements
-        int cdorm = NO_ELEM;                                           // largest cd of its still dormant elements
+        int cdorm = NO_CANDIDATE;                                           // largest cd of its still dormant elements
         int l1 = 0, qs[8];
         const int64_t round_bias = ((int64_t)1 << (F - 1)) - 1;
 #pragma unroll
@@ -423,15 +416,15 @@ __device__ __forceinline__ void store_slice_codes(const int (&q)[G], bool stores
     }
 }
 
-// Slices of at most 7 bits (FP8, FP6, INT8, FP16 in blocks of 1024 elements and more) of blocks of up to 16384 elements, along
-// ladders of units (slice_digits.hpp): the largest element gives the first exponent, one OR over the vector tells how many of the
-// following slices keep to the ladder, and these are read off each element's 96-bit number without any exchange; where a vector
-// leaves the ladder, the next exponent is found from the remainders and another ladder starts there (the inputs are read again).
-// What bounds it: memory, mostly.  About 60 integer instructions per element and 5 per element and slice, against 22 per element and
-// slice and a maximum over the vector for each slice when the remainders were carried from slice to slice: 2 x 4096 vectors of 4096,
-// 13 FP8 slices, 265 -> 160 us (704 MB: 4.4 of the 4.7 TB/s of a large copy); 2 x 8192 of 8192, 16 slices, 1300 -> 960 us; 2 x 256 of
-// 256, 12 slices, 9.5 -> 6.5 us; 96 + 6000 of 4097, 9 INT8 slices, 245 -> 152 us.  FP6 slices, whose 16- and 8-byte pieces of a
-// vector lie in three planes, take 330 us as before at 2 x 4096 of 4096.
+// Slices of at most 7 bits, blocks of up to 16384 elements (slice_digits.hpp): the largest element gives the first exponent, one OR over the vector those of the
+// following slices, and the slices are read off each element's 96-bit number without any further exchange.  Where they reach below
+// the number, the next exponent is found from the remainders, which are formed anew from the inputs, and another number starts there.
+// What bounds it: memory, mostly.  About 65 integer instructions per element and 5 per element and slice, 3 more for each move of the
+// numbers (every D = 31 / (b + 1) regular slices, or where a unit lies further down), against 22 per element and slice and a maximum
+// over the vector for each slice when the remainders were carried from slice to slice.  4096 vectors of 4096, 13 FP8 slices, us, with
+// the differences of the exponents: dense vectors 133 carrying remainders, 85 now; one non-zero element per vector 150 and 92 (388 when
+// each irregular unit took another reading of the vector, another maximum and another number); 2 non-zeros 148, 88 (316), bands of 5
+// 152, 84 (183).
 // U groups of G consecutive elements per thread.  Several waves per vector: the workgroup is one vector and has only the waves that
 // hold elements; one wave: four vectors per workgroup, no barrier.
 template <int U, int TPR, int G, int FMT>
@@ -441,10 +434,10 @@ __device__ __forceinline__ void slice_vectors(const SplitArgs& a) {
     constexpr int ROWB = fmt_is_fp6(FMT) ? CHUNK_BYTES_FP6 : CHUNK_BYTES;
     constexpr bool WHOLE = TPR > 64;
     constexpr int RPB = WHOLE ? 1 : 4, WAVES = TPR / 64;
-    __shared__ uint32_t red_key[2][WAVES], red_proof[3][WAVES];
+    __shared__ uint32_t red_key[2][WAVES], red_turns[3][WAVES];
     __shared__ int l1_share[FP16 && WHOLE ? MAX_SLICES : 1][WAVES];
 
-    const int tr = WHOLE ? threadIdx.x : threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int tr = WHOLE ? threadIdx.x : threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int threads = WHOLE ? blockDim.x : 64;
     // Workgroups are handed to the eight XCDs (each with an L2 of its own) round-robin by their index.  Neighbouring
     // vectors share the cache lines of the slice layout (a line holds the 16-byte pieces of eight vectors in the
@@ -466,7 +459,7 @@ __device__ __forceinline__ void slice_vectors(const SplitArgs& a) {
     const double* const src = v.X + row * v.ldv + k0 * v.es;
     struct Group {
         uint64_t bits[G];
-        uint32_t limb[3][G];
+        uint32_t x[3][G];                                            // the numbers, word by word
         size_t at;
         Fp6Slot slot;
     };
@@ -546,12 +539,12 @@ __device__ __forceinline__ void slice_vectors(const SplitArgs& a) {
 
     auto clear = [&](Group& g) {
 #pragma unroll
-        for (int e = 0; e < G; ++e) g.limb[0][e] = g.limb[1][e] = g.limb[2][e] = 0;
+        for (int e = 0; e < G; ++e) g.x[0][e] = g.x[1][e] = g.x[2][e] = 0;
     };
-    for (int p = 0;;) {
-        int levels = 3 * l.per_limb;
+    int my_exp = 0;                                                  // lane p of the first wave: c of slice p
+    for (int p = 0; p < a.s;) {
+        uint32_t turns[3] = {0, 0, 0};
         if (left) {
-            uint32_t proof[3] = {0, 0, 0};
             auto form = [&](auto beyond) {
                 each_group([&](int u, Group& g) {
                     if (!wave_has(u)) {
@@ -560,16 +553,12 @@ __device__ __forceinline__ void slice_vectors(const SplitArgs& a) {
                     }
 #pragma unroll
                     for (int e = 0; e < G; ++e) {
-                        uint32_t x[3], w[3];
+                        uint32_t x[3];
                         uint64_t bit = g.bits[e];
                         asm volatile("" : "+v"(bit));                // keeps what the two forms share from being worked out for all elements at once
-                        digit_number<decltype(beyond)::value>(bit, c, l, x);
-                        digit_limbs(x, l, w);
+                        digit_number<decltype(beyond)::value>(bit, c, x, turns);
 #pragma unroll
-                        for (int i = 0; i < 3; ++i) {
-                            g.limb[i][e] = w[i];
-                            proof[i] |= digit_proof(w[i]);
-                        }
+                        for (int i = 0; i < 3; ++i) g.x[i][e] = x[i];
                         // two elements at a time: with all of them in flight the compiler runs out of registers
                         if (e & 1) __builtin_amdgcn_sched_barrier(0);
                     }
@@ -578,84 +567,111 @@ __device__ __forceinline__ void slice_vectors(const SplitArgs& a) {
             if (p > 0 || c < -1021) form(std::true_type{});
             else form(std::false_type{});
 #pragma unroll
-            for (int i = 0; i < 3; ++i) proof[i] = wave_or(proof[i]);
+            for (int i = 0; i < 3; ++i) turns[i] = wave_or(turns[i]);
             if constexpr (WHOLE) {
                 if ((tr & 63) == 0) {
 #pragma unroll
-                    for (int i = 0; i < 3; ++i) red_proof[i][wave] = proof[i];
+                    for (int i = 0; i < 3; ++i) red_turns[i][wave] = turns[i];
                 }
                 __syncthreads();
                 for (int w = 0; w < threads / 64; ++w) {
 #pragma unroll
-                    for (int i = 0; i < 3; ++i) proof[i] |= red_proof[i][w];
+                    for (int i = 0; i < 3; ++i) turns[i] |= red_turns[i][w];
                 }
 #pragma unroll
-                for (int i = 0; i < 3; ++i) proof[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)proof[i]);
+                for (int i = 0; i < 3; ++i) turns[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)turns[i]);
             }
-            levels = digit_levels(proof, l);
-        } else {
+        } else {                                                     // nothing left: zero codes, c := 0
             each_group([&](int, Group& g) { clear(g); });
+            c = 0;
         }
-        levels = levels < a.s - p ? levels : a.s - p;
-        if (v.slices == nullptr) {
-            // count-only mode (slicing until the remainder is zero, paragraph before Eq. 4): something is left before the last
-            // of these slices
-            if (left && tr == 0) atomicMax(a.flags + 1, p + levels);
-        } else {
-            if (tr < levels) v.exps[(t * a.s + p + tr) * v.rows_pad + row] = left ? c - tr * l.step : 0;
-            auto store_limb = [&](auto i) {
-                const int rest = levels - i * l.per_limb, fields = rest < l.per_limb ? rest : l.per_limb;
-                for (int d = 0; d < fields; ++d, dst_slice += slice_bytes) {
-                    int l1 = 0;
-                    each_group([&](int u, Group& g) {
-                        if (!wave_has(u)) return;
-                        int q[G];
+        // the slices that can be read off these numbers, in runs of regular ones
+        auto move_up = [&](int places) {
+            for (; places > 0; places -= 31) {
+                const int up = places < 31 ? places : 31;
+                each_group([&](int, Group& g) {
 #pragma unroll
-                        for (int e = 0; e < G; ++e) {
-                            q[e] = digit_of(g.limb[i][e], d, l.step);
-                            if constexpr (FP16) l1 += q[e] < 0 ? -q[e] : q[e];
-                        }
-                        const bool stores = first_of(u) < padded && (G == 8 || !fmt_is_fp6(FMT) || (tr & 1) == 0);
-                        store_slice_codes<FMT, G>(q, stores, a.b, scale, code_unit, dst_slice, g.at, g.slot);
-                    });
-                    if constexpr (FP16) {
-                        if (v.l1 != nullptr) {                       // sum |q| of the slice
-                            const int at_slice = p + i * l.per_limb + d;
-                            l1 = wave_sum(l1);
-                            if constexpr (WHOLE) {
-                                if ((tr & 63) == 0) l1_share[at_slice][wave] = l1;
-                            } else {
-                                if (tr == 0) v.l1[(t * a.s + at_slice) * v.rows_pad + row] = l1;
+                    for (int e = 0; e < G; ++e) digit_shift(g.x[2][e], g.x[1][e], g.x[0][e], up);
+                });
+            }
+        };
+        int at = 0, last = 0;                                        // places below 2^c of the run's first slice, of its last
+        bool more = true;                                            // is there a remainder after the last one?
+        while (true) {
+            int run = left ? digit_run(turns, at, l) : a.s - p;
+            run = run < a.s - p ? run : a.s - p;
+            last = at + (run - 1) * l.step;
+            int moved = 0;                                           // places, within the run
+            if (v.slices != nullptr) {
+                if (tr >= p && tr < p + run) my_exp = left ? c - at - (tr - p) * l.step : 0;
+                for (int done = 0;;) {
+                    const int fields = run - done < l.fields ? run - done : l.fields;
+                    for (int d = 0; d < fields; ++d, dst_slice += slice_bytes) {
+                        int l1 = 0;
+                        each_group([&](int u, Group& g) {
+                            if (!wave_has(u)) return;
+                            int q[G];
+#pragma unroll
+                            for (int e = 0; e < G; ++e) {
+                                q[e] = digit_of(g.x[2][e], d, l.step);
+                                if constexpr (FP16) l1 += q[e] < 0 ? -q[e] : q[e];
+                            }
+                            const bool stores = first_of(u) < padded && (G == 8 || !fmt_is_fp6(FMT) || (tr & 1) == 0);
+                            store_slice_codes<FMT, G>(q, stores, a.b, scale, code_unit, dst_slice, g.at, g.slot);
+                        });
+                        if constexpr (FP16) {
+                            if (v.l1 != nullptr) {                   // sum |q| of the slice
+                                const int at_slice = p + done + d;
+                                l1 = wave_sum(l1);
+                                if constexpr (WHOLE) {
+                                    if ((tr & 63) == 0) l1_share[at_slice][wave] = l1;
+                                } else {
+                                    if (tr == 0) v.l1[(t * a.s + at_slice) * v.rows_pad + row] = l1;
+                                }
                             }
                         }
                     }
+                    done += fields;
+                    if (done == run) break;
+                    move_up(l.fields * l.step);
+                    moved += l.fields * l.step;
                 }
-            };
-            store_limb(std::integral_constant<int, 0>{});
-            store_limb(std::integral_constant<int, 1>{});
-            store_limb(std::integral_constant<int, 2>{});
+            }
+            p += run;
+            if (p == a.s) break;
+            const int next = digit_next(turns, run, l.step);
+            more = next != NUMBER_BITS;
+            if (!digit_in_number(at + next, l.step)) break;
+            at += next;
+            move_up(next - moved);
+            for (int rest = next; rest > 0; rest -= 31) digit_shift(turns[2], turns[1], turns[0], rest < 31 ? rest : 31);
         }
-        p += levels;
-        if (p >= a.s) break;
-        if (left) {
-            uint32_t next = 0;
-            const int unit = c - (levels - 1) * l.step - a.b;
-            each_group([&](int u, Group& g) {
-                load_group(u, g.bits);
+        // count-only mode (slicing until the remainder is zero, paragraph before Eq. 4): something was left before the last of these slices
+        if (v.slices == nullptr) {
+            if (left && tr == 0) atomicMax(a.flags + 1, p);
+        }
+        if (p < a.s) {                                               // beyond the numbers, or nothing left
+            uint32_t key = 0;
+            if (more) {
+                const int unit = c - last - a.b;
+                each_group([&](int u, Group& g) {
+                    load_group(u, g.bits);
 #pragma unroll
-                for (int e = 0; e < G; ++e) {
-                    uint64_t bit = g.bits[e];
-                    asm volatile("" : "+v"(bit));
-                    const uint32_t k = remainder_key(bit, unit);
-                    next = k > next ? k : next;
-                    if (e & 1) __builtin_amdgcn_sched_barrier(0);
-                }
-            });
-            next = vector_max(next, 1);
-            left = next != 0;
-            c = (int)next - CD_BIAS;
+                    for (int e = 0; e < G; ++e) {
+                        uint64_t bit = g.bits[e];
+                        asm volatile("" : "+v"(bit));
+                        const uint32_t k = remainder_key(bit, unit);
+                        key = k > key ? k : key;
+                        if (e & 1) __builtin_amdgcn_sched_barrier(0);
+                    }
+                });
+                key = vector_max(key, 1);
+            }
+            left = key != 0;
+            c = (int)key - CD_BIAS;
         }
     }
+    if (v.slices != nullptr && tr < a.s) v.exps[(t * a.s + tr) * v.rows_pad + row] = my_exp;
     if constexpr (FP16 && WHOLE) {
         if (v.l1 != nullptr) {
             __syncthreads();
@@ -668,8 +684,13 @@ __device__ __forceinline__ void slice_vectors(const SplitArgs& a) {
     }
 }
 
+// Waves per SIMD.  The registers would let six or seven share one, but the lines of the slice layout are put together in the L2s from
+// several vectors, and more vectors in flight push them out half written: 4096 vectors
+// of 4096, 13 FP6 slices, 187 us with five and 195 with six; 4 blocks of 4096, 9 FP16 slices, 413 and 454; 13 FP8 slices 81 with six, 88 with
+// five.
+constexpr int most_waves(int U, int TPR, int fmt) { return U == 2 ? 4 : TPR < 1024 && (fmt_is_fp6(fmt) || fmt == FMT_FP16) ? 5 : 6; }
 template <int U, int TPR, int FMT>
-__global__ void __launch_bounds__((TPR < 128 ? 256 : TPR)) __attribute__((amdgpu_waves_per_eu(U == 2 ? 3 : TPR == 1024 ? 6 : 5))) split_kernel(SplitArgs a) {
+__global__ void __launch_bounds__((TPR < 128 ? 256 : TPR)) __attribute__((amdgpu_waves_per_eu(U == 2 ? 3 : 4, most_waves(U, TPR, FMT)))) split_kernel(SplitArgs a) {
     slice_vectors<U, TPR, 8, FMT>(a);
 }
 // Blocks of at most 256 elements: four elements per lane (with eight, half the lanes are idle and a thread's chain is twice as long)
@@ -686,11 +707,12 @@ __global__ void __launch_bounds__(256) slice_short_kernel(SplitArgs a) {
 // elements, 11 FP8 slices: exponents 212 us when every slice's key was formed from the whole block, 71 us now (302 MB read once at
 // 4.7 TB/s: 64 us); slices 247 us carrying remainders, 228 us now (855 MB with the padding vectors: 182 us).
 
-// Eq. 4 for all slices of one vector and block: the largest element in one reading, then ladder by ladder (slice_digits.hpp) the
-// slices that the elements prove to keep to it.  The proofs need not see the whole block: the second reading stops as soon as every
-// slice is confirmed, as a rule after the first 8192 elements.
+// Eq. 4 for all slices of one vector and block: the largest element in one reading, then the exponents of all slices from the turns of
+// the elements' bits (slice_digits.hpp).  Those of part of the block are enough where they give regular units throughout, as a rule
+// after the first 8192 elements.  1024 vectors of 65536, 11 FP8 slices, us with the slices themselves: dense 450 (752 when the exponents
+// were found slice by slice); one non-zero element 617 (4134, and 2238 with two readings for each irregular unit).
 __global__ void __launch_bounds__(1024) long_exponents_kernel(SplitArgs a) {
-    __shared__ uint32_t red_key[16], red_proof[2][3][16];
+    __shared__ uint32_t red_key[16], red_turns[2][3][16];
     const int tid = threadIdx.x, wave = tid >> 6;
     const bool second = blockIdx.x >= a.wg_first;
     const SplitVectors& v = second ? a.v[1] : a.v[0];
@@ -751,39 +773,52 @@ __global__ void __launch_bounds__(1024) long_exponents_kernel(SplitArgs a) {
     int c = 0, p = 0;
     if (left) c = top >= 0x100000u ? magnitude_exponent(top) : (int)largest_remainder(2000) - CD_BIAS;      // 2^2000: x itself
     while (left && p < a.s) {
-        uint32_t proof[3] = {0, 0, 0};
-        const int wanted = a.s - p < 3 * l.per_limb ? a.s - p : 3 * l.per_limb;
-        int levels = 1;
-        for (int64_t i = 0, turn = 0; i < klen && levels < wanted; i += 8192, turn ^= 1) {
+        uint32_t turns[3] = {0, 0, 0}, all[3];
+        int levels, at, last, my_exp = 0;                            // slices off these numbers, places of the last run's first and last
+        bool more = true;                                            // is there a remainder after them?
+        for (int64_t i = 0, turn = 0;; turn ^= 1) {
             for_chunk(i, [&](uint64_t w) {
-                uint32_t x[3], limb[3];
-                digit_number<true>(w, c, l, x);
-                digit_limbs(x, l, limb);
-#pragma unroll
-                for (int j = 0; j < 3; ++j) proof[j] |= digit_proof(limb[j]);
+                uint32_t x[3];
+                digit_number<true>(w, c, x, turns);
             });
+            i += 8192;
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
-                const uint32_t m = wave_or(proof[j]);
-                if ((tid & 63) == 0) red_proof[turn][j][wave] = m;
+                const uint32_t m = wave_or(turns[j]);
+                if ((tid & 63) == 0) red_turns[turn][j][wave] = m;
             }
             __syncthreads();                                         // (the other buffer's readers are behind the previous one)
-            uint32_t all[3] = {0, 0, 0};
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
+                all[j] = 0;
 #pragma unroll
-                for (int w = 0; w < 16; ++w) all[j] |= red_proof[turn][j][w];
+                for (int w = 0; w < 16; ++w) all[j] |= red_turns[turn][j][w];
                 all[j] = (uint32_t)__builtin_amdgcn_readfirstlane((int)all[j]);
             }
-            levels = digit_levels(all, l);
+            // more elements can only bring the units closer, to `step` places at the least
+            bool regular = true;
+            for (at = 0, levels = 0;;) {
+                int run = digit_run(all, at, l);
+                run = run < a.s - p - levels ? run : a.s - p - levels;
+                if (tid >= levels && tid < levels + run) my_exp = c - at - (tid - levels) * l.step;
+                levels += run;
+                last = at + (run - 1) * l.step;
+                if (p + levels == a.s) break;
+                const int next = digit_next(all, run, l.step);
+                regular = regular && next == run * l.step;
+                more = next != NUMBER_BITS;
+                if (!digit_in_number(at + next, l.step)) break;
+                at += next;
+                for (int rest = next; rest > 0; rest -= 31) digit_shift(all[2], all[1], all[0], rest < 31 ? rest : 31);
+            }
+            if (i >= klen || regular) break;
         }
-        levels = levels < wanted ? levels : wanted;
-        if (exps != nullptr && tid < levels) exps[(int64_t)(p + tid) * v.rows_pad] = c - tid * l.step;
+        if (exps != nullptr && tid < levels) exps[(int64_t)(p + tid) * v.rows_pad] = my_exp;
         p += levels;
         if (p >= a.s) break;
-        const uint32_t next = largest_remainder(c - (levels - 1) * l.step - a.b);
-        left = next != 0;
-        c = (int)next - CD_BIAS;
+        const uint32_t key = more ? largest_remainder(c - last - a.b) : 0u;
+        left = key != 0;
+        c = (int)key - CD_BIAS;
     }
     // nothing left: the remaining slices are zero (c := 0); without slices to write, report how many there are
     if (exps != nullptr)
@@ -828,46 +863,46 @@ __global__ void __launch_bounds__(256) split_stream_kernel(SplitArgs a) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) bits[e] = (ke + e < klen) ? (uint64_t)__double_as_longlong(src[ke + e]) : 0ull;
     }
+    const Fp6Slot slot = fp6_slot(ke, v.rows_pad, row);
     // Where the units of all slices follow one ladder (the usual case), the slices are read off one number per element.
     {
+        const DigitLadder l = a.ladder;
         const int c0 = exps[0];
-        bool on_ladder = a.s <= 3 * a.ladder.per_limb && c0 >= -1021;
-        for (int p = 1; p < a.s; ++p) on_ladder = on_ladder && exps[(int64_t)p * v.rows_pad] == c0 - p * a.ladder.step;
+        bool on_ladder = digit_in_number((a.s - 1) * l.step, l.step) && c0 >= -1021;
+        for (int p = 1; p < a.s; ++p) on_ladder = on_ladder && exps[(int64_t)p * v.rows_pad] == c0 - p * l.step;
         if (__all(on_ladder || row >= v.rows)) {
-            const DigitLadder l = a.ladder;
-            uint32_t limb[3][8];
+            uint32_t x[3][8], turns[3];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                uint32_t x[3], w[3];
-                digit_number<false>(bits[e], c0, l, x);
-                digit_limbs(x, l, w);
+                uint32_t y[3];
+                digit_number<false>(bits[e], c0, y, turns);
 #pragma unroll
-                for (int i = 0; i < 3; ++i) limb[i][e] = w[i];
+                for (int i = 0; i < 3; ++i) x[i][e] = y[i];
                 if (e & 1) __builtin_amdgcn_sched_barrier(0);
             }
             const float scale = ldexpf(1.0f, a.b), unit_value = ldexpf(1.0f, -a.b);
-            const Fp6Slot at6 = fp6_slot(ke, v.rows_pad, row);
             const size_t at = ((size_t)kc * v.rows_pad + row) * CHUNK_BYTES + (size_t)(threadIdx.x % OCTETS) * (FP16 ? 16 : 8);
-            int rest = a.s;
+            for (int p = 0; p < a.s; p += l.fields) {
+                if (p > 0) {
 #pragma unroll
-            for (int i = 0; i < 3; ++i, rest -= l.per_limb) {
-                for (int d = 0; d < l.per_limb && d < rest; ++d, dst_slice += slice_bytes) {
+                    for (int e = 0; e < 8; ++e) digit_shift(x[2][e], x[1][e], x[0][e], l.fields * l.step);
+                }
+                for (int d = 0; d < l.fields && p + d < a.s; ++d, dst_slice += slice_bytes) {
                     int q[8];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) q[e] = digit_of(limb[i][e], d, l.step);
-                    store_slice_codes<FMT, 8>(q, true, a.b, scale, unit_value, dst_slice, at, at6);
+                    for (int e = 0; e < 8; ++e) q[e] = digit_of(x[2][e], d, l.step);
+                    store_slice_codes<FMT, 8>(q, true, a.b, scale, unit_value, dst_slice, at, slot);
                 }
             }
             return;
         }
     }
-    int cmax = NO_ELEM;
+    int cmax = NO_CANDIDATE;
     bool nonfinite = false;                                          // long_exponents_kernel has reported it
     // Blocks this long leave FP16 slices 4 bits at most, so the 32-bit element step serves every format.
     const int pos = F - 32, bias = (1 << (pos - 1)) - 1;
     const uint32_t keep = ~((1u << pos) - 1u);
     const float code_scale = ldexpf(1.0f, pos + a.b), code_unit = ldexpf(1.0f, -(pos + a.b));
-    const Fp6Slot slot = fp6_slot(ke, v.rows_pad, row);
     auto store = [&](const int (&qs)[8]) {                           // qs: q * 2^pos
         if constexpr (FMT == FMT_FP8) {
             store_fp8_codes_scaled(qs, code_scale, ke, dst_slice, v.rows_pad, row);
@@ -887,7 +922,7 @@ __global__ void __launch_bounds__(256) split_stream_kernel(SplitArgs a) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) decode_narrow(bits[e], F, T[e], pk[e], cmax, nonfinite);
     int unit_prev = 0, kmax = KEY_NONE_MAX, kmin = KEY_NONE_MIN, p = 0;
-    // while some element of the wave waits for its unit, then one shift for all (as in split_kernel)
+    // while some element of the wave waits for its unit, then one shift for all
     for (bool settled = false; p < a.s && !settled; ++p, dst_slice += slice_bytes) {
         const int unit = exps[(int64_t)p * v.rows_pad] - a.b;
         const int step16 = (unit_prev - unit) * 65536;
@@ -1067,9 +1102,7 @@ hipError_t launch_split(const double* X0, int64_t ldv0, int64_t es0, const Opera
     if (pl.kb > MAX_K_BLOCK_IN_REGISTERS) return launch_split_long(a, fmt, pl.T, st);
     const int64_t octets = pl.chunks * pl.epc / 8;                              // per vector and block, padded
     // Eight elements per thread while a workgroup has threads for them, sixteen beyond: with two exchanges per vector the waves are
-    // not held up by each other, and 80 to 86 registers let five or six of them share a SIMD (sixteen elements need 130).  Both operands, us:
-    // 16384 + 8192 vectors of 1024, 13 FP8 slices: 116, 120 with sixteen per lane and no barrier; 96 + 6000 of 4097, 9 INT8 slices:
-    // 152 and 217; 2 x 8192 of 8192, 16 FP8 slices: 990 and 960 (1024 threads of eight leave a CU no second workgroup).
+    // not held up by each other, and 65 to 80 registers let six of them share a SIMD (sixteen elements need 130).
     if (fmt == FMT_FP16 ? pl.b > 7 : octets <= 32) return launch_split_short(a, fmt, pl.T, st);
     if (octets <= 64) return launch_split_cfg<1, 64>(a, fmt, pl.T, st);
     if (octets <= 128) return launch_split_cfg<1, 128>(a, fmt, pl.T, st);

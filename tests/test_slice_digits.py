@@ -60,3 +60,30 @@ def test_ladder_slices_equal_the_oracle(digits, b):
         assert np.array_equal(c, want_c[:, r]), (r, c, want_c[:, r])
         assert np.array_equal(q, want_q[:, r, :]), r
     assert ladders > X.shape[0]                              # some vectors needed more than one
+
+
+@pytest.mark.parametrize("b", [2, 3, 4, 6, 7])
+@pytest.mark.parametrize("nonzeros", [1, 2, 4, 16])
+def test_few_nonzeros_take_one_number(digits, b, nonzeros):
+    """Vectors of few non-zero elements leave the ladder at every other unit; their slices still come from one reading of the vector,
+    as long as its bits fit into 96, and one more for each further 96."""
+    rng = np.random.default_rng(700 + 10 * b + nonzeros)
+    k, rows, s = 64, 60, 33
+    X = np.zeros((rows, k))
+    for j in range(rows):
+        X[j, rng.permutation(k)[:nonzeros]] = (rng.random(nonzeros) - 0.5) * np.exp(rng.normal(0.0, 2.0 if j < rows - 8 else 30.0, nonzeros))
+    slices, cs, _ = oo.slice_rows(X, 53 - b, s)
+    want_q = np.stack([oo.slice_integers(v, b) for v in slices]).astype(np.int64)
+    want_c = np.stack(cs)
+    for r in range(rows):
+        x = np.ascontiguousarray(X[r])
+        q, c = np.empty((s, k), dtype=np.int32), np.empty(s, dtype=np.int32)
+        digits.host_slice_vector_digits(x.ctypes.data_as(ctypes.c_void_p), ctypes.c_size_t(k), b, s, q.ctypes.data_as(ctypes.c_void_p),
+                                        c.ctypes.data_as(ctypes.c_void_p))
+        assert np.array_equal(c, want_c[:, r]), (r, c, want_c[:, r])
+        assert np.array_equal(q, want_q[:, r, :]), r
+        used = np.abs(x[x != 0])
+        span = int(np.log2(used.max() / used.min())) + 1 + 53 + 2 * (b + 1)
+        assert digits.host_numbers_of_last_vector() <= 1 + span // 80, (r, span)
+        if span <= 96:
+            assert digits.host_numbers_of_last_vector() == 1, (r, span)
