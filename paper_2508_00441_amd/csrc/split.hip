@@ -460,8 +460,6 @@ __device__ __forceinline__ void slice_vectors(const SplitArgs& a) {
     struct Group {
         uint64_t bits[G];
         uint32_t x[3][G];                                            // the numbers, word by word
-        size_t at;
-        Fp6Slot slot;
     };
     Group first_group, second_group;                                 // (two variables: an array of them does not stay in single registers)
     auto each_group = [&](auto f) {
@@ -502,11 +500,11 @@ __device__ __forceinline__ void slice_vectors(const SplitArgs& a) {
         }
         return (uint32_t)__builtin_amdgcn_readfirstlane((int)key);
     };
-    each_group([&](int u, Group& g) {
-        const int64_t ke = first_of(u);
-        if constexpr (fmt_is_fp6(FMT)) g.slot = fp6_slot(ke & ~(int64_t)7, v.rows_pad, row);
-        g.at = ((size_t)(ke / EPC) * v.rows_pad + row) * CHUNK_BYTES + (size_t)(ke % EPC) * (FP16 ? 2 : 1);
-    });
+    // where the codes of the first group go inside a slice matrix; the second one's lie a whole number of chunks further on
+    const size_t at_codes = ((size_t)(first_of(0) / EPC) * v.rows_pad + row) * CHUNK_BYTES + (size_t)(first_of(0) % EPC) * (FP16 ? 2 : 1);
+    const Fp6Slot slot = fp6_slot(first_of(0) & ~(int64_t)7, v.rows_pad, row);
+    const size_t second_at = (size_t)(G * threads / EPC) * v.rows_pad * ROWB;
+    static_assert(U == 1 || G * 64 % EPC == 0, "a wave's group is a whole number of chunks");
 
     uint32_t key = 0;
     each_group([&](int u, Group& g) {
@@ -559,8 +557,8 @@ __device__ __forceinline__ void slice_vectors(const SplitArgs& a) {
                         digit_number<decltype(beyond)::value>(bit, c, x, turns);
 #pragma unroll
                         for (int i = 0; i < 3; ++i) g.x[i][e] = x[i];
-                        // two elements at a time: with all of them in flight the compiler runs out of registers
-                        if (e & 1) __builtin_amdgcn_sched_barrier(0);
+                        // two elements at a time (sixteen per thread: one): with all of them in flight the compiler runs out of registers
+                        if (U == 2 || (e & 1)) __builtin_amdgcn_sched_barrier(0);
                     }
                 });
             };
@@ -617,7 +615,7 @@ __device__ __forceinline__ void slice_vectors(const SplitArgs& a) {
                                 if constexpr (FP16) l1 += q[e] < 0 ? -q[e] : q[e];
                             }
                             const bool stores = first_of(u) < padded && (G == 8 || !fmt_is_fp6(FMT) || (tr & 1) == 0);
-                            store_slice_codes<FMT, G>(q, stores, a.b, scale, code_unit, dst_slice, g.at, g.slot);
+                            store_slice_codes<FMT, G>(q, stores, a.b, scale, code_unit, dst_slice + u * second_at, at_codes, slot);
                         });
                         if constexpr (FP16) {
                             if (v.l1 != nullptr) {                   // sum |q| of the slice
@@ -690,7 +688,7 @@ __device__ __forceinline__ void slice_vectors(const SplitArgs& a) {
 // five.
 constexpr int most_waves(int U, int TPR, int fmt) { return U == 2 ? 4 : TPR < 1024 && (fmt_is_fp6(fmt) || fmt == FMT_FP16) ? 5 : 6; }
 template <int U, int TPR, int FMT>
-__global__ void __launch_bounds__((TPR < 128 ? 256 : TPR)) __attribute__((amdgpu_waves_per_eu(U == 2 ? 3 : 4, most_waves(U, TPR, FMT)))) split_kernel(SplitArgs a) {
+__global__ void __launch_bounds__((TPR < 128 ? 256 : TPR)) __attribute__((amdgpu_waves_per_eu(4, most_waves(U, TPR, FMT)))) split_kernel(SplitArgs a) {
     slice_vectors<U, TPR, 8, FMT>(a);
 }
 // Blocks of at most 256 elements: four elements per lane (with eight, half the lanes are idle and a thread's chain is twice as long)
@@ -1102,7 +1100,7 @@ hipError_t launch_split(const double* X0, int64_t ldv0, int64_t es0, const Opera
     if (pl.kb > MAX_K_BLOCK_IN_REGISTERS) return launch_split_long(a, fmt, pl.T, st);
     const int64_t octets = pl.chunks * pl.epc / 8;                              // per vector and block, padded
     // Eight elements per thread while a workgroup has threads for them, sixteen beyond: with two exchanges per vector the waves are
-    // not held up by each other, and 65 to 80 registers let six of them share a SIMD (sixteen elements need 130).
+    // not held up by each other, and 65 to 80 registers let six of them share a SIMD (sixteen elements need 128: four).
     if (fmt == FMT_FP16 ? pl.b > 7 : octets <= 32) return launch_split_short(a, fmt, pl.T, st);
     if (octets <= 64) return launch_split_cfg<1, 64>(a, fmt, pl.T, st);
     if (octets <= 128) return launch_split_cfg<1, 128>(a, fmt, pl.T, st);

@@ -26,3 +26,19 @@ def test_lengths_at_the_thread_edges(fmt, rows, k):
         for p in range(s):
             assert np.array_equal(got_exps[0][p], ref_exps[0][p]), (is_B, p)
             assert np.array_equal(got_codes[0][p], ref_codes[0][p]), (is_B, p)
+
+
+@pytest.mark.parametrize("fmt", ["fp8", "fp6", "fp6_e3m2", "int8", "fp16"])
+@pytest.mark.parametrize("k", [12289, 16384])
+def test_many_vectors_at_sixteen_elements_per_thread(fmt, k):
+    """The longest blocks that stay in registers, with more workgroups than the chip holds at once."""
+    X = inputs.phi_matrix(24, k, 2.0, np.random.default_rng(k))
+    X[5, :] = np.where(np.arange(k) % 4000 == 7, X[5, :], 0.0)
+    X[6, :] *= np.ldexp(1.0, -(np.arange(k) // 200))
+    s, rows = 4, 2050
+    ref_codes, ref_exps, _ = oz.split_operand(X, fmt, s, 0)
+    which = np.arange(rows) % 24
+    got_codes, got_exps = _gpu_split(np.ascontiguousarray(X[which]), 1, fmt, s, 0)
+    for p in range(s):
+        assert np.array_equal(got_exps[0][p], ref_exps[0][p][which]), p
+        assert np.array_equal(got_codes[0][p], ref_codes[0][p][which]), p
