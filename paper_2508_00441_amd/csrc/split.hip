@@ -188,11 +188,13 @@ __device__ __forceinline__ void store_fp16_codes(const float (&f)[8], int64_t ke
     *reinterpret_cast<uint4*>(dst_slice + ((size_t)(ke / EPC) * v_rows_pad + row) * CHUNK_BYTES + (ke % EPC) * 2) = w;
 }
 
-// Where the eight 6-bit codes of one octet of a vector go inside a slice matrix: a 32-bit and a 16-bit store (see
-// store_codes).  The same for every slice, so a thread works it out once per octet.
+// Where the 6-bit codes of one octet of a vector go inside a slice matrix.  Four octets are the 24 bytes of a k-group: 16 in
+// one plane, 8 in another.  Octets 0, 1 and 3 of the group store eight of them each, with the neighbours' share; stored octet by octet, as
+// 4 and 2 bytes, they are twice the accesses to lines of the cache, and these are what the slicing of FP6 spends its time on.
 struct Fp6Slot {
-    size_t at32, at16;     // byte offsets from the slice matrix
-    bool low32;            // the 32-bit store takes bits 0..31 of the 48 (else bits 16..47)
+    size_t at;             // byte offset from the slice matrix
+    uint32_t low, high;    // byte selections of the two words
+    bool last, stores;     // octet 3, octets 0, 1 and 3
 };
 __device__ __forceinline__ Fp6Slot fp6_slot(int64_t ke, int64_t v_rows_pad, int64_t row) {
     const int64_t kc = ke / CHUNK_BYTES;
@@ -200,33 +202,9 @@ __device__ __forceinline__ Fp6Slot fp6_slot(int64_t ke, int64_t v_rows_pad, int6
     const size_t chunk = (size_t)kc * v_rows_pad * CHUNK_BYTES_FP6;
     const size_t p16 = chunk + ((size_t)g * v_rows_pad + row) * 16;
     const size_t p8 = chunk + (size_t)v_rows_pad * 32 + ((size_t)g * v_rows_pad + row) * 8;
-    Fp6Slot s;
-    s.at32 = j == 0 ? p16 : j == 1 ? p16 + 8 : j == 2 ? p16 + 12 : p8 + 4;
-    s.at16 = j == 0 ? p16 + 4 : j == 1 ? p16 + 6 : j == 2 ? p8 : p8 + 2;
-    s.low32 = (j & 1) == 0;
-    return s;
+    return Fp6Slot{j == 0 ? p16 : j == 1 ? p16 + 8 : p8, j == 0 ? 0x03020100u : j == 1 ? 0x05040302u : 0x01000504u,
+                   j == 0 ? 0x01000504u : j == 1 ? 0x03020100u : 0x05040302u, j == 3, j != 2};
 }
-// FP6 codes of the eight slice integers given as q * 2^pos (the slicer's upper word), stored at a precomputed slot.
-// The code of the magnitude |q| 2^(K-b) (K = 4 for E2M3, 3 for E3M2) is the magnitude itself for E2M3 and a table
-// entry for E3M2 (see encode_e2m3 / encode_e3m2); bit 5 is the sign.
-template <int FMT>
-__device__ __forceinline__ void store_fp6_codes_at_pos(const int (&qs)[8], int pos, int b, const Fp6Slot& slot, uint8_t* dst_slice) {
-    constexpr int K = FMT == FMT_FP6_E3M2 ? 3 : 4;
-    const int down = pos - (K - b);
-    uint32_t c[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const int x = qs[e];
-        const uint32_t mag = (uint32_t)(x < 0 ? -x : x) >> down;
-        const uint32_t sign = ((uint32_t)x >> 26) & 32u;
-        c[e] = (FMT == FMT_FP6_E3M2 ? (uint32_t)((0xCBA986420ull >> (4 * mag)) & 0xFull) : mag) | sign;
-    }
-    const uint32_t lo32 = c[0] | (c[1] << 6) | (c[2] << 12) | (c[3] << 18) | (c[4] << 24) | (c[5] << 30);
-    const uint32_t hi16 = (c[5] >> 2) | (c[6] << 4) | (c[7] << 10);
-    *reinterpret_cast<uint32_t*>(dst_slice + slot.at32) = slot.low32 ? lo32 : (lo32 >> 16) | (hi16 << 16);
-    *reinterpret_cast<uint16_t*>(dst_slice + slot.at16) = (uint16_t)(slot.low32 ? hi16 : lo32);
-}
-
 // INT8 codes of the eight slice integers given as q * 2^pos: the byte at bit pos of each
 __device__ __forceinline__ void store_int8_codes_at_pos(const int (&qs)[8], int pos, int64_t ke, uint8_t* dst_slice, int64_t v_rows_pad, int64_t row) {
     uint32_t w[2];
@@ -355,8 +333,8 @@ __global__ void __launch_bounds__(256) slice_wide_kernel(SplitArgs a) {
 }
 
 // Type2 codes of G consecutive slice integers (G = 8, or 4 in blocks of at most 256 elements), stored where the layout wants them.
-// scale: 2^b, code_unit: 2^-b.  at: byte offset of the codes inside a slice matrix, slot the same for FP6 (an even lane of a pair
-// with G = 4 stores its own four codes and its neighbour's).
+// scale: 2^b, code_unit: 2^-b.  at: byte offset of the codes inside a slice matrix, slot the same for FP6 (with G = 4 the even lane of a
+// pair has the octet).  Called by all lanes of a k-group, whether they store or not.
 template <int FMT, int G>
 __device__ __forceinline__ void store_slice_codes(const int (&q)[G], bool stores, int b, float scale, float code_unit, uint8_t* dst_slice, size_t at,
                                                   const Fp6Slot& slot) {
@@ -371,20 +349,24 @@ __device__ __forceinline__ void store_slice_codes(const int (&q)[G], bool stores
             c[e] = digit_min((uint32_t)v, 32u - (uint32_t)v);
             if constexpr (FMT == FMT_FP6_E3M2) c[e] += digit_min(c[e] & 31u, 4u);
         }
+        // the octet's 48 bits; with G = 4 in the even lane of a pair
         uint32_t lo32, hi16;
         if constexpr (G == 8) {
             lo32 = c[0] | (c[1] << 6) | (c[2] << 12) | (c[3] << 18) | (c[4] << 24) | (c[5] << 30);
             hi16 = (c[5] >> 2) | (c[6] << 4) | (c[7] << 10);
         } else {
             const uint32_t w = c[0] | (c[1] << 6) | (c[2] << 12) | (c[3] << 18);
-            const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0xB1, 0xF, 0xF, false);     // the other lane of the pair
+            const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0xB1, 0xF, 0xF, true);      // the other lane of the pair
             lo32 = w | (next << 24);
             hi16 = next >> 8;
         }
-        if (stores) {
-            *reinterpret_cast<uint32_t*>(dst_slice + slot.at32) = slot.low32 ? lo32 : (lo32 >> 16) | (hi16 << 16);
-            *reinterpret_cast<uint16_t*>(dst_slice + slot.at16) = (uint16_t)(slot.low32 ? hi16 : lo32);
-        }
+        // the neighbouring octets' share of the eight bytes (row shifts to the left and right, by one octet)
+        const uint32_t next_lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo32, G == 8 ? 0x101 : 0x102, 0xF, 0xF, true);
+        const uint32_t prev_hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi16, G == 8 ? 0x111 : 0x112, 0xF, 0xF, true);
+        uint2 w;                                                     // octet 0: lo32 | hi16, next_lo; 1: the upper 32 bits | next_lo; 3: prev_hi, lo32 | hi16
+        w.x = __builtin_amdgcn_perm(slot.last ? prev_hi : hi16, lo32, slot.low);
+        w.y = __builtin_amdgcn_perm(hi16, slot.last ? lo32 : next_lo, slot.high);
+        if (stores && slot.stores) *reinterpret_cast<uint2*>(dst_slice + slot.at) = w;
     } else if constexpr (FMT == FMT_FP16) {
         uint32_t w[G / 2];
 #pragma unroll
@@ -683,9 +665,9 @@ __device__ __forceinline__ void slice_vectors(const SplitArgs& a) {
 }
 
 // Waves per SIMD.  The registers would let six or seven share one, but the lines of the slice layout are put together in the L2s from
-// several vectors, and more vectors in flight push them out half written: 4096 vectors
-// of 4096, 13 FP6 slices, 187 us with five and 195 with six; 4 blocks of 4096, 9 FP16 slices, 413 and 454; 13 FP8 slices 81 with six, 88 with
-// five.
+// several vectors, and more vectors in flight push them out half written.  4096 vectors, us: 13 FP6 slices of 4096 112 with five, 122
+// with four, 143 with six; 9 FP16 slices in blocks of 4096 413 with five, 454 with six.  13 FP8 slices of 4096 82 with six, 88 with five;
+// 6000 vectors of 4097 170 and 202 (five leave one workgroup of up to 1024 threads per CU).
 constexpr int most_waves(int U, int TPR, int fmt) { return U == 2 ? 4 : TPR < 1024 && (fmt_is_fp6(fmt) || fmt == FMT_FP16) ? 5 : 6; }
 template <int U, int TPR, int FMT>
 __global__ void __launch_bounds__((TPR < 128 ? 256 : TPR)) __attribute__((amdgpu_waves_per_eu(4, most_waves(U, TPR, FMT)))) split_kernel(SplitArgs a) {
@@ -912,7 +894,10 @@ __global__ void __launch_bounds__(256) split_stream_kernel(SplitArgs a) {
             for (int e = 0; e < 8; ++e) f[e] = (float)qs[e] * code_unit;
             store_fp16_codes(f, ke, dst_slice, v.rows_pad, row);
         } else {
-            store_fp6_codes_at_pos<FMT>(qs, pos, a.b, slot, dst_slice);
+            int q[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) q[e] = qs[e] >> pos;
+            store_slice_codes<FMT, 8>(q, true, a.b, 0.0f, 0.0f, dst_slice, 0, slot);
         }
     };
     uint64_t T[8];
