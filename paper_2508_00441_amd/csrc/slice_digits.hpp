@@ -1,4 +1,4 @@
-// Slices of at most 7 bits: all slices of an element read off ONE fixed-point number, the units of a vector's slices off one OR.
+// All slices of an element read off ONE fixed-point number, the units of a vector's slices off one OR.
 //
 // The nested roundings to nearest of Eq. 5-7 at units u_0 > u_1 > ... are a signed-digit recoding of the element: every remainder
 // is x less x rounded to a multiple of the last unit (a remainder is at most half a unit, so each unit is an even multiple of the next).

@@ -9,12 +9,10 @@
 // binade whose unit in the last place is 2^(rho+c-53) = 2^(c-b), sigma is an even multiple of that unit,
 // so the FP64 addition rounds x to the nearest multiple of 2^(c-b) with ties to even q, and the
 // subtraction of sigma is exact.  The kernels compute the same q with integers; no FP64 instruction is executed.
-//   * Slices of at most 7 bits, blocks of up to 16384 elements: the slices of an element are read off one 96-bit fixed-point number, and the exponents of all of
+//   * Blocks of up to 16384 elements: the slices of an element are read off one 96-bit fixed-point number, and the exponents of all of
 //     them off one OR over the vector (slice_digits.hpp, slice_vectors).
 //   * Longer blocks in two kernels (long_exponents_kernel, split_stream_kernel), the second of which carries the remainders from
 //     slice to slice where the units do not follow the regular ladder (slice_element.hpp).
-//   * Wider FP16 slices: slice by slice, once an element is within reach of the current unit as the signed 64-bit number
-//     x^(p) / 2^(c-b) with 60-b fraction bits, until then as its significand and exponent (decode_element, slice_element).
 // HBM sees each input element once (long blocks: two or three times; a vector whose slices reach below 96 bits once more per 96) and
 // each slice code once.
 #include <string.h>
@@ -71,89 +69,6 @@ struct SplitArgs {
     DigitLadder ladder;    // of b
     int* flags;            // [0]: non-finite input seen; [1]: slice count (count-only mode)
 };
-
-constexpr int ACTIVE = 0x7FFF;
-
-// Element state shared by the two slicing kernels.  Dormant (not yet representable exactly with F fraction bits of
-// the current unit): tv = signed 53-bit significand, pk = (E + F) | (cd << 16) with x = tv * 2^E and
-// cd = ceil(log2 |x|).  Active: tv = T = x^(p) / 2^(c_p - b) * 2^F as a signed 64-bit integer (|x^(p)| <= 2^(c_p)
-// bounds |T| by 2^(b+F) = 2^60), pk = ACTIVE.  An element becomes active at the first slice whose unit 2^u satisfies
-// u <= E + F and stays so.
-__device__ __forceinline__ void decode_element(uint64_t w, int F, int64_t& tv, int& pk, int& cmax, bool& nonfinite) {
-    const int e11 = (int)((w >> 52) & 0x7FF);
-    uint64_t mm = w & 0x000FFFFFFFFFFFFFull;
-    nonfinite |= (e11 == 0x7FF);
-    int E = -1074;
-    if (e11 != 0) { mm |= 0x0010000000000000ull; E = e11 - 1075; }
-    const int L = 64 - __clzll((long long)mm);                       // bit length (0 for mm == 0)
-    const int cd = E + L - (((mm & (mm - 1)) == 0) ? 1 : 0);         // smallest c with |x| <= 2^c
-    tv = (w >> 63) ? -(int64_t)mm : (int64_t)mm;
-    pk = mm == 0 ? ACTIVE : (((E + F) & 0xFFFF) | (cd << 16));
-    cmax = (mm != 0 && cd > cmax) ? cd : cmax;
-}
-
-// Eq. 5-8 for one element of an FP16 slicing and one slice whose unit is 2^unit: returns q, leaves the exact remainder
-// in (T, st), and keeps track of the largest remainder of the active elements (rmax, in units of 2^(unit - F)) and of
-// the largest ceil(log2 |x|) of the still dormant ones (cdorm).  rescale: left shift that brings an active remainder
-// from the previous slice's unit to this one.  (Slices of at most 7 bits use slice_element.hpp instead.)
-__device__ __forceinline__ int slice_element(int64_t& tv, int& pk, int unit, int rescale, int F, int64_t round_bias, uint64_t& rmax,
-                                             int& cdorm) {
-    // The bookkeeping of dormant elements is done with selects, the 64-bit arithmetic of active ones behind ONE
-    // divergent branch: dormant elements (most of a wide-range vector during its first slices) and zeros skip it.
-    const int st = pk;
-    const bool was_active = st == ACTIVE;
-    const int ef = (int)(short)(st & 0xFFFF);
-    const bool wakes = !was_active && unit <= ef;          // representable from now on: x / 2^unit * 2^F
-    const bool active = was_active || wakes;
-    if (!active && unit - ef + F <= 53) {
-        // With b >= 8 there are fewer than 53 fraction bits: the element reaches the unit but its low bits do not
-        // fit the fixed-point form yet.  Round its integer form tv * 2^E directly, by sh = unit - E bits, and let the
-        // remainder wait on as a dormant element with the same E.
-        int64_t T = tv;
-        const int sh = unit - ef + F;                      // F < sh <= 53
-        const int64_t q64 = (T + (((int64_t)1 << (sh - 1)) - 1) + ((T >> sh) & 1)) >> sh;
-        T -= q64 << sh;
-        tv = T;
-        const uint64_t ar = (uint64_t)(T < 0 ? -T : T);
-        if (ar == 0) {
-            pk = ACTIVE;                                   // nothing left: an active zero
-        } else {
-            const int L = 64 - __clzll((long long)ar);
-            const int cd = ef - F + L - (((ar & (ar - 1)) == 0) ? 1 : 0);
-            pk = (st & 0xFFFF) | (cd << 16);
-            cdorm = cd > cdorm ? cd : cdorm;
-        }
-        return (int)q64;
-    }
-    const int cd = st >> 16;
-    cdorm = (!active && cd > cdorm) ? cd : cdorm;          // still dormant: |x| < 2^(unit-1), q = 0, remainder = x
-    pk = active ? ACTIVE : st;
-    int q = 0;
-    if (active) {
-        // an active remainder is rescaled from the previous slice's unit, a waking element is brought to this unit
-        int64_t T = tv << (was_active ? rescale : ef - unit);
-        // nearest integer to T / 2^F, ties to even (two's complement form), and the exact remainder
-        const int64_t q64 = (T + round_bias + ((T >> F) & 1)) >> F;
-        q = (int)q64;
-        T -= q64 << F;
-        const uint64_t ar = (uint64_t)(T < 0 ? -T : T);
-        rmax = ar > rmax ? ar : rmax;
-        tv = T;
-    }
-    return q;
-}
-
-// FP16 codes of the eight slice values qs[e] * 2^-b of consecutive inner indices ke .. ke+7 of vector `row`.  The hardware FP32 ->
-// FP16 and FP32 -> FP8 (OCP E4M3 on gfx950) conversions are exact in this file because every slice value is a normal number of its
-// format, or zero (code 0); FP32 arithmetic is not FP64 arithmetic, so the integer-only property of the slicer is about FP64.
-__device__ __forceinline__ void store_wide_codes(const int (&qs)[8], int64_t ke, uint8_t* dst_slice, int64_t v_rows_pad, int64_t row, int b) {
-    constexpr int EPC = CHUNK_BYTES / 2;
-    uint32_t w[4];
-#pragma unroll
-    for (int h = 0; h < 4; ++h)
-        w[h] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(ldexpf((float)qs[2 * h], -b), ldexpf((float)qs[2 * h + 1], -b)));
-    *reinterpret_cast<uint4*>(dst_slice + ((size_t)(ke / EPC) * v_rows_pad + row) * CHUNK_BYTES + (ke % EPC) * 2) = uint4{w[0], w[1], w[2], w[3]};
-}
 
 // FP8 codes of the eight values qs[e] / scale (integers times a power of two, scale a power of two): the
 // scaled FP32 -> FP8 pair conversion of gfx950 divides by the scale, so the slice integer is converted from where it
@@ -220,12 +135,6 @@ __device__ __forceinline__ void store_int8_codes_at_pos(const int (&qs)[8], int 
     *reinterpret_cast<uint2*>(dst_slice + ((size_t)(ke / CHUNK_BYTES) * v_rows_pad + row) * CHUNK_BYTES + ke % CHUNK_BYTES) = v;
 }
 
-// smallest c with v * 2^(unit - F) <= 2^c, for v != 0
-__device__ __forceinline__ int ceil_log2_scaled(uint64_t v, int unit, int F) {
-    const int L = 64 - __clzll((long long)v);
-    return unit - F + L - (((v & (v - 1)) == 0) ? 1 : 0);
-}
-
 // Maximum and bitwise OR over the 64 lanes of a wave, returned to all of them: data-parallel-primitive steps inside rows of 16 lanes
 // (swap inside pairs, pairs inside quads, mirror the half rows, mirror the rows), then the last lane of a row is passed on to the next
 // row(s), and lane 63 holds the result.  A row that a step leaves out takes part with 0, which lets the compiler make one instruction of
@@ -247,8 +156,6 @@ __device__ __forceinline__ uint32_t wave_or(uint32_t v) {
     return wave_combine(v, [](uint32_t x, uint32_t y) { return x | y; });
 }
 
-__device__ __forceinline__ int wave_max(int v) { return (int)(wave_max((uint32_t)v ^ 0x80000000u) ^ 0x80000000u); }
-
 // The sum, in lane 63: the same steps; a row that a step leaves out adds zero.
 __device__ __forceinline__ int wave_sum(int v) {
     v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false);
@@ -258,78 +165,6 @@ __device__ __forceinline__ int wave_sum(int v) {
     v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);
     v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);
     return __builtin_amdgcn_readlane(v, 63);
-}
-
-// FP16 slices of more than 7 bits (blocks of at most 256 elements): a wave per vector, eight elements per lane, the 64-bit element
-// step (see decode_element).
-__global__ void __launch_bounds__(256) slice_wide_kernel(SplitArgs a) {
-    constexpr int EPC = CHUNK_BYTES / 2;
-    const int lane = threadIdx.x & 63;
-    const bool second = blockIdx.x >= a.wg_first;
-    const SplitVectors& v = second ? a.v[1] : a.v[0];
-    const unsigned li = blockIdx.x - (second ? a.wg_first : 0u);     // dealt to the XCDs as in slice_vectors
-    const int64_t row = (int64_t)((li & ~63u) + (li & 7) * 8 + ((li >> 3) & 7)) * 4 + (threadIdx.x >> 6);
-    const int64_t t = blockIdx.y, k0 = t * a.kb, padded = a.chunks * EPC;
-    int64_t klen = a.k - k0;
-    if (klen > a.kb) klen = a.kb;
-    if (row >= v.rows) klen = 0;                                     // padding vectors are all zero
-    const int F = 60 - a.b, ke = 8 * lane;
-    const double* const src = v.X + row * v.ldv + k0 * v.es;
-    bool nonfinite = false;
-    int cmax = NO_CANDIDATE;
-    int64_t tv[8];
-    int pk[8];
-    uint64_t bits[8];
-    if (v.es == 1 && ke + 8 <= klen) {
-#pragma unroll
-        for (int h = 0; h < 4; ++h) {
-            const two_doubles w = *reinterpret_cast<const two_doubles*>(src + ke + 2 * h);
-            bits[2 * h] = w.x;
-            bits[2 * h + 1] = w.y;
-        }
-    } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) bits[e] = (ke + e < klen) ? (uint64_t)__double_as_longlong(src[(ke + e) * v.es]) : 0ull;
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) decode_element(bits[e], F, tv[e], pk[e], cmax, nonfinite);
-    if (nonfinite) atomicOr(a.flags, 1);
-    int c_prev = 0;
-    for (int p = 0; p < a.s; ++p) {
-        cmax = wave_max(cmax);
-        if (v.slices == nullptr && cmax != NO_CANDIDATE && lane == 0) atomicMax(a.flags + 1, p + 1);      // count-only mode
-        const int c = (cmax == NO_CANDIDATE) ? 0 : cmax;
-        const int unit = c - a.b;                                      // the slice's unit is 2^(c-b)
-        // remainders of active elements were left in units of the previous slice: rescale them to this one (a
-        // left shift, exact and inside 2^60 because every remainder is at most 2^c; 0 << anything stays 0)
-        int rescale = p == 0 ? 0 : c_prev - c;
-        rescale = rescale < 0 ? 0 : (rescale > 63 ? 63 : rescale);
-        c_prev = c;
-        uint64_t rmax = 0;                                             // largest |remainder| of this thread's active elements
-        int cdorm = NO_CANDIDATE;                                           // largest cd of its still dormant elements
-        int l1 = 0, qs[8];
-        const int64_t round_bias = ((int64_t)1 << (F - 1)) - 1;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            qs[e] = slice_element(tv[e], pk[e], unit, rescale, F, round_bias, rmax, cdorm);
-            l1 += qs[e] < 0 ? -qs[e] : qs[e];
-        }
-        if (v.slices != nullptr) {
-            uint8_t* const dst_slice = v.slices + (size_t)((t * a.s + p) * a.chunks) * (size_t)v.rows_pad * CHUNK_BYTES;
-            if (ke < padded) store_wide_codes(qs, ke, dst_slice, v.rows_pad, row, a.b);
-            if (lane == 0) v.exps[(t * a.s + p) * v.rows_pad + row] = c;
-        }
-        if (v.l1 != nullptr) {
-            l1 = wave_sum(l1);
-            if (lane == 0) v.l1[(t * a.s + p) * v.rows_pad + row] = l1;
-        }
-        // this thread's candidate for the next exponent: remainders are rmax * 2^(unit - F)
-        cmax = cdorm;
-        if (rmax != 0) {
-            const int ca = ceil_log2_scaled(rmax, unit, F);
-            cmax = ca > cmax ? ca : cmax;
-        }
-    }
 }
 
 // Type2 codes of G consecutive slice integers (G = 8, or 4 in blocks of at most 256 elements), stored where the layout wants them.
@@ -344,7 +179,8 @@ __device__ __forceinline__ void store_slice_codes(const int (&q)[G], bool stores
 #pragma unroll
         for (int e = 0; e < G; ++e) {
             // The magnitude in eighths is at most 16 (8); as unsigned numbers the smaller of v and 32 - v is v, or 32 (the sign) + |v|.
-            // For E2M3 that is the code (see store_fp6_codes_at_pos), for E3M2 magnitudes up to 4 count twice, others are 4 more.
+            // For E2M3 that is the code (magnitudes 0 .. 7 are subnormal, 8 .. 16 follow without a gap); for E3M2 (0, 2, 4, 6, 8, 9, .. 12)
+            // magnitudes up to 4 count twice, others are 4 more.
             const int v = q[e] << (K - b);
             c[e] = digit_min((uint32_t)v, 32u - (uint32_t)v);
             if constexpr (FMT == FMT_FP6_E3M2) c[e] += digit_min(c[e] & 31u, 4u);
@@ -398,7 +234,7 @@ __device__ __forceinline__ void store_slice_codes(const int (&q)[G], bool stores
     }
 }
 
-// Slices of at most 7 bits, blocks of up to 16384 elements (slice_digits.hpp): the largest element gives the first exponent, one OR over the vector those of the
+// Blocks of up to 16384 elements (slice_digits.hpp): the largest element gives the first exponent, one OR over the vector those of the
 // following slices, and the slices are read off each element's 96-bit number without any further exchange.  Where they reach below
 // the number, the next exponent is found from the remainders, which are formed anew from the inputs, and another number starts there.
 // What bounds it: memory, mostly.  About 65 integer instructions per element and 5 per element and slice, 3 more for each move of the
@@ -666,9 +502,9 @@ __device__ __forceinline__ void slice_vectors(const SplitArgs& a) {
 
 // Waves per SIMD.  The registers would let six or seven share one, but the lines of the slice layout are put together in the L2s from
 // several vectors, and more vectors in flight push them out half written.  4096 vectors, us: 13 FP6 slices of 4096 112 with five, 122
-// with four, 143 with six; 9 FP16 slices in blocks of 4096 413 with five, 454 with six.  13 FP8 slices of 4096 82 with six, 88 with five;
-// 6000 vectors of 4097 170 and 202 (five leave one workgroup of up to 1024 threads per CU).
-constexpr int most_waves(int U, int TPR, int fmt) { return U == 2 ? 4 : TPR < 1024 && (fmt_is_fp6(fmt) || fmt == FMT_FP16) ? 5 : 6; }
+// with four, 143 with six; 8 FP16 slices in blocks of 2048 355 with four, 376 with five, 388 with six; 13 FP8 slices of 4096 82 with
+// six, 88 with five; 6000 vectors of 4097 170 and 202 (five leave one workgroup of up to 1024 threads per CU).
+constexpr int most_waves(int U, int TPR, int fmt) { return U == 2 || fmt == FMT_FP16 ? 4 : fmt_is_fp6(fmt) && TPR < 1024 ? 5 : 6; }
 template <int U, int TPR, int FMT>
 __global__ void __launch_bounds__((TPR < 128 ? 256 : TPR)) __attribute__((amdgpu_waves_per_eu(4, most_waves(U, TPR, FMT)))) split_kernel(SplitArgs a) {
     slice_vectors<U, TPR, 8, FMT>(a);
@@ -1026,8 +862,7 @@ hipError_t launch_split_short(const SplitArgs& a_in, int fmt, int64_t T, hipStre
     SplitArgs a = a_in;
     a.wg_first = (unsigned)(a.v[0].rows_pad / 4);
     const dim3 grid(a.wg_first + (unsigned)(a.v[1].rows_pad / 4), (unsigned)T), block(256);
-    if (fmt == FMT_FP16) hipLaunchKernelGGL(slice_wide_kernel, grid, block, 0, st, a);
-    else if (fmt == FMT_FP6) hipLaunchKernelGGL((slice_short_kernel<FMT_FP6>), grid, block, 0, st, a);
+    if (fmt == FMT_FP6) hipLaunchKernelGGL((slice_short_kernel<FMT_FP6>), grid, block, 0, st, a);
     else if (fmt == FMT_FP6_E3M2) hipLaunchKernelGGL((slice_short_kernel<FMT_FP6_E3M2>), grid, block, 0, st, a);
     else if (fmt == FMT_INT8) hipLaunchKernelGGL((slice_short_kernel<FMT_INT8>), grid, block, 0, st, a);
     else hipLaunchKernelGGL((slice_short_kernel<FMT_FP8>), grid, block, 0, st, a);
@@ -1085,8 +920,9 @@ hipError_t launch_split(const double* X0, int64_t ldv0, int64_t es0, const Opera
     if (pl.kb > MAX_K_BLOCK_IN_REGISTERS) return launch_split_long(a, fmt, pl.T, st);
     const int64_t octets = pl.chunks * pl.epc / 8;                              // per vector and block, padded
     // Eight elements per thread while a workgroup has threads for them, sixteen beyond: with two exchanges per vector the waves are
-    // not held up by each other, and 65 to 80 registers let six of them share a SIMD (sixteen elements need 128: four).
-    if (fmt == FMT_FP16 ? pl.b > 7 : octets <= 32) return launch_split_short(a, fmt, pl.T, st);
+    // not held up by each other, and 65 to 80 registers let six of them share a SIMD (sixteen elements need 128: four).  FP16 in short
+    // blocks keeps eight per lane, whose codes are one 16-byte store.
+    if (octets <= 32 && fmt != FMT_FP16) return launch_split_short(a, fmt, pl.T, st);
     if (octets <= 64) return launch_split_cfg<1, 64>(a, fmt, pl.T, st);
     if (octets <= 128) return launch_split_cfg<1, 128>(a, fmt, pl.T, st);
     if (octets <= 256) return launch_split_cfg<1, 256>(a, fmt, pl.T, st);

@@ -33,7 +33,7 @@ def _halves(rng, rows, k, b):
     return X
 
 
-@pytest.mark.parametrize("b", [0, 1, 2, 3, 4, 5, 6, 7])
+@pytest.mark.parametrize("b", [0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11])
 def test_ladder_slices_equal_the_oracle(digits, b):
     rng = np.random.default_rng(300 + b)
     k, s = 180, 18
@@ -62,7 +62,7 @@ def test_ladder_slices_equal_the_oracle(digits, b):
     assert ladders > X.shape[0]                              # some vectors needed more than one
 
 
-@pytest.mark.parametrize("b", [2, 3, 4, 6, 7])
+@pytest.mark.parametrize("b", [2, 3, 4, 6, 7, 8, 11])
 @pytest.mark.parametrize("nonzeros", [1, 2, 4, 16])
 def test_few_nonzeros_take_one_number(digits, b, nonzeros):
     """Vectors of few non-zero elements leave the ladder at every other unit; their slices still come from one reading of the vector,
