@@ -50,10 +50,6 @@ struct AccArgs {
     int two_b;               // 2b: a term is (stored product) * 2^(p_frac - two_b) * 2^e
     int p_frac;              // the stored products are integer multiples of 2^-p_frac (2b; 2b - 2 for FP6 codes; 0 for INT32)
     int read_S, write_S, add_to_C;
-    const double* W;         // add_to_C: what the block is added to (C itself, or the product so far)
-    int64_t ldw;
-    uint64_t alpha, beta;    // SCALED: the result is fl(fl(alpha * P) + fl(beta * C)), of fl(alpha * P) without reading C
-    int use_beta;
     int allow_chain;         // the GEMM kernel summed tile-wide runs
     const uint8_t* starts;   // measured runs (RunCheck), or null
     int merge;               // rule "runs": merge equal-scale products of an anti-diagonal element by element
@@ -61,6 +57,11 @@ struct AccArgs {
     const int32_t* db;       // [s][rows_pad_b / 32]
     PairOrder order;
     Pass pass;
+    int early;               // the first products are asked for before the list of runs
+    const double* W;         // add_to_C: what the block is added to (C itself, or the product so far)
+    int64_t ldw;
+    uint64_t alpha, beta;    // SCALED: the result is fl(fl(alpha * P) + fl(beta * C)), of fl(alpha * P) without reading C
+    int use_beta;
 };
 
 // Verification export: is pair `pos` of anti-diagonal g (0-based position) stored on its own, i.e. does it start a run of
@@ -130,12 +131,11 @@ __device__ __forceinline__ void accumulate_body(const AccArgs& a) {
             return Words{{*reinterpret_cast<const uint32_t*>(src)}};
         }
     };
-    // The first pair of every group starts a run, whatever the exponents: the first DEPTH of those products are asked for now, and
-    // are the ones needed where the GEMM kernel stored nothing else (regular ladders).  4096^2, hardware sum: 220 -> 184 us.  Few
-    // positions, whose launches are a chain of latencies of other kinds, gain nothing and pay for the list (600^2: 12.9 -> 13.5 us).
-    constexpr bool EARLY = R == 4;
+    // The first pair of every group starts a run, whatever the exponents: where `early` says so, the first DEPTH of those products are
+    // asked for now, and are the ones needed where the GEMM kernel stored nothing else (regular ladders).  See launch_accumulate.
+    constexpr bool EARLY = R == 4 && (PINT || !EMU);
     Words v[DEPTH];
-    if (EARLY && a.pass.npairs > 0) {
+    if (EARLY && a.early && a.pass.npairs > 0) {
         int g = a.pass.g_hi, len = diag_len(a.order, g), at = 0, slot = 0;      // the group at position `at` of anti-diagonal g, whose first slot is `slot`
 #pragma unroll
         for (int d = 0; d < DEPTH; ++d) {
@@ -273,7 +273,7 @@ __device__ __forceinline__ void accumulate_body(const AccArgs& a) {
     auto load_run = [&](int i) -> Words { return load_slot(entries[i < n_runs ? i : n_runs - 1] & 0xFFFu); };
     // DEPTH loads in flight per thread; the loop is unrolled by DEPTH so that each load keeps its registers
     if (n_runs > 0) {
-        if (!EARLY || n_runs != a.pass.ngroups) {                             // not the products asked for above
+        if (!EARLY || !a.early || n_runs != a.pass.ngroups) {                             // not the products asked for above
 #pragma unroll
             for (int d = 0; d < DEPTH; ++d) v[d] = load_run(d);
         }
@@ -469,7 +469,14 @@ hipError_t launch_accumulate(const Plan& pl, const Operand& A, const Operand& B,
     // With few positions a thread's serial chain (four elements per stored run, a round trip to memory per four runs) is the
     // kernel's length: 361 positions, 21 runs, emulated 28 -> 22 us; 64 positions 18.8 -> 12.7; at 800 the two are equal, and
     // beyond that four times the entry lists and word-wide loads lose (1024 positions 26 -> 37 us).
-    const bool fine = ((pl.m + 31) / 32) * ((pl.n + 31) / 32) <= 512;
+    const int64_t positions = ((pl.m + 31) / 32) * ((pl.n + 31) / 32);
+    const bool fine = positions <= 512;
+    // Products asked for before the list of runs is there, k = 256, us: FP8, hardware sum, 4096^2, 9 slices 157 -> 142, 4 slices 89 -> 78;
+    // 2048^2 40.5 -> 36; exact 8192^2, 5 slices 637 -> 633; INT8, emulated 8192^2, 5 slices 546 -> 525, exact 706 -> 682.  Not worth it for
+    // the emulated sum of FP32 products, which does not wait for its first products and loses the waves that their registers cost
+    // (8192^2, 9 slices 728 -> 756, 4096^2 198 -> 204); nor with few positions and no more groups than are asked for at once (1024^2,
+    // 4 slices 11.3 -> 11.9; 5 to 13 slices gain, 18.7 -> 17.9 with 9).  Where runs end off the ladder the early products are thrown away.
+    a.early = positions > 1024 || (accum_mode == ACC_HW && ps.ngroups > 4);
     const dim3 grid((unsigned)(fine ? 4 * blocks : blocks)), block(256);
     auto launch = [&](auto coarse_kernel, auto fine_kernel) {
         if (fine) hipLaunchKernelGGL(fine_kernel, grid, block, 0, st, a);
