@@ -150,15 +150,6 @@ __device__ __forceinline__ void accumulate_body(const AccArgs& a) {
         }
     }
 
-    uint64_t c_old[SCALED ? R : 1];                   // the C of a scaled product, asked for early as well
-    if constexpr (SCALED) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int64_t mi = m0 + ml, nj = n0 + nl + r;
-            c_old[r] = a.use_beta && mi < a.m && nj < a.n ? reinterpret_cast<const uint64_t*>(a.C)[mi + nj * a.ldc] : 0;
-        }
-    }
-
     // exponents of the 32 rows and 32 columns: slot 0 keeps the first-slice exponent, slots p >= 1 the difference to it
     for (int idx = tid; idx < a.order.s * 32; idx += 256) {
         const int p = idx >> 5, r = idx & 31;
@@ -309,6 +300,11 @@ __device__ __forceinline__ void accumulate_body(const AccArgs& a) {
     const int64_t mi = m0 + ml;
     if (mi >= a.m) return;
     const int baseA = relA[0][ml];
+    uint64_t c_old[SCALED ? R : 1];                   // the C of a scaled product; see accumulate_scaled_kernel
+    if constexpr (SCALED) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) c_old[r] = a.use_beta && n0 + nl + r < a.n ? reinterpret_cast<const uint64_t*>(a.C)[mi + (n0 + nl + r) * a.ldc] : 0;
+    }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int64_t nj = n0 + nl + r;
@@ -337,8 +333,10 @@ __global__ void __launch_bounds__(256) accumulate_kernel(const AccArgs a) { accu
 template <int MODE, bool PINT>
 __global__ void __launch_bounds__(256) accumulate_fine_kernel(const AccArgs a) { accumulate_body<MODE, PINT, 1, 8, false>(a); }
 
-// The last block of a scaled product: combined with C here, without a pass of its own over the product and C (1000 x 777, integer
-// only: 8.6 us).
+// The last block of a scaled product: combined with C here, without a pass of its own over the product and C.  C is read after the last
+// run: asked for before the first, it took 12 to 22 registers through the whole sum, which cost the launch all that the other pass
+// had taken.  FP8, 12 slices, beta = 1, us, with a pass of its own / C read first / last: emulated 2048^2 107 / 105 / 93, 4096^2 372 / 363 /
+// 309, 1537 x 1311 67 / 68 / 61; exact 4096^2 441 / 420 / 378; hardware 4096^2 288 / 200 / 191; 1000 x 777 emulated 41 / 40 / 39.
 template <int MODE, bool PINT>
 __global__ void __launch_bounds__(256) accumulate_scaled_kernel(const AccArgs a) { accumulate_body<MODE, PINT, 4, 4, true>(a); }
 template <int MODE, bool PINT>
