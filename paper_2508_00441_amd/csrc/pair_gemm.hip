@@ -8,10 +8,15 @@ namespace {
 template <int FMT>
 __global__ void __launch_bounds__(256) pair_gemm_kernel(const GemmArgs a) { pair_gemm_body<FMT, false>(a); }
 
-// FP8: the kernel of pair_gemm_fp8.hip, whose k-steps take two stages, for problems that keep the matrix unit busy (from 256 tiles
-// on: 2 - 5 % faster; 16 tiles: 2 - 6 % slower, figures there).  An odd number of stages is filled up to an even one, which costs
-// more than the kernel gains below some fifty.
-bool fp8_long_steps(int64_t tiles, int64_t chunks) { return tiles >= 256 && (chunks % 2 == 0 || chunks >= 64); }
+// FP8: the kernel of pair_gemm_fp8.hip, whose k-steps take two stages.  GEMM, us, pair_gemm_kernel and that one:
+//   stages per pair  4096^2, 13 slices: 2 stages 289 and 303, 4 stages 391 and 389, 8 stages 603 and 598, 64 stages 3880 and 3830; 8192^2:
+//                    930 and 983, 1380 and 1375, 2357 and 2347.  A pair of one long step has no second one to fetch for.
+//   odd numbers      are filled up to even ones.  4096^2, 9 slices: 97 stages 2920 and 2970, 129 stages 3940 and 3940, 161 stages 4940 and
+//                    4890, 257 stages 7800 and 7710; 8192 x 4096: 6040 and 6080, 8066 and 8040, 10010 and 9930, 15740 and 15570.
+//   tiles            64 stages, 13 slices: 16 tiles 2 to 6 % slower, 32 tiles 526 and 528, 64 tiles 1027 and 1009, 132 tiles 2017 and
+//                    1994, 224 tiles 3420 and 3393, 240 tiles 3665 and 3619.  Below 256 the length of the groups and the size of
+//                    the blocks are chosen by estimates that are pair_gemm_kernel's (choose_gemm), so the line stays there.
+bool fp8_long_steps(int64_t tiles, int64_t chunks) { return tiles >= 256 && (chunks % 2 == 0 ? chunks >= 4 : chunks >= 160); }
 
 // Products of this size pass the caches on their way to the accumulation whatever the kernel does: their stores need not push the slices
 // out of the L2s.  16384 x 8192 x 1024 FP8: GEMM 8.83 -> 8.39 ms; 4096^2 FP6, all pairs: GEMM 4.11 -> 4.07, accumulation 0.594 -> 0.564 ms;

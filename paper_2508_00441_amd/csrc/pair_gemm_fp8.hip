@@ -9,7 +9,7 @@
 // pair_gemm_kernel<FMT_FP8>, ms: 8192 x 8192 x 8192, 16 slices 45.1 -> 43.5 (3.43 PFLOP/s); 4096 x 4096 x 4096, 13 slices 3.92 -> 3.85;
 // 16384 x 8192 x 1024, 13 slices 8.87 -> 8.39, of which 0.44 are the non-temporal stores.  Problems of few
 // tiles, which wait for their panels rather than for the matrix unit, lose (1000 x 777 x 1301 94 -> 100 us, 1024 x 1024 x 1024 101 -> 103,
-// 256 x 320 x 65536 676 -> 685): see fp8_long_steps in pair_gemm.hip.
+// 256 x 320 x 65536 676 -> 685), and so do pairs of a single step and short odd numbers of stages: see fp8_long_steps in pair_gemm.hip.
 //
 // The work items, the stage ring, the LDS swizzle, the runs and the order of the stored words are those of pair_gemm_body.hpp.  What differs:
 //   * A k-step takes two stages (128 bytes of the inner dimension): lanes 0 .. 31 hold the first, lanes 32 .. 63 the second.  A pair
@@ -128,13 +128,17 @@ __device__ __forceinline__ void pair_gemm_fp8_body(const GemmArgs& a) {
     const unsigned lane_bytes = (unsigned)(((lane >> 5) * 64 + ((lane >> 4) & 1) * 32 + (lane & 15)) * 16);
     const int qn = tn * 2 + wn, qm = tm * 2 + wm;
     const bool has_block = qn < a.quads_n && qm < a.quads_m;
+    // Non-temporal whatever the size of the products: this kernel has 256 tiles and more, 64 MiB per group, and unlike with
+    // pair_gemm_kernel (STREAMED_PRODUCT_BYTES) that is the faster form from there on.  GEMM and accumulation, us, with ordinary stores below
+    // 512 MiB and without: 4096 x 4096 x 4096, 4 slices 579 and 572, 5 slices 738 and 728, 6 slices 957 and 950, 7 slices 1242 and 1220;
+    // 5120 x 4096 x 2048, 4 slices 456 and 438; 8192 x 4096 x 512, 4 slices 341 and 337.
     auto store_tile = [&](int slot, int i, int j) {
         if (!has_block) return;
         char* base = reinterpret_cast<char*>(a.P + ((size_t)(slot * a.quads_n + qn) * a.quads_m + qm) * QUAD_ELEMS + (size_t)(i * 4 + j) * 1024);
 #pragma unroll
         for (int h = 0; h < 4; ++h) {
             v4f* const dst = reinterpret_cast<v4f*>(base + (h >> 1) * 2048 + (h & 1) * 256 + lane_bytes);
-            __builtin_nontemporal_store(acc[2 * i + (h >> 1)][2 * j + (h & 1)], dst);      // (see STREAMED_PRODUCT_BYTES: this kernel's results are large)
+            __builtin_nontemporal_store(acc[2 * i + (h >> 1)][2 * j + (h & 1)], dst);
         }
     };
     // Measured runs: tile (i, j) may only go on if its accumulators leave room for every partial sum of the next pair.
