@@ -713,8 +713,6 @@ __global__ void __launch_bounds__(256) split_stream_kernel(SplitArgs a) {
             return;
         }
     }
-    int cmax = NO_CANDIDATE;
-    bool nonfinite = false;                                          // long_exponents_kernel has reported it
     // Blocks this long leave FP16 slices 4 bits at most, so the 32-bit element step serves every format.
     const int pos = F - 32, bias = (1 << (pos - 1)) - 1;
     const uint32_t keep = ~((1u << pos) - 1u);
@@ -737,28 +735,30 @@ __global__ void __launch_bounds__(256) split_stream_kernel(SplitArgs a) {
         }
     };
     uint64_t T[8];
-    int pk[8];
+    int wait[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) decode_narrow(bits[e], F, T[e], pk[e], cmax, nonfinite);
-    int unit_prev = 0, kmax = KEY_NONE_MAX, kmin = KEY_NONE_MIN, p = 0;
+    for (int e = 0; e < 8; ++e) decode_narrow(bits[e], F, T[e], wait[e]);
+    int unit_prev = 0, p = 0;
     // while some element of the wave waits for its unit, then one shift for all
     for (bool settled = false; p < a.s && !settled; ++p, dst_slice += slice_bytes) {
         const int unit = exps[(int64_t)p * v.rows_pad] - a.b;
-        const int step16 = (unit_prev - unit) * 65536;
+        const int step = unit_prev - unit;
         unit_prev = unit;
-        int qs[8];
-        uint32_t cd_wait = 0;
+        int qs[8], longest = 0;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) qs[e] = slice_narrow(T[e], pk[e], step16, pos, bias, keep, kmax, kmin, cd_wait);
+        for (int e = 0; e < 8; ++e) {
+            qs[e] = slice_narrow(T[e], wait[e], step, pos, bias, keep);
+            longest = wait[e] < longest ? wait[e] : longest;
+        }
         store(qs);
-        settled = __ballot(cd_wait != 0) == 0ull;
+        settled = __ballot(longest < 0) == 0ull;
     }
     for (; p < a.s; ++p, dst_slice += slice_bytes) {
         const int unit = exps[(int64_t)p * v.rows_pad] - a.b, step = unit_prev - unit;
         unit_prev = unit;
         int qs[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) qs[e] = slice_narrow_active(T[e], step, pos, bias, keep, kmax, kmin);
+        for (int e = 0; e < 8; ++e) qs[e] = slice_narrow_active(T[e], step, pos, bias, keep);
         store(qs);
     }
 }
