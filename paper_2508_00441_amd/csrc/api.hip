@@ -155,7 +155,10 @@ int dgemm_core(const Plan& plan, double alpha, const double* A, int64_t lda, con
     const ScaledResult result = {alpha, beta, C, ldc};
     if (k == 0) {
         HIP_TRY(launch_fill_zero_f64(out, ldo, m, n, st));
-        if (scaled) HIP_TRY(launch_axpby(alpha, beta, c.W, ldo, C, ldc, m, n, o.accum_mode != OZAKI_ACCUM_FP64_HW, st));
+        if (scaled) {
+            Phase ph(2);
+            HIP_TRY(launch_axpby(alpha, beta, c.W, ldo, C, ldc, m, n, o.accum_mode != OZAKI_ACCUM_FP64_HW, st));
+        }
     } else {
         const PairOrder order = order_of(pl);
         int rc = run_split(pl, c, A, lda, B, ldb, true, true);

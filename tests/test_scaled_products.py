@@ -58,3 +58,24 @@ def test_scaled_call_is_the_plain_product_scaled(fmt, m, n, k, k_block, s, small
         want = alpha * P if beta == 0.0 else alpha * P + beta * C0
         assert np.array_equal(np.ascontiguousarray(got[:, :m]).view(np.uint64), want.view(np.uint64)), (alpha, beta)
     ws.close()
+
+
+@pytest.mark.parametrize("accum", ["hw", "emu"])
+def test_scaled_call_without_inner_dimension(accum):
+    """C = beta C, and its time among the accumulation's."""
+    m, n, ldc = 70, 33, 73
+    C0 = inputs.phi_matrix(n, m, 2.0, np.random.default_rng(7))
+    start = np.full((n, ldc), np.nan)
+    start[:, :m] = C0
+    Cd, X = torch.from_numpy(start).cuda(), torch.zeros(8, dtype=torch.float64, device="cuda")
+    args = (FMT["fp8"], 4, 0)
+    ws = device.Workspace(lib.ozaki_workspace_bytes_scaled(m, n, 0, *args) + 4096)
+    lib.ozaki_profile_enable(True)
+    lib.ozaki_dgemm_scaled(m, n, 0, 2.0, X, m, X, 1, -1.7, Cd, ldc, *args, ACC[accum])
+    assert lib.ozaki_last_device_status() == 0
+    assert lib.ozaki_profile_read()[1] == [0, 0, 1]
+    lib.ozaki_profile_enable(False)
+    got = Cd.cpu().numpy()
+    assert np.all(np.isnan(got[:, m:]))
+    assert np.array_equal(got[:, :m], 2.0 * 0.0 + -1.7 * C0)
+    ws.close()
