@@ -72,7 +72,7 @@ struct SplitArgs {
 
 // FP8 codes of the eight values qs[e] / scale (integers times a power of two, scale a power of two): the
 // scaled FP32 -> FP8 pair conversion of gfx950 divides by the scale, so the slice integer is converted from where it
-// sits in the slicer's upper word, without a shift or a separate scaling.  Exact for the same reason as above.
+// sits in the slicer's upper word, without a shift or a separate scaling.  Exact: q 2^-b with |q| <= 2^b is a number of the format.
 __device__ __forceinline__ void store_fp8_codes_scaled(const int (&qs)[8], float scale, int64_t ke, uint8_t* dst_slice, int64_t v_rows_pad,
                                                        int64_t row) {
     typedef short short2v __attribute__((ext_vector_type(2)));
