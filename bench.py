@@ -37,7 +37,7 @@ if ROOT not in sys.path:
 PEAK_TFLOPS = {"fp8": 5000.0, "fp16": 2500.0, "fp6": 10100.0, "int8": 5000.0}          # MI355X dense MFMA peaks (INT8: TOP/s)
 DTYPE_NAMES = {"fp8": "fp8_e4m3", "fp16": "fp16", "fp6": "fp6_e2m3", "int8": "int8"}
 DEFAULT_CONFIG = "c3_8192_fp8_emu"                      # the configuration the metric is quoted on (n = 8192)
-# HBM-side bytes of one pair_gemm_kernel launch (L2 fills + write-backs) from the rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE
+# HBM-side bytes of one launch of the pair GEMM, by name of its kernel (L2 fills + write-backs) from the rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE
 # runs summarised in profiles/ (scaled by the 1 GiB copy-calibration pass); valid for the calibrated slice count only.
 PROFILED_TRAFFIC = {}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "pair_gemm_traffic.json")
@@ -251,7 +251,8 @@ def main():
     gemm_flop_per_launch = pairs * flop * args.steps / max(launches[1], 1)      # blocks x chunks launches share the pairs
     achieved = gemm_flop_per_launch / (gemm_launch_ms * 1e-3) / 1e12
     peak = PEAK_TFLOPS[fmt]
-    traffic = PROFILED_TRAFFIC.get(f"{args.config}:{fmt}:{s}") if not args.accum else None
+    profiled = PROFILED_TRAFFIC.get(f"{args.config}:{fmt}:{s}")           # the kernel as the profiler names it, and what it moves
+    traffic = profiled if not args.accum else None
 
     out = {
         "metric": "effective FP64 TFLOPS (2mnk/t) at n=8192; % FP8 MFMA peak; max rel err",
@@ -267,7 +268,7 @@ def main():
         "step_ms": {"best": min(per_step), "median": statistics.median(per_step), "mean": sec_per_step * 1e3,
                     "eff_tflops_at_best": flop / (min(per_step) * 1e-3) / 1e12},
         "roofline": {
-            "kernel": "pair_gemm_kernel", "bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
+            "kernel": profiled["kernel"] if profiled else "slice-pair GEMM", "bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
             "frac": achieved / peak,
             "traffic": traffic["bytes_per_launch"] if traffic else None, "traffic_unit": "bytes per launch",
             "traffic_source": traffic["source"] if traffic else None,
