@@ -1,4 +1,4 @@
-"""The integer-only accumulation kernels (emulated FP64 and the fixed-point mode) and the slicing kernels must contain
+"""The integer-only accumulation kernels (emulated FP64 and the fixed-point mode), the slicing and the GEMM kernels must contain
 no FP64 instruction at all, and the hardware-FP64 accumulation kernel no FP64 multiply or fused multiply-add (the
 product is formed on the matrix unit only).  Checked on the compiler's own assembly listing of the kernels (hipcc -S
 cross-compiles without a GPU); a kernel's body runs from its label to its .Lfunc_end marker, so code behind an early
@@ -15,7 +15,12 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 F64 = r"\bv_\w*f64\w*"
 
 
+_listings = {}
+
+
 def _kernel_bodies(src, tmp_path):
+    if src in _listings:
+        return _listings[src]
     from paper_2508_00441_amd import build
     out = tmp_path / (src + ".s")
     flags = [f for f in build.FLAGS if f != "-fPIC"]
@@ -25,6 +30,7 @@ def _kernel_bodies(src, tmp_path):
     bodies = {}
     for m in re.finditer(r"^(_Z\w+):[^\n]*\n(.*?)^\.Lfunc_end\d+:", text, flags=re.S | re.M):
         bodies[m.group(1)] = m.group(2)
+    _listings[src] = bodies
     return bodies
 
 
@@ -63,3 +69,27 @@ def test_integer_only_kernels_use_no_fp64(tmp_path):
     for n, body in gemm.items():
         assert not re.search(F64, body)
         assert "v_mfma_f32_32x32x64_f8f6f4" in body or "v_mfma_f32_32x32x16_f16" in body or "v_mfma_i32_32x32x32_i8" in body
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
+def test_the_other_integer_only_kernels_use_no_fp64(tmp_path):
+    """The forms for few elements and for scaled calls, short and long blocks, and the other GEMM kernels."""
+    acc = _kernel_bodies("accumulate.hip", tmp_path)
+    for name in ("accumulate_fine_kernel", "accumulate_scaled_kernel", "accumulate_scaled_fine_kernel"):
+        for pint in ("Lb0E", "Lb1E"):
+            for mode in (1, 2):
+                assert not re.search(F64, _only(acc, f"{name}ILi{mode}E{pint}")), (name, mode, pint)
+            used = set(re.findall(r"\b(v_\w*f64\w*)", _only(acc, f"{name}ILi0E{pint}")))
+            ops = "add|ldexp|cvt|mul" if "scaled" in name else "add|ldexp|cvt"
+            assert used and all(re.match(rf"v_({ops})_", u) for u in used), used         # no fused multiply-add
+    split = _kernel_bodies("split.hip", tmp_path)
+    short = [b for n, b in split.items() if "slice_short_kernel" in n]
+    assert len(short) == 4
+    for body in short + [_only(split, "long_exponents_kernel"), _only(split, "delta_kernel")]:
+        assert not re.search(F64, body), "FP64 instruction in a slicing kernel"
+    for source, kernels, mfma in (("pair_gemm_fp8.hip", 2, r"v_mfma_f32_16x16x128_f8f6f4"), ("pair_gemm_measured.hip", None, r"v_mfma_"), ("pair_gemm_small.hip", None, r"v_mfma_")):
+        gemm = {n: b for n, b in _kernel_bodies(source, tmp_path).items() if "pair_gemm" in n}
+        assert gemm and (kernels is None or len(gemm) == kernels)
+        for n, body in gemm.items():
+            assert not re.search(F64, body), n
+            assert re.search(mfma, body), n
