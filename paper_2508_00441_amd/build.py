@@ -15,7 +15,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJDIR = os.path.join(CSRC, "_build")
 LIB = os.path.join(HERE, "libozaki.so")
-SOURCES = ["api.hip", "split.hip", "pair_gemm.hip", "pair_gemm_fp8.hip", "pair_gemm_measured.hip", "pair_gemm_small.hip", "accumulate.hip"]
+SOURCES = ["api.hip", "split.hip", "pair_gemm.hip", "pair_gemm_fp8.hip", "pair_gemm_measured.hip", "pair_gemm_small.hip", "accumulate.hip",
+           "ladder_sums.hip"] + [f"ladder_sums_{fmt}_{mode}.hip" for mode in ("emu", "exact", "hw") for fmt in ("fp8", "fp6", "fp6_e3m2", "int8")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -39,7 +40,7 @@ def _compile(src: str) -> str:
 
 def build_library(verbose: bool = True) -> str:
     os.makedirs(OBJDIR, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=4) as ex:
+    with ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(_compile, SOURCES))
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     subprocess.check_call(cmd)

@@ -37,6 +37,7 @@ namespace ozaki {
 namespace {
 
 struct AccArgs {
+    OffLadder off;           // is there anything to do?
     const float* P;          // [nz][quads_n][quads_m][QUAD_ELEMS] FP32 (or INT32) words
     uint64_t* S;             // running block sum, word w of an element at S[w * plane + element] (may be null when unused)
     double* C;
@@ -73,21 +74,6 @@ __device__ __forceinline__ bool starts_run(const PairOrder& o, int allow_chain, 
     return pos % o.group_len == 0 || !(allow_chain && pair_linked(dA, ga, dB, gb, p - 1, q + 1));
 }
 
-// fl(fl(alpha * w) + fl(beta * c)), or fl(alpha * w) alone: the scaling around the product, with the FP64
-// multiplication and addition in hardware or emulated (Section 4.2).
-template <bool EMU>
-__device__ __forceinline__ uint64_t scaled_result(uint64_t alpha, uint64_t w, uint64_t beta, int use_beta, uint64_t c) {
-    if constexpr (EMU) {
-        uint64_t t = fp64_mul_emulated(alpha, w);
-        if (use_beta) t = fp64_add_emulated(t, fp64_mul_emulated(beta, c));
-        return t;
-    } else {
-        double t = __dmul_rn(__longlong_as_double((long long)alpha), __longlong_as_double((long long)w));
-        if (use_beta) t = __dadd_rn(t, __dmul_rn(__longlong_as_double((long long)beta), __longlong_as_double((long long)c)));
-        return (uint64_t)__double_as_longlong(t);
-    }
-}
-
 // R elements per thread: 4 (one workgroup per 32 x 32 position) or 1 (four workgroups per position, each eight of its
 // columns).  DEPTH product loads are kept in flight per thread.
 // SCALED: the last step of the last block of a product C = alpha * (A B) + beta * C.
@@ -116,6 +102,7 @@ __device__ __forceinline__ void accumulate_body(const AccArgs& a) {
     const int64_t m0 = (int64_t)tm * TILE + wm * 128 + tj * 32;       // first row of C of this 32 x 32 position
     const int64_t n0 = (int64_t)tn * TILE + wn * 128 + ti * 32;       // first column
     if (m0 >= a.m || n0 >= a.n) return;               // padding only
+    if (R == 4 && on_ladder(a.off)) return;
 
     const int ml = lane & 31;
     const int nl = g4 * 8 + (lane >> 5) * 4 + r0;
@@ -434,7 +421,7 @@ unsigned grid_for(int64_t work_items) {
 hipError_t launch_accumulate(const Plan& pl, const Operand& A, const Operand& B, const PairOrder& order, const Pass& ps,
                              bool first_pass, bool last_pass, int64_t t, const float* P, uint64_t* S_io,
                              double* C, int64_t ldc, const ScaledResult* scaled, int accum_mode, int sum_rule, bool chained, const uint8_t* starts,
-                             hipStream_t st) {
+                             const OffLadder& off, hipStream_t st) {
     if (pl.tiles_m == 0 || pl.tiles_n == 0) return hipSuccess;
     AccArgs a;
     a.P = P; a.S = S_io; a.C = C; a.ldc = ldc;
@@ -447,6 +434,7 @@ hipError_t launch_accumulate(const Plan& pl, const Operand& A, const Operand& B,
     a.p_frac = pl.p_frac;
     a.allow_chain = chained ? 1 : 0;
     a.starts = starts;
+    a.off = off;
     a.merge = (sum_rule == SUM_RUNS || accum_mode == ACC_EXACT) ? 1 : 0;
     a.da = A.deltas != nullptr ? A.deltas + (size_t)t * (A.rows_pad / LINK_ROWS) * pl.s : nullptr;
     a.db = B.deltas != nullptr ? B.deltas + (size_t)t * (B.rows_pad / LINK_ROWS) * pl.s : nullptr;
@@ -468,7 +456,8 @@ hipError_t launch_accumulate(const Plan& pl, const Operand& A, const Operand& B,
     // kernel's length: 361 positions, 21 runs, emulated 28 -> 22 us; 64 positions 18.8 -> 12.7; at 800 the two are equal, and
     // beyond that four times the entry lists and word-wide loads lose (1024 positions 26 -> 37 us).
     const int64_t positions = ((pl.m + 31) / 32) * ((pl.n + 31) / 32);
-    const bool fine = positions <= 512;
+    // (Not behind launch_ladder_sums, which as a rule leaves nothing to do: the question alone takes 0.3 us of the smallest calls.)
+    const bool fine = positions <= 512 && off.counts == nullptr;
     // Products asked for before the list of runs is there, k = 256, us: FP8, hardware sum, 4096^2, 9 slices 157 -> 142, 4 slices 89 -> 78;
     // 2048^2 40.5 -> 36; exact 8192^2, 5 slices 637 -> 633; INT8, emulated 8192^2, 5 slices 546 -> 525, exact 706 -> 682.  Not worth it for
     // the emulated sum of FP32 products, which does not wait for its first products and loses the waves that their registers cost

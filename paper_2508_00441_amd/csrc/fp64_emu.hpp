@@ -221,6 +221,43 @@ struct RoundedSum {
     OZAKI_HD uint64_t value() const { return int53_scaled_to_fp64(x, ex); }
 };
 
+// The same sum, for terms that come with rising scales e2 and |v| < 2^31, without a branch: RoundedSum::add where the term's unit is
+// not below the sum's.  A term and a sum that do not fit 64 bits together in the sum's unit: the sum is cut to a coarser one, by r
+// bits, with a sticky lowest bit (floor and sticky of the two's-complement number: an odd integer, and the exact one lies between
+// the same even integers); the term's leading bit is then at position 60, so at least 7 bits are rounded away, no boundary of which is
+// odd.  |x| <= 2^53: a cut by 63 bits leaves the same as a longer one.  MOST_D: no term's unit is further above the sum's.
+struct LadderAdd {
+    int64_t x;
+    int ex;
+
+    template <int MOST_D>
+    OZAKI_HD void add(int v, int e2) {
+        const int d = e2 - ex, nv = 32 - clz32(((uint32_t)v ^ (uint32_t)(v >> 31)) | 1u);      // |v| <= 2^nv
+        int r = nv + d - 61;
+        r = r > 0 ? r : 0;
+        if (MOST_D > 60) r = v == 0 ? 0 : r;                    // (below, a zero term never gets there)
+        const int cut = MOST_D > 92 && r > 63 ? 63 : r;
+        const int64_t kept = x >> cut;
+        const int64_t xs = kept | (int64_t)((uint64_t)x != (uint64_t)kept << cut);
+        const int64_t t = (int64_t)((uint64_t)xs + ((uint64_t)(int64_t)v << ((d - r) & 63)));
+        const uint32_t hi = (uint32_t)((uint64_t)t >> 32), flipped = hi ^ (uint32_t)((int32_t)hi >> 31);
+        int drop = 11 - clz32(flipped | 1u);                    // bits beyond 53
+        drop = drop > 0 ? drop : 0;
+        const uint32_t some = drop < 1 ? (uint32_t)drop : 1u, odd = (uint32_t)t >> drop;
+        const uint32_t half = ((1u << drop) >> 1) - (some & ~odd);      // 2^(drop - 1), one less if the last kept bit is even; 0 if none is dropped
+        x = (t + (int64_t)half) >> drop;                        // may reach +-2^53
+        ex += r + drop;
+    }
+    // The sum times 2^base as FP64 bits, flushed / saturated outside the normal range like int53_scaled_to_fp64.
+    OZAKI_HD uint64_t value(int base) const {
+        const uint64_t sx = (uint64_t)(x >> 63), a = ((uint64_t)x ^ sx) - sx;
+        const int top = 63 - clz64(a | 1u), e = 1023 + top + ex + base;
+        const uint64_t sig = (a << (53 - top)) >> 1;            // top == 53 only for 2^53 itself
+        uint64_t r = e <= 0 ? 0 : e >= 2047 ? F64_INF : (uint64_t)(uint32_t)e << 52 | (sig & F64_FRAC);
+        return a == 0 ? 0 : r | (sx & F64_SIGN);
+    }
+};
+
 // A 192-bit two's-complement fixed-point accumulator: the exact sum of terms v * 2^sh units (v an integer of at most
 // 2^36 in magnitude, sh <= 144), rounded to FP64 once at the end.  1024 such terms stay below 2^190: no overflow.
 struct Fixed192 {
@@ -294,6 +331,23 @@ struct Fixed192 {
         return sign | rbits;
     }
 };
+
+#if defined(__HIPCC__)
+// fl(fl(alpha * w) + fl(beta * c)), or fl(alpha * w) alone: the scaling around the product, with the FP64
+// multiplication and addition in hardware or emulated (Section 4.2).
+template <bool EMU>
+__device__ __forceinline__ uint64_t scaled_result(uint64_t alpha, uint64_t w, uint64_t beta, int use_beta, uint64_t c) {
+    if constexpr (EMU) {
+        uint64_t t = fp64_mul_emulated(alpha, w);
+        if (use_beta) t = fp64_add_emulated(t, fp64_mul_emulated(beta, c));
+        return t;
+    } else {
+        double t = __dmul_rn(__longlong_as_double((long long)alpha), __longlong_as_double((long long)w));
+        if (use_beta) t = __dadd_rn(t, __dmul_rn(__longlong_as_double((long long)beta), __longlong_as_double((long long)c)));
+        return (uint64_t)__double_as_longlong(t);
+    }
+}
+#endif
 
 // x * 2^e2 on FP64 bits (zeros stay zeros; the result is flushed / saturated outside the normal range).
 OZAKI_HD uint64_t fp64_scale_pow2_emulated(uint64_t x, int e2) {

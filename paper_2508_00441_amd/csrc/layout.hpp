@@ -306,13 +306,46 @@ __host__ __device__ inline void acc_order_to_mn(int idx, int& m_in_block, int& n
     m_in_block = (sub & 3) * 32 + (lane & 31);
 }
 
+// ---- tiles done by ladder_sums.hpp ----------------------------------------------------------------------------
+constexpr int LADDER_TILE = 64;
+// Slice counts that have a kernel (each takes time to build): what the formats need for full accuracy and less, of all pairs the counts of
+// the paper's Table 2 and their neighbours.  Accumulators for 16 anti-diagonals would fit, but not with what else a wave keeps.
+constexpr int ladder_min_slices(int fmt, bool full) { return fmt == FMT_FP6_E3M2 ? (full ? 13 : 10) : fmt == FMT_INT8 ? (full ? 7 : 6) : full ? 10 : 6; }
+constexpr int ladder_max_slices(int fmt, bool full) { return fmt == FMT_FP6_E3M2 ? 15 : fmt == FMT_INT8 ? (full ? 9 : 11) : full ? 12 : 14; }
+inline int64_t ladder_blocks(int64_t extent) { return (extent + LADDER_TILE - 1) / LADDER_TILE; }
+// Magnitude bits of a slice entry where the window holds an anti-diagonal of four pairs or more: the format's own limit
+constexpr int ladder_bits(int fmt) { return fmt == FMT_INT8 ? 6 : fmt == FMT_FP6_E3M2 ? 3 : 4; }
+// The launch's limits: accumulators for the anti-diagonals, 32-bit offsets in an operand's slices, anti-diagonals whose sums are
+// exact in the accumulators whatever the data.
+inline bool ladder_possible(const Plan& pl) {
+    const int64_t rows = pl.m_pad > pl.n_pad ? pl.m_pad : pl.n_pad, most = (int64_t)1 << 31;
+    return pl.fmt != FMT_FP16 && pl.s >= ladder_min_slices(pl.fmt, pl.full != 0) && pl.s <= ladder_max_slices(pl.fmt, pl.full != 0) && pl.run_limit >= pl.s && pl.b == ladder_bits(pl.fmt) && pl.m > 0 && pl.n > 0 &&
+           pl.chunks < most / (rows * pl.row_bytes * pl.s) && ladder_blocks(pl.m) * ladder_blocks(pl.n) < most;
+}
+// The exact mode keeps an element in 128 bits there: all terms fit, and none lies below the unit at which the 192 bits end.
+constexpr bool ladder_exact_fits(int fmt, int s, bool full) {
+    const int above = (ladder_bits(fmt) + 1) * (full ? 2 * s - 2 : s - 1);
+    return 31 + above + 1 <= 127 && above <= EXACT_WINDOW_BITS;
+}
+// How many vectors of the two operands are off the ladder (launch_deltas; the slicing kernels clear the counts).  Up to `limit` of each:
+// ladder_sums.hpp does the call's products, beyond that the GEMM kernels and the accumulation, which come behind it.
+struct OffLadder {
+    const int* counts;       // null: no such distinction, the latter do all
+    int limit;
+};
+#if defined(__HIPCC__)
+__device__ __forceinline__ bool on_ladder(const OffLadder& o) { return o.counts != nullptr && o.counts[0] <= o.limit && o.counts[1] <= o.limit; }
+#endif
+constexpr int OFF_LADDER_FLAG = 4;        // the counts' place in the flag words
+
 // ---- launchers (each enqueues on `st` and returns the launch status) ----------------------------------------
 hipError_t launch_transpose(const double* A, int64_t lda, int64_t m, int64_t k, double* At, hipStream_t st);
 
 // Vector r of an operand starts at X + r*ldv and has k entries, contiguous ones in the second operand, `es0` apart in the
 // first (1 for blocks beyond MAX_K_BLOCK_IN_REGISTERS).  Writes the internal layout of
 // up to two operands in one launch (a null Operand, or one without vectors, is skipped).  Blocks longer than
-// MAX_K_BLOCK_IN_REGISTERS take two launches: the exponents of all slices first, then the slices.
+// MAX_K_BLOCK_IN_REGISTERS take two launches: the exponents of all slices first, then the slices.  Clears OffLadder's counts (blocks beyond
+// 256 elements).
 hipError_t launch_split(const double* X0, int64_t ldv0, int64_t es0, const Operand* op0, const double* X1, int64_t ldv1, const Operand* op1,
                         const Plan& pl, int* flags, hipStream_t st);
 
@@ -323,17 +356,18 @@ hipError_t launch_count_slices(const double* X, int64_t ldv, const Plan& pl, int
 // Internal layout -> plain vector-major codes (verification export).
 hipError_t launch_export_slices(const Plan& pl, const Operand& op, void* out, hipStream_t st);
 
-// Fills Operand::deltas from Operand::exps, for up to two operands in one launch.
-hipError_t launch_deltas(const Plan& pl, const Operand* op0, const Operand* op1, hipStream_t st);
+// Fills Operand::deltas from Operand::exps, for up to two operands in one launch, and counts the vectors off the ladder (OffLadder::counts) if
+// that is not null.
+hipError_t launch_deltas(const Plan& pl, const Operand* op0, const Operand* op1, int* off_ladder, hipStream_t st);
 
 // Products of the pairs of pass `ps` of block t into P ([ps.npairs][quads_n][quads_m][QUAD_ELEMS] floats).  With
 // allow_chain, consecutive pairs of a group that are linked for a tile (pair_linked) form a run whose exact sum is
 // stored in the slot of the run's first pair; the slots of the other pairs of the run are left untouched.
 hipError_t launch_pair_gemm(const Plan& pl, const Operand& A, const Operand& B, const PairOrder& order, const Pass& ps,
-                            bool allow_chain, const RunCheck& check, int64_t t, float* P, hipStream_t st);
+                            bool allow_chain, const RunCheck& check, const OffLadder& off, int64_t t, float* P, hipStream_t st);
 // The same in 128 x 128 blocks (Plan::small_tiles; called by launch_pair_gemm).  Blocks without real elements are left out.
 hipError_t launch_pair_gemm_small(const Plan& pl, const Operand& A, const Operand& B, const PairOrder& order, const Pass& ps,
-                                  bool allow_chain, const RunCheck& check, int64_t t, float* P, hipStream_t st);
+                                  bool allow_chain, const RunCheck& check, const OffLadder& off, int64_t t, float* P, hipStream_t st);
 
 // C = alpha * (A B) + beta * C, formed where the last block's sum is added (one rounding per operation, no fused multiply-add;
 // beta == 0: C is not read).
@@ -352,7 +386,12 @@ struct ScaledResult {
 hipError_t launch_accumulate(const Plan& pl, const Operand& A, const Operand& B, const PairOrder& order, const Pass& ps,
                              bool first_pass, bool last_pass, int64_t t, const float* P, uint64_t* S_io,
                              double* C, int64_t ldc, const ScaledResult* scaled, int accum_mode, int sum_rule, bool chained,
-                             const uint8_t* starts, hipStream_t st);
+                             const uint8_t* starts, const OffLadder& off, hipStream_t st);
+
+// Products and sums of block t if all vectors are on the ladder (ladder_sums.hpp).  S: with all pairs, work memory for the sum of the less significant half, SUM_WORDS_MAX words per
+// element of the tiles.  The other arguments as in launch_accumulate.
+hipError_t launch_ladder_sums(const Plan& pl, const Operand& A, const Operand& B, int64_t t, const OffLadder& off, uint64_t* S, double* C,
+                              int64_t ldc, const ScaledResult* scaled, int accum_mode, hipStream_t st);
 
 // P in accumulator order -> [nz][n][m] column-major matrices (verification export): FP32 values of Eq. 10-11, or INT32
 // integers for INT8 slices.  run_len_out (may be null): for every element and pair slot of the pass, how many pairs'

@@ -26,9 +26,9 @@ constexpr double STREAMED_PRODUCT_BYTES = 512.0 * (1 << 20);
 }  // namespace
 
 hipError_t launch_pair_gemm(const Plan& pl, const Operand& A, const Operand& B, const PairOrder& order, const Pass& ps,
-                            bool allow_chain, const RunCheck& check, int64_t t, float* P, hipStream_t st) {
+                            bool allow_chain, const RunCheck& check, const OffLadder& off, int64_t t, float* P, hipStream_t st) {
     if (ps.ngroups <= 0 || pl.tiles_m == 0 || pl.tiles_n == 0 || pl.chunks == 0) return hipSuccess;
-    if (pl.small_tiles) return launch_pair_gemm_small(pl, A, B, order, ps, allow_chain, check, t, P, st);
+    if (pl.small_tiles) return launch_pair_gemm_small(pl, A, B, order, ps, allow_chain, check, off, t, P, st);
     GemmArgs a;
     const size_t slice_a = (size_t)pl.chunks * A.rows_pad * pl.row_bytes, slice_b = (size_t)pl.chunks * B.rows_pad * pl.row_bytes;
     a.sa = A.slices + (size_t)t * pl.s * slice_a;
@@ -48,6 +48,7 @@ hipError_t launch_pair_gemm(const Plan& pl, const Operand& A, const Operand& B, 
     a.pair_bound = pl.pair_bound;
     a.sure = pl.run_limit;
     a.unit = ldexpf(1.0f, -pl.p_frac);
+    a.off = off;
     const int64_t blocks = (int64_t)ps.ngroups * pl.tiles_m * pl.tiles_n;
     if (blocks > 0x7FFFFFFF || pl.chunks > 0x7FFFFFFF) return hipErrorInvalidValue;
     a.work = work_order(ps.npairs, ps.ngroups, longest_group(order, ps), 32, a.tiles_m, a.tiles_n, pl.chunks);

@@ -49,6 +49,7 @@
 namespace ozaki {
 
 struct GemmArgs {
+    OffLadder off;           // is there anything to do?
     const uint8_t* sa;       // A slices of the block: [s][chunks][rows_pad_a][row bytes]
     const uint8_t* sb;       // B slices of the block
     float* P;                // [nz][quads_n][quads_m][QUAD_ELEMS]
@@ -135,6 +136,7 @@ __device__ __forceinline__ void pair_gemm_body(const GemmArgs& a) {
     // one workgroup = one tile of one group of pairs (p0 + j, q0 - j), j < glen
     const WorkItem item = work_item(blockIdx.x, gridDim.x, a.work, a.tiles_m, a.tiles_n);
     const int tn = item.bn, tm = item.bm;
+    if (on_ladder(a.off)) return;
     const Group grp = listed_group(a.groups, a.order, a.pass, item.gi);
     const int glen = grp.len, p0 = grp.p0 - 1, q0 = grp.q0 - 1;       // 0-based slice indices from here on
     const int chunks = (int)a.chunks;

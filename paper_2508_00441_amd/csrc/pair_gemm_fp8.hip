@@ -39,6 +39,7 @@ __device__ __forceinline__ void pair_gemm_fp8_body(const GemmArgs& a) {
     const int wn = wave >> 1, wm = wave & 1;
     const WorkItem item = work_item(blockIdx.x, gridDim.x, a.work, a.tiles_m, a.tiles_n);
     const int tn = item.bn, tm = item.bm;
+    if (on_ladder(a.off)) return;
     const Group grp = listed_group(a.groups, a.order, a.pass, item.gi);
     const int glen = grp.len, p0 = grp.p0 - 1, q0 = grp.q0 - 1;
     const int chunks = (int)a.chunks, steps = (chunks + 1) >> 1;

@@ -27,6 +27,7 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 
 struct SmallGemmArgs {
+    OffLadder off;           // is there anything to do?
     const uint8_t* sa;       // A slices of the block: [s][chunks][rows_pad_a][row bytes]
     const uint8_t* sb;       // B slices of the block
     float* P;                // [nz][quads_n][quads_m][QUAD_ELEMS]
@@ -66,8 +67,9 @@ __device__ __forceinline__ void wait_and_barrier() {
     asm volatile("" ::: "memory");
 }
 
-template <int FMT>
-__global__ void __launch_bounds__(256, 2) pair_gemm_small_kernel(const SmallGemmArgs a) {
+template <int FMT, bool BEHIND>
+__device__ __forceinline__ void pair_gemm_small_body(const SmallGemmArgs& a) {
+    if (BEHIND && on_ladder(a.off)) return;
     constexpr bool FP16 = FMT == FMT_FP16;
     constexpr bool INT8 = FMT == FMT_INT8;
     constexpr bool HALF = FP16 || INT8;               // 16-byte fragments, two k-steps per 64-byte stage
@@ -384,10 +386,16 @@ __global__ void __launch_bounds__(256, 2) pair_gemm_small_kernel(const SmallGemm
     asm volatile("" ::: "memory");
 }
 
+template <int FMT>
+__global__ void __launch_bounds__(256, 2) pair_gemm_small_kernel(const SmallGemmArgs a) { pair_gemm_small_body<FMT, false>(a); }
+// Behind launch_ladder_sums (the question whether there is anything to do takes 0.3 us of the smallest calls)
+template <int FMT>
+__global__ void __launch_bounds__(256, 2) pair_gemm_small_rest_kernel(const SmallGemmArgs a) { pair_gemm_small_body<FMT, true>(a); }
+
 }  // namespace
 
 hipError_t launch_pair_gemm_small(const Plan& pl, const Operand& A, const Operand& B, const PairOrder& order, const Pass& ps,
-                                  bool allow_chain, const RunCheck& check, int64_t t, float* P, hipStream_t st) {
+                                  bool allow_chain, const RunCheck& check, const OffLadder& off, int64_t t, float* P, hipStream_t st) {
     SmallGemmArgs a;
     const size_t slice_a = (size_t)pl.chunks * A.rows_pad * pl.row_bytes, slice_b = (size_t)pl.chunks * B.rows_pad * pl.row_bytes;
     a.sa = A.slices + (size_t)t * pl.s * slice_a;
@@ -410,15 +418,17 @@ hipError_t launch_pair_gemm_small(const Plan& pl, const Operand& A, const Operan
     a.pair_bound = pl.pair_bound;
     a.sure = pl.run_limit;
     a.unit = ldexpf(1.0f, -pl.p_frac);
+    a.off = off;
     const int64_t blocks = (int64_t)ps.ngroups * a.quads_m * a.quads_n;
     if (blocks > 0x7FFFFFFF || pl.chunks * MAX_SLICES > 0x7FFFFFFF) return hipErrorInvalidValue;
     a.work = work_order(ps.npairs, ps.ngroups, longest_group(order, ps), 64, a.quads_m, a.quads_n, pl.chunks);
     const dim3 grid((unsigned)blocks), block(256);
-    if (pl.fmt == FMT_FP16) hipLaunchKernelGGL((pair_gemm_small_kernel<FMT_FP16>), grid, block, 0, st, a);
-    else if (pl.fmt == FMT_FP6) hipLaunchKernelGGL((pair_gemm_small_kernel<FMT_FP6>), grid, block, 0, st, a);
-    else if (pl.fmt == FMT_FP6_E3M2) hipLaunchKernelGGL((pair_gemm_small_kernel<FMT_FP6_E3M2>), grid, block, 0, st, a);
-    else if (pl.fmt == FMT_INT8) hipLaunchKernelGGL((pair_gemm_small_kernel<FMT_INT8>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((pair_gemm_small_kernel<FMT_FP8>), grid, block, 0, st, a);
+    auto launch = [&](auto kernel, auto rest_kernel) { hipLaunchKernelGGL(off.counts == nullptr ? kernel : rest_kernel, grid, block, 0, st, a); };
+    if (pl.fmt == FMT_FP16) launch(pair_gemm_small_kernel<FMT_FP16>, pair_gemm_small_rest_kernel<FMT_FP16>);
+    else if (pl.fmt == FMT_FP6) launch(pair_gemm_small_kernel<FMT_FP6>, pair_gemm_small_rest_kernel<FMT_FP6>);
+    else if (pl.fmt == FMT_FP6_E3M2) launch(pair_gemm_small_kernel<FMT_FP6_E3M2>, pair_gemm_small_rest_kernel<FMT_FP6_E3M2>);
+    else if (pl.fmt == FMT_INT8) launch(pair_gemm_small_kernel<FMT_INT8>, pair_gemm_small_rest_kernel<FMT_INT8>);
+    else launch(pair_gemm_small_kernel<FMT_FP8>, pair_gemm_small_rest_kernel<FMT_FP8>);
     return hipGetLastError();
 }
 

@@ -307,6 +307,7 @@ struct Route {
     Plan pl;              // with the blocks and groups of the call's launches
     Carve c;              // c.A.deltas / c.B.deltas are null where the kernels form the links themselves
     RunCheck check;
+    OffLadder off;        // counts null: launch_ladder_sums has no part in the call
     int32_t* deltas_a;    // where the deltas would go
     int32_t* deltas_b;
 };
@@ -314,6 +315,7 @@ struct Route {
 // groups that take the least time; otherwise in the longest groups of the worst case.  False if the memory does not hold it.
 inline bool place_call(const Plan& plan, bool want_product, int sum_words, bool chained, bool as_dgemm, WorkMem wm, Route& r) {
     r.pl = plan;
+    r.off = OffLadder{nullptr, 0};
     r.check = RunCheck{nullptr, nullptr, nullptr};
     if (!carve(plan, r.c, want_product, sum_words, wm)) return false;
     if (chained && as_dgemm) r.check = place_run_check(r.pl, r.c);
@@ -327,6 +329,23 @@ inline bool place_call(const Plan& plan, bool want_product, int sum_words, bool 
     r.deltas_b = r.c.B.deltas;
     if (r.pl.small_tiles && r.c.A.l1 == nullptr) r.c.A.deltas = r.c.B.deltas = nullptr;      // a launch less
     return true;
+}
+
+// Does the call start with launch_ladder_sums?  (The GEMM kernels and the accumulation come behind it.)
+// Of short vectors some are off the ladder as a rule, and the call then takes the other route and the launch for nothing (10 us of 600 x
+// 600 x 1000).  The share of vectors off it, entries (u - 1/2) exp(phi z), 13 FP8 slices (which reach the end of the mantissas): phi = 0.5,
+// k = 256 2.3 %, k = 512 0.1 %, k = 1024 none of 2048; phi = 1, k = 64 5 %, k = 128 0.15 %, from k = 256 on none; phi = 2 0.05 to 0.2 % up
+// to k = 1024; 9 INT8 slices none from k = 64 on (from 257 here: shorter blocks have a slicing kernel of their own).  With fewer than 64
+// tiles three quarters of the compute units have no part in the work, which the GEMM kernels deal out by groups of pairs as well.
+inline bool ladder_pays(const Plan& pl) {
+    return ladder_possible(pl) && pl.kb >= (pl.fmt == FMT_INT8 ? 257 : 512) && ladder_blocks(pl.m) * ladder_blocks(pl.n) >= 64;
+}
+// The launch that counts the vectors off the ladder also fills the deltas.
+inline void place_ladder(Route& r) {
+    if (!ladder_pays(r.pl)) return;
+    r.off.counts = r.c.flags + OFF_LADDER_FLAG;
+    r.c.A.deltas = r.deltas_a;
+    r.c.B.deltas = r.deltas_b;
 }
 
 inline PairOrder order_of(const Plan& pl) { return PairOrder{pl.s, pl.full, pl.group_len}; }

@@ -67,8 +67,13 @@ struct SplitArgs {
     int64_t chunks;        // chunks per block
     int s, b;
     DigitLadder ladder;    // of b
-    int* flags;            // [0]: non-finite input seen; [1]: slice count (count-only mode)
+    int* flags;            // [0]: non-finite input seen; [1]: slice count (count-only mode); OffLadder's counts, cleared here
 };
+
+// (not in slice_short_kernel: such blocks are below ladder_pays' line)
+__device__ __forceinline__ void clear_off_ladder(const SplitArgs& a) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 2) a.flags[OFF_LADDER_FLAG + threadIdx.x] = 0;
+}
 
 // FP8 codes of the eight values qs[e] / scale (integers times a power of two, scale a power of two): the
 // scaled FP32 -> FP8 pair conversion of gfx950 divides by the scale, so the slice integer is converted from where it
@@ -507,6 +512,7 @@ __device__ __forceinline__ void slice_vectors(const SplitArgs& a) {
 constexpr int most_waves(int U, int TPR, int fmt) { return U == 2 || fmt == FMT_FP16 ? 4 : fmt_is_fp6(fmt) && TPR < 1024 ? 5 : 6; }
 template <int U, int TPR, int FMT>
 __global__ void __launch_bounds__((TPR < 128 ? 256 : TPR)) __attribute__((amdgpu_waves_per_eu(4, most_waves(U, TPR, FMT)))) split_kernel(SplitArgs a) {
+    clear_off_ladder(a);
     slice_vectors<U, TPR, 8, FMT>(a);
 }
 // Blocks of at most 256 elements: four elements per lane (with eight, half the lanes are idle and a thread's chain is twice as long)
@@ -529,6 +535,7 @@ __global__ void __launch_bounds__(256) slice_short_kernel(SplitArgs a) {
 // were found slice by slice); one non-zero element 617 (4134, and 2238 with two readings for each irregular unit).
 __global__ void __launch_bounds__(1024) long_exponents_kernel(SplitArgs a) {
     __shared__ uint32_t red_key[16], red_turns[2][3][16];
+    clear_off_ladder(a);
     const int tid = threadIdx.x, wave = tid >> 6;
     const bool second = blockIdx.x >= a.wg_first;
     const SplitVectors& v = second ? a.v[1] : a.v[0];
@@ -807,7 +814,7 @@ struct DeltaOperand {
     int32_t* bounds;
     int64_t rows, rows_pad;
 };
-__global__ void __launch_bounds__(256) delta_kernel(DeltaOperand o0, DeltaOperand o1, unsigned tiles_first, int s, int b) {
+__global__ void __launch_bounds__(256) delta_kernel(DeltaOperand o0, DeltaOperand o1, unsigned tiles_first, int s, int b, int* off_ladder) {
     const bool second = blockIdx.x >= tiles_first;
     const int32_t* const exps = second ? o1.exps : o0.exps;
     int32_t* const deltas = second ? o1.deltas : o0.deltas;
@@ -818,15 +825,21 @@ __global__ void __launch_bounds__(256) delta_kernel(DeltaOperand o0, DeltaOperan
     const int lane = threadIdx.x & 63, half = lane & 32;
     const int32_t* e = exps + (size_t)t * s * rows_pad;
     int32_t* out = deltas + (size_t)t * s * groups + group;          // slice p of this group at out[p * groups]
+    bool off = false;
     for (int p = 0; p + 1 < s; ++p) {
         const int d = e[(size_t)p * rows_pad + row] - e[(size_t)(p + 1) * rows_pad + row];
         // the first vector of a group is a real one, or the whole group is padding (then every d is 0)
         const int ref = __shfl(d, half, 64);
+        off = off || d > b + 1;                                      // a remainder that is not zero gives b + 1 or more, a zero one 0 - (its slice's exponent is 0) or less
         const unsigned long long ok = __ballot(row >= rows || d == ref);
         const bool same = (uint32_t)(ok >> half) == 0xFFFFFFFFu;
         if ((lane & 31) == 0) out[(size_t)p * groups] = same ? ref : DELTA_IRREGULAR;
     }
     if ((lane & 31) == 0) out[(size_t)(s - 1) * groups] = DELTA_IRREGULAR;
+    if (off_ladder != nullptr) {
+        const int count = __popcll(__ballot(off));
+        if (lane == 0 && count != 0) atomicAdd(off_ladder + (second ? 1 : 0), count);
+    }
     const int32_t* const l1 = second ? o1.l1 : o0.l1;
     if (l1 == nullptr) return;
     // Operand::bounds: 2^b times the largest sum |q| of the group
@@ -946,7 +959,7 @@ hipError_t launch_count_slices(const double* X, int64_t ldv, const Plan& pl, int
     return launch_split(X, ldv, 1, &op, nullptr, 0, nullptr, cp, flags, st);
 }
 
-hipError_t launch_deltas(const Plan& pl, const Operand* op0, const Operand* op1, hipStream_t st) {
+hipError_t launch_deltas(const Plan& pl, const Operand* op0, const Operand* op1, int* off_ladder, hipStream_t st) {
     DeltaOperand o[2];
     memset(o, 0, sizeof(o));
     const Operand* ops[2] = {op0, op1};
@@ -954,7 +967,7 @@ hipError_t launch_deltas(const Plan& pl, const Operand* op0, const Operand* op1,
         if (ops[i] != nullptr && ops[i]->rows > 0) o[i] = DeltaOperand{ops[i]->exps, ops[i]->deltas, ops[i]->l1, ops[i]->bounds, ops[i]->rows, ops[i]->rows_pad};
     const unsigned t0 = (unsigned)(o[0].rows_pad / TILE), t1 = (unsigned)(o[1].rows_pad / TILE);
     if (t0 + t1 == 0 || pl.T == 0 || pl.s == 0) return hipSuccess;
-    hipLaunchKernelGGL(delta_kernel, dim3(t0 + t1, (unsigned)pl.T), dim3(256), 0, st, o[0], o[1], t0, pl.s, pl.b);
+    hipLaunchKernelGGL(delta_kernel, dim3(t0 + t1, (unsigned)pl.T), dim3(256), 0, st, o[0], o[1], t0, pl.s, pl.b, off_ladder);
     return hipGetLastError();
 }
 

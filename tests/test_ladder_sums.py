@@ -1,0 +1,120 @@
+"""Products and sums of a tile in one kernel (csrc/ladder_sums.hpp): its branch-free emulated sum against the general one on the host, the calls
+that take it, no FP64 instruction in its integer-only forms, and its results bit for bit the oracle's at the edges of tiles, slice
+counts, blocks and stages, with vectors that run out and with vectors off the ladder (which leave the call to the other kernels)."""
+import ctypes
+import os
+import re
+import subprocess
+
+import numpy as np
+import pytest
+
+from oracle import ozaki_oracle as oz
+from paper_2508_00441_amd import binding as lib, inputs
+from test_no_fp64_instructions import F64, HIPCC, _kernel_bodies
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+FMT, ACC = lib.SLICE_FORMATS, lib.ACCUM_MODES
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    out = tmp_path_factory.mktemp("ladder") / "libladder.so"
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-o", str(out), os.path.join(ROOT, "tests", "host_ladder_add_harness.cpp")])
+    return ctypes.CDLL(str(out))
+
+
+@pytest.mark.parametrize("terms,step,bits,narrow", [(13, 5, 24, 1), (13, 5, 12, 1), (9, 7, 31, 1), (6, 5, 24, 1), (23, 5, 24, 0), (17, 7, 31, 0), (29, 4, 16, 0),
+                                                    (23, 5, 3, 0)])
+def test_branch_free_sum_equals_the_general_one(host, terms, step, bits, narrow):
+    rng = np.random.default_rng(terms * step + bits)
+    n = 200000
+    v = rng.integers(-(1 << bits) + 1, 1 << bits, (n, terms))
+    v = np.where(rng.random((n, terms)) < 0.2, 0, v >> rng.integers(0, bits, (n, terms)))                # zeros, short terms
+    cancel = rng.random(n) < 0.5                                                                         # sums that almost vanish on the way
+    i = rng.integers(1, terms, n)
+    low = v[np.arange(n), i - 1] >> step
+    v[cancel, i[cancel]] = -low[cancel] + rng.integers(-1, 2, n)[cancel]
+    v = np.ascontiguousarray(v.astype(np.int32))
+    a, b = np.empty(n, np.uint64), np.empty(n, np.uint64)
+    host.host_ladder_sums(v.ctypes.data_as(ctypes.c_void_p), ctypes.c_size_t(n), terms, -70, step, narrow, a.ctypes.data_as(ctypes.c_void_p),
+                          b.ctypes.data_as(ctypes.c_void_p))
+    assert np.array_equal(a, b), np.nonzero(a != b)[0][:5]
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
+@pytest.mark.parametrize("mode", ["emu", "exact", "hw"])
+def test_integer_only_forms_use_no_fp64(tmp_path, mode):
+    bodies = {n: b for n, b in _kernel_bodies(f"ladder_sums_int8_{mode}.hip", tmp_path).items() if "ladder_sums_kernel" in n}
+    assert len(bodies) >= 6
+    for n, body in bodies.items():
+        used = set(re.findall(F64, body))
+        assert "v_mfma_i32_32x32x32_i8" in body
+        assert all(re.match(r"v_(add|ldexp|cvt|mul)_", u) for u in used) if mode == "hw" else not used, (n, used)
+
+
+def _operands(m, n, k, off):
+    A, B = inputs.phi_pair(m, n, k, 1.0, seed=m + n + k)
+    rng = np.random.default_rng(k)
+    A[3, :] = 0.0
+    A[m - 1, :] = np.ldexp(rng.integers(-7, 8, k).astype(np.float64), -30)             # runs out after a slice or two
+    B[:, 1] = np.ldexp(rng.integers(-1000, 1001, k).astype(np.float64), -12)
+    B[:, n - 2] *= 2.0 ** 300
+    if off in ("A", "both"):
+        A[m - 2, :] = 0.0
+        A[m - 2, [0, k // 2, k - 1]] = 1.0 + 2.0 ** -50, 3.0 * 2.0 ** -23, -5.0 * 2.0 ** -41
+    if off in ("B", "both"):
+        B[:, 5] = 0.0
+        B[[1, 2], 5] = 1.0, 2.0 ** -19
+    return A, B
+
+
+gpu_cases = pytest.mark.parametrize("fmt,m,n,k,k_block,s,pairs", [
+    ("fp8", 513, 577, 512, 0, 13, "triangle"),          # 9 x 10 tiles, ragged
+    ("fp8", 640, 448, 1031, 0, 6, "triangle"),          # the fewest slices, odd number of stages
+    ("fp8", 520, 500, 4600, 0, 14, "triangle"),         # the most; the window's edge
+    ("fp8", 65, 2100, 600, 0, 8, "triangle"),
+    ("fp8", 512, 520, 1100, 550, 11, "full"),           # two blocks, both halves of the pairs
+    ("fp8", 512, 512, 700, 0, 10, "full"),
+    ("fp6", 515, 530, 600, 0, 14, "triangle"),
+    ("fp6", 512, 520, 600, 0, 12, "full"),
+    ("fp6_e3m2", 512, 514, 700, 0, 15, "triangle"),
+    ("fp6_e3m2", 512, 514, 640, 0, 13, "full"),
+    ("int8", 512, 512, 300, 0, 11, "triangle"),
+    ("int8", 514, 513, 20000, 0, 6, "triangle"),        # a block that is sliced exponents first
+    ("int8", 530, 512, 520, 260, 9, "full"),
+])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("off", ["", "A", "both"])
+@gpu_cases
+def test_results_are_the_oracles(fmt, m, n, k, k_block, s, pairs, off):
+    torch = pytest.importorskip("torch")
+    from paper_2508_00441_amd import device
+    A, B = _operands(m, n, k, off)
+    rows = sorted({0, 3, 31, 32, 63, 64, m // 2, m - 2, m - 1} & set(range(m)))
+    cols = sorted({0, 1, 5, 31, 32, 63, 64, n // 2, n - 2, n - 1})
+    ldc = m + 3
+    Ad, Bd = device.to_device_colmajor(A), device.to_device_colmajor(B)
+    ws = device.Workspace(max(lib.ozaki_workspace_bytes_ex(m, n, k, FMT[fmt], s, k_block, lib.PAIR_SETS[pairs], False),
+                              lib.ozaki_workspace_bytes_scaled(m, n, k, FMT[fmt], s, k_block)))
+    for accum, rule in (("hw", "runs"), ("emu", "runs"), ("exact", "exact")):
+        want = oz.ozaki_dgemm(A[rows], B[:, cols], fmt, s, k_block, mode=pairs, accumulate=rule)
+        C = torch.full((n, ldc), float("nan"), dtype=torch.float64, device="cuda")
+        lib.ozaki_dgemm_ex(m, n, k, Ad, m, Bd, k, C, ldc, FMT[fmt], s, k_block, ACC[accum], lib.PAIR_SETS[pairs], lib.SUM_RUNS, 0)
+        assert lib.ozaki_last_device_status() == 0
+        got = C.cpu().numpy()
+        assert np.all(np.isnan(got[:, m:])) and not np.any(np.isnan(got[:, :m]))
+        part = np.ascontiguousarray(got[:, :m].T[np.ix_(rows, cols)])
+        assert np.array_equal(part.view(np.uint64), want.view(np.uint64)), accum
+        if pairs == "triangle":
+            # scaled: one rounding per operation on the plain product, on C as it is
+            C0 = inputs.phi_matrix(n, ldc, 2.0, np.random.default_rng(m * n))
+            D = torch.from_numpy(C0).cuda()
+            lib.ozaki_dgemm_scaled(m, n, k, -1.5, Ad, m, Bd, k, 0.3, D, ldc, FMT[fmt], s, k_block, ACC[accum])
+            assert lib.ozaki_last_device_status() == 0
+            scaled = D.cpu().numpy()
+            assert np.array_equal(scaled[:, m:], C0[:, m:])
+            assert np.array_equal(np.ascontiguousarray(scaled[:, :m]).view(np.uint64), (-1.5 * got[:, :m] + 0.3 * C0[:, :m]).view(np.uint64)), accum
+    ws.close()
