@@ -86,7 +86,7 @@ constexpr int64_t MAX_ELEMS_WITHOUT_TRANSPOSE = 1 << 20;
 
 // split both operands of the plan into the carved buffers
 int run_split(const Plan& pl, const Carve& c, const double* A, int64_t lda, const double* B, int64_t ldb, bool do_a, bool do_b,
-              int* off_ladder = nullptr) {
+              const OffLadder& off = OffLadder{nullptr, 0, nullptr, nullptr}) {
     Phase ph(0);
     hipStream_t st = ctx().stream;
     const bool a_on = do_a && pl.m > 0, b_on = do_b && pl.n > 0;
@@ -95,7 +95,7 @@ int run_split(const Plan& pl, const Carve& c, const double* A, int64_t lda, cons
     // both operands in one launch each: on a small problem neither fills the chip alone
     HIP_TRY(launch_split(transpose ? c.At : A, transpose ? pl.k : 1, transpose ? 1 : lda, a_on ? &c.A : nullptr, B, ldb, b_on ? &c.B : nullptr, pl,
                          c.flags, st));
-    if (c.A.deltas != nullptr) HIP_TRY(launch_deltas(pl, a_on ? &c.A : nullptr, b_on ? &c.B : nullptr, off_ladder, st));
+    if (c.A.deltas != nullptr) HIP_TRY(launch_deltas(pl, a_on ? &c.A : nullptr, b_on ? &c.B : nullptr, off, st));
     return 0;
 }
 
@@ -164,7 +164,7 @@ int dgemm_core(const Plan& plan, double alpha, const double* A, int64_t lda, con
         }
     } else {
         const PairOrder order = order_of(pl);
-        int rc = run_split(pl, c, A, lda, B, ldb, true, true, off.counts != nullptr ? c.flags + OFF_LADDER_FLAG : nullptr);
+        int rc = run_split(pl, c, A, lda, B, ldb, true, true, off);
         if (rc) return rc;
         for (int64_t t = 0; t < pl.T; ++t) {
             for (int g_hi = order_top_diag(order); g_hi >= 2;) {
@@ -173,9 +173,11 @@ int dgemm_core(const Plan& plan, double alpha, const double* A, int64_t lda, con
                 {
                     Phase ph(1);
                     // (between the halves of all pairs its sum lies where products will: an element's three words take less than s of them)
-                    if (off.counts != nullptr && first)
-                        HIP_TRY(launch_ladder_sums(pl, c.A, c.B, t, off, reinterpret_cast<uint64_t*>(c.P), out, ldo,
-                                                   scaled && t + 1 == pl.T ? &result : nullptr, o.accum_mode, st));
+                    if (off.counts != nullptr && first) {
+                        const ScaledResult* const combine = scaled && t + 1 == pl.T ? &result : nullptr;
+                        HIP_TRY(launch_ladder_sums(pl, c.A, c.B, t, off, reinterpret_cast<uint64_t*>(c.P), out, ldo, combine, o.accum_mode, st));
+                        if (off.limit > 0) HIP_TRY(launch_off_ladder(pl, c.A, c.B, off, out, ldo, combine, o.accum_mode, st));
+                    }
                     HIP_TRY(launch_pair_gemm(pl, c.A, c.B, order, ps, chained, check, off, t, c.P, st));
                 }
                 {
@@ -506,13 +508,13 @@ int ozaki_pair_products(int64_t m, int64_t n, int64_t k, const double* A, int64_
     Operand ea = c.A, eb = c.B;
     ea.deltas = r.deltas_a;
     eb.deltas = r.deltas_b;
-    if (c.A.deltas == nullptr) HIP_TRY(launch_deltas(pl, &ea, &eb, nullptr, stream));
+    if (c.A.deltas == nullptr) HIP_TRY(launch_deltas(pl, &ea, &eb, OffLadder{nullptr, 0, nullptr, nullptr}, stream));
     for (int64_t t = 0; t < pl.T; ++t) {
         int z0 = 0;
         for (int g_hi = order_top_diag(order); g_hi >= 2;) {
             const Pass ps = next_pass(order, g_hi, c.chunk_pairs);
             const size_t at = ((size_t)t * pl.npairs + z0) * (size_t)m * n;
-            HIP_TRY(launch_pair_gemm(pl, c.A, c.B, order, ps, chained != 0, r.check, OffLadder{nullptr, 0}, t, c.P, stream));
+            HIP_TRY(launch_pair_gemm(pl, c.A, c.B, order, ps, chained != 0, r.check, OffLadder{nullptr, 0, nullptr, nullptr}, t, c.P, stream));
             HIP_TRY(launch_export_products(pl, ea, eb, order, ps, chained != 0, r.check.starts, t, c.P, static_cast<float*>(P_out) + at,
                                            run_len_out ? run_len_out + at : nullptr, stream));
             z0 += ps.npairs;

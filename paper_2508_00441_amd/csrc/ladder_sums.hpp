@@ -20,9 +20,9 @@
 // stage say so (Ladder::A_FREE, MIDDLE and the last column), two of them also that the loads issued half a stage or more before
 // have landed.
 //
-// Where vectors of either operand are off the ladder (few entries that count at some depth, or the end of the mantissas reached),
-// the kernel does nothing, and the GEMM kernels and the accumulation, which come behind it, do all (OffLadder in layout.hpp).  A
-// vector whose remainder is zero from some slice on is regular as far as it goes: the slices behind add zeros, whatever their scale.
+// Vectors of either operand may be off the ladder (few entries that count at some depth, or the end of the mantissas reached).  Where
+// they are few, their rows and columns of C are left to off_ladder.hpp; where they are not, the kernel does nothing, and the GEMM
+// kernels and the accumulation, which come behind it, do all (OffLadder in layout.hpp).  A vector whose remainder is zero from some slice on is regular as far as it goes: the slices behind add zeros, whatever their scale.
 //
 // LESSER_HALF: the same for the pairs p + q > s + 1 of the all-pairs set: with p' = s + 1 - p, q' = s + 1 - q they are the triangle
 // p' + q' <= s of S = s - 1 slices, summed in the reverse order.
@@ -332,6 +332,13 @@ __global__ void __launch_bounds__(256, 1) ladder_sums_kernel(const LadderArgs a)
     uint64_t* const sum_at = a.S + (((size_t)bn * a.blocks_m + bm) * 4 + wave) * 1024 * SUM_WORDS_MAX + lane;
     uint64_t* const c_at = reinterpret_cast<uint64_t*>(a.C) + mi + first_n * a.ldc;
     const bool combine = a.add_to_C || a.scaled;
+    // the vectors off the ladder are not for this kernel to write
+    bool row_here = mi < a.m;
+    uint32_t cols_off = 0;                                            // of the wave's 32 columns
+    if (a.off.limit > 0) {
+        row_here = row_here && ((a.off.bits[(row0 >> 5) + wm] >> (lane & 31)) & 1u) == 0;
+        cols_off = a.off.bits[(a.rows_pad_a + col0) / 32 + wn] >> ((lane >> 5) * 4);
+    }
     uint64_t* const mine = reinterpret_cast<uint64_t*>(lds + wave * 8192) + lane;
     static_for<4>([&](auto gc) {
         constexpr int G = decltype(gc)::value;
@@ -350,7 +357,7 @@ __global__ void __launch_bounds__(256, 1) ladder_sums_kernel(const LadderArgs a)
             } else {
                 const uint64_t v = sum[r.value].result(base_a + lead_b[n_in]);
                 if (combine) mine[(4 * G + decltype(r)::value) * 64] = v;
-                else if (mi < a.m && first_n + n_in < a.n) c_at[n_in * a.ldc] = v;
+                else if (row_here && first_n + n_in < a.n && ((cols_off >> n_in) & 1u) == 0) c_at[n_in * a.ldc] = v;
             }
         });
     });
@@ -363,7 +370,7 @@ __global__ void __launch_bounds__(256, 1) ladder_sums_kernel(const LadderArgs a)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int64_t nj = first_n + 2 * r0 + r;
-                inside[r] = mi < a.m && nj < a.n;
+                inside[r] = row_here && nj < a.n && ((cols_off >> (2 * r0 + r)) & 1u) == 0;
                 if (inside[r] && a.add_to_C) w[r] = reinterpret_cast<const uint64_t*>(a.W)[mi + nj * a.ldw];
                 if (inside[r] && a.use_beta) c[r] = c_at[(2 * r0 + r) * a.ldc];
             }

@@ -328,10 +328,13 @@ constexpr bool ladder_exact_fits(int fmt, int s, bool full) {
     return 31 + above + 1 <= 127 && above <= EXACT_WINDOW_BITS;
 }
 // How many vectors of the two operands are off the ladder (launch_deltas; the slicing kernels clear the counts).  Up to `limit` of each:
-// ladder_sums.hpp does the call's products, beyond that the GEMM kernels and the accumulation, which come behind it.
+// ladder_sums.hpp does the call's products but for theirs, which off_ladder.hpp does; beyond that the GEMM kernels and the accumulation,
+// which come behind.
 struct OffLadder {
-    const int* counts;       // null: no such distinction, the latter do all
-    int limit;
+    int* counts;             // null: no such distinction, the latter do all
+    int limit;               // 0 or a multiple of 32
+    uint32_t* bits;          // limit > 0: a bit per vector that is off it, (m_pad + n_pad) / 32 words,
+    int* list;               // and these vectors, up to `limit` of A, up to `limit` of B, in no order
 };
 #if defined(__HIPCC__)
 __device__ __forceinline__ bool on_ladder(const OffLadder& o) { return o.counts != nullptr && o.counts[0] <= o.limit && o.counts[1] <= o.limit; }
@@ -356,9 +359,9 @@ hipError_t launch_count_slices(const double* X, int64_t ldv, const Plan& pl, int
 // Internal layout -> plain vector-major codes (verification export).
 hipError_t launch_export_slices(const Plan& pl, const Operand& op, void* out, hipStream_t st);
 
-// Fills Operand::deltas from Operand::exps, for up to two operands in one launch, and counts the vectors off the ladder (OffLadder::counts) if
-// that is not null.
-hipError_t launch_deltas(const Plan& pl, const Operand* op0, const Operand* op1, int* off_ladder, hipStream_t st);
+// Fills Operand::deltas from Operand::exps, for up to two operands in one launch, and counts and lists the vectors off the ladder if
+// off.counts is not null.
+hipError_t launch_deltas(const Plan& pl, const Operand* op0, const Operand* op1, const OffLadder& off, hipStream_t st);
 
 // Products of the pairs of pass `ps` of block t into P ([ps.npairs][quads_n][quads_m][QUAD_ELEMS] floats).  With
 // allow_chain, consecutive pairs of a group that are linked for a tile (pair_linked) form a run whose exact sum is
@@ -388,7 +391,13 @@ hipError_t launch_accumulate(const Plan& pl, const Operand& A, const Operand& B,
                              double* C, int64_t ldc, const ScaledResult* scaled, int accum_mode, int sum_rule, bool chained,
                              const uint8_t* starts, const OffLadder& off, hipStream_t st);
 
-// Products and sums of block t if all vectors are on the ladder (ladder_sums.hpp).  S: with all pairs, work memory for the sum of the less significant half, SUM_WORDS_MAX words per
+// The products of the vectors off the ladder if those are few (off_ladder.hpp); C, scaled as in launch_accumulate.  FP8 and INT8, the pairs
+// of the triangle, one block.
+constexpr int OFF_LADDER_MIN_SLICES = 6, OFF_LADDER_MAX_SLICES = 13;
+hipError_t launch_off_ladder(const Plan& pl, const Operand& A, const Operand& B, const OffLadder& off, double* C, int64_t ldc,
+                             const ScaledResult* scaled, int accum_mode, hipStream_t st);
+
+// Products and sums of block t if the vectors are on the ladder, all but those of the list (ladder_sums.hpp).  S: with all pairs, work memory for the sum of the less significant half, SUM_WORDS_MAX words per
 // element of the tiles.  The other arguments as in launch_accumulate.
 hipError_t launch_ladder_sums(const Plan& pl, const Operand& A, const Operand& B, int64_t t, const OffLadder& off, uint64_t* S, double* C,
                               int64_t ldc, const ScaledResult* scaled, int accum_mode, hipStream_t st);

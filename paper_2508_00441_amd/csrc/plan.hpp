@@ -315,7 +315,7 @@ struct Route {
 // groups that take the least time; otherwise in the longest groups of the worst case.  False if the memory does not hold it.
 inline bool place_call(const Plan& plan, bool want_product, int sum_words, bool chained, bool as_dgemm, WorkMem wm, Route& r) {
     r.pl = plan;
-    r.off = OffLadder{nullptr, 0};
+    r.off = OffLadder{nullptr, 0, nullptr, nullptr};
     r.check = RunCheck{nullptr, nullptr, nullptr};
     if (!carve(plan, r.c, want_product, sum_words, wm)) return false;
     if (chained && as_dgemm) r.check = place_run_check(r.pl, r.c);
@@ -341,9 +341,20 @@ inline bool ladder_pays(const Plan& pl) {
     return ladder_possible(pl) && pl.kb >= (pl.fmt == FMT_INT8 ? 257 : 512) && ladder_blocks(pl.m) * ladder_blocks(pl.n) >= 64;
 }
 // The launch that counts the vectors off the ladder also fills the deltas.
+constexpr int OFF_LADDER_MOST = 64;
 inline void place_ladder(Route& r) {
     if (!ladder_pays(r.pl)) return;
     r.off.counts = r.c.flags + OFF_LADDER_FLAG;
+    // Some vectors off it: where the call is long against one more launch (3 to 5 us where there are none).  Their bits and the list lie in the
+    // transposed A's memory, which is dead once the operands are sliced; the runs of such a call have no use for it (place_run_check:
+    // run_limit covers an anti-diagonal).
+    const size_t words = (size_t)((r.pl.m_pad + r.pl.n_pad) / 32);
+    if ((r.pl.fmt == FMT_FP8 || r.pl.fmt == FMT_INT8) && r.pl.s <= OFF_LADDER_MAX_SLICES && !r.pl.full && r.pl.T == 1 && r.check.starts == nullptr &&
+        ladder_blocks(r.pl.m) * ladder_blocks(r.pl.n) >= 1024 && (words + 2 * OFF_LADDER_MOST) * sizeof(uint32_t) <= (size_t)r.pl.m * r.pl.k * sizeof(double)) {
+        r.off.limit = OFF_LADDER_MOST;
+        r.off.bits = reinterpret_cast<uint32_t*>(r.c.At);
+        r.off.list = reinterpret_cast<int*>(r.c.At) + words;
+    }
     r.c.A.deltas = r.deltas_a;
     r.c.B.deltas = r.deltas_b;
 }

@@ -814,7 +814,7 @@ struct DeltaOperand {
     int32_t* bounds;
     int64_t rows, rows_pad;
 };
-__global__ void __launch_bounds__(256) delta_kernel(DeltaOperand o0, DeltaOperand o1, unsigned tiles_first, int s, int b, int* off_ladder) {
+__global__ void __launch_bounds__(256) delta_kernel(DeltaOperand o0, DeltaOperand o1, unsigned tiles_first, int s, int b, OffLadder off_ladder) {
     const bool second = blockIdx.x >= tiles_first;
     const int32_t* const exps = second ? o1.exps : o0.exps;
     int32_t* const deltas = second ? o1.deltas : o0.deltas;
@@ -836,9 +836,15 @@ __global__ void __launch_bounds__(256) delta_kernel(DeltaOperand o0, DeltaOperan
         if ((lane & 31) == 0) out[(size_t)p * groups] = same ? ref : DELTA_IRREGULAR;
     }
     if ((lane & 31) == 0) out[(size_t)(s - 1) * groups] = DELTA_IRREGULAR;
-    if (off_ladder != nullptr) {
-        const int count = __popcll(__ballot(off));
-        if (lane == 0 && count != 0) atomicAdd(off_ladder + (second ? 1 : 0), count);
+    if (off_ladder.counts != nullptr) {
+        const uint64_t bits = __ballot(off);
+        if (off_ladder.limit > 0 && (lane & 31) == 0) off_ladder.bits[blockIdx.x * (TILE / 32) + (threadIdx.x >> 5)] = (uint32_t)(bits >> half);
+        if (bits != 0) {                                             // (they are few, or their list is of no use)
+            int place = 0;
+            if (lane == 0) place = atomicAdd(off_ladder.counts + (second ? 1 : 0), __popcll(bits));
+            place = __shfl(place, 0, 64) + __popcll(bits & ((1ull << lane) - 1ull));
+            if (off && place < off_ladder.limit) off_ladder.list[(second ? off_ladder.limit : 0) + place] = (int)row;
+        }
     }
     const int32_t* const l1 = second ? o1.l1 : o0.l1;
     if (l1 == nullptr) return;
@@ -959,7 +965,7 @@ hipError_t launch_count_slices(const double* X, int64_t ldv, const Plan& pl, int
     return launch_split(X, ldv, 1, &op, nullptr, 0, nullptr, cp, flags, st);
 }
 
-hipError_t launch_deltas(const Plan& pl, const Operand* op0, const Operand* op1, int* off_ladder, hipStream_t st) {
+hipError_t launch_deltas(const Plan& pl, const Operand* op0, const Operand* op1, const OffLadder& off, hipStream_t st) {
     DeltaOperand o[2];
     memset(o, 0, sizeof(o));
     const Operand* ops[2] = {op0, op1};
@@ -967,7 +973,7 @@ hipError_t launch_deltas(const Plan& pl, const Operand* op0, const Operand* op1,
         if (ops[i] != nullptr && ops[i]->rows > 0) o[i] = DeltaOperand{ops[i]->exps, ops[i]->deltas, ops[i]->l1, ops[i]->bounds, ops[i]->rows, ops[i]->rows_pad};
     const unsigned t0 = (unsigned)(o[0].rows_pad / TILE), t1 = (unsigned)(o[1].rows_pad / TILE);
     if (t0 + t1 == 0 || pl.T == 0 || pl.s == 0) return hipSuccess;
-    hipLaunchKernelGGL(delta_kernel, dim3(t0 + t1, (unsigned)pl.T), dim3(256), 0, st, o[0], o[1], t0, pl.s, pl.b, off_ladder);
+    hipLaunchKernelGGL(delta_kernel, dim3(t0 + t1, (unsigned)pl.T), dim3(256), 0, st, o[0], o[1], t0, pl.s, pl.b, off);
     return hipGetLastError();
 }
 

@@ -118,3 +118,42 @@ def test_results_are_the_oracles(fmt, m, n, k, k_block, s, pairs, off):
             assert np.array_equal(scaled[:, m:], C0[:, m:])
             assert np.array_equal(np.ascontiguousarray(scaled[:, :m]).view(np.uint64), (-1.5 * got[:, :m] + 0.3 * C0[:, :m]).view(np.uint64)), accum
     ws.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows_off,cols_off", [(0, 0), (1, 0), (0, 33), (32, 3), (64, 64), (65, 1), (2, 65)])
+@pytest.mark.parametrize("fmt,m,n,k,s", [("fp8", 2050, 2082, 513, 13), ("fp8", 1100, 4000, 640, 6), ("int8", 2049, 2050, 261, 9)])
+def test_vectors_off_the_ladder_in_large_results(fmt, m, n, k, s, rows_off, cols_off):
+    """Up to 64 of each operand are done by a kernel of their own, more leave the call to the general kernels; plain and scaled."""
+    torch = pytest.importorskip("torch")
+    from paper_2508_00441_amd import device
+    A, B = inputs.phi_pair(m, n, k, 1.0, seed=m + n + k)
+    rng = np.random.default_rng(rows_off * 100 + cols_off)
+    odd_rows, odd_cols = rng.permutation(m)[:rows_off], rng.permutation(n)[:cols_off]
+    for X, at in ((A, odd_rows), (B.T, odd_cols)):
+        X[at, :] = 0.0
+        for i in at:
+            X[i, rng.permutation(k)[:3]] = 1.0 + 2.0 ** -50, 3.0 * 2.0 ** -23, -5.0 * 2.0 ** -41
+    rows = sorted({0, 31, 32, m - 1} | set(odd_rows[:6].tolist()))
+    cols = sorted({0, 63, 64, n - 1} | set(odd_cols[:6].tolist()))
+    Ad, Bd = device.to_device_colmajor(A), device.to_device_colmajor(B)
+    ws = torch.zeros(lib.ozaki_workspace_bytes_scaled(m, n, k, FMT[fmt], s, 0), dtype=torch.uint8, device="cuda")
+    lib.ozaki_set_stream(torch.cuda.current_stream().cuda_stream)
+    lib.ozaki_set_workspace(ws, ws.numel())
+    C0 = inputs.phi_matrix(n, m, 2.0, np.random.default_rng(m * n))
+    for accum, rule in (("hw", "runs"), ("emu", "runs"), ("exact", "exact")):
+        want = oz.ozaki_dgemm(A[rows], B[:, cols], fmt, s, 0, accumulate=rule)
+        C = torch.full((n, m), float("nan"), dtype=torch.float64, device="cuda")
+        lib.ozaki_dgemm(m, n, k, Ad, m, Bd, k, C, m, FMT[fmt], s, 0, ACC[accum])
+        assert lib.ozaki_last_device_status() == 0
+        counts = ws[:32].cpu().numpy().view(np.int32)[4:6].tolist()
+        assert counts == [rows_off, cols_off], counts                                # the kernels' choice rests on these
+        got = C.cpu().numpy()
+        assert not np.any(np.isnan(got))
+        part = np.ascontiguousarray(got.T[np.ix_(rows, cols)])
+        assert np.array_equal(part.view(np.uint64), want.view(np.uint64)), accum
+        D = torch.from_numpy(C0).cuda()
+        lib.ozaki_dgemm_scaled(m, n, k, -1.5, Ad, m, Bd, k, 0.3, D, m, FMT[fmt], s, 0, ACC[accum])
+        assert lib.ozaki_last_device_status() == 0
+        assert np.array_equal(D.cpu().numpy().view(np.uint64), (-1.5 * got + 0.3 * C0).view(np.uint64)), accum
+    lib.ozaki_set_workspace(None, 0)
