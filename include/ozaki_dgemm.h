@@ -306,7 +306,8 @@ int ozaki_count_slices(int is_B, int64_t rows, int64_t k, const double* X, int64
  *               anti-diagonal, the matrix unit keeps accumulating and ONE slot receives the exact sum of the run.
  *               Every anti-diagonal is cut into groups of floor(window / (k_block 4^b)) pairs (at least one), whose sum is
  *               inside the exact window (2^24; INT8: 2^31 - 1) whatever the data; a run ends with its group.
- *               2: the launch configuration of ozaki_dgemm with OZAKI_SUM_RUNS in this workspace.  Its groups are shorter
+ *               2: the launch configuration of ozaki_dgemm with OZAKI_SUM_RUNS in this workspace, of its kernels that store
+ *               products (where all exponents are regular ladders a call may form its sums without storing any).  Its groups are shorter
  *               where that is faster, and longer where the limit of 1 would cut the longest anti-diagonal into three
  *               groups or more (not for INT8): there the matrix unit sums on as long as the accumulators, together with
  *               a bound on every partial sum of the next pair, stay inside the window, so that the length of a run

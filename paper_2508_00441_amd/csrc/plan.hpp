@@ -332,13 +332,21 @@ inline bool place_call(const Plan& plan, bool want_product, int sum_words, bool 
 }
 
 // Does the call start with launch_ladder_sums?  (The GEMM kernels and the accumulation come behind it.)
-// Of short vectors some are off the ladder as a rule, and the call then takes the other route and the launch for nothing (10 us of 600 x
+// Tiles: a workgroup does all pairs of its tile, so with few tiles most compute units have no part in the work, which the GEMM kernels deal
+// out by groups of pairs as well.  Time of a call by those over its time by this one, 520, 1500 and 4500 inner indices:
+//   tiles       64                 100                144                160                256                576                2209
+//   FP8, 13     0.90 0.80 0.66     1.14 1.10 0.96     1.28 1.18 1.02     1.52 1.40 1.36     1.44 1.30 1.26     1.32 1.23 1.13     1.53 1.40 1.27
+//   FP8, 7      1.02 0.80 0.72     1.03 1.07 0.90     1.16 1.16 0.95     1.28 1.26 1.11     1.40 1.26 1.16     1.25 1.29 1.06     1.80 1.31 1.18
+//   INT8, 9     0.97 0.83 0.78     1.10 1.11 1.05     1.15 1.34 1.09     1.43 1.48 1.37     1.52 1.32 1.23     1.26 1.22 1.17     1.45 1.27 1.20
+//   FP6, 13     1.18 0.96 0.81     1.06 1.26 1.09     1.39 1.36 1.16     1.59 1.53 1.51     1.51 1.36 1.31     1.39 1.34 1.21     1.65 1.49 1.36
+// 94 tiles, 96 x 3000: 1.00 to 1.17, FP8 with 7 slices and 4500 inner indices 0.93.  Hence 90 tiles, for FP8 and more than 32 stages 160.
+// Blocks: of short vectors some are off the ladder as a rule, and the call then takes the other route and the launch for nothing (10 us of 600 x
 // 600 x 1000).  The share of vectors off it, entries (u - 1/2) exp(phi z), 13 FP8 slices (which reach the end of the mantissas): phi = 0.5,
 // k = 256 2.3 %, k = 512 0.1 %, k = 1024 none of 2048; phi = 1, k = 64 5 %, k = 128 0.15 %, from k = 256 on none; phi = 2 0.05 to 0.2 % up
-// to k = 1024; 9 INT8 slices none from k = 64 on (from 257 here: shorter blocks have a slicing kernel of their own).  With fewer than 64
-// tiles three quarters of the compute units have no part in the work, which the GEMM kernels deal out by groups of pairs as well.
+// to k = 1024; 9 INT8 slices none from k = 64 on (from 257 here: shorter blocks have a slicing kernel of their own).
 inline bool ladder_pays(const Plan& pl) {
-    return ladder_possible(pl) && pl.kb >= (pl.fmt == FMT_INT8 ? 257 : 512) && ladder_blocks(pl.m) * ladder_blocks(pl.n) >= 64;
+    return ladder_possible(pl) && pl.kb >= (pl.fmt == FMT_INT8 ? 257 : 512) &&
+           ladder_blocks(pl.m) * ladder_blocks(pl.n) >= (pl.fmt == FMT_FP8 && pl.chunks > 32 ? 160 : 90);
 }
 // The launch that counts the vectors off the ladder also fills the deltas.
 constexpr int OFF_LADDER_MOST = 64;

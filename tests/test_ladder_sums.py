@@ -70,19 +70,20 @@ def _operands(m, n, k, off):
 
 
 gpu_cases = pytest.mark.parametrize("fmt,m,n,k,k_block,s,pairs", [
-    ("fp8", 513, 577, 512, 0, 13, "triangle"),          # 9 x 10 tiles, ragged
-    ("fp8", 640, 448, 1031, 0, 6, "triangle"),          # the fewest slices, odd number of stages
-    ("fp8", 520, 500, 4600, 0, 14, "triangle"),         # the most; the window's edge
-    ("fp8", 65, 2100, 600, 0, 8, "triangle"),
-    ("fp8", 512, 520, 1100, 550, 11, "full"),           # two blocks, both halves of the pairs
-    ("fp8", 512, 512, 700, 0, 10, "full"),
-    ("fp6", 515, 530, 600, 0, 14, "triangle"),
-    ("fp6", 512, 520, 600, 0, 12, "full"),
-    ("fp6_e3m2", 512, 514, 700, 0, 15, "triangle"),
-    ("fp6_e3m2", 512, 514, 640, 0, 13, "full"),
-    ("int8", 512, 512, 300, 0, 11, "triangle"),
-    ("int8", 514, 513, 20000, 0, 6, "triangle"),        # a block that is sliced exponents first
-    ("int8", 530, 512, 520, 260, 9, "full"),
+    ("fp8", 513, 577, 512, 0, 13, "triangle"),          # 9 x 10 tiles, ragged; the shortest block, the fewest tiles
+    ("fp8", 640, 577, 1031, 0, 6, "triangle"),          # the fewest slices, odd number of stages
+    ("fp8", 833, 800, 4600, 0, 14, "triangle"),         # the most; the window's edge; 14 x 13 tiles
+    ("fp8", 65, 3000, 600, 0, 8, "triangle"),
+    ("fp8", 512, 770, 1100, 550, 11, "full"),           # two blocks, both halves of the pairs
+    ("fp8", 640, 600, 700, 0, 10, "full"),
+    ("fp6", 641, 530, 600, 0, 14, "triangle"),
+    ("fp6", 640, 570, 600, 0, 12, "full"),
+    ("fp6_e3m2", 640, 580, 700, 0, 15, "triangle"),
+    ("fp6_e3m2", 640, 580, 640, 0, 13, "full"),
+    ("int8", 640, 576, 300, 0, 11, "triangle"),
+    ("int8", 641, 576, 20000, 0, 6, "triangle"),        # a block that is sliced exponents first
+    ("int8", 660, 640, 520, 260, 9, "full"),
+    ("int8", 512, 511, 300, 0, 11, "triangle"),         # 64 tiles: the other kernels
 ])
 
 
