@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJDIR = os.path.join(CSRC, "_build")
 LIB = os.path.join(HERE, "libozaki.so")
-SOURCES = ["api.hip", "split.hip", "pair_gemm.hip", "pair_gemm_fp8.hip", "pair_gemm_measured.hip", "pair_gemm_small.hip", "accumulate.hip",
+SOURCES = ["api.hip", "split.hip", "pair_gemm.hip", "pair_gemm_fp8.hip", "pair_gemm_measured.hip", "pair_gemm_small.hip", "pair_gemm_small_behind.hip", "accumulate.hip",
            "ladder_sums.hip", "off_ladder.hip", "off_ladder_fp8.hip", "off_ladder_int8.hip"] + [f"ladder_sums_{fmt}_{mode}.hip" for mode in ("emu", "exact", "hw") for fmt in ("fp8", "fp6", "fp6_e3m2", "int8")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -77,7 +77,8 @@ __device__ __forceinline__ bool starts_run(const PairOrder& o, int allow_chain, 
 // R elements per thread: 4 (one workgroup per 32 x 32 position) or 1 (four workgroups per position, each eight of its
 // columns).  DEPTH product loads are kept in flight per thread.
 // SCALED: the last step of the last block of a product C = alpha * (A B) + beta * C.
-template <int MODE, bool PINT, int R, int DEPTH, bool SCALED>
+// BEHIND: behind launch_ladder_sums.
+template <int MODE, bool PINT, int R, int DEPTH, bool SCALED, bool BEHIND = false>
 __device__ __forceinline__ void accumulate_body(const AccArgs& a) {
     static_assert(R == 4 || R == 1, "a thread reads 16 bytes or one word of a stored product");
     constexpr bool HW = MODE == ACC_HW, EMU = MODE == ACC_EMU, EXACT = MODE == ACC_EXACT;
@@ -102,7 +103,7 @@ __device__ __forceinline__ void accumulate_body(const AccArgs& a) {
     const int64_t m0 = (int64_t)tm * TILE + wm * 128 + tj * 32;       // first row of C of this 32 x 32 position
     const int64_t n0 = (int64_t)tn * TILE + wn * 128 + ti * 32;       // first column
     if (m0 >= a.m || n0 >= a.n) return;               // padding only
-    if (R == 4 && on_ladder(a.off)) return;
+    if (BEHIND && on_ladder(a.off)) return;
 
     const int ml = lane & 31;
     const int nl = g4 * 8 + (lane >> 5) * 4 + r0;
@@ -316,6 +317,12 @@ __device__ __forceinline__ void accumulate_body(const AccArgs& a) {
 template <int MODE, bool PINT>
 __global__ void __launch_bounds__(256) accumulate_kernel(const AccArgs a) { accumulate_body<MODE, PINT, 4, 4, false>(a); }
 
+// Behind launch_ladder_sums (the question whether there is anything to do takes 0.3 us of the smallest calls)
+template <int MODE, bool PINT>
+__global__ void __launch_bounds__(256) accumulate_rest_kernel(const AccArgs a) { accumulate_body<MODE, PINT, 4, 4, false, true>(a); }
+template <int MODE, bool PINT>
+__global__ void __launch_bounds__(256) accumulate_scaled_rest_kernel(const AccArgs a) { accumulate_body<MODE, PINT, 4, 4, true, true>(a); }
+
 // Few elements: a quarter of the work per thread
 template <int MODE, bool PINT>
 __global__ void __launch_bounds__(256) accumulate_fine_kernel(const AccArgs a) { accumulate_body<MODE, PINT, 1, 8, false>(a); }
@@ -456,8 +463,7 @@ hipError_t launch_accumulate(const Plan& pl, const Operand& A, const Operand& B,
     // kernel's length: 361 positions, 21 runs, emulated 28 -> 22 us; 64 positions 18.8 -> 12.7; at 800 the two are equal, and
     // beyond that four times the entry lists and word-wide loads lose (1024 positions 26 -> 37 us).
     const int64_t positions = ((pl.m + 31) / 32) * ((pl.n + 31) / 32);
-    // (Not behind launch_ladder_sums, which as a rule leaves nothing to do: the question alone takes 0.3 us of the smallest calls.)
-    const bool fine = positions <= 512 && off.counts == nullptr;
+    const bool fine = positions <= 512 && off.counts == nullptr;               // (behind launch_ladder_sums: as a rule nothing is left to do)
     // Products asked for before the list of runs is there, k = 256, us: FP8, hardware sum, 4096^2, 9 slices 157 -> 142, 4 slices 89 -> 78;
     // 2048^2 40.5 -> 36; exact 8192^2, 5 slices 637 -> 633; INT8, emulated 8192^2, 5 slices 546 -> 525, exact 706 -> 682.  Not worth it for
     // the emulated sum of FP32 products, which does not wait for its first products and loses the waves that their registers cost
@@ -465,15 +471,16 @@ hipError_t launch_accumulate(const Plan& pl, const Operand& A, const Operand& B,
     // 4 slices 11.3 -> 11.9; 5 to 13 slices gain, 18.7 -> 17.9 with 9).  Where runs end off the ladder the early products are thrown away.
     a.early = positions > 1024 || (accum_mode == ACC_HW && ps.ngroups > 4);
     const dim3 grid((unsigned)(fine ? 4 * blocks : blocks)), block(256);
-    auto launch = [&](auto coarse_kernel, auto fine_kernel) {
-        if (fine) hipLaunchKernelGGL(fine_kernel, grid, block, 0, st, a);
+    auto launch = [&](auto coarse_kernel, auto fine_kernel, auto rest_kernel) {
+        if (off.counts != nullptr) hipLaunchKernelGGL(rest_kernel, grid, block, 0, st, a);
+        else if (fine) hipLaunchKernelGGL(fine_kernel, grid, block, 0, st, a);
         else hipLaunchKernelGGL(coarse_kernel, grid, block, 0, st, a);
     };
     auto launch_mode = [&](auto mode, auto pint) {
         constexpr int M = decltype(mode)::value;
         constexpr bool I = decltype(pint)::value;
-        if (scaled != nullptr) launch(accumulate_scaled_kernel<M, I>, accumulate_scaled_fine_kernel<M, I>);
-        else launch(accumulate_kernel<M, I>, accumulate_fine_kernel<M, I>);
+        if (scaled != nullptr) launch(accumulate_scaled_kernel<M, I>, accumulate_scaled_fine_kernel<M, I>, accumulate_scaled_rest_kernel<M, I>);
+        else launch(accumulate_kernel<M, I>, accumulate_fine_kernel<M, I>, accumulate_rest_kernel<M, I>);
     };
     auto launch_words = [&](auto pint) {
         if (accum_mode == ACC_EXACT) launch_mode(std::integral_constant<int, ACC_EXACT>{}, pint);

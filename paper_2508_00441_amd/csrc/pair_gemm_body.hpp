@@ -136,7 +136,6 @@ __device__ __forceinline__ void pair_gemm_body(const GemmArgs& a) {
     // one workgroup = one tile of one group of pairs (p0 + j, q0 - j), j < glen
     const WorkItem item = work_item(blockIdx.x, gridDim.x, a.work, a.tiles_m, a.tiles_n);
     const int tn = item.bn, tm = item.bm;
-    if (on_ladder(a.off)) return;
     const Group grp = listed_group(a.groups, a.order, a.pass, item.gi);
     const int glen = grp.len, p0 = grp.p0 - 1, q0 = grp.q0 - 1;       // 0-based slice indices from here on
     const int chunks = (int)a.chunks;
@@ -353,6 +352,7 @@ __device__ __forceinline__ void pair_gemm_body(const GemmArgs& a) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) zero_tile(acc[i][j]);
     // prologue: fill the ring, wait for stage 0, read its first fragments
+    if (on_ladder(a.off)) return;                     // (here and not at the top, where the other calls would wait for the argument)
 #pragma unroll
     for (int st = 0; st < NSTAGE; ++st) issue_next(st);
     wait_and_barrier<(NSTAGE - 1) * 2 * LPW>();

@@ -345,7 +345,8 @@ inline bool place_call(const Plan& plan, bool want_product, int sum_words, bool 
 // k = 256 2.3 %, k = 512 0.1 %, k = 1024 none of 2048; phi = 1, k = 64 5 %, k = 128 0.15 %, from k = 256 on none; phi = 2 0.05 to 0.2 % up
 // to k = 1024; 9 INT8 slices none from k = 64 on (from 257 here: shorter blocks have a slicing kernel of their own).
 inline bool ladder_pays(const Plan& pl) {
-    return ladder_possible(pl) && pl.kb >= (pl.fmt == FMT_INT8 ? 257 : 512) &&
+    const int64_t shortest = pl.k - (pl.T - 1) * pl.kb;          // the last block
+    return ladder_possible(pl) && shortest >= (pl.fmt == FMT_INT8 ? 257 : 512) &&
            ladder_blocks(pl.m) * ladder_blocks(pl.n) >= (pl.fmt == FMT_FP8 && pl.chunks > 32 ? 160 : 90);
 }
 // The launch that counts the vectors off the ladder also fills the deltas.
