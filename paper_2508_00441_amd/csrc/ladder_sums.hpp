@@ -177,8 +177,13 @@ struct LadderSum<FMT, ACC_EXACT, GO_ON, S> {
 // The sums of a launch: of a triangle of pairs, or of all pairs in two launches, the less significant triangle first.
 constexpr int WHOLE = 0, LESSER_HALF = 1, GREATER_HALF = 2;
 
+// Workgroups per compute unit: two up to 8 slices, whose registers (128 accumulators of 256) and LDS (66 KB) allow it, one beyond.  One
+// of the two multiplies while the other waits at a barrier or sums.  The bound has to say so: left to themselves the sums took 296 registers
+// with 6 INT8 slices in the emulated mode, and 8 slices 276 in any, so that one workgroup was left.  4096^3, us, with one and with two: INT8
+// emulated, 6 slices 1661 and 1295, 7 of all pairs 3363 and 2698; hardware sum, 8 slices FP8 1895 and 1627, FP6 1580 and 1251, INT8 2071 and 1911.
+constexpr int ladder_workgroups(int s) { return s <= 8 ? 2 : 1; }
 template <int FMT, int S, int MODE, int PART>
-__global__ void __launch_bounds__(256, 1) ladder_sums_kernel(const LadderArgs a) {
+__global__ void __launch_bounds__(256, ladder_workgroups(S)) ladder_sums_kernel(const LadderArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)                                   // buffer descriptors are not a type on the host
     typedef Ladder<FMT, S> L;
     typedef LadderScale<FMT> Scale;

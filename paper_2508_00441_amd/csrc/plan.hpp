@@ -340,15 +340,14 @@ inline bool place_call(const Plan& plan, bool want_product, int sum_words, bool 
 //   INT8, 9     0.97 0.83 0.78     1.10 1.11 1.05     1.15 1.34 1.09     1.43 1.48 1.37     1.52 1.32 1.23     1.26 1.22 1.17     1.45 1.27 1.20
 //   FP6, 13     1.18 0.96 0.81     1.06 1.26 1.09     1.39 1.36 1.16     1.59 1.53 1.51     1.51 1.36 1.31     1.39 1.34 1.21     1.65 1.49 1.36
 // 94 tiles, 96 x 3000: 1.00 to 1.17, FP8 with 7 slices and 4500 inner indices 0.93.  Hence 90 tiles, for FP8 and more than 32 stages 160.
-// 4096^3, hardware sum, FP8 with 6 to 10 slices, ms: 1.11 and 1.08, 1.41 and 1.29, 1.75 and 1.82, 2.16 and 2.08, 2.60 and 2.37: with 8
-// the slices' stream still bounds the kernel, so those stay with the GEMM kernels where these have tiles for every compute unit.
+// Few slices gain least where these have tiles for every compute unit and the blocks are long: 2048 x 8192 x 6000, hardware sum, 6 to 9
+// slices FP8 1.00, 1.05, 1.09, 1.05, FP6 1.10, 1.15, 1.18, 1.02, INT8 1.05, 1.14, 1.16 (6 to 8).
 // Blocks: of short vectors some are off the ladder as a rule, and the call then takes the other route and the launch for nothing (10 us of 600 x
 // 600 x 1000).  The share of vectors off it, entries (u - 1/2) exp(phi z), 13 FP8 slices (which reach the end of the mantissas): phi = 0.5,
 // k = 256 2.3 %, k = 512 0.1 %, k = 1024 none of 2048; phi = 1, k = 64 5 %, k = 128 0.15 %, from k = 256 on none; phi = 2 0.05 to 0.2 % up
 // to k = 1024; 9 INT8 slices none from k = 64 on (from 257 here: shorter blocks have a slicing kernel of their own).
 inline bool ladder_pays(const Plan& pl) {
     const int64_t shortest = pl.k - (pl.T - 1) * pl.kb;          // the last block
-    if (pl.fmt == FMT_FP8 && pl.s == 8 && pl.tiles_m * pl.tiles_n >= 256) return false;
     return ladder_possible(pl) && shortest >= (pl.fmt == FMT_INT8 ? 257 : 512) &&
            ladder_blocks(pl.m) * ladder_blocks(pl.n) >= (pl.fmt == FMT_FP8 && pl.chunks > 32 ? 160 : 90);
 }

@@ -25,6 +25,12 @@ int plan_route(int64_t m, int64_t n, int64_t k, int fmt, int s, int64_t k_block,
     return 0;
 }
 
+// Does a call in the documented work memory start with launch_ladder_sums?
+int starts_on_ladder(int64_t m, int64_t n, int64_t k, int fmt, int s, int64_t k_block, int full) {
+    Plan plan;
+    return make_plan(m, n, k, fmt, s, k_block, full != 0, plan) == 0 && ladder_pays(plan);
+}
+
 // 1: strips, 0: the plain order, for a launch of groups of `len` pairs and less over the anti-diagonals of s slices, in blocks_m x blocks_n
 // blocks of 256 (small: 128)
 int order_of_launch(int small, int s, int full, int len, int64_t blocks_m, int64_t blocks_n, int64_t chunks) {

@@ -28,3 +28,9 @@ def route(m, n, k, fmt, s, k_block=0, mode="triangle", chained=True, minimum=Fal
     assert load().plan_route(i64(m), i64(n), i64(k), lib.SLICE_FORMATS[fmt], s, i64(k_block), lib.PAIR_SETS[mode], int(chained),
                              i64(-1 if minimum else 0), r) == 0
     return Route(*r)
+
+
+def starts_on_ladder(m, n, k, fmt, s, k_block=0, mode="triangle") -> bool:
+    """Does the call start with the one pass over all pairs?"""
+    i64 = ctypes.c_int64
+    return bool(load().starts_on_ladder(i64(m), i64(n), i64(k), lib.SLICE_FORMATS[fmt], s, i64(k_block), lib.PAIR_SETS[mode]))

@@ -11,6 +11,7 @@ import pytest
 
 from oracle import ozaki_oracle as oz
 from paper_2508_00441_amd import binding as lib, inputs
+import planner
 from test_no_fp64_instructions import F64, HIPCC, _kernel_bodies
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -51,6 +52,11 @@ def test_integer_only_forms_use_no_fp64(tmp_path, mode):
         used = set(re.findall(F64, body))
         assert "v_mfma_i32_32x32x32_i8" in body
         assert all(re.match(r"v_(add|ldexp|cvt|mul)_", u) for u in used) if mode == "hw" else not used, (n, used)
+
+
+def test_eight_slices_take_the_pass_in_large_results_as_others_do():
+    for fmt in ("fp8", "fp6", "int8"):
+        assert all(planner.starts_on_ladder(4096, 4096, k, fmt, s) for s in (6, 7, 8, 9) for k in (1024, 4096)), fmt
 
 
 def _operands(m, n, k, off):
