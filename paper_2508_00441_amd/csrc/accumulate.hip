@@ -335,6 +335,13 @@ template <int MODE, bool PINT>
 __global__ void __launch_bounds__(256) accumulate_scaled_kernel(const AccArgs a) { accumulate_body<MODE, PINT, 4, 4, true>(a); }
 template <int MODE, bool PINT>
 __global__ void __launch_bounds__(256) accumulate_scaled_fine_kernel(const AccArgs a) { accumulate_body<MODE, PINT, 1, 8, true>(a); }
+// Both behind launch_ladder_sums, where small results have as few positions as anywhere.  Calls with vectors off the ladder, emulated, by the
+// coarse forms and by these: 640 x 640 x 600, 9 INT8 slices 77.6 and 62.7 us, 600 x 600 x 1000, 11 FP8 slices in 64 MiB 135.5 and 117.7; with nothing to do
+// the four times as many workgroups take 0.5 us of a launch.
+template <int MODE, bool PINT>
+__global__ void __launch_bounds__(256) accumulate_fine_rest_kernel(const AccArgs a) { accumulate_body<MODE, PINT, 1, 8, false, true>(a); }
+template <int MODE, bool PINT>
+__global__ void __launch_bounds__(256) accumulate_scaled_fine_rest_kernel(const AccArgs a) { accumulate_body<MODE, PINT, 1, 8, true, true>(a); }
 
 // Verification export: one thread per stored word; grid.y = pair slot of the pass.  Writes the plain column-major
 // matrices and, if asked, the number of pairs each slot sums for the element (see launch_export_products).
@@ -463,7 +470,7 @@ hipError_t launch_accumulate(const Plan& pl, const Operand& A, const Operand& B,
     // kernel's length: 361 positions, 21 runs, emulated 28 -> 22 us; 64 positions 18.8 -> 12.7; at 800 the two are equal, and
     // beyond that four times the entry lists and word-wide loads lose (1024 positions 26 -> 37 us).
     const int64_t positions = ((pl.m + 31) / 32) * ((pl.n + 31) / 32);
-    const bool fine = positions <= 512 && off.counts == nullptr;               // (behind launch_ladder_sums: as a rule nothing is left to do)
+    const bool fine = positions <= 512;
     // Products asked for before the list of runs is there, k = 256, us: FP8, hardware sum, 4096^2, 9 slices 157 -> 142, 4 slices 89 -> 78;
     // 2048^2 40.5 -> 36; exact 8192^2, 5 slices 637 -> 633; INT8, emulated 8192^2, 5 slices 546 -> 525, exact 706 -> 682.  Not worth it for
     // the emulated sum of FP32 products, which does not wait for its first products and loses the waves that their registers cost
@@ -471,16 +478,19 @@ hipError_t launch_accumulate(const Plan& pl, const Operand& A, const Operand& B,
     // 4 slices 11.3 -> 11.9; 5 to 13 slices gain, 18.7 -> 17.9 with 9).  Where runs end off the ladder the early products are thrown away.
     a.early = positions > 1024 || (accum_mode == ACC_HW && ps.ngroups > 4);
     const dim3 grid((unsigned)(fine ? 4 * blocks : blocks)), block(256);
-    auto launch = [&](auto coarse_kernel, auto fine_kernel, auto rest_kernel) {
-        if (off.counts != nullptr) hipLaunchKernelGGL(rest_kernel, grid, block, 0, st, a);
+    auto launch = [&](auto coarse_kernel, auto fine_kernel, auto rest_kernel, auto fine_rest_kernel) {
+        const bool rest = off.counts != nullptr;
+        if (fine && rest) hipLaunchKernelGGL(fine_rest_kernel, grid, block, 0, st, a);
         else if (fine) hipLaunchKernelGGL(fine_kernel, grid, block, 0, st, a);
+        else if (rest) hipLaunchKernelGGL(rest_kernel, grid, block, 0, st, a);
         else hipLaunchKernelGGL(coarse_kernel, grid, block, 0, st, a);
     };
     auto launch_mode = [&](auto mode, auto pint) {
         constexpr int M = decltype(mode)::value;
         constexpr bool I = decltype(pint)::value;
-        if (scaled != nullptr) launch(accumulate_scaled_kernel<M, I>, accumulate_scaled_fine_kernel<M, I>, accumulate_scaled_rest_kernel<M, I>);
-        else launch(accumulate_kernel<M, I>, accumulate_fine_kernel<M, I>, accumulate_rest_kernel<M, I>);
+        if (scaled != nullptr)
+            launch(accumulate_scaled_kernel<M, I>, accumulate_scaled_fine_kernel<M, I>, accumulate_scaled_rest_kernel<M, I>, accumulate_scaled_fine_rest_kernel<M, I>);
+        else launch(accumulate_kernel<M, I>, accumulate_fine_kernel<M, I>, accumulate_rest_kernel<M, I>, accumulate_fine_rest_kernel<M, I>);
     };
     auto launch_words = [&](auto pint) {
         if (accum_mode == ACC_EXACT) launch_mode(std::integral_constant<int, ACC_EXACT>{}, pint);

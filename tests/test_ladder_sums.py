@@ -54,6 +54,17 @@ def test_integer_only_forms_use_no_fp64(tmp_path, mode):
         assert all(re.match(r"v_(add|ldexp|cvt|mul)_", u) for u in used) if mode == "hw" else not used, (n, used)
 
 
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
+def test_few_elements_behind_the_pass_are_accumulated_by_forms_for_few(tmp_path):
+    """One element per thread (a quarter of the work) also where the vectors turn out to be off the ladder, in every mode, plain and scaled."""
+    acc = _kernel_bodies("accumulate.hip", tmp_path)
+    for name in ("accumulate_fine_rest_kernel", "accumulate_scaled_fine_rest_kernel"):
+        for pint in ("Lb0E", "Lb1E"):
+            for mode in (0, 1, 2):
+                body = [b for n, b in acc.items() if f"{name}ILi{mode}E{pint}" in n]
+                assert len(body) == 1 and (mode == 0 or not re.search(F64, body[0])), (name, mode, pint)
+
+
 def test_eight_slices_take_the_pass_in_large_results_as_others_do():
     for fmt in ("fp8", "fp6", "int8"):
         assert all(planner.starts_on_ladder(4096, 4096, k, fmt, s) for s in (6, 7, 8, 9) for k in (1024, 4096)), fmt
