@@ -50,6 +50,7 @@ struct Operand {
     int32_t* exps;        // [T][s][rows_pad]   exponent c of Eq. 4 (0 for padding vectors)
     int32_t* l1;          // [T][s][rows_pad]   sum |q| of the slice (null: not wanted)
     int32_t* bounds;      // [T][s][rows_pad/LINK_ROWS]  2^b times the largest l1 of the group (see RunCheck)
+    uint8_t* off_ladder;  // [T][rows_pad]   is the vector off the ladder (OffLadder)? (null: not wanted)
     int32_t* deltas;      // [T][s][rows_pad/LINK_ROWS]  per slice p and group of 32 vectors (one matrix-unit tile edge):
                           //                        c_p - c_(p+1) if that difference is the same for all real vectors of
                           //                        the group, else DELTA_IRREGULAR (always for the last slice); null:
@@ -327,7 +328,9 @@ constexpr bool ladder_exact_fits(int fmt, int s, bool full) {
     const int above = (ladder_bits(fmt) + 1) * (full ? 2 * s - 2 : s - 1);
     return 31 + above + 1 <= 127 && above <= EXACT_WINDOW_BITS;
 }
-// How many vectors of the two operands are off the ladder (launch_deltas; the slicing kernels clear the counts).  Up to `limit` of each:
+// How many vectors of the two operands are off the ladder: those with a slice, other than zeros, whose exponent lies more than b + 1 below
+// that of the slice before.  (The slicing kernels say so of every vector, Operand::off_ladder, and clear the counts; the exponents alone do not
+// tell a slice that is left without a remainder, whose exponent is 0, from others.)  launch_deltas counts them.  Up to `limit` of each:
 // ladder_sums.hpp does the call's products but for theirs, which off_ladder.hpp does; beyond that the GEMM kernels and the accumulation,
 // which come behind.
 struct OffLadder {

@@ -255,6 +255,7 @@ inline bool carve(const Plan& pl, Carve& c, bool want_product, int sum_words, Wo
     c.A.deltas = reinterpret_cast<int32_t*>(ws + off); off += deltas_bytes(pl, pl.m_pad);
     c.B.deltas = reinterpret_cast<int32_t*>(ws + off); off += deltas_bytes(pl, pl.n_pad);
     c.A.l1 = c.B.l1 = c.A.bounds = c.B.bounds = nullptr;
+    c.A.off_ladder = c.B.off_ladder = nullptr;
     c.W = nullptr;
     if (want_product) { c.W = reinterpret_cast<double*>(ws + off); off += product_bytes(pl); }
     if (off > ws_bytes) return false;
@@ -355,6 +356,13 @@ inline bool ladder_pays(const Plan& pl) {
 constexpr int OFF_LADDER_MOST = 64;
 inline void place_ladder(Route& r) {
     if (!ladder_pays(r.pl)) return;
+    // What the slicing kernels say of the vectors lies at the end of the products' memory, which the first launch that reads it leaves alone: with
+    // all pairs the sums between its halves take 24 bytes per element of a 64 x 64 tile from the front.
+    const size_t products = (size_t)r.c.chunk_pairs * stored_bytes(r.pl), marks = (size_t)r.pl.T * (size_t)(r.pl.m_pad + r.pl.n_pad);
+    const size_t halves = r.pl.full ? (size_t)ladder_blocks(r.pl.m) * (size_t)ladder_blocks(r.pl.n) * LADDER_TILE * LADDER_TILE * sizeof(uint64_t) * SUM_WORDS_MAX : 0;
+    if (halves + marks > products) return;
+    r.c.A.off_ladder = reinterpret_cast<uint8_t*>(r.c.P) + (products - marks);
+    r.c.B.off_ladder = r.c.A.off_ladder + (size_t)r.pl.T * (size_t)r.pl.m_pad;
     r.off.counts = r.c.flags + OFF_LADDER_FLAG;
     // Some vectors off it: where the call is long against one more launch (3 to 5 us where there are none).  Their bits and the list lie in the
     // transposed A's memory, which is dead once the operands are sliced; the runs of such a call have no use for it (place_run_check:

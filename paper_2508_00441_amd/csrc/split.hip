@@ -56,6 +56,7 @@ struct SplitVectors {
     uint8_t* slices;       // null: count only, nothing is stored
     int32_t* exps;
     int32_t* l1;           // sum |q| per slice, or null (FP16 slices only)
+    uint8_t* off_ladder;   // is a slice's exponent more than b + 1 below that of the slice before? (null: not wanted)
 };
 
 // A launch splits the vectors of up to two operands (same k, block length, format and slice count): the first wg_first
@@ -363,6 +364,7 @@ __device__ __forceinline__ void slice_vectors(const SplitArgs& a) {
         for (int e = 0; e < G; ++e) g.x[0][e] = g.x[1][e] = g.x[2][e] = 0;
     };
     int my_exp = 0;                                                  // lane p of the first wave: c of slice p
+    bool off_ladder = false;
     for (int p = 0; p < a.s;) {
         uint32_t turns[3] = {0, 0, 0};
         if (left) {
@@ -463,6 +465,7 @@ __device__ __forceinline__ void slice_vectors(const SplitArgs& a) {
             const int next = digit_next(turns, run, l.step);
             more = next != NUMBER_BITS;
             if (!digit_in_number(at + next, l.step)) break;
+            off_ladder = off_ladder || next != run * l.step;
             at += next;
             move_up(next - moved);
             for (int rest = next; rest > 0; rest -= 31) digit_shift(turns[2], turns[1], turns[0], rest < 31 ? rest : 31);
@@ -489,9 +492,11 @@ __device__ __forceinline__ void slice_vectors(const SplitArgs& a) {
                 key = vector_max(key, 1);
             }
             left = key != 0;
+            off_ladder = off_ladder || (left && (int)key - CD_BIAS != c - last - l.step);
             c = (int)key - CD_BIAS;
         }
     }
+    if (v.off_ladder != nullptr && tr == 0) v.off_ladder[t * v.rows_pad + row] = off_ladder ? 1 : 0;
     if (v.slices != nullptr && tr < a.s) v.exps[(t * a.s + tr) * v.rows_pad + row] = my_exp;
     if constexpr (FP16 && WHOLE) {
         if (v.l1 != nullptr) {
@@ -546,6 +551,7 @@ __global__ void __launch_bounds__(1024) long_exponents_kernel(SplitArgs a) {
     int32_t* const exps = v.exps != nullptr ? v.exps + t * a.s * v.rows_pad + row : nullptr;
     if (row >= v.rows) {                                             // a padding vector: c = 0 throughout
         if (exps != nullptr && tid < a.s) exps[(int64_t)tid * v.rows_pad] = 0;
+        if (v.off_ladder != nullptr && tid == 0) v.off_ladder[t * v.rows_pad + row] = 0;
         return;
     }
     const double* const src = v.X + row * v.ldv + t * a.kb;
@@ -592,13 +598,13 @@ __global__ void __launch_bounds__(1024) long_exponents_kernel(SplitArgs a) {
         });
     if (top >= 0x7FF00000u) atomicOr(a.flags, 1);                    // infinity or NaN
     top = block_max(top);
-    bool left = top != 0;                                            // is there a remainder before slice p?
+    bool left = top != 0, off_ladder = false;                        // is there a remainder before slice p?
     int c = 0, p = 0;
     if (left) c = top >= 0x100000u ? magnitude_exponent(top) : (int)largest_remainder(2000) - CD_BIAS;      // 2^2000: x itself
     while (left && p < a.s) {
         uint32_t turns[3] = {0, 0, 0}, all[3];
         int levels, at, last, my_exp = 0;                            // slices off these numbers, places of the last run's first and last
-        bool more = true;                                            // is there a remainder after them?
+        bool more = true, gap = false;                               // is there a remainder after them?
         for (int64_t i = 0, turn = 0;; turn ^= 1) {
             for_chunk(i, [&](uint64_t w) {
                 uint32_t x[3];
@@ -620,6 +626,7 @@ __global__ void __launch_bounds__(1024) long_exponents_kernel(SplitArgs a) {
             }
             // more elements can only bring the units closer, to `step` places at the least
             bool regular = true;
+            gap = false;
             for (at = 0, levels = 0;;) {
                 int run = digit_run(all, at, l);
                 run = run < a.s - p - levels ? run : a.s - p - levels;
@@ -631,6 +638,7 @@ __global__ void __launch_bounds__(1024) long_exponents_kernel(SplitArgs a) {
                 regular = regular && next == run * l.step;
                 more = next != NUMBER_BITS;
                 if (!digit_in_number(at + next, l.step)) break;
+                gap = gap || next != run * l.step;
                 at += next;
                 for (int rest = next; rest > 0; rest -= 31) digit_shift(all[2], all[1], all[0], rest < 31 ? rest : 31);
             }
@@ -638,11 +646,14 @@ __global__ void __launch_bounds__(1024) long_exponents_kernel(SplitArgs a) {
         }
         if (exps != nullptr && tid < levels) exps[(int64_t)(p + tid) * v.rows_pad] = my_exp;
         p += levels;
+        off_ladder = off_ladder || gap;
         if (p >= a.s) break;
         const uint32_t key = more ? largest_remainder(c - last - a.b) : 0u;
         left = key != 0;
+        off_ladder = off_ladder || (left && (int)key - CD_BIAS != c - last - l.step);
         c = (int)key - CD_BIAS;
     }
+    if (v.off_ladder != nullptr && tid == 0) v.off_ladder[t * v.rows_pad + row] = off_ladder ? 1 : 0;
     // nothing left: the remaining slices are zero (c := 0); without slices to write, report how many there are
     if (exps != nullptr)
         for (int i = p + tid; i < a.s; i += 1024) exps[(int64_t)i * v.rows_pad] = 0;
@@ -812,6 +823,7 @@ struct DeltaOperand {
     int32_t* deltas;
     const int32_t* l1;
     int32_t* bounds;
+    const uint8_t* off_ladder;
     int64_t rows, rows_pad;
 };
 __global__ void __launch_bounds__(256) delta_kernel(DeltaOperand o0, DeltaOperand o1, unsigned tiles_first, int s, int b, OffLadder off_ladder) {
@@ -825,12 +837,12 @@ __global__ void __launch_bounds__(256) delta_kernel(DeltaOperand o0, DeltaOperan
     const int lane = threadIdx.x & 63, half = lane & 32;
     const int32_t* e = exps + (size_t)t * s * rows_pad;
     int32_t* out = deltas + (size_t)t * s * groups + group;          // slice p of this group at out[p * groups]
-    bool off = false;
+    const uint8_t* const marks = second ? o1.off_ladder : o0.off_ladder;
+    const bool off = off_ladder.counts != nullptr && marks[(size_t)t * rows_pad + row] != 0;
     for (int p = 0; p + 1 < s; ++p) {
         const int d = e[(size_t)p * rows_pad + row] - e[(size_t)(p + 1) * rows_pad + row];
         // the first vector of a group is a real one, or the whole group is padding (then every d is 0)
         const int ref = __shfl(d, half, 64);
-        off = off || d > b + 1;                                      // a remainder that is not zero gives b + 1 or more, a zero one 0 - (its slice's exponent is 0) or less
         const unsigned long long ok = __ballot(row >= rows || d == ref);
         const bool same = (uint32_t)(ok >> half) == 0xFFFFFFFFu;
         if ((lane & 31) == 0) out[(size_t)p * groups] = same ? ref : DELTA_IRREGULAR;
@@ -921,7 +933,7 @@ SplitVectors split_vectors(const double* X, int64_t ldv, int64_t es, const Opera
     SplitVectors v;
     memset(&v, 0, sizeof(v));
     if (op == nullptr || op->rows == 0) return v;                                 // no vectors: no workgroups
-    v.X = X; v.ldv = ldv; v.es = es; v.rows = op->rows; v.rows_pad = op->rows_pad; v.slices = op->slices; v.exps = op->exps; v.l1 = op->l1;
+    v.X = X; v.ldv = ldv; v.es = es; v.rows = op->rows; v.rows_pad = op->rows_pad; v.slices = op->slices; v.exps = op->exps; v.l1 = op->l1; v.off_ladder = op->off_ladder;
     return v;
 }
 }  // namespace
@@ -961,7 +973,7 @@ hipError_t launch_count_slices(const double* X, int64_t ldv, const Plan& pl, int
     Operand op;
     op.rows = rows;
     op.rows_pad = (rows + TILE - 1) / TILE * TILE;
-    op.slices = nullptr; op.exps = nullptr; op.deltas = nullptr; op.l1 = nullptr; op.bounds = nullptr;
+    op.slices = nullptr; op.exps = nullptr; op.deltas = nullptr; op.l1 = nullptr; op.bounds = nullptr; op.off_ladder = nullptr;
     return launch_split(X, ldv, 1, &op, nullptr, 0, nullptr, cp, flags, st);
 }
 
@@ -970,7 +982,7 @@ hipError_t launch_deltas(const Plan& pl, const Operand* op0, const Operand* op1,
     memset(o, 0, sizeof(o));
     const Operand* ops[2] = {op0, op1};
     for (int i = 0; i < 2; ++i)
-        if (ops[i] != nullptr && ops[i]->rows > 0) o[i] = DeltaOperand{ops[i]->exps, ops[i]->deltas, ops[i]->l1, ops[i]->bounds, ops[i]->rows, ops[i]->rows_pad};
+        if (ops[i] != nullptr && ops[i]->rows > 0) o[i] = DeltaOperand{ops[i]->exps, ops[i]->deltas, ops[i]->l1, ops[i]->bounds, ops[i]->off_ladder, ops[i]->rows, ops[i]->rows_pad};
     const unsigned t0 = (unsigned)(o[0].rows_pad / TILE), t1 = (unsigned)(o[1].rows_pad / TILE);
     if (t0 + t1 == 0 || pl.T == 0 || pl.s == 0) return hipSuccess;
     hipLaunchKernelGGL(delta_kernel, dim3(t0 + t1, (unsigned)pl.T), dim3(256), 0, st, o[0], o[1], t0, pl.s, pl.b, off);

@@ -175,3 +175,35 @@ def test_vectors_off_the_ladder_in_large_results(fmt, m, n, k, s, rows_off, cols
         assert lib.ozaki_last_device_status() == 0
         assert np.array_equal(D.cpu().numpy().view(np.uint64), (-1.5 * got + 0.3 * C0).view(np.uint64)), accum
     lib.ozaki_set_workspace(None, 0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fmt,m,n,k,k_block,s", [("fp8", 640, 577, 600, 0, 11), ("int8", 640, 577, 600, 300, 9), ("fp6", 700, 600, 1200, 0, 13),
+                                                 ("int8", 600, 640, 20000, 0, 7), ("fp8", 2050, 2082, 513, 0, 13)])
+@pytest.mark.parametrize("scale", [0, 20, -300])
+def test_vectors_that_run_out_are_on_the_ladder_at_any_scale(fmt, m, n, k, k_block, s, scale):
+    """Integers of ten bits times a power of two, whose later slices are zeros; a vector that runs out behind a gap is off the ladder, also where the
+    slice behind the gap has the exponent of one without a remainder (zero)."""
+    torch = pytest.importorskip("torch")
+    from paper_2508_00441_amd import device
+    rng = np.random.default_rng(m + k)
+    A, B = (np.ldexp(rng.integers(-1000, 1001, shape).astype(np.float64), scale) for shape in ((m, k), (k, n)))
+    rows, cols = [0, 7, 63, 64, m - 1], [0, 5, 63, 64, n - 1]
+    f = FMT[fmt]
+    ws = torch.zeros(lib.ozaki_workspace_bytes_scaled(m, n, k, f, s, k_block), dtype=torch.uint8, device="cuda")
+    lib.ozaki_set_stream(torch.cuda.current_stream().cuda_stream)
+    lib.ozaki_set_workspace(ws, ws.numel())
+    for gap in (False, True):
+        if gap:
+            A[7, :] = 0.0
+            A[7, [1, k - 1]] = 2.0 ** 20, 1.0
+        want = oz.ozaki_dgemm(A[rows], B[:, cols], fmt, s, k_block, accumulate="runs")
+        C = torch.full((n, m), float("nan"), dtype=torch.float64, device="cuda")
+        lib.ozaki_dgemm(m, n, k, device.to_device_colmajor(A), m, device.to_device_colmajor(B), k, C, m, f, s, k_block, ACC["emu"])
+        assert lib.ozaki_last_device_status() == 0
+        counts = ws[:32].cpu().numpy().view(np.int32)[4:6].tolist()
+        got = np.ascontiguousarray(C.cpu().numpy().T[np.ix_(rows, cols)])
+        assert np.array_equal(got.view(np.uint64), want.view(np.uint64))
+        off = gap and k_block == 0                                    # (in two blocks the row's entries lie in different ones)
+        assert counts == [int(off), 0], counts
+    lib.ozaki_set_workspace(None, 0)
