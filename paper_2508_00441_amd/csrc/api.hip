@@ -86,7 +86,7 @@ constexpr int64_t MAX_ELEMS_WITHOUT_TRANSPOSE = 1 << 20;
 
 // split both operands of the plan into the carved buffers
 int run_split(const Plan& pl, const Carve& c, const double* A, int64_t lda, const double* B, int64_t ldb, bool do_a, bool do_b,
-              const OffLadder& off = OffLadder{nullptr, 0, nullptr, nullptr}) {
+              const OffLadder& off = NO_LADDER) {
     Phase ph(0);
     hipStream_t st = ctx().stream;
     const bool a_on = do_a && pl.m > 0, b_on = do_b && pl.n > 0;
@@ -508,13 +508,13 @@ int ozaki_pair_products(int64_t m, int64_t n, int64_t k, const double* A, int64_
     Operand ea = c.A, eb = c.B;
     ea.deltas = r.deltas_a;
     eb.deltas = r.deltas_b;
-    if (c.A.deltas == nullptr) HIP_TRY(launch_deltas(pl, &ea, &eb, OffLadder{nullptr, 0, nullptr, nullptr}, stream));
+    if (c.A.deltas == nullptr) HIP_TRY(launch_deltas(pl, &ea, &eb, NO_LADDER, stream));
     for (int64_t t = 0; t < pl.T; ++t) {
         int z0 = 0;
         for (int g_hi = order_top_diag(order); g_hi >= 2;) {
             const Pass ps = next_pass(order, g_hi, c.chunk_pairs);
             const size_t at = ((size_t)t * pl.npairs + z0) * (size_t)m * n;
-            HIP_TRY(launch_pair_gemm(pl, c.A, c.B, order, ps, chained != 0, r.check, OffLadder{nullptr, 0, nullptr, nullptr}, t, c.P, stream));
+            HIP_TRY(launch_pair_gemm(pl, c.A, c.B, order, ps, chained != 0, r.check, NO_LADDER, t, c.P, stream));
             HIP_TRY(launch_export_products(pl, ea, eb, order, ps, chained != 0, r.check.starts, t, c.P, static_cast<float*>(P_out) + at,
                                            run_len_out ? run_len_out + at : nullptr, stream));
             z0 += ps.npairs;

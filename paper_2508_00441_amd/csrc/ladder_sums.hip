@@ -59,6 +59,7 @@ hipError_t launch_ladder_sums(const Plan& pl, const Operand& A, const Operand& B
     }
     for (int part = pl.full ? LESSER_HALF : WHOLE; part <= (pl.full ? GREATER_HALF : WHOLE); ++part) {
         const int S_kernel = part == LESSER_HALF ? pl.s - 1 : pl.s;
+        if (t > 0 || part == GREATER_HALF) a.off.marks = nullptr;      // the call's first launch has left its answer
         const unsigned blocks = (unsigned)(bm * bn);
         hipError_t e;
         if (pl.fmt == FMT_FP6) e = launch_mode<FMT_FP6>(a, S_kernel, accum_mode, part, blocks, st);

@@ -195,8 +195,21 @@ __global__ void __launch_bounds__(256, ladder_workgroups(S)) ladder_sums_kernel(
     __shared__ __attribute__((aligned(16))) uint8_t lds[L::LDS_BYTES + 512];     // one array: with several, the compiler waits for all loads into LDS before every read
     int* const leading = reinterpret_cast<int*>(lds + L::LDS_BYTES);  // first-slice exponents of the 64 rows and 64 columns
 
-    if (!on_ladder(a.off)) return;
     const int tid = threadIdx.x, lane = tid & 63;
+    if (a.off.marks != nullptr) {
+        const v4i* const marks = reinterpret_cast<const v4i*>(a.off.marks);
+        v4i any = {0, 0, 0, 0};
+#pragma unroll 4
+        for (int i = lane; i < a.off.mark_bytes / 16; i += 64) any |= marks[i];
+        const bool off = __ballot((any[0] | any[1] | any[2] | any[3]) != 0) != 0;
+        if (blockIdx.x == 0 && tid == 0) {                            // for the launches behind this one
+            a.off.counts[0] = off ? 1 : 0;
+            a.off.counts[1] = 0;
+        }
+        if (off) return;
+    } else if (!on_ladder(a.off)) {
+        return;
+    }
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave >> 1, wm = wave & 1;
     const WorkItem item = work_item(blockIdx.x, gridDim.x, a.work, a.blocks_m, a.blocks_n);

@@ -316,7 +316,7 @@ struct Route {
 // groups that take the least time; otherwise in the longest groups of the worst case.  False if the memory does not hold it.
 inline bool place_call(const Plan& plan, bool want_product, int sum_words, bool chained, bool as_dgemm, WorkMem wm, Route& r) {
     r.pl = plan;
-    r.off = OffLadder{nullptr, 0, nullptr, nullptr};
+    r.off = NO_LADDER;
     r.check = RunCheck{nullptr, nullptr, nullptr};
     if (!carve(plan, r.c, want_product, sum_words, wm)) return false;
     if (chained && as_dgemm) r.check = place_run_check(r.pl, r.c);
@@ -352,7 +352,6 @@ inline bool ladder_pays(const Plan& pl) {
     return ladder_possible(pl) && shortest >= (pl.fmt == FMT_INT8 ? 257 : 512) &&
            ladder_blocks(pl.m) * ladder_blocks(pl.n) >= (pl.fmt == FMT_FP8 && pl.chunks > 32 ? 160 : 90);
 }
-// The launch that counts the vectors off the ladder also fills the deltas.
 constexpr int OFF_LADDER_MOST = 64;
 inline void place_ladder(Route& r) {
     if (!ladder_pays(r.pl)) return;
@@ -373,6 +372,15 @@ inline void place_ladder(Route& r) {
         r.off.limit = OFF_LADDER_MOST;
         r.off.bits = reinterpret_cast<uint32_t*>(r.c.At);
         r.off.list = reinterpret_cast<int*>(r.c.At) + words;
+    }
+    // The launch that counts the vectors off the ladder also fills the deltas.  Where the other kernels have no use for these (place_call), and
+    // nothing is listed, the one pass looks at the vectors itself, us with that launch and without: 600 x 600 x 1000, 11 FP8 slices 64.2 and 59.6
+    // (off the ladder 78.4 and 75.6, where the GEMM kernels and the accumulation alone take 72.1); 640 x 640 x 600, 13 FP6 slices 53.4 and 47.9
+    // (68.7, 64.4; 61.0); 9 INT8 slices, emulated 50.0 and 46.0 (62.4, 59.0; 55.7).
+    if (r.c.A.deltas == nullptr && r.off.limit == 0 && marks <= MOST_MARKS) {
+        r.off.marks = r.c.A.off_ladder;
+        r.off.mark_bytes = (int)marks;
+        return;
     }
     r.c.A.deltas = r.deltas_a;
     r.c.B.deltas = r.deltas_b;

@@ -465,7 +465,7 @@ __device__ __forceinline__ void slice_vectors(const SplitArgs& a) {
             const int next = digit_next(turns, run, l.step);
             more = next != NUMBER_BITS;
             if (!digit_in_number(at + next, l.step)) break;
-            off_ladder = off_ladder || next != run * l.step;
+            if constexpr (!FP16) off_ladder = off_ladder || next != run * l.step;
             at += next;
             move_up(next - moved);
             for (int rest = next; rest > 0; rest -= 31) digit_shift(turns[2], turns[1], turns[0], rest < 31 ? rest : 31);
@@ -492,11 +492,11 @@ __device__ __forceinline__ void slice_vectors(const SplitArgs& a) {
                 key = vector_max(key, 1);
             }
             left = key != 0;
-            off_ladder = off_ladder || (left && (int)key - CD_BIAS != c - last - l.step);
+            if constexpr (!FP16) off_ladder = off_ladder || (left && (int)key - CD_BIAS != c - last - l.step);
             c = (int)key - CD_BIAS;
         }
     }
-    if (v.off_ladder != nullptr && tr == 0) v.off_ladder[t * v.rows_pad + row] = off_ladder ? 1 : 0;
+    if (!FP16 && v.off_ladder != nullptr && tr == 0) v.off_ladder[t * v.rows_pad + row] = off_ladder ? 1 : 0;
     if (v.slices != nullptr && tr < a.s) v.exps[(t * a.s + tr) * v.rows_pad + row] = my_exp;
     if constexpr (FP16 && WHOLE) {
         if (v.l1 != nullptr) {

@@ -25,10 +25,23 @@ int plan_route(int64_t m, int64_t n, int64_t k, int fmt, int s, int64_t k_block,
     return 0;
 }
 
-// Does a call in the documented work memory start with launch_ladder_sums?
-int starts_on_ladder(int64_t m, int64_t n, int64_t k, int fmt, int s, int64_t k_block, int full) {
+// How a call in the documented work memory (with room for a scaled call's product) begins.  route: with launch_ladder_sums?, vectors off the ladder
+// that it leaves out, does it look at the vectors itself?, is there a launch_deltas?, bytes at the end of the products' memory.
+int ladder_route(int64_t m, int64_t n, int64_t k, int fmt, int s, int64_t k_block, int full, int exact, int64_t route[5]) {
     Plan plan;
-    return make_plan(m, n, k, fmt, s, k_block, full != 0, plan) == 0 && ladder_pays(plan);
+    const int st = make_plan(m, n, k, fmt, s, k_block, full != 0, plan);
+    if (st != 0) return st;
+    Route r;
+    const size_t size = recommended_bytes(plan) + product_bytes(plan);
+    if (!place_call(plan, false, exact ? SUM_WORDS_MAX : 1, true, true, WorkMem{reinterpret_cast<uint8_t*>((uintptr_t)1 << 40), size}, r))
+        return OZAKI_STATUS_WORKSPACE;
+    if (!exact || ladder_exact_fits(fmt, s, full != 0)) place_ladder(r);
+    route[0] = r.off.counts != nullptr;
+    route[1] = r.off.limit;
+    route[2] = r.off.marks != nullptr;
+    route[3] = r.c.A.deltas != nullptr;
+    route[4] = r.c.A.off_ladder ? reinterpret_cast<uint8_t*>(r.c.P) + (size_t)r.c.chunk_pairs * stored_bytes(r.pl) - r.c.A.off_ladder : 0;
+    return 0;
 }
 
 // 1: strips, 0: the plain order, for a launch of groups of `len` pairs and less over the anti-diagonals of s slices, in blocks_m x blocks_n

@@ -9,6 +9,7 @@ import tempfile
 from paper_2508_00441_amd import binding as lib
 
 HERE = os.path.dirname(os.path.abspath(__file__))
+Ladder = collections.namedtuple("Ladder", "starts limit reads_marks delta_launch mark_bytes")
 Route = collections.namedtuple("Route", "small group_len run_limit measured bounds_from_slices pairs_per_pass")
 
 
@@ -30,7 +31,9 @@ def route(m, n, k, fmt, s, k_block=0, mode="triangle", chained=True, minimum=Fal
     return Route(*r)
 
 
-def starts_on_ladder(m, n, k, fmt, s, k_block=0, mode="triangle") -> bool:
-    """Does the call start with the one pass over all pairs?"""
+def ladder(m, n, k, fmt, s, k_block=0, mode="triangle", exact=False) -> Ladder:
+    """How a DGEMM begins: with the one pass over all pairs?"""
+    r = (ctypes.c_int64 * 5)()
     i64 = ctypes.c_int64
-    return bool(load().starts_on_ladder(i64(m), i64(n), i64(k), lib.SLICE_FORMATS[fmt], s, i64(k_block), lib.PAIR_SETS[mode]))
+    assert load().ladder_route(i64(m), i64(n), i64(k), lib.SLICE_FORMATS[fmt], s, i64(k_block), lib.PAIR_SETS[mode], int(exact), r) == 0
+    return Ladder(*r)
