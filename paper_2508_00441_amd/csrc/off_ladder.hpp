@@ -48,7 +48,8 @@ constexpr int MIN_S = OFF_LADDER_MIN_SLICES, MAX_S = OFF_LADDER_MAX_SLICES;
 constexpr int AGPR_SLOTS = 16;
 
 // Which wave forms the product of pair (p, q), 0-based, p + q < S: the pairs in the order (0,0) (0,1) ... (1,0) ...  At most
-// ceil(pairs / 4) per wave (9 slices: one more), the fewest slices per wave that a simulated annealing found.
+// ceil(pairs / 4) per wave; any such table will do that table_ok takes, these were found by moving pairs about at random and keep the number of different slices that a
+// wave reads low.
 constexpr const char* OWNERS[MAX_S + 1] = {
     "", "", "", "", "", "",
     "300033300032211221223",
@@ -123,6 +124,14 @@ template <int S> constexpr int most_slots() {
     if (SHARE<S, 2>.count > c) c = SHARE<S, 2>.count;
     if (SHARE<S, 3>.count > c) c = SHARE<S, 3>.count;
     return c;
+}
+// Every pair has an owner, no wave more than its share, and each at least the two columns that its loop reads ahead.
+template <int S> constexpr bool table_ok() {
+    constexpr int PAIRS = S * (S + 1) / 2;
+    for (int i = 0; i < PAIRS; ++i)
+        if (OWNERS[S][i] < '0' || OWNERS[S][i] > '3') return false;
+    return OWNERS[S][PAIRS] == 0 && SHARE<S, 0>.count + SHARE<S, 1>.count + SHARE<S, 2>.count + SHARE<S, 3>.count == PAIRS &&
+           most_slots<S>() == (PAIRS + 3) / 4 && SHARE<S, 0>.cols >= 2 && SHARE<S, 1>.cols >= 2 && SHARE<S, 2>.cols >= 2 && SHARE<S, 3>.cols >= 2;
 }
 template <int S>
 struct Places {
@@ -304,6 +313,7 @@ template <int FMT, int S, bool INTEGER_ONLY>
 __global__ void __launch_bounds__(256, 1) off_ladder_kernel(const OffLadderArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)                                   // buffer descriptors are not a type on the host
     typedef Ring<S> R;
+    static_assert(table_ok<S>(), "OWNERS");
     constexpr bool INT8 = FMT == FMT_INT8;
     constexpr int BK = CHUNK_BYTES;
     constexpr int NSLOT = most_slots<S>();
@@ -398,7 +408,9 @@ __global__ void __launch_bounds__(256, 1) off_ladder_kernel(const OffLadderArgs 
     // The compiler keeps the results of the builtins in the 256 accumulator registers, 16 slots' worth; further slots go to ordinary
     // registers, of which this kernel has 256 too, by instructions of their own.  Their hazards are not the compiler's
     // business: the wait states after a write of a source register stand in front of them, and a result is only read by the next product of the
-    // same slot, sixteen matrix instructions later, and after the wait states behind the k loop.
+    // same slot, as the summand that it writes in place (which needs none but those; with INT8 the two steps of a product are a column
+    // apart, three instructions for 11 slices), and after the wait states behind the k loop.  That nothing else touches those registers inside
+    // the loop is checked on the built kernels (tests/test_off_ladder_listing.py).
     constexpr int KS = INT8 ? 2 : 1;                                  // matrix instructions per slot and stage
     auto multiply = [&](auto slot, auto ks, const Frag& x, const Frag& y, acc_t& c) {
         constexpr int k = decltype(ks)::value;
