@@ -9,6 +9,8 @@ import subprocess
 
 import pytest
 
+import listing
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2508_00441_amd", "csrc")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -93,3 +95,27 @@ def test_the_other_integer_only_kernels_use_no_fp64(tmp_path):
         for n, body in gemm.items():
             assert not re.search(F64, body), n
             assert re.search(mfma, body), n
+
+
+@pytest.mark.skipif(not listing.AVAILABLE, reason="no LLVM tools")
+def test_no_integer_only_kernel_of_the_library_uses_fp64():
+    """Every kernel of the built library: the one pass over all pairs and the vectors off its ladder in all formats, slice counts and parts, the forms
+    behind it, and all the others."""
+    seen = {}
+    for symbol, text in listing.texts().items():
+        used = set(re.findall(r"^\s+(v_\w*f64\w*)", text, flags=re.M))
+        name = re.search(r"\d+([a-z_0-9]+_kernel)", symbol).group(1)
+        # the kernels with a mode: its place among the template arguments, and the value of the hardware sum
+        at, hardware = {"ladder_sums_kernel": (2, "0"), "off_ladder_kernel": (2, "0"), "axpby_kernel": (0, "0")}.get(name, (0, "0") if name.startswith("accumulate_") else (None, None))
+        if at is not None and re.findall(r"L[ib](\d+)E", symbol)[at] == hardware:
+            seen[name, "hw"] = seen.get((name, "hw"), 0) + 1
+            assert used and all(re.match(r"v_(add|ldexp|cvt|mul)_", u) for u in used), (symbol, used)      # no fused multiply-add
+        else:
+            seen[name, ""] = seen.get((name, ""), 0) + 1
+            assert not used, (symbol, used)
+    for name in ("accumulate_kernel", "accumulate_fine_kernel", "accumulate_rest_kernel", "accumulate_fine_rest_kernel", "accumulate_scaled_kernel",
+                 "accumulate_scaled_fine_kernel", "accumulate_scaled_rest_kernel", "accumulate_scaled_fine_rest_kernel"):
+        assert seen[name, "hw"] == 2 and seen[name, ""] == 4, name    # INT32 and FP32 products
+    assert seen["off_ladder_kernel", "hw"] == seen["off_ladder_kernel", ""] == 14        # FP8 with 6 to 13 slices, INT8 with 6 to 11
+    assert seen["ladder_sums_kernel", ""] > seen["ladder_sums_kernel", "hw"] >= 40
+    assert seen["pair_gemm_small_kernel", ""] == 10 and seen["split_kernel", ""] == 40 and seen["slice_short_kernel", ""] == 4
