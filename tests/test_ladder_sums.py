@@ -82,8 +82,29 @@ def test_where_the_links_are_formed_in_the_kernels_there_is_no_launch_for_the_ve
     assert planner.ladder(600, 600, 400, "fp8", 11).starts == 0 and planner.ladder(600, 600, 1000, "fp16", 7).mark_bytes == 0
 
 
-def _operands(m, n, k, off):
+def _off_ladder(X, fmt, s, k_block):
+    """How many rows of X, block by block, have a slice other than zeros more than b + 1 places below the one before."""
+    plan, count = oz.make_plan(X.shape[1], fmt, k_block), 0
+    for t in range(plan.num_blocks):
+        slices, c, _ = oz.slice_rows(X[:, t * plan.k_block:(t + 1) * plan.k_block], plan.rho, s)
+        off = np.zeros(len(X), bool)
+        for p in range(1, s):
+            off |= slices[p].any(axis=1) & (c[p - 1] - c[p] > plan.b + 1)
+        count += int(off.sum())
+    return count
+
+
+def _matrices(m, n, k, fmt, s):
+    """More slices than a mantissa and the spread of the entries fill would leave the ladder at its end: then a third of the entries lie lower."""
     A, B = inputs.phi_pair(m, n, k, 1.0, seed=m + n + k)
+    if s * (oz.make_plan(k, fmt).b + 1) > 66:
+        A[:, ::3] *= 2.0 ** -24
+        B[::3, :] *= 2.0 ** -24
+    return A, B
+
+
+def _operands(m, n, k, fmt, s, off):
+    A, B = _matrices(m, n, k, fmt, s)
     rng = np.random.default_rng(k)
     A[3, :] = 0.0
     A[m - 1, :] = np.ldexp(rng.integers(-7, 8, k).astype(np.float64), -30)             # runs out after a slice or two
@@ -103,13 +124,23 @@ gpu_cases = pytest.mark.parametrize("fmt,m,n,k,k_block,s,pairs", [
     ("fp8", 640, 577, 1031, 0, 6, "triangle"),          # the fewest slices, odd number of stages
     ("fp8", 833, 800, 4600, 0, 14, "triangle"),         # the most; the window's edge; 14 x 13 tiles
     ("fp8", 65, 3000, 600, 0, 8, "triangle"),
+    ("fp8", 640, 577, 600, 0, 7, "triangle"),
+    ("fp8", 641, 580, 512, 0, 9, "triangle"),
+    ("fp8", 1000, 777, 1150, 600, 12, "triangle"),      # two blocks, the second one shorter: the scaled call's product so far is not C
     ("fp8", 512, 770, 1100, 550, 11, "full"),           # two blocks, both halves of the pairs
     ("fp8", 640, 600, 700, 0, 10, "full"),
     ("fp6", 641, 530, 600, 0, 14, "triangle"),
+    ("fp6", 640, 580, 1600, 800, 6, "triangle"),
+    ("fp6", 640, 580, 600, 0, 10, "triangle"),
     ("fp6", 640, 570, 600, 0, 12, "full"),
     ("fp6_e3m2", 640, 580, 700, 0, 15, "triangle"),
     ("fp6_e3m2", 640, 580, 640, 0, 13, "full"),
+    ("fp6_e3m2", 640, 580, 520, 0, 10, "triangle"),
+    ("fp6_e3m2", 640, 580, 1300, 650, 12, "triangle"),
     ("int8", 640, 576, 300, 0, 11, "triangle"),
+    ("int8", 640, 580, 300, 0, 7, "triangle"),
+    ("int8", 640, 580, 580, 290, 8, "triangle"),
+    ("int8", 640, 580, 600, 0, 10, "triangle"),
     ("int8", 641, 576, 20000, 0, 6, "triangle"),        # a block that is sliced exponents first
     ("int8", 660, 640, 520, 260, 9, "full"),
     ("int8", 512, 511, 300, 0, 11, "triangle"),         # 64 tiles: the other kernels
@@ -122,7 +153,13 @@ gpu_cases = pytest.mark.parametrize("fmt,m,n,k,k_block,s,pairs", [
 def test_results_are_the_oracles(fmt, m, n, k, k_block, s, pairs, off):
     torch = pytest.importorskip("torch")
     from paper_2508_00441_amd import device
-    A, B = _operands(m, n, k, off)
+    A, B = _operands(m, n, k, fmt, s, off)
+    route = planner.ladder(m, n, k, fmt, s, k_block, pairs)
+    vectors_off = [_off_ladder(A, fmt, s, k_block), _off_ladder(B.T, fmt, s, k_block)]
+    assert route.starts == (min(m, n) != 511) and route.limit == 0
+    assert [c > 0 for c in vectors_off] == [off != "", off == "both"]                    # off == "": the one pass does the call
+    if route.reads_marks:
+        vectors_off = [int(any(vectors_off)), 0]
     rows = sorted({0, 3, 31, 32, 63, 64, m // 2, m - 2, m - 1} & set(range(m)))
     cols = sorted({0, 1, 5, 31, 32, 63, 64, n // 2, n - 2, n - 1})
     ldc = m + 3
@@ -134,6 +171,8 @@ def test_results_are_the_oracles(fmt, m, n, k, k_block, s, pairs, off):
         C = torch.full((n, ldc), float("nan"), dtype=torch.float64, device="cuda")
         lib.ozaki_dgemm_ex(m, n, k, Ad, m, Bd, k, C, ldc, FMT[fmt], s, k_block, ACC[accum], lib.PAIR_SETS[pairs], lib.SUM_RUNS, 0)
         assert lib.ozaki_last_device_status() == 0
+        if planner.ladder(m, n, k, fmt, s, k_block, pairs, exact=accum == "exact").starts:
+            assert ws.buf[:32].cpu().numpy().view(np.int32)[4:6].tolist() == vectors_off
         got = C.cpu().numpy()
         assert np.all(np.isnan(got[:, m:])) and not np.any(np.isnan(got[:, :m]))
         part = np.ascontiguousarray(got[:, :m].T[np.ix_(rows, cols)])
@@ -150,14 +189,20 @@ def test_results_are_the_oracles(fmt, m, n, k, k_block, s, pairs, off):
     ws.close()
 
 
+LARGE = [("fp8", 2050, 2082, 513, 13), ("fp8", 1100, 4000, 640, 6), ("int8", 2049, 2050, 261, 9)]
+# The other slice counts that have a kernel, each with a table of its own and from 11 on products in ordinary registers
+OTHERS = [("fp8", 2049, 2050, 513, s) for s in range(7, 13)] + [("int8", 2050, 2049, 261 + 64 * (s % 2), s) for s in (6, 7, 8, 10, 11)]
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("rows_off,cols_off", [(0, 0), (1, 0), (0, 33), (32, 3), (64, 64), (65, 1), (2, 65)])
-@pytest.mark.parametrize("fmt,m,n,k,s", [("fp8", 2050, 2082, 513, 13), ("fp8", 1100, 4000, 640, 6), ("int8", 2049, 2050, 261, 9)])
+@pytest.mark.parametrize("fmt,m,n,k,s,rows_off,cols_off", [c + o for c in LARGE for o in ((0, 0), (1, 0), (0, 33), (32, 3), (64, 64), (65, 1), (2, 65))] +
+                         [c + (33, 2) for c in OTHERS])
 def test_vectors_off_the_ladder_in_large_results(fmt, m, n, k, s, rows_off, cols_off):
     """Up to 64 of each operand are done by a kernel of their own, more leave the call to the general kernels; plain and scaled."""
     torch = pytest.importorskip("torch")
     from paper_2508_00441_amd import device
-    A, B = inputs.phi_pair(m, n, k, 1.0, seed=m + n + k)
+    A, B = _matrices(m, n, k, fmt, s)
+    assert planner.ladder(m, n, k, fmt, s)[:2] == (1, 64)
     rng = np.random.default_rng(rows_off * 100 + cols_off)
     odd_rows, odd_cols = rng.permutation(m)[:rows_off], rng.permutation(n)[:cols_off]
     for X, at in ((A, odd_rows), (B.T, odd_cols)):

@@ -16,9 +16,9 @@ from paper_2508_00441_amd import binding as lib, device  # noqa: E402
 @pytest.mark.parametrize("fmt,m,n,k,s,pairs", [("fp8", 4096, 4080, 128, 4, "triangle"), ("fp8", 4090, 4100, 384, 3, "full"), ("fp8", 4096, 4096, 4160, 3, "triangle"),
                                                ("fp8", 4095, 4097, 180, 5, "triangle"), ("fp8", 4096, 4100, 250, 4, "triangle"),
                                                ("fp8", 4093, 4096, 10300, 3, "triangle"), ("fp8", 4096, 4090, 10420, 2, "full"), ("fp8", 3841, 4100, 16400, 12, "triangle"),
-                                               ("fp8", 3900, 4200, 512, 9, "triangle"),
+                                               ("fp8", 3900, 4200, 512, 9, "triangle"), ("fp8", 3900, 4200, 500, 9, "triangle"),
                                                ("fp8", 3841, 4096, 16384, 12, "triangle"), ("fp6", 4096, 3999, 128, 9, "triangle"),
-                                               ("int8", 4001, 4096, 320, 9, "triangle"), ("fp16", 4096, 4096, 1024, 9, "triangle")])
+                                               ("int8", 4001, 4096, 320, 9, "triangle"), ("int8", 4001, 4096, 256, 9, "triangle"), ("fp16", 4096, 4096, 1024, 9, "triangle")])
 def test_large_results(fmt, m, n, k, s, pairs):
     gen = torch.Generator(device="cuda").manual_seed(m + n + k)
     draw = lambda r, c: torch.randn((r, c), dtype=torch.float64, device="cuda", generator=gen).mul_(torch.randn((r, c), dtype=torch.float64, device="cuda", generator=gen).exp_())
