@@ -197,7 +197,7 @@ def short_run(name, cfg, s, cache, steps=5, sample=48):
     Csub = r.Cd[torch.from_numpy(cols).cuda()][:, torch.from_numpy(rows).cuda()].cpu().numpy().T
     Cref = oz.ozaki_dgemm(r.A[rows, :], r.B[:, cols], fmt, s, cfg["k_block"], mode="full" if r.all_pairs else "triangle",
                           accumulate=oracle_rule(cfg["accum"]))
-    gemm_ms = phase_ms[1] / steps
+    gemm_ms = phase_ms[1] / steps                # (with the sums where the library forms both in one pass)
     out = {"config": name, "slice_format": fmt, "num_slices": s, "slice_pairs": r.pairs, "k_block": cfg["k_block"] or k,
            "accum_mode": cfg["accum"], "ms_best": min(per_step), "ms_median": statistics.median(per_step),
            "eff_tflops": flop / (statistics.median(per_step) * 1e-3) / 1e12,

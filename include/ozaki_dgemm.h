@@ -254,7 +254,8 @@ const char* ozaki_status_string(int status);
  * on the context's stream; ozaki_profile_read waits for the stream and returns, in HOST arrays of three
  * floats / three ints, the accumulated milliseconds and the number of kernel launches of the phases
  * [0] slicing (Eq. 4-8, includes the transposition of A), [1] slice-pair GEMMs (Eq. 10-11),
- * [2] accumulation and rescaling; then resets the counters.  ozaki_profile_enable(0) turns it off.
+ * [2] accumulation and rescaling; then resets the counters.  Where a call forms products and sums in one pass, [1] is both
+ * and [2] the launches that then find nothing to do.  ozaki_profile_enable(0) turns it off.
  * At most 4096 spans are kept between two reads (later ones are dropped), and nothing is recorded while the
  * stream is being captured into a HIP graph.
  */

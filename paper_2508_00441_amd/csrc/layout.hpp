@@ -310,7 +310,8 @@ __host__ __device__ inline void acc_order_to_mn(int idx, int& m_in_block, int& n
 // ---- tiles done by ladder_sums.hpp ----------------------------------------------------------------------------
 constexpr int LADDER_TILE = 64;
 // Slice counts that have a kernel (each takes time to build): what the formats need for full accuracy and less, of all pairs the counts of
-// the paper's Table 2 and their neighbours.  Accumulators for 16 anti-diagonals would fit, but not with what else a wave keeps.
+// the paper's Table 2 and their neighbours.  Accumulators for 16 anti-diagonals would fit, but not with what else a wave keeps (FP8, INT8; with
+// FP6's smaller fragments it was not tried).
 constexpr int ladder_min_slices(int fmt, bool full) { return fmt == FMT_FP6_E3M2 ? (full ? 13 : 10) : fmt == FMT_INT8 ? (full ? 7 : 6) : full ? 10 : 6; }
 constexpr int ladder_max_slices(int fmt, bool full) { return fmt == FMT_FP6_E3M2 ? 15 : fmt == FMT_INT8 ? (full ? 9 : 11) : full ? 12 : 14; }
 inline int64_t ladder_blocks(int64_t extent) { return (extent + LADDER_TILE - 1) / LADDER_TILE; }

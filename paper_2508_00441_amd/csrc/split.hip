@@ -598,13 +598,13 @@ __global__ void __launch_bounds__(1024) long_exponents_kernel(SplitArgs a) {
         });
     if (top >= 0x7FF00000u) atomicOr(a.flags, 1);                    // infinity or NaN
     top = block_max(top);
-    bool left = top != 0, off_ladder = false;                        // is there a remainder before slice p?
+    bool left = top != 0;                                            // is there a remainder before slice p?
     int c = 0, p = 0;
     if (left) c = top >= 0x100000u ? magnitude_exponent(top) : (int)largest_remainder(2000) - CD_BIAS;      // 2^2000: x itself
     while (left && p < a.s) {
         uint32_t turns[3] = {0, 0, 0}, all[3];
         int levels, at, last, my_exp = 0;                            // slices off these numbers, places of the last run's first and last
-        bool more = true, gap = false;                               // is there a remainder after them?
+        bool more = true;                                            // is there a remainder after them?
         for (int64_t i = 0, turn = 0;; turn ^= 1) {
             for_chunk(i, [&](uint64_t w) {
                 uint32_t x[3];
@@ -626,7 +626,6 @@ __global__ void __launch_bounds__(1024) long_exponents_kernel(SplitArgs a) {
             }
             // more elements can only bring the units closer, to `step` places at the least
             bool regular = true;
-            gap = false;
             for (at = 0, levels = 0;;) {
                 int run = digit_run(all, at, l);
                 run = run < a.s - p - levels ? run : a.s - p - levels;
@@ -638,7 +637,6 @@ __global__ void __launch_bounds__(1024) long_exponents_kernel(SplitArgs a) {
                 regular = regular && next == run * l.step;
                 more = next != NUMBER_BITS;
                 if (!digit_in_number(at + next, l.step)) break;
-                gap = gap || next != run * l.step;
                 at += next;
                 for (int rest = next; rest > 0; rest -= 31) digit_shift(all[2], all[1], all[0], rest < 31 ? rest : 31);
             }
@@ -646,14 +644,17 @@ __global__ void __launch_bounds__(1024) long_exponents_kernel(SplitArgs a) {
         }
         if (exps != nullptr && tid < levels) exps[(int64_t)(p + tid) * v.rows_pad] = my_exp;
         p += levels;
-        off_ladder = off_ladder || gap;
         if (p >= a.s) break;
         const uint32_t key = more ? largest_remainder(c - last - a.b) : 0u;
         left = key != 0;
-        off_ladder = off_ladder || (left && (int)key - CD_BIAS != c - last - l.step);
         c = (int)key - CD_BIAS;
     }
-    if (v.off_ladder != nullptr && tid == 0) v.off_ladder[t * v.rows_pad + row] = off_ladder ? 1 : 0;
+    if (v.off_ladder != nullptr) {                                   // off the exponents of the slices that are there (noted on the way it took 3 us of 65)
+        __syncthreads();
+        const bool gap = tid > 0 && tid < p && exps[(int64_t)(tid - 1) * v.rows_pad] - exps[(int64_t)tid * v.rows_pad] != l.step;
+        const uint64_t gaps = __ballot(gap);                         // (of the first wave: 32 slices at most)
+        if (tid == 0) v.off_ladder[t * v.rows_pad + row] = gaps != 0 ? 1 : 0;
+    }
     // nothing left: the remaining slices are zero (c := 0); without slices to write, report how many there are
     if (exps != nullptr)
         for (int i = p + tid; i < a.s; i += 1024) exps[(int64_t)i * v.rows_pad] = 0;
