@@ -364,7 +364,7 @@ __device__ __forceinline__ void slice_vectors(const SplitArgs& a) {
         for (int e = 0; e < G; ++e) g.x[0][e] = g.x[1][e] = g.x[2][e] = 0;
     };
     int my_exp = 0;                                                  // lane p of the first wave: c of slice p
-    bool off_ladder = false;
+    int filled = left ? a.s : 0;                                     // slices before there is nothing left
     for (int p = 0; p < a.s;) {
         uint32_t turns[3] = {0, 0, 0};
         if (left) {
@@ -465,7 +465,6 @@ __device__ __forceinline__ void slice_vectors(const SplitArgs& a) {
             const int next = digit_next(turns, run, l.step);
             more = next != NUMBER_BITS;
             if (!digit_in_number(at + next, l.step)) break;
-            if constexpr (!FP16) off_ladder = off_ladder || next != run * l.step;
             at += next;
             move_up(next - moved);
             for (int rest = next; rest > 0; rest -= 31) digit_shift(turns[2], turns[1], turns[0], rest < 31 ? rest : 31);
@@ -492,11 +491,15 @@ __device__ __forceinline__ void slice_vectors(const SplitArgs& a) {
                 key = vector_max(key, 1);
             }
             left = key != 0;
-            if constexpr (!FP16) off_ladder = off_ladder || (left && (int)key - CD_BIAS != c - last - l.step);
+            if (!left && filled > p) filled = p;
             c = (int)key - CD_BIAS;
         }
     }
-    if (!FP16 && v.off_ladder != nullptr && tr == 0) v.off_ladder[t * v.rows_pad + row] = off_ladder ? 1 : 0;
+    if (!FP16 && v.off_ladder != nullptr && tr < 64) {               // (the wave that has the exponents)
+        const int before = __shfl_up(my_exp, 1, 64);
+        const uint64_t gaps = __ballot(tr > 0 && tr < filled && before - my_exp != l.step);
+        if (tr == 0) v.off_ladder[t * v.rows_pad + row] = gaps != 0 ? 1 : 0;
+    }
     if (v.slices != nullptr && tr < a.s) v.exps[(t * a.s + tr) * v.rows_pad + row] = my_exp;
     if constexpr (FP16 && WHOLE) {
         if (v.l1 != nullptr) {
