@@ -12,7 +12,7 @@
 // of C and sums them itself, at scales that are the same for the whole launch: no product is stored or read again.
 // One call by the GEMM kernels with the accumulation, and by this one: 4096^3 FP8, 13 slices, hardware sum 4.36 and 3.63 ms; 4096^3 FP6,
 // 121 pairs, emulated 4.92 and 4.12 ms; 1000 x 777 x 1301 FP8, 12 slices, scaled, emulated 164 and 113 us; 600 x 600 x 1000 FP8, 11
-// slices, emulated, in 64 MiB 108 and 76 us; 96 x 6000 x 4097 INT8, 9 slices 352 and 282 us; 1024^3 FP8, 121 pairs 150 and 109 us.
+// slices, emulated, in 64 MiB 108 and 73 us; 96 x 6000 x 4097 INT8, 9 slices 355 and 276 us; 1024^3 FP8, 121 pairs 150 and 109 us.
 //
 // A wave holds the S fragments of its A slices and walks the B slices from the last to the first: column j is B slice S - 1 - j (0-based) with
 // the A slices 0 .. j, j + 1 products.  Every A slice meets B slice 0 in the last column, and its fragment of the next stage is read right
@@ -20,7 +20,8 @@
 // stage say so (Ladder::A_FREE, MIDDLE and the last column), two of them also that the loads issued half a stage or more before
 // have landed.
 //
-// Vectors of either operand may be off the ladder (few entries that count at some depth, or the end of the mantissas reached).  Where
+// Vectors of either operand may be off the ladder (few entries that count at some depth, or the end of the mantissas reached); the slicing
+// kernels say which.  Where
 // they are few, their rows and columns of C are left to off_ladder.hpp; where they are not, the kernel does nothing, and the GEMM
 // kernels and the accumulation, which come behind it, do all (OffLadder in layout.hpp).  A vector whose remainder is zero from some slice on is regular as far as it goes: the slices behind add zeros, whatever their scale.
 //

@@ -343,8 +343,7 @@ inline bool place_call(const Plan& plan, bool want_product, int sum_words, bool 
 // 94 tiles, 96 x 3000: 1.00 to 1.17, FP8 with 7 slices and 4500 inner indices 0.93.  Hence 90 tiles, for FP8 and more than 32 stages 160.
 // Few slices gain least where these have tiles for every compute unit and the blocks are long: 2048 x 8192 x 6000, hardware sum, 6 to 9
 // slices FP8 1.00, 1.05, 1.09, 1.05, FP6 1.10, 1.15, 1.18, 1.02, INT8 1.05, 1.14, 1.16 (6 to 8).
-// Blocks: of short vectors some are off the ladder as a rule, and the call then takes the other route and the launch for nothing (10 us of 600 x
-// 600 x 1000).  The share of vectors off it, entries (u - 1/2) exp(phi z), 13 FP8 slices (which reach the end of the mantissas): phi = 0.5,
+// Blocks: of short vectors some are off the ladder as a rule, and the call then takes the other route and the launch for nothing (3 to 5 us).  The share of vectors off it, entries (u - 1/2) exp(phi z), 13 FP8 slices (which reach the end of the mantissas): phi = 0.5,
 // k = 256 2.3 %, k = 512 0.1 %, k = 1024 none of 2048; phi = 1, k = 64 5 %, k = 128 0.15 %, from k = 256 on none; phi = 2 0.05 to 0.2 % up
 // to k = 1024; 9 INT8 slices none from k = 64 on (from 257 here: shorter blocks have a slicing kernel of their own).
 inline bool ladder_pays(const Plan& pl) {
