@@ -46,6 +46,8 @@ hipError_t launch_ladder_sums(const Plan& pl, const Operand& A, const Operand& B
     a.m = pl.m; a.n = pl.n;
     a.add_to_C = t > 0;
     a.off = off;
+    a.deltas = delta_args(pl, &A, &B);
+    a.deltas_of = a.deltas.tiles * (unsigned)pl.T * (unsigned)pl.s;      // (with off.marks: of MOST_MARKS / 256 tiles at most)
     a.S = S;
     a.C = C; a.ldc = ldc;
     a.W = C; a.ldw = ldc;

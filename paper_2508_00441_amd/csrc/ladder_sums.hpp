@@ -31,6 +31,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "deltas.hpp"
 #include "fp64_emu.hpp"
 #include "layout.hpp"
 
@@ -38,6 +39,8 @@ namespace ozaki {
 
 struct LadderArgs {
     OffLadder off;
+    DeltaArgs deltas;        // off.marks: filled for the kernels behind it where a vector is off the ladder
+    unsigned deltas_of;      // so many pieces of work, a slice of 256 vectors and a block each
     const uint8_t* sa;       // A slices of the block: [s][chunks][rows_pad_a][row bytes]
     const uint8_t* sb;       // B slices of the block
     const int32_t* ea;       // exponents of the block: [s][rows_pad_a]
@@ -207,7 +210,13 @@ __global__ void __launch_bounds__(256, ladder_workgroups(S)) ladder_sums_kernel(
             a.off.counts[0] = off ? 1 : 0;
             a.off.counts[1] = 0;
         }
-        if (off) return;
+        if (off) {
+            for (unsigned i = blockIdx.x; i < a.deltas_of; i += gridDim.x) {
+                const unsigned tile = i / (unsigned)a.s, p = i - tile * (unsigned)a.s, t = tile / a.deltas.tiles;
+                fill_delta(a.deltas, tile - t * a.deltas.tiles, t, (int)p);
+            }
+            return;
+        }
     } else if (!on_ladder(a.off)) {
         return;
     }

@@ -340,7 +340,7 @@ struct OffLadder {
     uint32_t* bits;          // limit > 0: a bit per vector that is off it, (m_pad + n_pad) / 32 words,
     int* list;               // and these vectors, up to `limit` of A, up to `limit` of B, in no order
     const uint8_t* marks;    // not null: there is no launch_deltas; the first launch of ladder_sums.hpp reads what the slicing kernels say of
-    int mark_bytes;          // both operands' vectors, and leaves in the counts whether any is off it
+    int mark_bytes;          // both operands' vectors, leaves in the counts whether any is off it, and fills the deltas if so
 };
 constexpr OffLadder NO_LADDER{nullptr, 0, nullptr, nullptr, nullptr, 0};
 // Up to so many vectors and blocks every wave of that launch looks at all of them (128 bytes per lane, a round trip to memory as the counts
@@ -369,7 +369,7 @@ hipError_t launch_count_slices(const double* X, int64_t ldv, const Plan& pl, int
 // Internal layout -> plain vector-major codes (verification export).
 hipError_t launch_export_slices(const Plan& pl, const Operand& op, void* out, hipStream_t st);
 
-// Fills Operand::deltas from Operand::exps, for up to two operands in one launch, and counts and lists the vectors off the ladder if
+// Fills Operand::deltas from Operand::exps (deltas.hpp), for up to two operands in one launch, and counts and lists the vectors off the ladder if
 // off.counts is not null.
 hipError_t launch_deltas(const Plan& pl, const Operand* op0, const Operand* op1, const OffLadder& off, hipStream_t st);
 

@@ -17,6 +17,7 @@
 // each slice code once.
 #include <string.h>
 
+#include "deltas.hpp"
 #include "layout.hpp"
 #include "slice_digits.hpp"
 #include "slice_element.hpp"
@@ -819,39 +820,15 @@ __global__ void __launch_bounds__(256) export_slices_kernel(const uint8_t* __res
     }
 }
 
-// One workgroup per 256 vectors and block, one half-wave per group of 32 vectors: for every slice p, is c_p - c_(p+1)
-// the same for all real vectors of the group?  The first tiles_first workgroups of a grid row belong to the first
-// operand, the rest to the second.
-struct DeltaOperand {
-    const int32_t* exps;
-    int32_t* deltas;
-    const int32_t* l1;
-    int32_t* bounds;
-    const uint8_t* off_ladder;
-    int64_t rows, rows_pad;
-};
-__global__ void __launch_bounds__(256) delta_kernel(DeltaOperand o0, DeltaOperand o1, unsigned tiles_first, int s, int b, OffLadder off_ladder) {
-    const bool second = blockIdx.x >= tiles_first;
-    const int32_t* const exps = second ? o1.exps : o0.exps;
-    int32_t* const deltas = second ? o1.deltas : o0.deltas;
-    const int64_t rows = second ? o1.rows : o0.rows, rows_pad = second ? o1.rows_pad : o0.rows_pad;
-    const int64_t tile = blockIdx.x - (second ? tiles_first : 0u), groups = rows_pad / LINK_ROWS, t = blockIdx.y;
+// One workgroup per 256 vectors and block: the deltas, which vectors are off the ladder, the bounds.
+__global__ void __launch_bounds__(256) delta_kernel(DeltaArgs a, OffLadder off_ladder) {
+    const bool second = blockIdx.x >= a.tiles_first;
+    const DeltaOperand& o = a.o[second ? 1 : 0];
+    const int64_t tile = blockIdx.x - (second ? a.tiles_first : 0u), groups = o.rows_pad / LINK_ROWS, t = blockIdx.y;
     const int64_t row = tile * TILE + threadIdx.x;
-    const int64_t group = row / LINK_ROWS;
     const int lane = threadIdx.x & 63, half = lane & 32;
-    const int32_t* e = exps + (size_t)t * s * rows_pad;
-    int32_t* out = deltas + (size_t)t * s * groups + group;          // slice p of this group at out[p * groups]
-    const uint8_t* const marks = second ? o1.off_ladder : o0.off_ladder;
-    const bool off = off_ladder.counts != nullptr && marks[(size_t)t * rows_pad + row] != 0;
-    for (int p = 0; p + 1 < s; ++p) {
-        const int d = e[(size_t)p * rows_pad + row] - e[(size_t)(p + 1) * rows_pad + row];
-        // the first vector of a group is a real one, or the whole group is padding (then every d is 0)
-        const int ref = __shfl(d, half, 64);
-        const unsigned long long ok = __ballot(row >= rows || d == ref);
-        const bool same = (uint32_t)(ok >> half) == 0xFFFFFFFFu;
-        if ((lane & 31) == 0) out[(size_t)p * groups] = same ? ref : DELTA_IRREGULAR;
-    }
-    if ((lane & 31) == 0) out[(size_t)(s - 1) * groups] = DELTA_IRREGULAR;
+    const bool off = off_ladder.counts != nullptr && o.off_ladder[(size_t)t * o.rows_pad + row] != 0;
+    for (int p = 0; p < a.s; ++p) fill_delta(a, blockIdx.x, t, p);
     if (off_ladder.counts != nullptr) {
         const uint64_t bits = __ballot(off);
         if (off_ladder.limit > 0 && (lane & 31) == 0) off_ladder.bits[blockIdx.x * (TILE / 32) + (threadIdx.x >> 5)] = (uint32_t)(bits >> half);
@@ -862,18 +839,17 @@ __global__ void __launch_bounds__(256) delta_kernel(DeltaOperand o0, DeltaOperan
             if (off && place < off_ladder.limit) off_ladder.list[(second ? off_ladder.limit : 0) + place] = (int)row;
         }
     }
-    const int32_t* const l1 = second ? o1.l1 : o0.l1;
-    if (l1 == nullptr) return;
+    if (o.l1 == nullptr) return;
     // Operand::bounds: 2^b times the largest sum |q| of the group
-    int32_t* const bounds = (second ? o1.bounds : o0.bounds) + (size_t)t * s * groups + group;
-    for (int p = 0; p < s; ++p) {
-        int most = l1[(size_t)(t * s + p) * rows_pad + row];
+    int32_t* const bounds = o.bounds + (size_t)t * a.s * groups + row / LINK_ROWS;
+    for (int p = 0; p < a.s; ++p) {
+        int most = o.l1[(size_t)(t * a.s + p) * o.rows_pad + row];
 #pragma unroll
         for (int off = 1; off < 32; off <<= 1) {
-            const int o = __shfl_xor(most, off, 64);
-            most = o > most ? o : most;
+            const int other = __shfl_xor(most, off, 64);
+            most = other > most ? other : most;
         }
-        if ((lane & 31) == 0) bounds[(size_t)p * groups] = most << b;
+        if ((lane & 31) == 0) bounds[(size_t)p * groups] = most << a.b;
     }
 }
 
@@ -982,14 +958,9 @@ hipError_t launch_count_slices(const double* X, int64_t ldv, const Plan& pl, int
 }
 
 hipError_t launch_deltas(const Plan& pl, const Operand* op0, const Operand* op1, const OffLadder& off, hipStream_t st) {
-    DeltaOperand o[2];
-    memset(o, 0, sizeof(o));
-    const Operand* ops[2] = {op0, op1};
-    for (int i = 0; i < 2; ++i)
-        if (ops[i] != nullptr && ops[i]->rows > 0) o[i] = DeltaOperand{ops[i]->exps, ops[i]->deltas, ops[i]->l1, ops[i]->bounds, ops[i]->off_ladder, ops[i]->rows, ops[i]->rows_pad};
-    const unsigned t0 = (unsigned)(o[0].rows_pad / TILE), t1 = (unsigned)(o[1].rows_pad / TILE);
-    if (t0 + t1 == 0 || pl.T == 0 || pl.s == 0) return hipSuccess;
-    hipLaunchKernelGGL(delta_kernel, dim3(t0 + t1, (unsigned)pl.T), dim3(256), 0, st, o[0], o[1], t0, pl.s, pl.b, off);
+    const DeltaArgs a = delta_args(pl, op0, op1);
+    if (a.tiles == 0 || pl.T == 0 || pl.s == 0) return hipSuccess;
+    hipLaunchKernelGGL(delta_kernel, dim3(a.tiles, (unsigned)pl.T), dim3(256), 0, st, a, off);
     return hipGetLastError();
 }
 

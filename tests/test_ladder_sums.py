@@ -70,14 +70,15 @@ def test_eight_slices_take_the_pass_in_large_results_as_others_do():
         assert all(planner.ladder(4096, 4096, k, fmt, s).starts for s in (6, 7, 8, 9) for k in (1024, 4096)), fmt
 
 
-def test_where_the_links_are_formed_in_the_kernels_there_is_no_launch_for_the_vectors_off_the_ladder():
-    for m, n, k, fmt, s, pairs in ((600, 600, 1000, "fp8", 11, "triangle"), (640, 640, 600, "fp6", 13, "triangle"), (640, 600, 700, "fp8", 10, "full"),
-                                   (96, 6000, 4097, "int8", 9, "triangle")):
-        assert planner.route(m, n, k, fmt, s, mode=pairs).small
+def test_no_launch_in_front_of_the_pass_for_the_vectors_off_the_ladder():
+    """Where nothing is listed and a wave can look at all vectors, whether the other kernels use the deltas or not."""
+    for m, n, k, fmt, s, pairs, small in ((600, 600, 1000, "fp8", 11, "triangle", 1), (640, 640, 600, "fp6", 13, "triangle", 1), (640, 600, 700, "fp8", 10, "full", 1),
+                                          (96, 6000, 4097, "int8", 9, "triangle", 1), (1000, 777, 1301, "fp8", 12, "triangle", 0), (1024, 1024, 1024, "fp8", 11, "full", 0),
+                                          (4096, 4096, 1024, "fp6", 13, "triangle", 0)):
+        assert planner.route(m, n, k, fmt, s, mode=pairs).small == small
         vectors = sum((x + 255) // 256 * 256 for x in (m, n))
         assert planner.ladder(m, n, k, fmt, s, mode=pairs) == planner.Ladder(1, 0, 1, 0, vectors)
-    for m, n, k, fmt, s, limit in ((4096, 4096, 1024, "fp8", 13, 64), (4096, 4096, 1024, "fp6", 13, 0)):      # where they are not: that one counts
-        assert planner.ladder(m, n, k, fmt, s) == planner.Ladder(1, limit, 0, 1, m + n)
+    assert planner.ladder(4096, 4096, 1024, "fp8", 13) == planner.Ladder(1, 64, 0, 1, 8192)                    # listed
     assert planner.ladder(64, 9000, 600, "fp6", 13) == planner.Ladder(1, 0, 0, 1, 256 + 9216)                  # more vectors than a wave looks at
     assert planner.ladder(600, 600, 400, "fp8", 11).starts == 0 and planner.ladder(600, 600, 1000, "fp16", 7).mark_bytes == 0
 
