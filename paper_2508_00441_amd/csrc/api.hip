@@ -95,7 +95,7 @@ int run_split(const Plan& pl, const Carve& c, const double* A, int64_t lda, cons
     // both operands in one launch each: on a small problem neither fills the chip alone
     HIP_TRY(launch_split(transpose ? c.At : A, transpose ? pl.k : 1, transpose ? 1 : lda, a_on ? &c.A : nullptr, B, ldb, b_on ? &c.B : nullptr, pl,
                          c.flags, st));
-    if (c.A.deltas != nullptr && off.marks == nullptr) HIP_TRY(launch_deltas(pl, a_on ? &c.A : nullptr, b_on ? &c.B : nullptr, off, st));
+    if (c.A.deltas != nullptr && off.uncounted == nullptr) HIP_TRY(launch_deltas(pl, a_on ? &c.A : nullptr, b_on ? &c.B : nullptr, off, st));
     return 0;
 }
 

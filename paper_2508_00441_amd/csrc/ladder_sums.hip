@@ -47,7 +47,7 @@ hipError_t launch_ladder_sums(const Plan& pl, const Operand& A, const Operand& B
     a.add_to_C = t > 0;
     a.off = off;
     a.deltas = delta_args(pl, &A, &B);
-    a.deltas_of = a.deltas.tiles * (unsigned)pl.T * (unsigned)pl.s;      // (with off.marks: of MOST_MARKS / 256 tiles at most)
+    a.deltas_of = a.deltas.tiles * (unsigned)pl.T * (unsigned)pl.s;      // (with off.uncounted: of MOST_MARKS / 256 tiles at most)
     a.S = S;
     a.C = C; a.ldc = ldc;
     a.W = C; a.ldw = ldc;
@@ -61,7 +61,7 @@ hipError_t launch_ladder_sums(const Plan& pl, const Operand& A, const Operand& B
     }
     for (int part = pl.full ? LESSER_HALF : WHOLE; part <= (pl.full ? GREATER_HALF : WHOLE); ++part) {
         const int S_kernel = part == LESSER_HALF ? pl.s - 1 : pl.s;
-        if (t > 0 || part == GREATER_HALF) a.off.marks = nullptr;      // the call's first launch has left its answer
+        if (t > 0 || part == GREATER_HALF) a.off.uncounted = nullptr;      // the call's first launch has left its answer
         const unsigned blocks = (unsigned)(bm * bn);
         hipError_t e;
         if (pl.fmt == FMT_FP6) e = launch_mode<FMT_FP6>(a, S_kernel, accum_mode, part, blocks, st);

@@ -39,7 +39,7 @@ namespace ozaki {
 
 struct LadderArgs {
     OffLadder off;
-    DeltaArgs deltas;        // off.marks: filled for the kernels behind it where a vector is off the ladder
+    DeltaArgs deltas;        // off.uncounted: filled for the kernels behind it where too many vectors are off the ladder
     unsigned deltas_of;      // so many pieces of work, a slice of 256 vectors and a block each
     const uint8_t* sa;       // A slices of the block: [s][chunks][rows_pad_a][row bytes]
     const uint8_t* sb;       // B slices of the block
@@ -191,7 +191,7 @@ __global__ void __launch_bounds__(256, ladder_workgroups(S)) ladder_sums_kernel(
 #if defined(__HIP_DEVICE_COMPILE__)                                   // buffer descriptors are not a type on the host
     typedef Ladder<FMT, S> L;
     typedef LadderScale<FMT> Scale;
-    constexpr bool FLIP = PART == LESSER_HALF, GO_ON = PART == GREATER_HALF;
+    constexpr bool FLIP = PART == LESSER_HALF, GO_ON = PART == GREATER_HALF, LISTS = PART == WHOLE && !fmt_is_fp6(FMT);      // (OffLadder::limit: place_ladder)
     constexpr bool INT8 = FMT == FMT_INT8, FP6 = fmt_is_fp6(FMT);
     static_assert(L::LDS_BYTES >= 4 * 8192, "the waves' results");
     constexpr int FP6_CODE = FMT == FMT_FP6_E3M2 ? 3 : 2;
@@ -200,22 +200,59 @@ __global__ void __launch_bounds__(256, ladder_workgroups(S)) ladder_sums_kernel(
     int* const leading = reinterpret_cast<int*>(lds + L::LDS_BYTES);  // first-slice exponents of the 64 rows and 64 columns
 
     const int tid = threadIdx.x, lane = tid & 63;
-    if (a.off.marks != nullptr) {
-        const v4i* const marks = reinterpret_cast<const v4i*>(a.off.marks);
-        v4i any = {0, 0, 0, 0};
+    if (!GO_ON && a.off.uncounted != nullptr) {                       // (that one comes second)
+        const v4i* const marks = reinterpret_cast<const v4i*>(a.off.uncounted);
+        const int all = a.off.mark_bytes / 16;
+        int found = 0;                                                // vectors of A off the ladder, and 2^16 times those of B; without a list: any?
 #pragma unroll 4
-        for (int i = lane; i < a.off.mark_bytes / 16; i += 64) any |= marks[i];
-        const bool off = __ballot((any[0] | any[1] | any[2] | any[3]) != 0) != 0;
-        if (blockIdx.x == 0 && tid == 0) {                            // for the launches behind this one
-            a.off.counts[0] = off ? 1 : 0;
-            a.off.counts[1] = 0;
+        for (int i = lane; i < all; i += 64) {
+            const v4i v = marks[i];
+            if constexpr (LISTS) {
+                const int c = __popc(v[0]) + __popc(v[1]) + __popc(v[2]) + __popc(v[3]);
+                found += i < a.off.first_bytes / 16 ? c : c << 16;
+            } else {
+                found |= v[0] | v[1] | v[2] | v[3];
+            }
         }
-        if (off) {
+        if constexpr (LISTS) {
+            if (__ballot(found != 0) != 0) {
+#pragma unroll
+                for (int by = 1; by < 64; by <<= 1) found += __shfl_xor(found, by, 64);
+            }
+            found = __builtin_amdgcn_readfirstlane(found);
+        } else {
+            found = __ballot(found != 0) != 0 ? 1 : 0;
+        }
+        const int rows_off = found & 0xFFFF, cols_off = found >> 16;
+        if (blockIdx.x == 0 && tid == 0) {                            // for the launches behind this one
+            a.off.counts[0] = rows_off;
+            a.off.counts[1] = cols_off;
+        }
+        if (rows_off > a.off.limit || cols_off > a.off.limit) {
             for (unsigned i = blockIdx.x; i < a.deltas_of; i += gridDim.x) {
                 const unsigned tile = i / (unsigned)a.s, p = i - tile * (unsigned)a.s, t = tile / a.deltas.tiles;
                 fill_delta(a.deltas, tile - t * a.deltas.tiles, t, (int)p);
             }
             return;
+        }
+        if (LISTS && found != 0 && blockIdx.x == 0 && tid < 64) {      // the list, for off_ladder.hpp
+            int of_a = 0, of_b = a.off.limit;
+            for (int first = 0; first < all; first += 64) {
+                const v4i v = first + lane < all ? marks[first + lane] : v4i{0, 0, 0, 0};
+#pragma unroll
+                for (int w = 0; w < 4; ++w)
+                    for (uint64_t lanes = __ballot(v[w] != 0); lanes != 0; lanes &= lanes - 1) {
+                        const int l = __ffsll((unsigned long long)lanes) - 1, word = __builtin_amdgcn_readlane(v[w], l);
+                        for (int byte = 0; byte < 4; ++byte) {
+                            if (((word >> (8 * byte)) & 1) == 0) continue;
+                            const int vector = (first + l) * 16 + w * 4 + byte;
+                            const bool of_first = vector < a.off.first_bytes;
+                            if (lane == 0) a.off.list[of_first ? of_a : of_b] = of_first ? vector : vector - a.off.first_bytes;
+                            of_a += of_first ? 1 : 0;
+                            of_b += of_first ? 0 : 1;
+                        }
+                    }
+            }
         }
     } else if (!on_ladder(a.off)) {
         return;
@@ -363,9 +400,9 @@ __global__ void __launch_bounds__(256, ladder_workgroups(S)) ladder_sums_kernel(
     // the vectors off the ladder are not for this kernel to write
     bool row_here = mi < a.m;
     uint32_t cols_off = 0;                                            // of the wave's 32 columns
-    if (a.off.limit > 0) {
-        row_here = row_here && ((a.off.bits[(row0 >> 5) + wm] >> (lane & 31)) & 1u) == 0;
-        cols_off = a.off.bits[(a.rows_pad_a + col0) / 32 + wn] >> ((lane >> 5) * 4);
+    if (LISTS && a.off.limit > 0) {
+        row_here = row_here && a.off.marks[row0 + wm * 32 + (lane & 31)] == 0;
+        cols_off = (uint32_t)__ballot(a.off.marks[a.rows_pad_a + col0 + wn * 32 + (lane & 31)] != 0) >> ((lane >> 5) * 4);
     }
     uint64_t* const mine = reinterpret_cast<uint64_t*>(lds + wave * 8192) + lane;
     static_for<4>([&](auto gc) {

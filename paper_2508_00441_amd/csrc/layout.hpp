@@ -331,20 +331,19 @@ constexpr bool ladder_exact_fits(int fmt, int s, bool full) {
 }
 // How many vectors of the two operands are off the ladder: those with a slice, other than zeros, whose exponent lies more than b + 1 below
 // that of the slice before.  (The slicing kernels say so of every vector, Operand::off_ladder, and clear the counts; the exponents alone do not
-// tell a slice that is left without a remainder, whose exponent is 0, from others.)  launch_deltas counts them, where the call has one.  Up to `limit` of each:
-// ladder_sums.hpp does the call's products but for theirs, which off_ladder.hpp does; beyond that the GEMM kernels and the accumulation,
-// which come behind.
+// tell a slice that is left without a remainder, whose exponent is 0, from others.)  Up to `limit` of each: ladder_sums.hpp does the call's
+// products but for theirs, which off_ladder.hpp does; beyond that the GEMM kernels and the accumulation, which come behind.
 struct OffLadder {
     int* counts;             // null: no such distinction, the latter do all
-    int limit;               // 0 or a multiple of 32
-    uint32_t* bits;          // limit > 0: a bit per vector that is off it, (m_pad + n_pad) / 32 words,
-    int* list;               // and these vectors, up to `limit` of A, up to `limit` of B, in no order
-    const uint8_t* marks;    // not null: there is no launch_deltas; the first launch of ladder_sums.hpp reads what the slicing kernels say of
-    int mark_bytes;          // both operands' vectors, leaves in the counts whether any is off it, and fills the deltas if so
+    int limit;
+    int* list;               // limit > 0: these vectors, up to `limit` of A, up to `limit` of B, in no order
+    const uint8_t* marks;    // Operand::off_ladder of A, behind it that of B
+    const uint8_t* uncounted;      // null, or the marks: there is no launch_deltas; the first launch of ladder_sums.hpp counts the vectors and lists
+    int mark_bytes, first_bytes;   // them, or fills the deltas.  Then: all marks, and A's
 };
-constexpr OffLadder NO_LADDER{nullptr, 0, nullptr, nullptr, nullptr, 0};
+constexpr OffLadder NO_LADDER{nullptr, 0, nullptr, nullptr, nullptr, 0, 0};
 // Up to so many vectors and blocks every wave of that launch looks at all of them (128 bytes per lane, a round trip to memory as the counts
-// are); a multiple of 4096.
+// are); a multiple of 4096, below 2^16.
 constexpr int MOST_MARKS = 8192;
 #if defined(__HIPCC__)
 __device__ __forceinline__ bool on_ladder(const OffLadder& o) { return o.counts != nullptr && o.counts[0] <= o.limit && o.counts[1] <= o.limit; }

@@ -369,7 +369,7 @@ __global__ void __launch_bounds__(256, 1) off_ladder_kernel(const OffLadderArgs 
     }
     // what the workgroup writes: of columns off the ladder the rows on it
     const bool listed_too = (int)panel * 32 + (tid & 31) < count;
-    const bool row_here = of_a ? listed_too : my_row < a.m && ((a.off.bits[my_row >> 5] >> (my_row & 31)) & 1u) == 0;
+    const bool row_here = of_a ? listed_too : my_row < a.m && a.off.marks[my_row] == 0;
     const bool col_here = of_a ? my_col < a.n : listed_too;
     static_assert(S <= 16, "two slices' exponents per thread");
     // lane i: where the product of the wave's slot i comes in the accumulation

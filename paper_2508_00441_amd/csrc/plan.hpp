@@ -362,15 +362,14 @@ inline void place_ladder(Route& r) {
     r.c.A.off_ladder = reinterpret_cast<uint8_t*>(r.c.P) + (products - marks);
     r.c.B.off_ladder = r.c.A.off_ladder + (size_t)r.pl.T * (size_t)r.pl.m_pad;
     r.off.counts = r.c.flags + OFF_LADDER_FLAG;
-    // Some vectors off it: where the call is long against one more launch (3 to 5 us where there are none).  Their bits and the list lie in the
+    r.off.marks = r.c.A.off_ladder;
+    // Some vectors off it: where the call is long against one more launch (3 to 5 us where there are none).  Their list lies in the
     // transposed A's memory, which is dead once the operands are sliced; the runs of such a call have no use for it (place_run_check:
     // run_limit covers an anti-diagonal).
-    const size_t words = (size_t)((r.pl.m_pad + r.pl.n_pad) / 32);
     if ((r.pl.fmt == FMT_FP8 || r.pl.fmt == FMT_INT8) && r.pl.s <= OFF_LADDER_MAX_SLICES && !r.pl.full && r.pl.T == 1 && r.check.starts == nullptr &&
-        ladder_blocks(r.pl.m) * ladder_blocks(r.pl.n) >= 1024 && (words + 2 * OFF_LADDER_MOST) * sizeof(uint32_t) <= (size_t)r.pl.m * r.pl.k * sizeof(double)) {
+        ladder_blocks(r.pl.m) * ladder_blocks(r.pl.n) >= 1024 && 2 * OFF_LADDER_MOST * sizeof(int) <= (size_t)r.pl.m * r.pl.k * sizeof(double)) {
         r.off.limit = OFF_LADDER_MOST;
-        r.off.bits = reinterpret_cast<uint32_t*>(r.c.At);
-        r.off.list = reinterpret_cast<int*>(r.c.At) + words;
+        r.off.list = reinterpret_cast<int*>(r.c.At);
     }
     // The launch that counts the vectors off the ladder also fills the deltas, which only the kernels behind the one pass use.  Where nothing is
     // listed the pass looks at the vectors itself, and fills the deltas if there are such, so that the launch for nothing takes that one's place
@@ -379,9 +378,10 @@ inline void place_ladder(Route& r) {
     // 110, 103.4 (172.7); 1024^3, 121 pairs (147, 153) 110, 103.2 (147.9); 600 x 600 x 1000, 11 FP8 slices (71.4, 78.4) 64.2, 59.7 (74.7); 640 x 640 x
     // 600, 13 FP6 slices (61.0, 68.7) 53.4, 48.2 (64.2); 9 INT8 slices, emulated (55.5, 62.4) 50.0, 46.4 (59.3).  In the last three the other
     // kernels form the links themselves if they have to (place_call); without the deltas they take 0.5 us more.
-    if (r.off.limit == 0 && marks <= MOST_MARKS) {
-        r.off.marks = r.c.A.off_ladder;
+    if (marks <= MOST_MARKS) {
+        r.off.uncounted = r.off.marks;
         r.off.mark_bytes = (int)marks;
+        r.off.first_bytes = (int)(r.pl.T * r.pl.m_pad);
     }
     r.c.A.deltas = r.deltas_a;
     r.c.B.deltas = r.deltas_b;

@@ -826,12 +826,11 @@ __global__ void __launch_bounds__(256) delta_kernel(DeltaArgs a, OffLadder off_l
     const DeltaOperand& o = a.o[second ? 1 : 0];
     const int64_t tile = blockIdx.x - (second ? a.tiles_first : 0u), groups = o.rows_pad / LINK_ROWS, t = blockIdx.y;
     const int64_t row = tile * TILE + threadIdx.x;
-    const int lane = threadIdx.x & 63, half = lane & 32;
+    const int lane = threadIdx.x & 63;
     const bool off = off_ladder.counts != nullptr && o.off_ladder[(size_t)t * o.rows_pad + row] != 0;
     for (int p = 0; p < a.s; ++p) fill_delta(a, blockIdx.x, t, p);
     if (off_ladder.counts != nullptr) {
         const uint64_t bits = __ballot(off);
-        if (off_ladder.limit > 0 && (lane & 31) == 0) off_ladder.bits[blockIdx.x * (TILE / 32) + (threadIdx.x >> 5)] = (uint32_t)(bits >> half);
         if (bits != 0) {                                             // (they are few, or their list is of no use)
             int place = 0;
             if (lane == 0) place = atomicAdd(off_ladder.counts + (second ? 1 : 0), __popcll(bits));

@@ -38,8 +38,8 @@ int ladder_route(int64_t m, int64_t n, int64_t k, int fmt, int s, int64_t k_bloc
     if (!exact || ladder_exact_fits(fmt, s, full != 0)) place_ladder(r);
     route[0] = r.off.counts != nullptr;
     route[1] = r.off.limit;
-    route[2] = r.off.marks != nullptr;
-    route[3] = r.c.A.deltas != nullptr && r.off.marks == nullptr;
+    route[2] = r.off.uncounted != nullptr;
+    route[3] = r.c.A.deltas != nullptr && r.off.uncounted == nullptr;
     route[4] = r.c.A.off_ladder ? reinterpret_cast<uint8_t*>(r.c.P) + (size_t)r.c.chunk_pairs * stored_bytes(r.pl) - r.c.A.off_ladder : 0;
     return 0;
 }
