@@ -11,8 +11,8 @@
 // 5824; of 11 slices 4400 and 4224; of 9 INT8 slices, 45 products, 3940 and 2880 (there the slices' stream again).  Every lane ends with all anti-diagonals of its sixteen elements
 // of C and sums them itself, at scales that are the same for the whole launch: no product is stored or read again.
 // One call by the GEMM kernels with the accumulation, and by this one: 4096^3 FP8, 13 slices, hardware sum 4.36 and 3.63 ms; 4096^3 FP6,
-// 121 pairs, emulated 4.92 and 4.12 ms; 1000 x 777 x 1301 FP8, 12 slices, scaled, emulated 164 and 113 us; 600 x 600 x 1000 FP8, 11
-// slices, emulated, in 64 MiB 108 and 73 us; 96 x 6000 x 4097 INT8, 9 slices 355 and 276 us; 1024^3 FP8, 121 pairs 150 and 109 us.
+// 121 pairs, emulated 4.92 and 4.12 ms; 1000 x 777 x 1301 FP8, 12 slices, scaled, emulated 165 and 109 us; 600 x 600 x 1000 FP8, 11
+// slices, emulated, in 64 MiB 108 and 73 us; 96 x 6000 x 4097 INT8, 9 slices 355 and 276 us; 1024^3 FP8, 121 pairs 148 and 104 us.
 //
 // A wave holds the S fragments of its A slices and walks the B slices from the last to the first: column j is B slice S - 1 - j (0-based) with
 // the A slices 0 .. j, j + 1 products.  Every A slice meets B slice 0 in the last column, and its fragment of the next stage is read right

@@ -371,13 +371,14 @@ inline void place_ladder(Route& r) {
         r.off.limit = OFF_LADDER_MOST;
         r.off.list = reinterpret_cast<int*>(r.c.At);
     }
-    // The launch that counts the vectors off the ladder also fills the deltas, which only the kernels behind the one pass use.  Where nothing is
-    // listed the pass looks at the vectors itself, and fills the deltas if there are such, so that the launch for nothing takes that one's place
-    // (a slice of 256 vectors per workgroup: 1 us more than without, where one workgroup takes all slices of 256 vectors 5).  us, with one vector off the ladder in brackets, by the GEMM
-    // kernels and the accumulation alone, with a launch in front of the pass, now: 1000 x 777 x 1301, 12 FP8 slices, scaled, emulated (174, 179)
-    // 110, 103.4 (172.7); 1024^3, 121 pairs (147, 153) 110, 103.2 (147.9); 600 x 600 x 1000, 11 FP8 slices (71.4, 78.4) 64.2, 59.7 (74.7); 640 x 640 x
-    // 600, 13 FP6 slices (61.0, 68.7) 53.4, 48.2 (64.2); 9 INT8 slices, emulated (55.5, 62.4) 50.0, 46.4 (59.3).  In the last three the other
-    // kernels form the links themselves if they have to (place_call); without the deltas they take 0.5 us more.
+    // A launch in front of the pass that counts and lists the vectors off the ladder would also fill the deltas, which only the kernels behind the
+    // pass use.  Up to MOST_MARKS the pass looks at the vectors itself, and fills the deltas if there are too many, so that the launch for nothing
+    // takes that one's place (a slice of 256 vectors per workgroup: 1 us more than without; all slices of them by one workgroup 5).  us, with a vector
+    // off the ladder in brackets, by the GEMM kernels and the accumulation alone, with a launch in front of the pass, now: 1000 x 777 x 1301, 12 FP8 slices,
+    // scaled, emulated (174, 179) 110, 103.4 (172.7); 1024^3, 121 pairs (147, 153) 110, 103.2 (147.9); 2048 x 2048 x 1024, 13 FP8 slices (368, 300)
+    // 263, 258 (296); 600 x 600 x 1000, 11 FP8 slices (71.4, 78.4) 64.2, 59.7 (74.7); 640 x 640 x 600, 13 FP6 slices (61.0, 68.7) 53.4, 48.2 (64.2);
+    // 9 INT8 slices, emulated (55.5, 62.4) 50.0, 46.4 (59.3).  In the last three the other kernels form the links themselves if they have to
+    // (place_call); without the deltas they take 0.5 us more.
     if (marks <= MOST_MARKS) {
         r.off.uncounted = r.off.marks;
         r.off.mark_bytes = (int)marks;
