@@ -265,3 +265,48 @@ def test_vectors_that_run_out_are_on_the_ladder_at_any_scale(fmt, m, n, k, k_blo
         off = gap and k_block == 0                                    # (in two blocks the row's entries lie in different ones)
         assert counts == [int(off), 0], counts
     lib.ozaki_set_workspace(None, 0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fmt,m,n,k,s,pairs", [("fp8", 640, 600, 700, 10, "full"), ("int8", 2049, 2050, 261, 9, "triangle"), ("fp8", 600, 8000, 513, 6, "triangle")])
+def test_a_captured_call_decides_anew_on_every_replay(fmt, m, n, k, s, pairs):
+    """None off the ladder, a few, too many, none again: counted by the pass itself, with a list, and by a launch in front."""
+    torch = pytest.importorskip("torch")
+    from paper_2508_00441_amd import device
+    A, B = _matrices(m, n, k, fmt, s)
+    Ad, Bd = device.to_device_colmajor(A), device.to_device_colmajor(B)
+    C = torch.zeros((n, m), dtype=torch.float64, device="cuda")
+    f, ps = FMT[fmt], lib.PAIR_SETS[pairs]
+    ws = torch.zeros(lib.ozaki_workspace_bytes_ex(m, n, k, f, s, 0, ps, False), dtype=torch.uint8, device="cuda")
+    call = lambda: lib.ozaki_dgemm_ex(m, n, k, Ad, m, Bd, k, C, m, f, s, 0, ACC["emu"], ps, lib.SUM_RUNS, 0)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        lib.ozaki_set_stream(side.cuda_stream)
+        lib.ozaki_set_workspace(ws, ws.numel())
+        call()
+        side.synchronize()
+        with torch.cuda.graph(graph, stream=side):
+            call()
+        rows, cols = [0, 1, 31, 64, m - 1], [0, 63, n - 1]
+        whole = Ad.clone()
+        for count in (0, 3, 80, 0, 3):
+            Ad.copy_(whole)
+            if count:
+                Ad[:, :count] *= 2.0 ** -45
+                Ad[5, :count] = 3.0
+            C.fill_(float("nan"))
+            graph.replay()
+            side.synchronize()
+            got = C.clone()
+            counts = ws[:32].cpu().numpy().view(np.int32)[4:6].tolist()
+            assert (counts[0] > 0) == (count > 0) and counts[1] == 0, counts
+            want = oz.ozaki_dgemm(device.from_device_colmajor(Ad)[rows], B[:, cols], fmt, s, 0, mode=pairs, accumulate="runs")
+            assert np.array_equal(np.ascontiguousarray(got.cpu().numpy().T[np.ix_(rows, cols)]).view(np.uint64), want.view(np.uint64)), count
+            C.fill_(float("nan"))
+            call()
+            side.synchronize()
+            assert torch.equal(got.view(torch.int64), C.view(torch.int64)), count
+        lib.ozaki_set_workspace(None, 0)
+    lib.ozaki_set_stream(torch.cuda.current_stream().cuda_stream)
